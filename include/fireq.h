@@ -310,8 +310,9 @@ int fq_kv4_output(const uint8_t *P_fp8, const float *p_scale, const uint8_t *V_p
  *              128 x 64 / 64 x 64 tiles (plain GEMM and residual form; the fused gate/up form
  *              always takes the large-M or the M <= 64 kernel), its number of tiles in plan[5] and
  *              the number of workgroups that share a tile along K in plan[6]
- *     plan[1]  large-M kernel: whole tiles (256 rows x 128 channels) written with whole-row stores
- *     plan[2]  whole tiles written element by element (a ragged edge, or N not a multiple of 8)
+ *     plan[1]  large-M kernel: whole tiles (256 rows x 128 channels) with nothing masked in their stores
+ *     plan[2]  whole tiles with a ragged edge (masked whole-row stores) or N not a multiple of 8 (written
+ *              element by element)
  *     plan[3], plan[4]  the same two counts for the 128-row half tiles of the last round
  *     plan[7]  0
  * fq_test_force_kernel: "simple", "small", "large" or "ksplit" makes every GEMM entry point use that kernel

@@ -243,6 +243,27 @@ void fq_gemm_ksplit_kernel(
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[NMT - 1][r] = fmaf(sprev, pprev[r], acc[NMT - 1][r]);
 
+    // ---- residual tile: requested now, used in the epilogue ----
+    // (step `it` of the epilogue: rows 8 * it + 4 * (lane / 32) + 0..3 of the wave's own rows; the even lane of a pair
+    // fetches both channels' bf16 of rows 0, 1 as dwords, the odd lane those of rows 2, 3.  Rows past M lie behind the
+    // descriptor's range and read zero, channels past N wrap into the next row and are never stored.  A slice that
+    // does not finish the tile fetches values it never uses.)
+    const int mrows = M - m0 < cfg::BM ? M - m0 : cfg::BM;   // rows of the tile that exist
+    const bool wide_rows = (N & 7) == 0;                  // rows of Y and R in 16-byte steps: whole-row stores
+    const bool add_wide = R != nullptr && wide_rows;
+    unsigned rres[4 * OWN][2];
+    if (add_wide && kw * OWN < NMT) {
+        const __amdgpu_buffer_rsrc_t rsR = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint16_t*>(R) + (size_t)m0 * N + n0, 0, (int)(((unsigned)mrows * (unsigned)N - (unsigned)n0) * 2u), 0x00020000);
+        const unsigned rlane = ((unsigned)(kw * (32 * OWN) + 4 * (lane >> 5) + 2 * (lane & 1)) * (unsigned)N +
+                                (unsigned)(nw * 32 + ((lane & 31) & ~1))) * 2u;
+#pragma unroll
+        for (int it = 0; it < 4 * OWN; ++it)
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+                rres[it][x] = __builtin_amdgcn_raw_buffer_load_b32(rsR, rlane + (unsigned)(8 * it + x) * (unsigned)N * 2u, 0, 0);
+    }
+
     // ---- fold: add the K splits' partial tiles through LDS ----
     // Row tiles are handed out in blocks: split kw finishes row tiles kw * OWN .. kw * OWN + OWN - 1 (for its
     // NW waves' channels).  All row tiles go through LDS at once where they fit, else half of them at a time: every
@@ -287,7 +308,6 @@ void fq_gemm_ksplit_kernel(
             __syncthreads();
         }
     }
-    const int mown = m0 + kw * (32 * OWN);                // first row of this wave's own row tiles
 
     // the first round of zero-point units is requested now: it travels while the slices hand over
     const int rounds = ZPM ? 0 : (ZU + 7) >> 3;
@@ -386,8 +406,7 @@ void fq_gemm_ksplit_kernel(
     float* osc = reinterpret_cast<float*>(reinterpret_cast<char*>(lds) + cfg::BM * cfg::OUT_STRIDE);
     if ((int)threadIdx.x < cfg::BM) osc[threadIdx.x] = row_factor;
     __syncthreads();
-    const bool full_tile = (m0 + cfg::BM <= M) && (n0 + cfg::BN <= N) && ((N & 7) == 0);
-    if (full_tile) {
+    if (wide_rows) {
         // transpose through LDS so that every store instruction writes whole rows of the tile
         char* tile = reinterpret_cast<char*>(lds);
         char* wcol = tile + (kw * (32 * OWN) + 4 * (lane >> 5)) * cfg::OUT_STRIDE + (nw * 32 + (lane & 31)) * 2;
@@ -396,14 +415,22 @@ void fq_gemm_ksplit_kernel(
         for (int it = 0; it < (owner ? 4 * OWN : 0); ++it) {   // step it: rows 8 * it + 4 * (lane / 32) + 0..3 of the wave's own rows
             const int i = it >> 2, jj = it & 3;
             const fq_v4f sc4 = *reinterpret_cast<const fq_v4f*>(&oscl[8 * it]);
+            fq_v4f res = {0.f, 0.f, 0.f, 0.f};
+            if (add_wide) {                               // this lane's four residual values: the pair of lanes swaps halves
+                const bool oddl = lane & 1;
+                const unsigned d0 = rres[it][0], d1 = rres[it][1];
+                const unsigned p0 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)d0, 0xB1, 0xF, 0xF, false);
+                const unsigned p1 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)d1, 0xB1, 0xF, 0xF, false);
+                const unsigned a[4] = {oddl ? p0 : d0, oddl ? p1 : d1, oddl ? d0 : p0, oddl ? d1 : p1};
+                const unsigned sh = oddl ? 0u : 16u;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) res[e] = __uint_as_float((a[e] << sh) & 0xFFFF0000u);
+            }
 #pragma unroll
             for (int e = 0; e < 4; e += 2) {
-                fq_v2f pr = {fin[i][4 * jj + e] * sc4[e], fin[i][4 * jj + e + 1] * sc4[e + 1]};
-                if (R) {                                  // this lane's residual values, in their own positions
-                    const size_t ro = (size_t)(mown + 8 * it + 4 * (lane >> 5) + e) * N + n;
-                    pr[0] = fmaf(fin[i][4 * jj + e], sc4[e], __uint_as_float((unsigned)R[ro] << 16));
-                    pr[1] = fmaf(fin[i][4 * jj + e + 1], sc4[e + 1], __uint_as_float((unsigned)R[ro + N] << 16));
-                }
+                const fq_v2f pr = add_wide ? (fq_v2f){fmaf(fin[i][4 * jj + e], sc4[e], res[e]),
+                                                      fmaf(fin[i][4 * jj + e + 1], sc4[e + 1], res[e + 1])}
+                                           : (fq_v2f){fin[i][4 * jj + e] * sc4[e], fin[i][4 * jj + e + 1] * sc4[e + 1]};
                 const unsigned pk = __builtin_bit_cast(unsigned, __builtin_convertvector(pr, fq_v2bf));
                 char* dst = wcol + (8 * it + e) * cfg::OUT_STRIDE;
                 *reinterpret_cast<unsigned short*>(dst) = (unsigned short)pk;
@@ -412,18 +439,20 @@ void fq_gemm_ksplit_kernel(
         }
         __syncthreads();                                  // (all residual reads of the tile precede all of its stores)
         constexpr int RPW = cfg::BM / FQK_WAVES, LPR = cfg::BN / 8, RPI = 64 / LPR;
+        // (rows past M lie behind the descriptor's range, 16-byte steps past N get an offset out of range)
         const __amdgpu_buffer_rsrc_t rsY = __builtin_amdgcn_make_buffer_rsrc(
-            Y + (size_t)(m0 + wave * RPW) * N + n0, 0, (int)((unsigned)RPW * (unsigned)N * 2u), 0x00020000);
-        const unsigned ylane = (unsigned)(lane / LPR) * (unsigned)N * 2u + (unsigned)(lane % LPR) * 16u;
+            Y + (size_t)m0 * N + n0, 0, (int)(((unsigned)mrows * (unsigned)N - (unsigned)n0) * 2u), 0x00020000);
+        const unsigned ylane = (unsigned)(wave * RPW + lane / LPR) * (unsigned)N * 2u + (unsigned)(lane % LPR) * 16u;
+        const bool col_ok = n0 + (lane % LPR) * 8 < N;
         const char* rd = tile + (wave * RPW + (lane / LPR)) * cfg::OUT_STRIDE + (lane % LPR) * 16;
 #pragma unroll
         for (int j = 0; j < RPW / RPI; ++j) {
             const fq_v4i v = *reinterpret_cast<const fq_v4i*>(rd + RPI * j * cfg::OUT_STRIDE);
-            __builtin_amdgcn_raw_buffer_store_b128(v, rsY, ylane, RPI * j * N * 2, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(v, rsY, col_ok ? ylane + (unsigned)(RPI * j) * (unsigned)N * 2u : FQL_OOB, 0, 0);
         }
         return;
     }
-    // ragged tile: element-wise, with bounds checks.  (In-place residual: an element is read and written by the
+    // rows not in 16-byte steps: element-wise, with bounds checks.  (In-place residual: an element is read and written by the
     // same lane, and nobody else touches it.)
     if (!wave_on || !n_ok || !owner) return;
 #pragma unroll

@@ -342,22 +342,24 @@ __device__ __forceinline__ void fql_item(
     // Step `it` of the epilogue handles rows 8 * it + 4 * (lane / 32) + 0..3 of this lane's channel.
     // Lanes l, l ^ 1 hold neighbouring channels: the even lane fetches the pair's two bf16 of rows
     // 0, 1 as one dword each, the odd lane those of rows 2, 3, and they swap in the epilogue.
-    // Channels past N wrap into the next row (never stored), rows past M read zero.  All of these
+    // Channels past N wrap into the next row (never stored); rows past M lie behind the descriptor's range and read
+    // zero (the range check sees the per-lane offset only, so the row steps are part of it).  All of these
     // loads have landed before this workgroup's first store (the zero-point rounds wait for every
     // transfer), and no other workgroup touches this tile: R may be the output array itself.
-    const bool full_tile = (m0 + 32 * NMT <= M) && (n0 + FQL_BN <= N) && ((N & 7) == 0);
-    const bool add_full = R != nullptr && full_tile;
+    const int mrows = M - m0 < 32 * NMT ? M - m0 : 32 * NMT;   // rows of the tile that exist
+    const bool wide_rows = (N & 7) == 0;                  // rows of Y and R in 16-byte steps: whole-row stores
+    const bool add_full = R != nullptr && wide_rows;
     unsigned rres[4 * NMT][2];
     if (add_full) {
         const __amdgpu_buffer_rsrc_t rsR = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint16_t*>(R) + (size_t)m0 * N + n0, 0, (int)((unsigned)(32 * NMT) * (unsigned)N * 2u), 0x00020000);
+            const_cast<uint16_t*>(R) + (size_t)m0 * N + n0, 0, (int)(((unsigned)mrows * (unsigned)N - (unsigned)n0) * 2u), 0x00020000);
         const unsigned rlane = ((unsigned)(4 * (lane >> 5) + 2 * (lane & 1)) * (unsigned)N +
                                 (unsigned)(wave * 32 + ((lane & 31) & ~1))) * 2u;
 #pragma unroll
         for (int it = 0; it < 4 * NMT; ++it)
 #pragma unroll
             for (int x = 0; x < 2; ++x)
-                rres[it][x] = __builtin_amdgcn_raw_buffer_load_b32(rsR, rlane, (8 * it + x) * N * 2, 0);
+                rres[it][x] = __builtin_amdgcn_raw_buffer_load_b32(rsR, rlane + (unsigned)(8 * it + x) * (unsigned)N * 2u, 0, 0);
     }
 
     // ---- zero point: acc += Z * gscale^T over the groups, on the fp16 matrix cores ----
@@ -415,8 +417,7 @@ __device__ __forceinline__ void fql_item(
         // of a pair for the same rows: the even lane finishes rows rl, rl+1 of a step, the odd lane
         // rows rl+2, rl+3, each after getting the other's two values by a lane swap.
         const int NH = N >> 1;
-        const bool full_h = (m0 + 32 * NMT <= M) && (n0 + FQL_BN <= N) && ((NH & 7) == 0);
-        if (full_h) {
+        if ((NH & 7) == 0) {                              // rows of H in 16-byte steps
             constexpr int HS = FQL_BN + 16;               // LDS row stride in bytes: 64 bf16 + pad
             char* tile = reinterpret_cast<char*>(lds);
             const int odd = lane & 1;
@@ -446,14 +447,18 @@ __device__ __forceinline__ void fql_item(
             }
             __syncthreads();
             // wave w stores rows 8*NMT*w ..., eight rows of 128 bytes per instruction
+            // (rows past M lie behind the descriptor's range, channels past N get an offset out of range: such
+            // lanes store nothing.  Element-wise stores here, with an atomic per element for the row maxima, took
+            // 4.2 ms of a 1000 x 22016 x 4096 layer's 4.3; masked it is 96 us.)
             const __amdgpu_buffer_rsrc_t rsH = __builtin_amdgcn_make_buffer_rsrc(
-                Y + (size_t)(m0 + wave * (8 * NMT)) * NH + (n0 >> 1), 0, (int)((unsigned)(8 * NMT) * (unsigned)NH * 2u), 0x00020000);
-            const unsigned hlane = (unsigned)(lane >> 3) * (unsigned)NH * 2u + (unsigned)(lane & 7) * 16u;
+                Y + (size_t)m0 * NH + (n0 >> 1), 0, (int)(((unsigned)mrows * (unsigned)NH - (unsigned)(n0 >> 1)) * 2u), 0x00020000);
+            const bool col_ok = (n0 >> 1) + (lane & 7) * 8 < NH;
+            const unsigned hlane = (unsigned)(wave * (8 * NMT) + (lane >> 3)) * (unsigned)NH * 2u + (unsigned)(lane & 7) * 16u;
             const char* rd = tile + (wave * (8 * NMT) + (lane >> 3)) * HS + (lane & 7) * 16;
 #pragma unroll
             for (int j = 0; j < NMT; ++j) {
                 const fq_v4i v = *reinterpret_cast<const fq_v4i*>(rd + 8 * j * HS);
-                __builtin_amdgcn_raw_buffer_store_b128(v, rsH, hlane, 8 * j * NH * 2, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(v, rsH, col_ok ? hlane + (unsigned)(8 * j) * (unsigned)NH * 2u : FQL_OOB, 0, 0);
                 if (rowmax) {
                     // largest |H| of this row's 64 columns of the tile: bf16 magnitudes order like 16-bit integers;
                     // the 8 lanes of a row fold theirs and one of them raises the row's maximum (the bits of the
@@ -464,17 +469,20 @@ __device__ __forceinline__ void fql_item(
                     for (int e = 1; e < 4; ++e)
                         mx = __builtin_elementwise_max(mx, __builtin_bit_cast(v2us, (unsigned)v[e] & 0x7FFF7FFFu));
                     unsigned m16 = mx[0] > mx[1] ? mx[0] : mx[1];
+                    m16 = col_ok ? m16 : 0u;
 #pragma unroll
                     for (int o = 1; o < 8; o <<= 1) {
                         const unsigned other = (unsigned)__shfl_xor((int)m16, o, 64);
                         m16 = other > m16 ? other : m16;
                     }
-                    if ((lane & 7) == 0) atomicMax(&rowmax[m0 + wave * (8 * NMT) + (lane >> 3) + 8 * j], m16 << 16);
+                    const int row = wave * (8 * NMT) + (lane >> 3) + 8 * j;
+                    if ((lane & 7) == 0 && row < mrows) atomicMax(&rowmax[m0 + row], m16 << 16);
                 }
             }
             return;
         }
-        // ragged tile: element-wise (both lanes of a pair are inside or both outside, N being even)
+        // rows of H not in 16-byte steps: element-wise (both lanes of a pair are inside or both outside, N being
+        // even; never with rowmax, whose callers need N / 2 a multiple of 8)
         if (!wave_on || !n_ok) return;
 #pragma unroll
         for (int mt = 0; mt < NMT; ++mt) {
@@ -488,13 +496,12 @@ __device__ __forceinline__ void fql_item(
                     fq_v2bf pk = __builtin_convertvector(pr, fq_v2bf);
                     const unsigned short hb = __builtin_bit_cast(unsigned short, pk[0]);
                     Y[(size_t)(m0 + ml) * NH + (n >> 1)] = hb;
-                    if (rowmax) atomicMax(&rowmax[m0 + ml], ((unsigned)hb & 0x7FFFu) << 16);
                 }
             }
         }
         return;
     }
-    if (full_tile) {
+    if (wide_rows) {
         // Transpose through LDS so that every store instruction writes whole 256-byte rows.
         // A step covers four rows of the lane's channel (registers 4 j .. 4 j + 3).  The four lanes of a quad hold
         // the same four rows of four neighbouring channels: a 4 x 4 transpose inside the quad (bf16 pairs, two
@@ -554,22 +561,26 @@ __device__ __forceinline__ void fql_item(
             *reinterpret_cast<fq_v2i*>(wrow + it * (8 * 256)) = out;
         }
         __syncthreads();
-        // wave w stores rows 8*NMT*w ..., four rows of 256 bytes per instruction; the row steps
-        // travel in the scalar offset of the buffer store
+        // wave w stores rows 8*NMT*w ..., four rows of 256 bytes per instruction.  The row steps are part of the per-lane
+        // offset, which is what the range check sees: rows past M lie behind the descriptor's range, 16-byte steps past
+        // N get an offset out of range, such lanes store nothing (M = 500, N = 14336, quantiser and GEMM: 40.8 us with
+        // element-wise stores in the edge tiles, 37.4 us; a second, unmasked copy of these stores for inner tiles,
+        // row steps in the scalar offset, was no faster at 2048 or 8192 rows and 39.3 us here).
         const __amdgpu_buffer_rsrc_t rsY = __builtin_amdgcn_make_buffer_rsrc(
-            Y + (size_t)(m0 + wave * (8 * NMT)) * N + n0, 0, (int)((unsigned)(8 * NMT) * (unsigned)N * 2u), 0x00020000);
-        const unsigned ylane = (unsigned)(lane >> 4) * (unsigned)N * 2u + (unsigned)(lane & 15) * 16u;
+            Y + (size_t)m0 * N + n0, 0, (int)(((unsigned)mrows * (unsigned)N - (unsigned)n0) * 2u), 0x00020000);
+        const unsigned ylane = (unsigned)(wave * (8 * NMT) + (lane >> 4)) * (unsigned)N * 2u + (unsigned)(lane & 15) * 16u;
+        const bool col_ok = n0 + (lane & 15) * 8 < N;
         // (row R of the tile keeps its segment s at s ^ (R & 3); R & 3 = (lane / 16) & 3 for every row this lane reads)
         const int rq = (lane >> 4) & 3, ch = lane & 15;
         const char* rd = tile + (wave * (8 * NMT) + (lane >> 4)) * 256 + (((ch >> 2) ^ rq) * 64) + (ch & 3) * 16;
 #pragma unroll
         for (int j = 0; j < 2 * NMT; ++j) {
             const fq_v4i v = *reinterpret_cast<const fq_v4i*>(rd + 4 * j * 256);
-            __builtin_amdgcn_raw_buffer_store_b128(v, rsY, ylane, 4 * j * N * 2, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(v, rsY, col_ok ? ylane + (unsigned)(4 * j) * (unsigned)N * 2u : FQL_OOB, 0, 0);
         }
         return;
     }
-    // ragged tile: element-wise stores with bounds checks
+    // rows not in 16-byte steps (N not a multiple of 8): element-wise stores with bounds checks
     if (!wave_on || !n_ok) return;
 #pragma unroll
     for (int mt = 0; mt < NMT; ++mt) {

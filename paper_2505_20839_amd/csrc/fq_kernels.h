@@ -60,9 +60,9 @@ void fq_launch_gemm_simple(const uint8_t* A, const float* a_scale, const uint8_t
 size_t fq_gemm_plane_bytes(int M, int K);
 size_t fq_gemm_large_workspace_bytes(int M, int K);
 // How the large-M kernel cuts an M x N problem on `cus` compute units: out[0] whole tiles (256 rows x
-// 128 channels) stored with whole-row vector stores, out[1] whole tiles stored element by element (rows
-// past M, channels past N, or N not a multiple of 8), out[2] / out[3] the same for the 128-row halves of
-// the tail round.
+// 128 channels) stored with whole-row vector stores and no mask, out[1] whole tiles with rows past M or channels
+// past N (masked vector stores) or N not a multiple of 8 (stored element by element), out[2] / out[3] the same for
+// the 128-row halves of the tail round.
 void fq_gemm_large_plan(int M, int N, int cus, int out[4]);
 void fq_launch_zero_point(const uint8_t* A, void* workspace, int M, int K, hipStream_t stream);
 void fq_launch_gemm_large(const uint8_t* A, const float* a_scale, const uint8_t* wp, const uint8_t* gs,

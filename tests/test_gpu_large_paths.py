@@ -151,6 +151,47 @@ def test_attention_output_projection_with_residual_at_prefill_size(fq):
     check_gemm(bf16_bits_from_gpu(R)[rows], Y, B, "o_proj + residual")
 
 
+@pytest.mark.parametrize("shape", [(300, 200, 1024), (129, 72, 1024), (1000, 1160, 256), (257, 136, 128), (513, 4104, 256)])
+def test_masked_stores_at_ragged_edges(fq, shape):
+    """Rows past M and channels past N inside an edge tile (N a multiple of 8: whole-row stores with a mask): every element
+    against the oracle, plain and with the residual read from an array that ends where the output ends, and no byte
+    behind the output written (a store that ignored the mask would land in the next row or behind the array)."""
+    M, N, K = shape
+    d = _problem(shape, seed=M + N)
+    A, s = fq.fq_quantize_act(to_gpu_bf16(d["X_bf16"]))
+    packed, gs = fq.fq_pack_weights(_gpu(d["q"])), _gpu(d["gscale"])
+    Rb = workloads.draw_residual(M, N, scale=workloads.RESIDUAL_SCALE, seed=M)
+    arena = torch.full((M * N + 4096,), -1, dtype=torch.int16, device="cuda")
+    out = arena[:M * N].view(torch.bfloat16).view(M, N)
+    A_ref, s_ref = A.cpu().numpy(), s.cpu().numpy()
+    fq.fq_w4a8_gemm(A, s, packed, gs, d["w_tscale"], N, out=out)
+    torch.cuda.synchronize()
+    assert bool((arena[M * N:] == -1).all())
+    Y, B = oracle.w4a8_gemm(A_ref, s_ref, d["q"], d["gscale"], d["w_tscale"], want_bound=True)
+    check_gemm(bf16_bits_from_gpu(out), Y, B, "masked %s" % (shape,))
+    out.copy_(to_gpu_bf16(Rb))
+    fq.fq_w4a8_gemm_add(A, s, packed, gs, d["w_tscale"], N, out, out=out)
+    torch.cuda.synchronize()
+    assert bool((arena[M * N:] == -1).all())
+    Y, B = oracle.w4a8_gemm_add(A_ref, s_ref, d["q"], d["gscale"], d["w_tscale"], Rb, want_bound=True)
+    check_gemm(bf16_bits_from_gpu(out), Y, B, "masked residual %s" % (shape,))
+
+
+@pytest.mark.parametrize("M,N", [(1000, 1296), (300, 528), (129, 2064)])
+def test_masked_gate_up_tiles_keep_the_row_maxima(fq, M, N):
+    """The fused gate/up layer with quantised output at ragged edges: the masked rows and channels of an edge tile
+    neither reach the output nor the row maxima (the scales and codes are the separate quantiser's, bit for bit)."""
+    K = 512
+    d = _problem((M, N, K), seed=M + N)
+    A, s = fq.fq_quantize_act(to_gpu_bf16(d["X_bf16"]))
+    packed, gs = fq.fq_pack_weights(_gpu(d["q"])), _gpu(d["gscale"])
+    H, codes, scales = fq.fq_w4a8_gemm_swiglu_quant(A, s, packed, gs, d["w_tscale"], N)
+    codes2, scales2 = fq.fq_quantize_act(H)
+    torch.cuda.synchronize()
+    assert torch.equal(codes, codes2) and torch.equal(scales, scales2)
+    Hr, B = oracle.w4a8_gemm_swiglu(A.cpu().numpy(), s.cpu().numpy(), d["q"], d["gscale"], d["w_tscale"], want_bound=True)
+    check_gemm(bf16_bits_from_gpu(H), Hr, B, "masked gate/up %d x %d" % (M, N))
+
 # ---- the K-split kernel (8-wave workgroups that split K inside the workgroup) --------------------------
 
 KSPLIT_SHAPES = [(65, 64, 1024), (128, 128, 1024), (300, 256, 1024), (129, 200, 1408), (512, 520, 2048),
