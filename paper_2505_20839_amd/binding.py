@@ -52,6 +52,10 @@ def lib() -> ctypes.CDLL:
     L.fq_kv4_scores.argtypes = [vp, vp, vp, vp, cf, vp, ci, ci, ci, vp]
     L.fq_kv4_output.restype = ci
     L.fq_kv4_output.argtypes = [vp, vp, vp, vp, vp, ci, ci, ci, ci, vp]
+    L.fq_kv4_output_workspace_bytes.restype = ctypes.c_size_t
+    L.fq_kv4_output_workspace_bytes.argtypes = [ci, ci, ci]
+    L.fq_kv4_output_ws.restype = ci
+    L.fq_kv4_output_ws.argtypes = [vp, vp, vp, vp, vp, ci, ci, ci, ci, vp, ctypes.c_size_t, vp]
     L.fq_w4a8_gemm_ws.restype = ci
     L.fq_w4a8_gemm_ws.argtypes = [vp, vp, vp, vp, cf, vp, ci, ci, ci, vp, ctypes.c_size_t, ci, vp]
     L.fq_w4a8_gemm_add_ws.restype = ci
@@ -498,8 +502,11 @@ def fq_kv4_output(P: torch.Tensor, p_scale: torch.Tensor, V_packed: torch.Tensor
             or V_packed.numel() < lib().fq_kv4_packed_bytes(H, T, 1):
         raise FireqError(-2, "fq_kv4_output")
     O = torch.empty((H, R, GROUP), dtype=torch.bfloat16, device=P.device)
-    rc = lib().fq_kv4_output(P.data_ptr(), p_scale.data_ptr(), V_packed.data_ptr(), v_scale.data_ptr(), O.data_ptr(),
-                             H, R, T, ldp, _stream())
+    # scratch from torch's caching allocator (stream-ordered), where the tokens are cut into slices
+    need = lib().fq_kv4_output_workspace_bytes(H, R, T)
+    ws = torch.empty((need,), dtype=torch.uint8, device=P.device) if need else None
+    rc = lib().fq_kv4_output_ws(P.data_ptr(), p_scale.data_ptr(), V_packed.data_ptr(), v_scale.data_ptr(), O.data_ptr(),
+                                H, R, T, ldp, ws.data_ptr() if need else 0, need, _stream())
     if rc != 0:
         raise FireqError(rc, "fq_kv4_output")
     return O

@@ -444,16 +444,32 @@ int fq_kv4_scores(const uint8_t* Q_fp8, const float* q_scale, const uint8_t* K_p
     return after_launch();
 }
 
-int fq_kv4_output(const uint8_t* P_fp8, const float* p_scale, const uint8_t* V_packed, const uint8_t* v_scale,
-                  uint16_t* O_bf16, int H, int R, int T, int ldp, void* stream) {
+size_t fq_kv4_output_workspace_bytes(int H, int R, int T) {
+    if (H <= 0 || R <= 0 || T <= 0 || R > 32) return 0;
+    return fq_kv4_output_scratch_bytes(H, R, T);
+}
+
+int fq_kv4_output_ws(const uint8_t* P_fp8, const float* p_scale, const uint8_t* V_packed, const uint8_t* v_scale,
+                     uint16_t* O_bf16, int H, int R, int T, int ldp, void* workspace, size_t workspace_bytes, void* stream) {
     if (H < 0 || R < 0 || T < 0 || R > 32 || ldp < T) return FQ_ERR_SHAPE;
     if (H == 0 || R == 0) return FQ_OK;
     if (T == 0) return FQ_ERR_SHAPE;                      // an empty sum: nothing to attend to
     if (!P_fp8 || !p_scale || !V_packed || !v_scale || !O_bf16) return FQ_ERR_NULL;
     if (!aligned16(V_packed)) return FQ_ERR_ALIGN;
     if (fq_kv4_value_bytes(T) >= 0xFFFFFF00ull) return FQ_ERR_SHAPE;
-    fq_launch_kv4_output(P_fp8, p_scale, V_packed, v_scale, O_bf16, H, R, T, ldp, static_cast<hipStream_t>(stream));
+    const size_t need = workspace ? fq_kv4_output_workspace_bytes(H, R, T) : 0;
+    if (need > 0) {
+        if (workspace_bytes < need) return FQ_ERR_MEMORY;
+        if (!aligned16(workspace)) return FQ_ERR_ALIGN;
+    }
+    fq_launch_kv4_output(P_fp8, p_scale, V_packed, v_scale, O_bf16, H, R, T, ldp, need > 0 ? workspace : nullptr,
+                         static_cast<hipStream_t>(stream));
     return after_launch();
+}
+
+int fq_kv4_output(const uint8_t* P_fp8, const float* p_scale, const uint8_t* V_packed, const uint8_t* v_scale,
+                  uint16_t* O_bf16, int H, int R, int T, int ldp, void* stream) {
+    return fq_kv4_output_ws(P_fp8, p_scale, V_packed, v_scale, O_bf16, H, R, T, ldp, nullptr, 0, stream);
 }
 
 size_t fq_w4a8_gemm_static_max_workspace(void) { return FQ_STATIC_SCRATCH_BYTES; }

@@ -100,8 +100,11 @@ void fq_launch_kv4_pack(const int8_t* codes, uint8_t* packed, int H, int T, bool
 void fq_launch_kv4_unpack(const uint8_t* packed, int8_t* codes, int H, int T, bool values, hipStream_t stream);
 void fq_launch_kv4_scores(const uint8_t* Q, const float* q_scale, const uint8_t* kp, const uint8_t* ks, float out_scale,
                           uint16_t* S, int H, int R, int T, hipStream_t stream);
+// `scratch` (may be NULL): fq_kv4_output_scratch_bytes(H, R, T) bytes, 16-byte aligned; with it, few heads with long
+// caches are cut into token slices, whose partial sums a second kernel adds.
+size_t fq_kv4_output_scratch_bytes(int H, int R, int T);
 void fq_launch_kv4_output(const uint8_t* P, const float* p_scale, const uint8_t* vp, const uint8_t* vs, uint16_t* O,
-                          int H, int R, int T, int ldp, hipStream_t stream);
+                          int H, int R, int T, int ldp, void* scratch, hipStream_t stream);
 
 // K-split kernel (fq_gemm_ksplit.hip): 8-wave workgroups that split K inside the workgroup, for problems with
 // too few tiles for the large-M kernel.  fq_gemm_ksplit_choice: 0 = not used for this shape, 1 = 256 x 128 tiles

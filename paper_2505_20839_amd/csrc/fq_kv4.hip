@@ -81,11 +81,14 @@ __device__ __forceinline__ fq_v8i fqk_join(fq_v4i lo, fq_v4i hi) {
 // w * NSUB .. of 16 tokens each.  Lane l = 16 * kq + r holds, of the A operand, dimensions 32 kq .. of query
 // row r, and of the B operand the same dimensions of token r of the sub-tile: one 16-byte chunk of the
 // packed cache.  MT row tiles of 16 queries share every unpacked operand.
-// WIDE (T a multiple of 4, S 8-byte aligned): a lane ends up with 4 rows x 1 token; the four lanes of a quad hold the
-// same rows of four neighbouring tokens, and a 4 x 4 transpose of bf16 pairs inside the quad (two DPP exchanges)
-// leaves each lane with one row x four tokens = one 8-byte store instead of four 2-byte ones.
+// A lane ends up with 4 rows x 1 token; the four lanes of a quad hold the same rows of four neighbouring tokens, and a
+// 4 x 4 transpose of bf16 pairs inside the quad (two DPP exchanges) leaves each lane with one row x four tokens = one
+// 8-byte store instead of four 2-byte ones, which cost the address path four times as much.  Rows of S start at any
+// multiple of 2 bytes (T is whatever the cache has grown to), so the store is one of 2-byte alignment; the last, partial
+// quad of a row is written token by token.
 #define FQK_S_NSUB 4
-template <int MT, bool WIDE>
+typedef int fqk_v2i_a2 __attribute__((ext_vector_type(2), aligned(2)));
+template <int MT>
 __global__ __launch_bounds__(256) void fq_kv4_scores_kernel(
     const uint8_t* __restrict__ Q, const float* __restrict__ q_scale, const uint8_t* __restrict__ kp,
     const uint8_t* __restrict__ ks, float out_scale, uint16_t* __restrict__ S, int R, int T) {
@@ -138,37 +141,32 @@ __global__ __launch_bounds__(256) void fq_kv4_scores_kernel(
 #pragma unroll
     for (int j = 0; j < FQK_S_NSUB; ++j) {
         const fq_v8i b = fq_unpack_chunk(bq[j]);
-        const int t = t_first + 16 * j + r16;             // this lane's output column
 #pragma unroll
         for (int m = 0; m < MT; ++m) {
             const fq_v4f p = FQ_MFMA16(a[m], b, c0[m]);
-            if (WIDE) {
-                const fq_v2f pr0 = {(sig[j] * p[0]) * rs[m][0], (sig[j] * p[1]) * rs[m][1]};
-                const fq_v2f pr1 = {(sig[j] * p[2]) * rs[m][2], (sig[j] * p[3]) * rs[m][3]};
-                const unsigned pk0 = __builtin_bit_cast(unsigned, __builtin_convertvector(pr0, fq_v2bf));   // rows 0, 1
-                const unsigned pk1 = __builtin_bit_cast(unsigned, __builtin_convertvector(pr1, fq_v2bf));   // rows 2, 3
-                const bool oddl = lane & 1, upper = (lane & 2) != 0;
-                const unsigned sel = oddl ? 0x03020706u : 0x05040100u;   // even: (own.lo, partner.lo); odd: (partner.hi, own.hi)
-                const unsigned n0 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)pk0, 0xB1, 0xF, 0xF, false);
-                const unsigned n1 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)pk1, 0xB1, 0xF, 0xF, false);
-                const unsigned a0 = __builtin_amdgcn_perm(n0, pk0, sel);  // row 0 (even lane) / 1 (odd), the pair's two tokens
-                const unsigned a1 = __builtin_amdgcn_perm(n1, pk1, sel);  // row 2 / 3
-                const unsigned give = upper ? a0 : a1;
-                const unsigned got = (unsigned)__builtin_amdgcn_update_dpp(0, (int)give, 0x4E, 0xF, 0xF, false);
-                const fq_v2i out = upper ? (fq_v2i){(int)got, (int)a1} : (fq_v2i){(int)a0, (int)got};
-                const int orow = 16 * m + 4 * kq + (lane & 3);            // the row this lane now holds, for tokens t4 .. t4 + 3
-                const int t4 = t_first + 16 * j + (r16 & 12);
-                if (orow < R && t4 < T)
-                    *reinterpret_cast<fq_v2i*>(S + ((size_t)h * R + orow) * T + t4) = out;
-            } else {
+            const fq_v2f pr0 = {(sig[j] * p[0]) * rs[m][0], (sig[j] * p[1]) * rs[m][1]};
+            const fq_v2f pr1 = {(sig[j] * p[2]) * rs[m][2], (sig[j] * p[3]) * rs[m][3]};
+            const unsigned pk0 = __builtin_bit_cast(unsigned, __builtin_convertvector(pr0, fq_v2bf));   // rows 0, 1
+            const unsigned pk1 = __builtin_bit_cast(unsigned, __builtin_convertvector(pr1, fq_v2bf));   // rows 2, 3
+            const bool oddl = lane & 1, upper = (lane & 2) != 0;
+            const unsigned sel = oddl ? 0x03020706u : 0x05040100u;   // even: (own.lo, partner.lo); odd: (partner.hi, own.hi)
+            const unsigned n0 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)pk0, 0xB1, 0xF, 0xF, false);
+            const unsigned n1 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)pk1, 0xB1, 0xF, 0xF, false);
+            const unsigned a0 = __builtin_amdgcn_perm(n0, pk0, sel);  // row 0 (even lane) / 1 (odd), the pair's two tokens
+            const unsigned a1 = __builtin_amdgcn_perm(n1, pk1, sel);  // row 2 / 3
+            const unsigned give = upper ? a0 : a1;
+            const unsigned got = (unsigned)__builtin_amdgcn_update_dpp(0, (int)give, 0x4E, 0xF, 0xF, false);
+            const fq_v2i out = upper ? (fq_v2i){(int)got, (int)a1} : (fq_v2i){(int)a0, (int)got};
+            const int orow = 16 * m + 4 * kq + (lane & 3);            // the row this lane now holds, for tokens t4 .. t4 + 3
+            const int t4 = t_first + 16 * j + (r16 & 12);
+            if (orow < R && t4 < T) {
+                uint16_t* dst = S + ((size_t)h * R + orow) * T + t4;
+                if (t4 + 4 <= T) {
+                    *reinterpret_cast<fqk_v2i_a2*>(dst) = out;
+                } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int orow = 16 * m + 4 * kq + i;
-                    if (orow < R && t < T) {
-                        const fq_v2f pr = {(sig[j] * p[i]) * rs[m][i], 0.f};
-                        const fq_v2bf pk = __builtin_convertvector(pr, fq_v2bf);
-                        S[((size_t)h * R + orow) * T + t] = __builtin_bit_cast(unsigned short, pk[0]);
-                    }
+                    for (int i = 0; i < 3; ++i)
+                        if (t4 + i < T) dst[i] = (uint16_t)((unsigned)out[i >> 1] >> (16 * (i & 1)));
                 }
             }
         }
@@ -176,41 +174,33 @@ __global__ __launch_bounds__(256) void fq_kv4_scores_kernel(
 }
 
 // ---- O = P V --------------------------------------------------------------------------------------------
-// A workgroup of 8 waves per head and slice of DT of the 8 dimension tiles (grid: heads x 8 / DT; fewer tiles per
-// workgroup when there are few heads, so that the grid still covers the chip); wave w takes the 32-token blocks
-// w, w + 8, ...; the partial results are added through LDS.  Per block: A' = bf16(P * sigma) for (16 query rows) x (32 tokens) -- lane
-// l = 16 * kq + r holds tokens 8 kq .. 8 kq + 7 of row r -- and, for each of the 8 tiles of 16 dimensions,
-// the B operand for (32 tokens) x (16 dimensions): lane l holds tokens 8 kq .. of dimension l % 16, which are
-// 8 nibbles of one 16-byte chunk of the packed cache (chunk: 32 consecutive tokens of one dimension; low
-// nibbles of bytes 0-7 are tokens 0-7, of bytes 8-15 tokens 8-15, the high nibbles tokens 16-31).
-// A 4-bit code c = q + 8 becomes a bf16 number by bit operations alone: 0x4180 | c << 3 is 16 + c (the binade
-// [16, 32) has a spacing of 1/8).  The matrix cores therefore sum A' * (q + 24); one more MFMA per block against
-// an all-ones operand delivers sum A', and 24 times that is taken off at the end (all products are exact; the
-// offset costs a few FP32 roundings of the larger intermediate sum, far below the tolerance).
-// FAST: P rows and the scale rows are 8-byte aligned (ldp and T multiples of 8), so a lane's 8 codes are one
-// 8-byte load each, converted by the hardware; otherwise byte loads.  (16-byte aligned rows take the kernel of
-// 16-byte steps further down.)
-#define FQK_O_WAVES 8
-#ifndef FQK_O_FILL
-#define FQK_O_FILL 2                                     // workgroups per compute unit the grid aims for
-#endif
-// the kernel of 16-byte steps: at most 4 dimension tiles per workgroup, and one workgroup per compute unit is enough
-// (measured, 128-wide heads x 4 rows x 4096 tokens: 128 heads 10.0 us with 4 tiles, 11.0 with 2, 13.8 with 1; 256 heads
-// 16.3 us with 4 tiles, 21.9 with 8)
-#ifndef FQK_O_WIDE_FILL
-#define FQK_O_WIDE_FILL 1
-#endif
-#ifndef FQK_O_WIDE_MAXDT
-#define FQK_O_WIDE_MAXDT 4
-#endif
-#ifndef FQK_O_WIDE_PF
-#define FQK_O_WIDE_PF(MT, DT) ((DT) <= 4)                // request a group ahead (registers allow it)
-#endif
-// The tail both output kernels share: the waves' partial sums (DT dimension tiles and the row sums of A') are added through
-// LDS in the order of the waves, the offset of 24 per code comes off, the row's scale goes on, one rounding to bf16.
-template <int MT, int DT>
+// A workgroup per head and slice of DT of the 8 dimension tiles (grid: heads x 8 / DT; fewer tiles per workgroup when
+// there are few heads, so that the grid still covers the chip); its NW waves take the 128-token groups w, w + NW, ...
+// and their partial results are added through LDS.  Lane l = 16 * kq + r fetches, per dimension tile, the 16-byte
+// chunk of tokens 32 kq .. 32 kq + 31 of dimension r (one packed chunk), and the 32 probability codes (of query row r)
+// and 32 scales of the same tokens: wide loads only, since a load costs the address path the same whatever its width.
+// Four matrix instructions use a group up: number j4 takes, in every lane, tokens 32 kq + 8 j4 .. + 7 (the order of the
+// summation index is free as long as both operands agree), i.e. bytes 8 j4 .. of the codes and scales and, of the
+// chunk, the low (j4 < 2) or high nibbles of bytes 8 (j4 % 2) ...  A' = bf16(P * sigma) is the A operand.  A 4-bit code
+// c = q + 8 becomes the bf16 number 16 + c in a byte shuffle (low byte 0x80 | c << 3, high byte 0x41: the binade [16, 32)
+// has a spacing of 1/8).  The matrix cores therefore sum A' * (q + 24); one more MFMA against an all-ones operand
+// delivers sum A', and 24 times that is taken off at the end (all products are exact; the offset costs a few FP32
+// roundings of the larger intermediate sum, far below the tolerance).
+// A wave keeps DEPTH groups in flight: what bounds a long cache is the latency of a group's loads times the groups a
+// wave takes one after the other (8 heads x 32001 tokens: 394 us with byte loads and one block of 32 tokens ahead, 26.7
+// us in this form on one workgroup per head and tile).
+// ALIGNED: rows of P and of the scales start at multiples of 16 bytes and T is one (16-byte loads as they are).
+// Otherwise -- a cache that grows by a token per step has any length -- the aligned words around the 32 bytes are
+// fetched (one more 4-byte load each) and shifted into place; what lies past T in the last group is cleared, in the
+// scales and in the codes, since neither the next row's bytes nor a padding's need be finite numbers.
+//
+// The waves' partial sums (DT dimension tiles and the row sums of A') are added through LDS in the order of the waves,
+// the offset of 24 per code comes off, the row's scale goes on, one rounding to bf16.
+// SPLIT: the workgroup has seen one slice of the tokens only; its sums go to `part` ([slice][head][row][128] FP32, offset
+// already off) and fqk_output_combine_kernel adds the slices in their order.
+template <int MT, int DT, int NW, bool SPLIT>
 __device__ __forceinline__ void fqk_output_finish(const fq_v4f (&acc)[MT][DT + 1], float* red, const float* __restrict__ p_scale,
-                                                  uint16_t* __restrict__ O, int h, int d0, int R) {
+                                                  uint16_t* __restrict__ O, float* __restrict__ part, int h, int d0, int R, int r0, int rows) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
     for (int m = 0; m < MT; ++m)
@@ -219,165 +209,72 @@ __device__ __forceinline__ void fqk_output_finish(const fq_v4f (&acc)[MT][DT + 1
 #pragma unroll
             for (int i = 0; i < 4; ++i) red[(((wave * MT + m) * (DT + 1) + d) * 4 + i) * 64 + lane] = acc[m][d][i];
     __syncthreads();
-    for (int idx = threadIdx.x; idx < MT * DT * 4 * 64; idx += 64 * FQK_O_WAVES) {
+    for (int idx = threadIdx.x; idx < MT * DT * 4 * 64; idx += 64 * NW) {
         const int l = idx & 63, i = (idx >> 6) & 3, d = (idx >> 8) % DT, m = (idx >> 8) / DT;
         const int row = 16 * m + 4 * (l >> 4) + i, dim = 16 * (d0 + d) + (l & 15);
-        if (row < R) {
+        if (row < rows) {
             float v = 0.f, s1 = 0.f;                      // fixed order: deterministic
 #pragma unroll
-            for (int w = 0; w < FQK_O_WAVES; ++w) {
+            for (int w = 0; w < NW; ++w) {
                 v += red[(((w * MT + m) * (DT + 1) + d) * 4 + i) * 64 + l];
                 s1 += red[(((w * MT + m) * (DT + 1) + DT) * 4 + i) * 64 + l];
             }
-            const fq_v2f pr = {fmaf(-24.0f, s1, v) * p_scale[(size_t)h * R + row], 0.f};
+            const size_t orow = (size_t)h * R + r0 + row;
+            const float o = fmaf(-24.0f, s1, v);
+            if (SPLIT) {
+                part[((size_t)blockIdx.z * gridDim.x * R + orow) * FQK_HEAD + dim] = o;
+                continue;
+            }
+            const fq_v2f pr = {o * p_scale[orow], 0.f};
             const fq_v2bf pk = __builtin_convertvector(pr, fq_v2bf);
-            O[((size_t)h * R + row) * FQK_HEAD + dim] = __builtin_bit_cast(unsigned short, pk[0]);
+            O[orow * FQK_HEAD + dim] = __builtin_bit_cast(unsigned short, pk[0]);
         }
     }
 }
 
-template <int MT, bool FAST, int DT, bool PF>
-__global__ __launch_bounds__(64 * FQK_O_WAVES) void fq_kv4_output_kernel(
+// Adds the slices' partial sums in the order of the slices (a fixed order: the result does not depend on timing).
+__global__ __launch_bounds__(256) void fqk_output_combine_kernel(const float* __restrict__ part, const float* __restrict__ p_scale,
+                                                                 uint16_t* __restrict__ O, unsigned n4, int slices) {
+    const unsigned i = blockIdx.x * 256u + threadIdx.x;   // four dimensions of one row
+    if (i >= n4) return;
+    fq_v4f v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int s = 0; s < slices; ++s) v += reinterpret_cast<const fq_v4f*>(part)[(size_t)s * n4 + i];
+    const float ps = p_scale[i >> 5];
+    const fq_v2bf lo = __builtin_convertvector((fq_v2f){v[0] * ps, v[1] * ps}, fq_v2bf);
+    const fq_v2bf hi = __builtin_convertvector((fq_v2f){v[2] * ps, v[3] * ps}, fq_v2bf);
+    uint16_t* dst = O + (size_t)i * 4;
+    *reinterpret_cast<fqk_v2i_a2*>(dst) = (fq_v2i){__builtin_bit_cast(int, lo), __builtin_bit_cast(int, hi)};
+}
+
+// Rows r0 .. r0 + rows - 1 (at most 16 * MT) of the R query rows of every head; SPLIT: the token groups of slice blockIdx.z,
+// `gper` of them.
+template <int MT, int DT, int NW, int DEPTH, bool ALIGNED, bool SPLIT>
+__global__ __launch_bounds__(64 * NW) void fq_kv4_output_kernel(
     const uint8_t* __restrict__ P, const float* __restrict__ p_scale, const uint8_t* __restrict__ vp,
-    const uint8_t* __restrict__ vs, uint16_t* __restrict__ O, int R, int T, int ldp) {
-    extern __shared__ float red[];                        // [waves][MT][DT + 1][4][64]: DT dimension tiles + the row sums
+    const uint8_t* __restrict__ vs, uint16_t* __restrict__ O, float* __restrict__ part, int R, int r0, int rows, int T, int ldp,
+    int gper) {
+    extern __shared__ float red[];                        // [NW][MT][DT + 1][4][64]
+    constexpr int NWD = ALIGNED ? 8 : 9;                  // words fetched per 32 bytes
     const int d0 = blockIdx.y * DT;                       // first dimension tile of this workgroup
     const int h = blockIdx.x;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
     const int G = (T + 127) / 128;                        // 128-token groups of the packed value cache
+    const int g_begin = SPLIT ? (int)blockIdx.z * gper : 0;
+    const int g_end = SPLIT && g_begin + gper < G ? g_begin + gper : G;
     const size_t vbytes = fqk_value_bytes(T);
     const __amdgpu_buffer_rsrc_t rsV = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t*>(vp) + (size_t)h * vbytes, 0, (int)vbytes, 0x00020000);
-    fq_v4f acc[MT][DT + 1];
-#pragma unroll
-    for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int d = 0; d < DT + 1; ++d) acc[m][d] = (fq_v4f){0.f, 0.f, 0.f, 0.f};
-    fqk_v8bf ones;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) ones[j] = __builtin_bit_cast(__bf16, (unsigned short)0x3F80);
-    const int nblocks = (T + 31) / 32;
-    // what a lane needs of one block, as it comes from memory: the DT dimension tiles' codes (8 bytes of chunk
-    // (group blk / 4, half, kh, dimension)), and in FAST mode the 8 scale bytes and the 8 P codes of each row tile;
-    // with PF (grids that leave compute units with a single workgroup or none: nothing else hides the latency) the
-    // next block's are requested before the current one is worked on
-    struct fqk_raw { fq_v2i vq[DT]; fq_v2i ws; fq_v2i wp[MT]; };
-    auto fetch = [&](int blk, fqk_raw& raw) __attribute__((always_inline)) {
-        const int t0 = 32 * blk + 8 * kq;
-        const bool on = blk < nblocks;
-#pragma unroll
-        for (int d = 0; d < DT; ++d) {
-            const int dim = 16 * (d0 + d) + r16;
-            const int g = blk >> 2, hh = (blk >> 1) & 1, kh = blk & 1;
-            const unsigned off = ((unsigned)(dim >> 5) * (unsigned)G + (unsigned)g) * 2048u + (unsigned)hh * 1024u +
-                                 (unsigned)(kh * 32 + (dim & 31)) * 16u + (unsigned)(kq & 1) * 8u;
-            raw.vq[d] = __builtin_bit_cast(fq_v2i, __builtin_amdgcn_raw_buffer_load_b64(rsV, on ? off : 0xFFFFFF00u, 0, 2));
-        }
-        if (FAST) {
-            raw.ws = (fq_v2i){0, 0};
-            if (on && t0 < T) raw.ws = *reinterpret_cast<const fq_v2i*>(vs + (size_t)h * T + t0);   // T % 8 == 0: all 8 or none
-#pragma unroll
-            for (int m = 0; m < MT; ++m) {
-                const int row = 16 * m + r16;
-                raw.wp[m] = (fq_v2i){0, 0};
-                if (on && t0 < T)
-                    raw.wp[m] = *reinterpret_cast<const fq_v2i*>(P + ((size_t)h * R + (row < R ? row : R - 1)) * ldp + t0);
-            }
-        }
-    };
-    fqk_raw cur, nxt;
-    if (PF) fetch(wave, cur);
-    for (int blk = wave; blk < nblocks; blk += FQK_O_WAVES) {
-        const int t0 = 32 * blk + 8 * kq;                 // this lane's first token of the block
-        if (PF) fetch(blk + FQK_O_WAVES, nxt);
-        else    fetch(blk, cur);
-        const fq_v2i* vq = cur.vq;
-        // sigma of the lane's 8 tokens (zero past T), as FP32
-        float sg[8];
-        if (FAST) {
-            const fq_v2i w = cur.ws;
-#pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                const fq_v2f lo = __builtin_amdgcn_cvt_pk_f32_fp8(w[x], false), hi = __builtin_amdgcn_cvt_pk_f32_fp8(w[x], true);
-                sg[4 * x] = lo[0]; sg[4 * x + 1] = lo[1]; sg[4 * x + 2] = hi[0]; sg[4 * x + 3] = hi[1];
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) sg[j] = (t0 + j < T) ? fq_e4m3_to_float(vs[(size_t)h * T + t0 + j]) : 0.f;
-        }
-        fqk_v8bf a[MT];
-#pragma unroll
-        for (int m = 0; m < MT; ++m) {
-            const int row = 16 * m + r16;
-            const uint8_t* prow = P + ((size_t)h * R + (row < R ? row : R - 1)) * ldp + t0;
-            float pv[8];
-            if (FAST) {
-                const fq_v2i w = cur.wp[m];
-#pragma unroll
-                for (int x = 0; x < 2; ++x) {
-                    const fq_v2f lo = __builtin_amdgcn_cvt_pk_f32_fp8(w[x], false), hi = __builtin_amdgcn_cvt_pk_f32_fp8(w[x], true);
-                    pv[4 * x] = lo[0]; pv[4 * x + 1] = lo[1]; pv[4 * x + 2] = hi[0]; pv[4 * x + 3] = hi[1];
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) pv[j] = (t0 + j < T) ? fq_e4m3_to_float(prow[j]) : 0.f;
-            }
-            // P * sigma: at most 8 significant bits, exact in FP32 and in bf16 (tokens past T: both factors are 0)
-            // (so the conversion's rounding never acts: one v_cvt_pk_bf16_f32 per pair)
-#pragma unroll
-            for (int j = 0; j < 8; j += 2) {
-                const fq_v2f pr = {pv[j] * sg[j], pv[j + 1] * sg[j + 1]};
-                const fq_v2bf pb = __builtin_convertvector(pr, fq_v2bf);
-                a[m][j] = pb[0];
-                a[m][j + 1] = pb[1];
-            }
-            acc[m][DT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], ones, acc[m][DT], 0, 0, 0);   // sum_t A'[r, t], every column
-        }
-#pragma unroll
-        for (int d = 0; d < DT; ++d) {
-            // codes of this lane's 8 tokens: the low (kq < 2) or high nibbles of the 8 bytes
-            const unsigned x0 = ((kq & 2) ? ((unsigned)vq[d][0] >> 4) : (unsigned)vq[d][0]) & 0x0F0F0F0Fu;
-            const unsigned x1 = ((kq & 2) ? ((unsigned)vq[d][1] >> 4) : (unsigned)vq[d][1]) & 0x0F0F0F0Fu;
-            fq_v4i bw;                                    // two bf16 per word: 0x4180 | c << 3 = 16 + c
-            bw[0] = (int)((__builtin_amdgcn_perm(0u, x0, 0x0C010C00u) << 3) | 0x41804180u);
-            bw[1] = (int)((__builtin_amdgcn_perm(0u, x0, 0x0C030C02u) << 3) | 0x41804180u);
-            bw[2] = (int)((__builtin_amdgcn_perm(0u, x1, 0x0C010C00u) << 3) | 0x41804180u);
-            bw[3] = (int)((__builtin_amdgcn_perm(0u, x1, 0x0C030C02u) << 3) | 0x41804180u);
-            const fqk_v8bf b = __builtin_bit_cast(fqk_v8bf, bw);
-#pragma unroll
-            for (int m = 0; m < MT; ++m) acc[m][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc[m][d], 0, 0, 0);
-        }
-        if (PF) cur = nxt;
-    }
-    fqk_output_finish<MT, DT>(acc, red, p_scale, O, h, d0, R);
-}
-
-
-// The same product for caches and probability rows in 16-byte steps (T and ldp multiples of 16, P and the scales 16-byte
-// aligned): a step of a wave is a whole 128-token group.  Lane l = 16 * kq + r fetches, per dimension tile, the
-// whole 16-byte chunk of tokens 32 kq .. 32 kq + 31 of dimension r, and the 32 probability codes and 32 scales of the
-// same tokens (two 16-byte loads each): 4 + DT wave-level loads per 128 tokens where the kernel above issues
-// 4 * (2 + DT) -- a load costs the address path the same whatever its width.  Four matrix instructions use them up:
-// number j4 takes, in every lane, tokens 32 kq + 8 j4 .. + 7 (the order of the summation index is free as long
-// as both operands agree), i.e. bytes 8 j4 .. of the codes and scales and, of the chunk, the low (j4 < 2) or high
-// nibbles of bytes 8 (j4 % 2) ...  A nibble becomes the bf16 number 16 + c in a byte shuffle: low byte 0x80 | c << 3,
-// high byte 0x41.  The next group's loads are requested before the current one is worked on.
-template <int MT, int DT, bool PF>
-__global__ __launch_bounds__(64 * FQK_O_WAVES) void fq_kv4_output_wide_kernel(
-    const uint8_t* __restrict__ P, const float* __restrict__ p_scale, const uint8_t* __restrict__ vp,
-    const uint8_t* __restrict__ vs, uint16_t* __restrict__ O, int R, int T, int ldp) {
-    extern __shared__ float red[];                        // [waves][MT][DT + 1][4][64]
-    const int d0 = blockIdx.y * DT;
-    const int h = blockIdx.x;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
-    const int G = (T + 127) / 128;
-    const size_t vbytes = fqk_value_bytes(T);
-    const __amdgpu_buffer_rsrc_t rsV = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t*>(vp) + (size_t)h * vbytes, 0, (int)vbytes, 0x00020000);
+    // descriptors of the head's scales and probability rows: from the aligned word that holds the first byte to the one
+    // that holds the last (bytes of those words outside the arrays never enter a sum)
+    const uint8_t* s_base = vs + (size_t)h * T;
+    const uint8_t* p_base = P + ((size_t)h * R + r0) * ldp;
+    const unsigned s_off = ALIGNED ? 0u : (unsigned)(reinterpret_cast<uintptr_t>(s_base) & 3u);
+    const unsigned p_off = ALIGNED ? 0u : (unsigned)(reinterpret_cast<uintptr_t>(p_base) & 3u);
     const __amdgpu_buffer_rsrc_t rsS = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t*>(vs) + (size_t)h * T, 0, T, 0x00020000);
+        const_cast<uint8_t*>(s_base) - s_off, 0, (int)((s_off + (unsigned)T + 3u) & ~3u), 0x00020000);
     const __amdgpu_buffer_rsrc_t rsP = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t*>(P) + (size_t)h * R * ldp, 0, R * ldp, 0x00020000);
+        const_cast<uint8_t*>(p_base) - p_off, 0, (int)((p_off + (unsigned)rows * (unsigned)ldp + 3u) & ~3u), 0x00020000);
     fq_v4f acc[MT][DT + 1];
 #pragma unroll
     for (int m = 0; m < MT; ++m)
@@ -386,12 +283,13 @@ __global__ __launch_bounds__(64 * FQK_O_WAVES) void fq_kv4_output_wide_kernel(
     fqk_v8bf ones;
 #pragma unroll
     for (int j = 0; j < 8; ++j) ones[j] = __builtin_bit_cast(__bf16, (unsigned short)0x3F80);
-    unsigned prow[MT];                                    // byte offset of this lane's probability row(s) in the head
+    unsigned prow[MT];                                    // byte offset of this lane's 32 codes of group 0, per row tile
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
         const int row = 16 * m + r16;
-        prow[m] = (unsigned)(row < R ? row : R - 1) * (unsigned)ldp;
+        prow[m] = p_off + (unsigned)(row < rows ? row : rows - 1) * (unsigned)ldp + 32u * kq;
     }
+    const unsigned srow = s_off + 32u * kq;               // the same of its scales
     unsigned vlane[DT];                                   // this lane's chunk inside a 2048-byte block, per dimension tile
 #pragma unroll
     for (int d = 0; d < DT; ++d) {
@@ -399,37 +297,54 @@ __global__ __launch_bounds__(64 * FQK_O_WAVES) void fq_kv4_output_wide_kernel(
         vlane[d] = (unsigned)(dim >> 5) * (unsigned)G * 2048u + (unsigned)(kq >> 1) * 1024u +
                    (unsigned)((kq & 1) * 32 + (dim & 31)) * 16u;
     }
-    struct fqk_raw { fq_v4i vq[DT]; fq_v4i ws[2]; fq_v4i wp[MT][2]; };
+    struct fqk_raw { fq_v4i vq[DT]; unsigned ws[NWD]; unsigned wp[MT][NWD]; };
+    auto fetch32 = [&](__amdgpu_buffer_rsrc_t rs, unsigned off, bool on, unsigned (&w)[NWD]) __attribute__((always_inline)) {
+        const unsigned o = on ? (off & ~3u) : FQK_OOB;    // (steps in the per-lane offset: the range check sees only that)
+        const fq_v4i lo = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0));
+        const fq_v4i hi = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, o + 16u, 0, 0));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { w[i] = (unsigned)lo[i]; w[4 + i] = (unsigned)hi[i]; }
+        if (!ALIGNED) w[NWD - 1] = __builtin_amdgcn_raw_buffer_load_b32(rs, o + 32u, 0, 0);
+    };
     auto fetch = [&](int g, fqk_raw& raw) __attribute__((always_inline)) {
-        const bool on = g < G;
-        const int t0 = 128 * g + 32 * kq;
+        const unsigned dead = g < g_end ? 0u : FQK_OOB;       // (a group past the end: zeros, which add nothing; no branch)
 #pragma unroll
         for (int d = 0; d < DT; ++d)                      // (streamed once: non-temporal)
             raw.vq[d] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(
-                rsV, on ? vlane[d] + (unsigned)g * 2048u : FQK_OOB, 0, 2));
+                rsV, (vlane[d] + (unsigned)g * 2048u) | dead, 0, 2));
+        // (32 tokens that start past T hold nothing: not fetched)
+        const bool in = g < g_end && 128 * g + 32 * kq < T;
+        fetch32(rsS, srow + 128u * (unsigned)g, in, raw.ws);
 #pragma unroll
-        for (int x = 0; x < 2; ++x) {                     // T % 16 == 0: a 16-byte step lies before T or past it
-            const int tt = t0 + 16 * x;
-            const bool in = on && tt < T;
-            raw.ws[x] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsS, in ? (unsigned)tt : FQK_OOB, 0, 0));
+        for (int m = 0; m < MT; ++m) fetch32(rsP, prow[m] + 128u * (unsigned)g, in, raw.wp[m]);
+    };
+    // the 8 words of 32 bytes as fetched -> the bytes themselves; `nv` of them are valid
+    auto settle = [&](unsigned (&w)[NWD], unsigned off, int nv, bool ragged) __attribute__((always_inline)) {
+        if (!ALIGNED) {
 #pragma unroll
-            for (int m = 0; m < MT; ++m)
-                raw.wp[m][x] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(
-                    rsP, in ? prow[m] + (unsigned)tt : FQK_OOB, 0, 0));
+            for (int i = 0; i < 8; ++i) w[i] = __builtin_amdgcn_alignbyte(w[i + 1 < NWD ? i + 1 : NWD - 1], w[i], off & 3u);
+        }
+        if (ragged) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int n = nv - 4 * i;
+                w[i] &= n >= 4 ? 0xFFFFFFFFu : n <= 0 ? 0u : (1u << (8 * n)) - 1u;
+            }
         }
     };
-    fqk_raw cur, nxt;
-    if (PF) fetch(wave, cur);
-    for (int g = wave; g < G; g += FQK_O_WAVES) {
-        if (PF) fetch(g + FQK_O_WAVES, nxt);
-        else    fetch(g, cur);
+    auto work = [&](int g, fqk_raw& cur) __attribute__((always_inline)) {
+        const bool ragged = g == G - 1 && (T & 127) != 0;
+        const int nv = T - (128 * g + 32 * kq);
+        settle(cur.ws, srow, nv, ragged);
+#pragma unroll
+        for (int m = 0; m < MT; ++m) settle(cur.wp[m], prow[m], nv, ragged);
 #pragma unroll
         for (int j4 = 0; j4 < 4; ++j4) {
-            const int x = j4 >> 1, w0 = 2 * (j4 & 1);     // which 16-byte step of codes and scales, which 8 bytes of it
+            const int x = j4 >> 1, w0 = 2 * (j4 & 1);     // which 8 bytes of the 16-byte chunk
             float sg[8];                                  // sigma of the lane's 8 tokens (zero past T)
 #pragma unroll
             for (int y = 0; y < 2; ++y) {
-                const int w = cur.ws[x][w0 + y];
+                const int w = (int)cur.ws[4 * x + w0 + y];
                 const fq_v2f lo = __builtin_amdgcn_cvt_pk_f32_fp8(w, false), hi = __builtin_amdgcn_cvt_pk_f32_fp8(w, true);
                 sg[4 * y] = lo[0]; sg[4 * y + 1] = lo[1]; sg[4 * y + 2] = hi[0]; sg[4 * y + 3] = hi[1];
             }
@@ -439,7 +354,7 @@ __global__ __launch_bounds__(64 * FQK_O_WAVES) void fq_kv4_output_wide_kernel(
                 float pv[8];
 #pragma unroll
                 for (int y = 0; y < 2; ++y) {
-                    const int w = cur.wp[m][x][w0 + y];
+                    const int w = (int)cur.wp[m][4 * x + w0 + y];
                     const fq_v2f lo = __builtin_amdgcn_cvt_pk_f32_fp8(w, false), hi = __builtin_amdgcn_cvt_pk_f32_fp8(w, true);
                     pv[4 * y] = lo[0]; pv[4 * y + 1] = lo[1]; pv[4 * y + 2] = hi[0]; pv[4 * y + 3] = hi[1];
                 }
@@ -468,9 +383,25 @@ __global__ __launch_bounds__(64 * FQK_O_WAVES) void fq_kv4_output_wide_kernel(
                 for (int m = 0; m < MT; ++m) acc[m][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc[m][d], 0, 0, 0);
             }
         }
-        if (PF) cur = nxt;
+    };
+    fqk_raw ring[DEPTH];
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) fetch(g_begin + wave + i * NW, ring[i]);
+    __builtin_amdgcn_sched_barrier(0);                    // all requests go out before any arithmetic
+    int g = g_begin + wave;
+    for (; g + (DEPTH - 1) * NW < g_end; g += DEPTH * NW) {   // whole rounds of the ring
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i) {
+            work(g + i * NW, ring[i]);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(g + (i + DEPTH) * NW, ring[i]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
-    fqk_output_finish<MT, DT>(acc, red, p_scale, O, h, d0, R);
+#pragma unroll
+    for (int i = 0; i < DEPTH - 1; ++i)                   // the last, partial one
+        if (g + i * NW < g_end) work(g + i * NW, ring[i]);
+    fqk_output_finish<MT, DT, NW, SPLIT>(acc, red, p_scale, O, part, h, d0, R, r0, rows);
 }
 
 }  // namespace
@@ -495,12 +426,8 @@ void fq_launch_kv4_unpack(const uint8_t* packed, int8_t* codes, int H, int T, bo
 void fq_launch_kv4_scores(const uint8_t* Q, const float* q_scale, const uint8_t* kp, const uint8_t* ks, float out_scale,
                           uint16_t* S, int H, int R, int T, hipStream_t stream) {
     const dim3 grid((unsigned)((T + 4 * FQK_S_NSUB * 16 - 1) / (4 * FQK_S_NSUB * 16)), (unsigned)H);
-    const bool wide = (T % 4) == 0 && (reinterpret_cast<uintptr_t>(S) % 8) == 0;   // rows of S are then 8-byte aligned
 #define FQK_SCORES(MT_) \
-    do { \
-        if (wide) hipLaunchKernelGGL((fq_kv4_scores_kernel<MT_, true>), grid, dim3(256), 0, stream, Q, q_scale, kp, ks, out_scale, S, R, T); \
-        else      hipLaunchKernelGGL((fq_kv4_scores_kernel<MT_, false>), grid, dim3(256), 0, stream, Q, q_scale, kp, ks, out_scale, S, R, T); \
-    } while (0)
+    hipLaunchKernelGGL(fq_kv4_scores_kernel<MT_>, grid, dim3(256), 0, stream, Q, q_scale, kp, ks, out_scale, S, R, T)
     switch ((R + 15) / 16) {
         case 1: FQK_SCORES(1); break;
         case 2: FQK_SCORES(2); break;
@@ -512,75 +439,91 @@ void fq_launch_kv4_scores(const uint8_t* Q, const float* q_scale, const uint8_t*
 
 namespace {
 
-template <int MT, bool FAST, int DT, bool PF>
-void fqk_launch_output_pf(const uint8_t* P, const float* p_scale, const uint8_t* vp, const uint8_t* vs, uint16_t* O,
-                          int H, int R, int T, int ldp, hipStream_t stream) {
-    constexpr size_t lds = (size_t)FQK_O_WAVES * MT * (DT + 1) * 4 * 64 * sizeof(float);
+template <int MT, int DT, int NW, int DEPTH, bool ALIGNED, bool SPLIT>
+void fqk_launch_output(const uint8_t* P, const float* p_scale, const uint8_t* vp, const uint8_t* vs, uint16_t* O, float* part,
+                       int H, int R, int r0, int rows, int T, int ldp, int slices, int gper, hipStream_t stream) {
+    constexpr size_t lds = (size_t)NW * MT * (DT + 1) * 4 * 64 * sizeof(float);
     static fq_device_once attr_once;                      // (one per template instance)
     fq_once_per_device(attr_once, [] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_kv4_output_kernel<MT, FAST, DT, PF>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_kv4_output_kernel<MT, DT, NW, DEPTH, ALIGNED, SPLIT>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
-    hipLaunchKernelGGL((fq_kv4_output_kernel<MT, FAST, DT, PF>), dim3((unsigned)H, 8 / DT), dim3(64 * FQK_O_WAVES), lds,
-                       stream, P, p_scale, vp, vs, O, R, T, ldp);
+    hipLaunchKernelGGL((fq_kv4_output_kernel<MT, DT, NW, DEPTH, ALIGNED, SPLIT>), dim3((unsigned)H, 8 / DT, (unsigned)slices),
+                       dim3(64 * NW), lds, stream, P, p_scale, vp, vs, O, part, R, r0, rows, T, ldp, gper);
 }
 
-template <int MT, int DT>
-void fqk_launch_output_wide(const uint8_t* P, const float* p_scale, const uint8_t* vp, const uint8_t* vs, uint16_t* O,
-                            int H, int R, int T, int ldp, hipStream_t stream) {
-    constexpr size_t lds = (size_t)FQK_O_WAVES * MT * (DT + 1) * 4 * 64 * sizeof(float);
-    constexpr bool PF = FQK_O_WIDE_PF(MT, DT);
-    static fq_device_once attr_once;                      // (one per template instance)
-    fq_once_per_device(attr_once, [] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_kv4_output_wide_kernel<MT, DT, PF>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    });
-    hipLaunchKernelGGL((fq_kv4_output_wide_kernel<MT, DT, PF>), dim3((unsigned)H, 8 / DT), dim3(64 * FQK_O_WAVES), lds,
-                       stream, P, p_scale, vp, vs, O, R, T, ldp);
+template <int MT, bool ALIGNED>
+void fqk_launch_output_dt(int dt, const uint8_t* P, const float* p_scale, const uint8_t* vp, const uint8_t* vs, uint16_t* O, float* part,
+                          int H, int R, int r0, int rows, int T, int ldp, int slices, int gper, hipStream_t stream) {
+    if (slices > 1)   fqk_launch_output<MT, 4, 8, 2, ALIGNED, true>(P, p_scale, vp, vs, O, part, H, R, r0, rows, T, ldp, slices, gper, stream);
+    else if (dt == 4) fqk_launch_output<MT, 4, 8, 2, ALIGNED, false>(P, p_scale, vp, vs, O, nullptr, H, R, r0, rows, T, ldp, 1, 0, stream);
+    else if (dt == 2) fqk_launch_output<MT, 2, 8, 2, ALIGNED, false>(P, p_scale, vp, vs, O, nullptr, H, R, r0, rows, T, ldp, 1, 0, stream);
+    // (up to 32 groups: four per wave of 8, all requested at once; 8 heads x 2048 tokens 4.5 us, 5.6 with 16 waves)
+    else if (T <= 4096) fqk_launch_output<MT, 1, 8, 4, ALIGNED, false>(P, p_scale, vp, vs, O, nullptr, H, R, r0, rows, T, ldp, 1, 0, stream);
+    else              fqk_launch_output<MT, 1, 16, (MT == 1 ? 3 : 2), ALIGNED, false>(P, p_scale, vp, vs, O, nullptr, H, R, r0, rows, T, ldp, 1, 0, stream);
 }
 
-// MODE 0: byte loads; 1: 8-byte steps; 2: 16-byte steps (the wide kernel)
-template <int MT, int MODE, int DT>
-void fqk_launch_output(const uint8_t* P, const float* p_scale, const uint8_t* vp, const uint8_t* vs, uint16_t* O,
-                       int H, int R, int T, int ldp, hipStream_t stream) {
-    if (MODE == 2)
-        fqk_launch_output_wide<MT, DT>(P, p_scale, vp, vs, O, H, R, T, ldp, stream);
-    // fewer workgroups than twice the compute units (only possible at one dimension tile per workgroup): prefetch
-    else if (DT == 1 && (long)H * 8 < (long)FQK_O_FILL * fq_device_cus())
-        fqk_launch_output_pf<MT, MODE == 1, DT, true>(P, p_scale, vp, vs, O, H, R, T, ldp, stream);
-    else
-        fqk_launch_output_pf<MT, MODE == 1, DT, false>(P, p_scale, vp, vs, O, H, R, T, ldp, stream);
+// Dimension tiles per workgroup without slices: the most (of 4) that still give a workgroup per compute unit.  Every
+// workgroup of a head converts the same P * sigma, so fewer tiles mean more redundant conversions, more of them fewer
+// workgroups (4 rows x 4096 tokens, an earlier form of the kernel: 128 heads 10.0 us with 4 tiles, 11.0 with 2, 13.8 with 1).
+int fqk_output_tiles(int H, int cus) {
+    int dt = 4;
+    while (dt > 1 && (long)H * (8 / dt) < (long)cus) dt >>= 1;
+    return dt;
 }
 
-template <int MT, int MODE>
-void fqk_launch_output_dt(int dt, const uint8_t* P, const float* p_scale, const uint8_t* vp, const uint8_t* vs, uint16_t* O,
-                          int H, int R, int T, int ldp, hipStream_t stream) {
-    if (dt == 8)      fqk_launch_output<MT, MODE, 8>(P, p_scale, vp, vs, O, H, R, T, ldp, stream);
-    else if (dt == 4) fqk_launch_output<MT, MODE, 4>(P, p_scale, vp, vs, O, H, R, T, ldp, stream);
-    else if (dt == 2) fqk_launch_output<MT, MODE, 2>(P, p_scale, vp, vs, O, H, R, T, ldp, stream);
-    else              fqk_launch_output<MT, MODE, 1>(P, p_scale, vp, vs, O, H, R, T, ldp, stream);
+// Token slices of an output product that is given a workspace, and the groups of each: as many as fill the device with
+// workgroups of 4 dimension tiles, every wave with at least one group.  A group costs a wave about 1.2 us (the conversions
+// of its four waves per SIMD), the second kernel 3.5 us, so slices are taken where they save a wave three
+// groups or more.  Measured without -> with (4 rows): 8 heads x 32001 tokens 26.7 -> 9.9 us, x 8192 10.1 -> 6.6, x 4096
+// 6.4 -> 8.6 (not taken); 1 head x 32768 21.7 -> 7.2; 64 heads x 16384 21.5 -> 17.1, x 4096 7.0 -> 9.1 (not taken).
+int fqk_output_slices(int H, int T, int cus, int* gper) {
+    const int G = (T + 127) / 128;
+    *gper = G;
+    int S = H > 0 ? cus / (2 * H) : 1;
+    if (S > G / 8) S = G / 8;
+    if (S < 2) return 1;
+    const int per = (G + S - 1) / S;
+    const int waves = fqk_output_tiles(H, cus) == 1 ? 16 : 8;
+    if ((G + waves - 1) / waves - (per + 7) / 8 < 3) return 1;
+    *gper = per;
+    return (G + per - 1) / per;                           // (none of them empty)
 }
 
 }  // namespace
 
+size_t fq_kv4_output_scratch_bytes(int H, int R, int T) {
+    int gper;
+    const int S = fqk_output_slices(H, T, fq_device_cus(), &gper);
+    return S > 1 ? (size_t)S * (size_t)H * (size_t)R * FQK_HEAD * sizeof(float) : 0;
+}
+
 void fq_launch_kv4_output(const uint8_t* P, const float* p_scale, const uint8_t* vp, const uint8_t* vs, uint16_t* O,
-                          int H, int R, int T, int ldp, hipStream_t stream) {
-    const uintptr_t both = reinterpret_cast<uintptr_t>(P) | reinterpret_cast<uintptr_t>(vs) | (uintptr_t)T | (uintptr_t)ldp;
-    // (the kernel of 16-byte steps addresses a head's probability rows through 32-bit buffer offsets)
-    const bool rows32 = (unsigned long long)R * (unsigned long long)ldp < 0xFFFFFF00ull;
-    const int mode = ((both % 16) == 0 && rows32) ? 2 : (both % 8) == 0 ? 1 : 0;
-    // dimension tiles per workgroup: the most that still give `fill` workgroups per compute unit
+                          int H, int R, int T, int ldp, void* scratch, hipStream_t stream) {
+    const uintptr_t all = reinterpret_cast<uintptr_t>(P) | reinterpret_cast<uintptr_t>(vs) | (uintptr_t)T | (uintptr_t)ldp;
+    const bool aligned = (all % 16) == 0;
     const int cus = fq_device_cus();
-    int dt = mode == 2 ? FQK_O_WIDE_MAXDT : 8;
-    const int fill = mode == 2 ? FQK_O_WIDE_FILL : FQK_O_FILL;
-    while (dt > 1 && (long)H * (8 / dt) < (long)fill * cus) dt >>= 1;
+    int slices = 1, gper = 0;
+    if (scratch) slices = fqk_output_slices(H, T, cus, &gper);
+    float* part = static_cast<float*>(scratch);
+    const int dt = fqk_output_tiles(H, cus);
+    // rows of a head are addressed through 32-bit buffer offsets: all of them at once, unless rows are so long that
+    // fewer fit (a row has less than 2^31 codes)
+    const unsigned long long fit = 0xFFFFFF00ull / (unsigned long long)ldp;
+    const int step = (unsigned long long)R <= fit ? R : (int)fit;
+    for (int r0 = 0; r0 < R; r0 += step) {
+        const int rows = R - r0 < step ? R - r0 : step;
 #define FQK_OUTPUT(MT_) \
-    do { \
-        if (mode == 2)      fqk_launch_output_dt<MT_, 2>(dt, P, p_scale, vp, vs, O, H, R, T, ldp, stream); \
-        else if (mode == 1) fqk_launch_output_dt<MT_, 1>(dt, P, p_scale, vp, vs, O, H, R, T, ldp, stream); \
-        else                fqk_launch_output_dt<MT_, 0>(dt, P, p_scale, vp, vs, O, H, R, T, ldp, stream); \
-    } while (0)
-    if (R <= 16) FQK_OUTPUT(1);
-    else         FQK_OUTPUT(2);
+        do { \
+            if (aligned) fqk_launch_output_dt<MT_, true>(dt, P, p_scale, vp, vs, O, part, H, R, r0, rows, T, ldp, slices, gper, stream); \
+            else         fqk_launch_output_dt<MT_, false>(dt, P, p_scale, vp, vs, O, part, H, R, r0, rows, T, ldp, slices, gper, stream); \
+        } while (0)
+        if (rows <= 16) FQK_OUTPUT(1);
+        else            FQK_OUTPUT(2);
 #undef FQK_OUTPUT
+    }
+    if (slices > 1) {
+        const unsigned n4 = (unsigned)H * (unsigned)R * (FQK_HEAD / 4);
+        hipLaunchKernelGGL(fqk_output_combine_kernel, dim3((n4 + 255u) / 256u), dim3(256), 0, stream, part, p_scale, O, n4, slices);
+    }
 }

@@ -86,6 +86,56 @@ def test_outputs_match_the_oracle(fq, H, R, T):
                "output %s" % ((H, R, T),), frobenius=False)   # (token 0 carries the largest scale and most of the norm)
 
 
+@pytest.mark.parametrize("H,R,T,ldp,skew", [(1, 1, 1, 1, 0), (3, 4, 31, 33, 1), (2, 16, 127, 131, 2), (2, 5, 129, 129, 3),
+                                            (9, 17, 2001, 2008, 0), (70, 2, 1153, 1168, 4), (260, 4, 385, 390, 1), (8, 4, 8191, 8192, 0),
+                                            # few heads, long caches: token slices (the last one shorter, a last group of 1 token)
+                                            (1, 3, 9000, 9000, 0), (5, 20, 8833, 8840, 2), (64, 1, 12400, 12400, 0)])
+def test_outputs_of_caches_of_any_length_and_alignment(fq, H, R, T, ldp, skew):
+    """Token counts, row strides and base addresses that are multiples of nothing, on every number of dimension tiles per
+    workgroup: what lies behind the T codes of a row (here NaN codes) and behind the scales must not enter a sum."""
+    rng = np.random.default_rng(H + R + T + skew)
+    P = np.full((H, R, ldp), 0x7F, np.uint8); P[:, :, :T] = _codes(rng, (H, R, T), top=0x70, signed=False)
+    Vq = rng.integers(-8, 8, (H, T, 128), dtype=np.int8)
+    vs = _codes(rng, (H, T), top=0x50); ps = rng.uniform(0.001, 0.1, (H, R)).astype(np.float32)
+    def skewed(a):                                             # the array at `skew` bytes past an aligned address, NaN codes around it
+        buf = torch.full((a.size + 64 + skew,), 0x7F, dtype=torch.uint8, device="cuda")
+        buf[skew:skew + a.size] = _gpu(a).view(-1)
+        return buf[skew:skew + a.size].view(a.shape)
+    Pd, pd, vp, vd = skewed(P), _gpu(ps), fq.fq_kv4_pack(_gpu(Vq), True), skewed(vs)
+    O = fq.fq_kv4_output(Pd, pd, vp, vd)
+    # the call without scratch takes no slices: the same sums in another order
+    O1 = torch.empty_like(O)
+    assert fq.lib().fq_kv4_output(Pd.data_ptr(), pd.data_ptr(), vp.data_ptr(), vd.data_ptr(), O1.data_ptr(), H, R, T, ldp,
+                                  torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert (fq.lib().fq_kv4_output_workspace_bytes(H, R, T) > 0) == (T > 8000)
+    if T < 8000:
+        assert torch.equal(O, O1)
+    Or, B = oracle.kv4_output(P[:, :, :T], ps, Vq, vs, want_bound=True)
+    check_gemm(bf16_bits_from_gpu(O).reshape(H * R, 128), Or.reshape(H * R, 128), B.reshape(H * R, 128),
+               "output %s" % ((H, R, T, ldp, skew),), frobenius=False)
+    check_gemm(bf16_bits_from_gpu(O1).reshape(H * R, 128), Or.reshape(H * R, 128), B.reshape(H * R, 128),
+               "output without scratch %s" % ((H, R, T, ldp, skew),), frobenius=False)
+
+
+@pytest.mark.parametrize("H,R,T", [(2, 4, 1), (3, 3, 5), (1, 33, 255), (4, 7, 1022), (2, 16, 4097)])
+def test_scores_of_rows_at_odd_addresses(fq, H, R, T):
+    """Rows of S that start at odd multiples of 2 bytes: every element, and nothing written before or behind the array."""
+    rng = np.random.default_rng(H + R + T)
+    Q = _codes(rng, (H, R, 128)); Kq = rng.integers(-8, 8, (H, T, 128), dtype=np.int8)
+    ks = _codes(rng, (H, T), top=0x50); qs = rng.uniform(0.01, 2, (H, R)).astype(np.float32)
+    kp, Qd, qd, kd = fq.fq_kv4_pack(_gpu(Kq), False), _gpu(Q), _gpu(qs), _gpu(ks)
+    for skew in (0, 1, 3):
+        arena = torch.full((H * R * T + 64,), 0x1234, dtype=torch.int16, device="cuda")
+        assert fq.lib().fq_kv4_scores(Qd.data_ptr(), qd.data_ptr(), kp.data_ptr(), kd.data_ptr(), 0.0883883461,
+                                      arena.data_ptr() + 2 * skew, H, R, T, torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        got = arena.cpu().numpy().view(np.uint16)
+        assert (got[:skew] == 0x1234).all() and (got[skew + H * R * T:] == 0x1234).all()
+        Sr, B = oracle.kv4_scores(Q, qs, Kq, ks, np.float32(0.0883883461), want_bound=True)
+        check_gemm(got[skew:skew + H * R * T].reshape(H * R, T), Sr.reshape(H * R, T), B.reshape(H * R, T),
+                   "scores %s skew %d" % ((H, R, T), skew), frobenius=False)
+
 def test_one_hot_operands_read_back_every_cache_element(fq):
     """A one-hot query reads one key element per token, a one-hot probability row one token's values: every packed
     code and every scale of both caches arrives where the oracle says (exact products: only bf16 rounding left)."""
