@@ -26,6 +26,8 @@ inline void fq_once_per_device(fq_device_once& st, F&& f) {
 // Each launcher validates nothing: arguments were checked by the C entry point.  They enqueue on
 // `stream` and return; the caller reads hipGetLastError().
 void fq_launch_pack(const int8_t* q, uint8_t* wp, int N, int K, hipStream_t stream);
+// `matrices` of the same shape, one behind the other (codes and packed).
+void fq_launch_pack_many(const int8_t* q, uint8_t* wp, int matrices, int N, int K, hipStream_t stream);
 void fq_launch_unpack(const uint8_t* wp, int8_t* q, int N, int K, hipStream_t stream);
 void fq_launch_quantize(const uint16_t* X, uint8_t* A, float* a_scale, int M, int K, hipStream_t stream);
 // The same, also filling the large-M GEMM's workspace (fq_gemm_large_workspace_bytes(M, K)) with the

@@ -67,6 +67,24 @@ def test_pack_unpack_roundtrip(fq, N, K):
     assert np.array_equal(back, q)
 
 
+@pytest.mark.parametrize("N,K,skew", [(1, 128, 1), (33, 384, 2), (160, 1408, 3), (64, 256, 8)])
+def test_pack_takes_codes_at_any_address(fq, N, K, skew):
+    """The code array needs no alignment: packed bytes as from an aligned copy, with garbage in the codes' high nibbles
+    (only the low four bits are read) and around the array, and unpacking gives the codes back."""
+    rng = np.random.default_rng(N + K)
+    q = rng.integers(-8, 8, (N, K), dtype=np.int8)
+    buf = torch.full((N * K + 64,), 0x55, dtype=torch.int8, device="cuda")
+    buf[skew:skew + N * K] = torch.from_numpy((q & 0x0F) | (rng.integers(0, 16, (N, K), dtype=np.int8) << 4)).cuda().view(-1)
+    packed = fq.fq_pack_weights(buf[skew:skew + N * K].view(N, K))
+    assert torch.equal(packed, fq.fq_pack_weights(torch.from_numpy(q).cuda()))
+    assert np.array_equal(fq.fq_unpack_weights(packed, N, K).cpu().numpy(), q)
+    T = N * K // 128                                           # the same codes as one head's cache of N * K / 128 tokens
+    for values in (False, True):
+        pk = fq.fq_kv4_pack(buf[skew:skew + N * K].view(1, T, 128), values)
+        assert torch.equal(pk, fq.fq_kv4_pack(torch.from_numpy(q).cuda().view(1, T, 128), values))
+        assert np.array_equal(fq.fq_kv4_unpack(pk, 1, T, values).cpu().numpy().reshape(N, K), q)
+
+
 def test_pack_every_code_at_every_position(fq):
     N, K = 64, 256
     base = (np.arange(N)[:, None] * 5 + np.arange(K)[None, :] * 3)
