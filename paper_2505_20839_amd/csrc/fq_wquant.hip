@@ -31,25 +31,43 @@ __device__ __forceinline__ int fqw_log2_over_7(unsigned bits) {
     return frac >= 0x600000u ? E - 2 : E - 3;
 }
 
+// Consecutive bands of `step` rows of W, one 16-byte load per lane each (`lane_off`: the lane's bytes inside a band): a wave
+// keeps a ring of them in flight and asks for the next band as soon as it has used one, so that the reading never
+// pauses (workgroups that fetch a batch, work on it and fetch the next do so in step, and the memory idles in between:
+// 11008 x 4096 channel means: 37.9 instead of 34.1 us).  Rows past N lie behind the descriptor's range and read as zeros.
+struct fqw_bands {
+    const uint16_t* p;
+    long long left;                                       // bytes from p to the end of W
+    long long band;                                       // bytes of a band
+    __device__ __forceinline__ fqw_bands(const uint16_t* W, int N, int K, int k0, int step)
+        : p(W + k0), left(((long long)N * K - k0) * 2), band((long long)step * K * 2) {}
+    __device__ __forceinline__ fq_v4i next(unsigned lane_off) {
+        const long long n = left < 0 ? 0 : left < 0xFFFFFF00ll ? left : 0xFFFFFF00ll;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, (int)(unsigned)n, 0x00020000);
+        p += band / 2;
+        left -= band;
+        return __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, lane_off, 0, 0));
+    }
+};
+#define FQW_OOB 0xFFFFFFF0u                               // an offset behind any range
+
 }  // namespace
 
 // ---- channel-wise absmean scaling ------------------------------------------------------------------
-// One workgroup of 16 waves per 32 input channels (a column sum has to stay inside one workgroup to keep its
-// order fixed without a scratch buffer, so the bytes in flight come from the workgroup's size).  16 lanes cover
-// the 32 channels of a row (a dword = two channels each), so a wave reads 4 rows per instruction and the 16
-// waves 64; FQW_CAS_UNROLL such loads are in flight per lane.  FP64 sums, combined in a fixed order: the result
-// does not depend on timing.
+// FP64 sums over the rows of a channel, combined in a fixed order: the result does not depend on timing.  A column sum
+// stays inside one workgroup (there is no scratch buffer for partial sums).
+//
+// Any W: 16 waves per 32 input channels; 16 lanes cover the 32 channels of a row (a dword = two channels each), so a
+// wave reads 4 rows per instruction and the 16 waves 64; FQW_CAS_UNROLL such loads are in flight per lane.
 #define FQW_CAS_UNROLL 16
 #define FQW_CAS_THREADS 1024
-// LPR lanes per row (2 channels each): 16 -> 32 channels per workgroup.  (8 -> 16 channels and twice the workgroups
-// is slower, 57 against 35 us on 11008 x 4096: four workgroups then fetch every 128-byte line.)
-template <int LPR>
+#define FQW_CAS_LPR 16                                    // lanes per row
 __global__ __launch_bounds__(FQW_CAS_THREADS) void fq_cas_scales_kernel(const uint16_t* __restrict__ W, float target,
                                                             float* __restrict__ lambda, int N, int K) {
-    constexpr int FQW_CAS_ROWS = FQW_CAS_THREADS / LPR, CH = 2 * LPR;
+    constexpr int FQW_CAS_ROWS = FQW_CAS_THREADS / FQW_CAS_LPR, CH = 2 * FQW_CAS_LPR;
     __shared__ double part[FQW_CAS_ROWS][CH];
-    const int sub = threadIdx.x / LPR;                    // which of the rows of a pass
-    const int k = blockIdx.x * CH + 2 * (threadIdx.x % LPR);
+    const int sub = threadIdx.x / FQW_CAS_LPR;            // which of the rows of a pass
+    const int k = blockIdx.x * CH + 2 * (threadIdx.x % FQW_CAS_LPR);
     const bool two = k + 1 < K, one = k < K;              // K may be odd: the last channel then loads 2 bytes
     double s0 = 0.0, s1 = 0.0;
     for (int n0 = sub; n0 < N; n0 += FQW_CAS_ROWS * FQW_CAS_UNROLL) {
@@ -71,8 +89,8 @@ __global__ __launch_bounds__(FQW_CAS_THREADS) void fq_cas_scales_kernel(const ui
             s1 += (double)fabsf(fqw_bf16((unsigned short)(w[u] >> 16)));
         }
     }
-    part[sub][2 * (threadIdx.x % LPR)] = s0;
-    part[sub][2 * (threadIdx.x % LPR) + 1] = s1;
+    part[sub][2 * (threadIdx.x % FQW_CAS_LPR)] = s0;
+    part[sub][2 * (threadIdx.x % FQW_CAS_LPR) + 1] = s1;
     __syncthreads();
     if (threadIdx.x < CH && blockIdx.x * CH + (int)threadIdx.x < K) {
         double t = 0.0;
@@ -83,55 +101,74 @@ __global__ __launch_bounds__(FQW_CAS_THREADS) void fq_cas_scales_kernel(const ui
     }
 }
 
-// The same for rows in 16-byte steps (K a multiple of 8, W 16-byte aligned), 64 channels per workgroup: a workgroup
-// then reads whole 128-byte lines (with 32 channels two workgroups fetch each line, and the memory side moved the
-// matrix twice: 35 us; with 16 channels four times: 57 us), 8 lanes x 16 bytes per row, 8 rows per wave-level load,
-// and keeps FQW_CASW_UNROLL of them in flight per lane -- with K / 64 workgroups (64 for K = 4096) it is the bytes in
-// flight per workgroup that set the rate.  The 8 rows of a wave are added by shuffles, the 16 waves through LDS, both
-// in a fixed order.
+// Rows in 16-byte steps (K a multiple of 8, W 16-byte aligned; every weight matrix): 8 * LPR channels per workgroup, LPR
+// lanes x 16 bytes per row, 64 / LPR rows per wave-level load, FQW_CASW_UNROLL of them in flight per lane.  With fewer
+// than 8 lanes per row several workgroups read every 128-byte line; they are given neighbouring turns on one XCD (workgroup
+// b runs on XCD b % 8), so that its L2 fetches the line once (on different XCDs the memory side moved the matrix twice
+// or four times, which used to cap this at 32 channels).  |bf16| becomes FP64 by its bits alone: shifted to the top of
+// the double's exponent and fraction it is the value times 2^-896, subnormals included (the double is subnormal
+// then, in the same steps), so an element costs two integer instructions and an FP64 addition, no conversion; all sums
+// carry that factor, which comes off exactly at the end.
 #define FQW_CASW_UNROLL 8
-#define FQW_CASW_ROWS 128
-__global__ __launch_bounds__(8 * FQW_CASW_ROWS) void fq_cas_scales_wide_kernel(const uint16_t* __restrict__ W, float target,
+#define FQW_CASW_THREADS 1024
+template <int CTRL>
+__device__ __forceinline__ double fqw_dpp_f64(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false));
+}
+
+template <int LPR>
+__global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_scales_wide_kernel(const uint16_t* __restrict__ W, float target,
                                                                               float* __restrict__ lambda, int N, int K) {
-    __shared__ double part[16][64];
+    constexpr int ROWS = FQW_CASW_THREADS / LPR, CH = 8 * LPR, SHARE = 8 / LPR;
+    __shared__ double part[64][CH];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int sub = threadIdx.x >> 3;                     // which of the 128 rows of a pass
-    const int k = blockIdx.x * 64 + 8 * (lane & 7);
+    const int sub = threadIdx.x / LPR;                    // which of the rows of a pass
+    const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const int k0 = ((j / SHARE) * 8 + x) * 64 + (j % SHARE) * CH;
+    const int k = k0 + 8 * (lane % LPR);
+    if (k0 >= K) return;
     const bool on = k < K;                                // (K % 8 == 0: the 8 channels are inside or outside together)
     double s[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) s[i] = 0.0;
-    for (int n0 = sub; n0 < N; n0 += FQW_CASW_ROWS * FQW_CASW_UNROLL) {
-        fq_v4i w[FQW_CASW_UNROLL];
+    fqw_bands bands(W, N, K, k0, ROWS);
+    const unsigned lane_off = on ? (unsigned)sub * (unsigned)K * 2u + 16u * (threadIdx.x % LPR) : FQW_OOB;
+    fq_v4i w[FQW_CASW_UNROLL];
+#pragma unroll
+    for (int u = 0; u < FQW_CASW_UNROLL; ++u) w[u] = bands.next(lane_off);
+    for (int n0 = 0; n0 < N; n0 += ROWS * FQW_CASW_UNROLL) {
 #pragma unroll
         for (int u = 0; u < FQW_CASW_UNROLL; ++u) {
-            const int n = n0 + FQW_CASW_ROWS * u;
-            w[u] = (fq_v4i){0, 0, 0, 0};
-            if (n < N && on) w[u] = __builtin_nontemporal_load(reinterpret_cast<const fq_v4i*>(W + (size_t)n * K + k));
-        }
-#pragma unroll
-        for (int u = 0; u < FQW_CASW_UNROLL; ++u)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const unsigned word = (unsigned)w[u][i];
-                s[2 * i] += (double)__uint_as_float((word << 16) & 0x7FFF0000u);     // |bf16| as FP32, exact in FP64
-                s[2 * i + 1] += (double)__uint_as_float(word & 0x7FFF0000u);
+                s[2 * i] += __hiloint2double((int)((word << 13) & 0x0FFFE000u), 0);
+                s[2 * i + 1] += __hiloint2double((int)((word >> 3) & 0x0FFFE000u), 0);
             }
+            w[u] = bands.next(lane_off);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
+    // the rows of a wave are added inside its four 16-lane rows by rotations (lanes LPR apart hold the same channels; DPP:
+    // shuffles through LDS took 3 us), the rest through LDS, all in a fixed order
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 8; ++i) {
+        if (LPR <= 2) s[i] += fqw_dpp_f64<0x4E>(s[i]);    // quad_perm [2,3,0,1]
+        if (LPR <= 4) s[i] += fqw_dpp_f64<0x124>(s[i]);   // row_ror:4
+        s[i] += fqw_dpp_f64<0x128>(s[i]);                 // row_ror:8
+    }
+    if ((lane & 15) < LPR) {
 #pragma unroll
-        for (int m = 8; m < 64; m <<= 1) s[i] += __shfl_xor(s[i], m, 64);
-    if (lane < 8) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) part[wave][8 * lane + i] = s[i];
+        for (int i = 0; i < 8; ++i) part[4 * wave + (lane >> 4)][8 * (lane & 15) + i] = s[i];
     }
     __syncthreads();
-    if (threadIdx.x < 64 && blockIdx.x * 64 + (int)threadIdx.x < K) {
+    if ((int)threadIdx.x < CH && k0 + (int)threadIdx.x < K) {
         double t = 0.0;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) t += part[r][threadIdx.x];
-        lambda[blockIdx.x * 64 + threadIdx.x] =
+#pragma unroll 16
+        for (int r = 0; r < 64; ++r) t += part[r][threadIdx.x];
+        t *= 0x1p+896;
+        lambda[k0 + threadIdx.x] =
             t == 0.0 ? 1.0f : (float)((double)target / (t / (double)N));            // an all-zero channel keeps 1
     }
 }
@@ -165,40 +202,46 @@ __device__ __forceinline__ int fqw_pts_resolve(unsigned vmin, unsigned vmax) {
 
 // Thread t works on the 16-byte chunk (8 weights) t % (K / 8) of the rows t / (K / 8), + rows_par, ...: its 8
 // input channels never change, so their lambda sit in registers, and neighbouring threads read neighbouring
-// chunks.  FQW_PTS_UNROLL rows are in flight per thread.
-#ifndef FQW_PTS_UNROLL
-#define FQW_PTS_UNROLL 4
-#endif
-__global__ __launch_bounds__(256) void fq_pts_stats_kernel(const uint16_t* __restrict__ W,
+// chunks.  FQW_PTS_UNROLL rows are in flight per thread.  One workgroup per compute unit: they all end together
+// and close with two atomics each, which queue up (11008 x 4096, all three launches: 24.8 us with 256 workgroups of
+// 1024 threads, 29.0 with 512 of 512, 43.9 with 1024 of 256; counting the workgroups in, so that the last one resolves n
+// and the third launch goes, cost 12 us more than that launch; 37 us with 512 workgroups that fetch four rows at a time).
+#define FQW_PTS_UNROLL 6
+#define FQW_PTS_THREADS 1024
+#define FQW_PTS_WGS 256
+__global__ __launch_bounds__(FQW_PTS_THREADS) void fq_pts_stats_kernel(const uint16_t* __restrict__ W,
                                                            const float* __restrict__ lambda,
                                                            unsigned* __restrict__ stats,
                                                            int N, int K, int rows_par) {
-    unsigned vmin = 0xFFFFFFFFu, vmax = 0u;
+    __shared__ unsigned red[FQW_PTS_THREADS / 64][2];
+    unsigned vmin = 0xFFFFFFFFu, vmax = 0u;               // vmin: the smallest non-zero pattern minus 1
     const int KC = K / 8;
-    const unsigned t = blockIdx.x * 256u + threadIdx.x;
+    const unsigned t = blockIdx.x * (unsigned)FQW_PTS_THREADS + threadIdx.x;
     const int r0 = (int)(t / (unsigned)KC), cc = (int)(t % (unsigned)KC);
     float lam[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) lam[i] = lambda ? lambda[8 * cc + i] : 1.0f;
-    for (int n0 = r0; n0 < N && r0 < rows_par; n0 += FQW_PTS_UNROLL * rows_par) {
-        fq_v4i w[FQW_PTS_UNROLL];
+    fqw_bands bands(W, N, K, 0, rows_par);
+    const unsigned lane_off = r0 < rows_par ? (unsigned)r0 * (unsigned)K * 2u + 16u * (unsigned)cc : FQW_OOB;
+    fq_v4i w[FQW_PTS_UNROLL];
+#pragma unroll
+    for (int u = 0; u < FQW_PTS_UNROLL; ++u) w[u] = bands.next(lane_off);
+    for (int n0 = 0; n0 < N; n0 += FQW_PTS_UNROLL * rows_par) {
 #pragma unroll
         for (int u = 0; u < FQW_PTS_UNROLL; ++u) {
-            const int n = n0 + u * rows_par;
-            w[u] = (fq_v4i){0, 0, 0, 0};                  // zeros change neither statistic
-            if (n < N) w[u] = *reinterpret_cast<const fq_v4i*>(W + ((size_t)n * KC + cc) * 8);
-        }
-#pragma unroll
-        for (int u = 0; u < FQW_PTS_UNROLL; ++u)
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const unsigned word = (unsigned)w[u][i >> 1];
-                float v = fqw_bf16((unsigned short)((i & 1) ? (word >> 16) : (word & 0xFFFFu)));
-                if (lambda) v *= lam[i];
+                float v = __uint_as_float((i & 1) ? (word & 0xFFFF0000u) : (word << 16));
+                v *= lam[i];                              // (exact where there is no lambda)
                 const unsigned b = __float_as_uint(v) & 0x7FFFFFFFu;
-                vmin = (b != 0u && b < vmin) ? b : vmin;
-                vmax = (b < FQW_BAND0_END && b > vmax) ? b : vmax;
+                vmin = b - 1u < vmin ? b - 1u : vmin;     // (a zero wraps to the largest number)
+                const unsigned below = b < FQW_BAND0_END ? b : 0u;
+                vmax = below > vmax ? below : vmax;
             }
+            w[u] = bands.next(lane_off);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -206,7 +249,6 @@ __global__ __launch_bounds__(256) void fq_pts_stats_kernel(const uint16_t* __res
         vmin = lo < vmin ? lo : vmin;
         vmax = hi > vmax ? hi : vmax;
     }
-    __shared__ unsigned red[4][2];
     if ((threadIdx.x & 63) == 0) {
         red[threadIdx.x >> 6][0] = vmin;
         red[threadIdx.x >> 6][1] = vmax;
@@ -215,13 +257,13 @@ __global__ __launch_bounds__(256) void fq_pts_stats_kernel(const uint16_t* __res
     if (threadIdx.x == 0) {
         unsigned m0 = red[0][0], m1 = red[0][1];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) {
+        for (int w = 1; w < FQW_PTS_THREADS / 64; ++w) {
             m0 = red[w][0] < m0 ? red[w][0] : m0;
             m1 = red[w][1] > m1 ? red[w][1] : m1;
         }
+        if (m0 != 0xFFFFFFFFu) m0 += 1u;
         // only the atomics that would change a statistic (the plain reads may be stale: that costs at most an
-        // atomic that changes nothing): thousands of atomics on two addresses would otherwise take longer than
-        // reading the matrix
+        // atomic that changes nothing)
         const volatile unsigned* seen = stats;
         if (m0 < seen[0]) atomicMin(&stats[0], m0);
         if (m1 > seen[1]) atomicMax(&stats[1], m1);
@@ -233,89 +275,118 @@ __global__ void fq_pts_resolve_kernel(const unsigned* __restrict__ stats, int* _
 }
 
 // ---- group-wise INT4 quantisation ------------------------------------------------------------------
-// 16 lanes per group of 128 weights (8 neighbouring weights = 16 bytes per lane): a wave quantises four
-// groups, a workgroup sixteen.
+// 16 lanes per group of 128 weights (8 neighbouring weights = 16 bytes per lane): a wave quantises four groups at a time,
+// FQW_QW_UNROLL times, all of them requested before the first is worked on (11008 x 4096: 37.6 us with a division per
+// weight, 32.9 / 30.9 / 32.8 with 1 / 2 / 4 at a time).  Bound by HBM (3 bytes per weight) once
+// the quotient is short: a full IEEE division per weight (about eleven instructions) made it VALU bound.  With r = the
+// correctly rounded 1 / sigma8 (one division per group), q0 = v * r, the exact residual e = fma(-q0, sigma8, v) and
+// q1 = fma(e, r, q0), rint(q1) equals rint of the IEEE quotient for every FP32 v and every E4M3 sigma8 (a host program
+// checks all of them; sigma8 has four significant bits, and a power of two moves nothing).  v is cut to
+// +-16 sigma8 first, which changes no code (they end at -8 and 7) and keeps the residual finite.
+#define FQW_QW_UNROLL 2
 __global__ __launch_bounds__(256) void fq_quantize_weights_kernel(const uint16_t* __restrict__ W,
                                                                   const float* __restrict__ lambda, int n_pts,
                                                                   int sigma_rne, int8_t* __restrict__ q,
                                                                   uint8_t* __restrict__ gs, size_t groups, int K) {
-    const size_t grp = (size_t)blockIdx.x * 16u + (threadIdx.x >> 4);
-    if (grp >= groups) return;                            // whole 16-lane teams leave together
-    const size_t e0 = grp * FQ_GROUP + 8 * (threadIdx.x & 15);   // K is a multiple of 128: a group never straddles rows
-    const fq_v4i w = *reinterpret_cast<const fq_v4i*>(W + e0);
+    const size_t grp0 = (size_t)blockIdx.x * (16u * FQW_QW_UNROLL) + (threadIdx.x >> 4);
     const float p2n = __uint_as_float((unsigned)(n_pts + 127) << 23);    // 2^n, 0 <= n <= 126
-    float v[8];
+    const int sub = threadIdx.x & 15;
+    fq_v4i w[FQW_QW_UNROLL];
+    fq_v4f l0[FQW_QW_UNROLL], l1[FQW_QW_UNROLL];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const unsigned word = (unsigned)w[i >> 1];
-        v[i] = fqw_bf16((unsigned short)((i & 1) ? (word >> 16) : (word & 0xFFFFu)));
-    }
-    if (lambda) {
-        const int k = (int)(e0 % (size_t)K);
-        const fq_v4f l0 = *reinterpret_cast<const fq_v4f*>(lambda + k), l1 = *reinterpret_cast<const fq_v4f*>(lambda + k + 4);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[i] *= l0[i];
-            v[4 + i] *= l1[i];
+    for (int u = 0; u < FQW_QW_UNROLL; ++u) {
+        const size_t grp = grp0 + 16u * u < groups ? grp0 + 16u * u : groups - 1;   // (past the end: repeated, not stored)
+        const size_t e0 = grp * FQ_GROUP + 8 * sub;       // K is a multiple of 128: a group never straddles rows
+        w[u] = *reinterpret_cast<const fq_v4i*>(W + e0);
+        if (lambda) {
+            const int k = (int)(grp % (size_t)(K / FQ_GROUP)) * FQ_GROUP + 8 * sub;
+            l0[u] = *reinterpret_cast<const fq_v4f*>(lambda + k);
+            l1[u] = *reinterpret_cast<const fq_v4f*>(lambda + k + 4);
         }
     }
-    float vmax = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        v[i] *= p2n;
-        vmax = fmaxf(vmax, fabsf(v[i]));
-    }
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, o, 64));
-    const float sigma = fminf(vmax / 7.0f, 448.0f);
-    unsigned code = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(sigma, sigma, 0, false) & 0xFFu;   // nearest even
-    float s8 = __builtin_amdgcn_cvt_f32_fp8((int)code, 0);
-    if (!sigma_rne && s8 > sigma) {                       // toward zero: one code down (positive codes are ordered)
-        code -= 1u;
-        s8 = __builtin_amdgcn_cvt_f32_fp8((int)code, 0);
-    }
-    unsigned out[2] = {0u, 0u};
-    if (s8 > 0.f) {
+    for (int u = 0; u < FQW_QW_UNROLL; ++u) {
+        const size_t grp = grp0 + 16u * u;
+        float v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int c = (int)fminf(fmaxf(rintf(v[i] / s8), -8.f), 7.f);
+            const unsigned word = (unsigned)w[u][i >> 1];
+            v[i] = __uint_as_float((i & 1) ? (word & 0xFFFF0000u) : (word << 16));
+        }
+        if (lambda) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[i] *= l0[u][i];
+                v[4 + i] *= l1[u][i];
+            }
+        }
+        float vmax = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            v[i] *= p2n;
+            vmax = fmaxf(vmax, fabsf(v[i]));
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, o, 64));
+        const float sigma = fminf(vmax / 7.0f, 448.0f);
+        unsigned code = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(sigma, sigma, 0, false) & 0xFFu;   // nearest even
+        float s8 = __builtin_amdgcn_cvt_f32_fp8((int)code, 0);
+        if (!sigma_rne && s8 > sigma) {                   // toward zero: one code down (positive codes are ordered)
+            code -= 1u;
+            s8 = __builtin_amdgcn_cvt_f32_fp8((int)code, 0);
+        }
+        unsigned out[2] = {0u, 0u};
+        const float r = s8 > 0.f ? 1.0f / s8 : 0.f, cut = 16.0f * s8;    // (sigma8 = 0: every code comes out 0)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float x = fminf(fmaxf(v[i], -cut), cut);
+            const float q0 = x * r;
+            const float q1 = fmaf(fmaf(-q0, s8, x), r, q0);
+            const int c = (int)fminf(fmaxf(rintf(q1), -8.f), 7.f);
             out[i >> 2] |= (unsigned)(c & 0xFF) << (8 * (i & 3));
         }
+        if (grp < groups) {
+            *reinterpret_cast<fq_v2i*>(q + grp * FQ_GROUP + 8 * sub) = (fq_v2i){(int)out[0], (int)out[1]};
+            if (sub == 0) gs[grp] = (uint8_t)code;
+        }
     }
-    *reinterpret_cast<fq_v2i*>(q + e0) = (fq_v2i){(int)out[0], (int)out[1]};
-    if ((threadIdx.x & 15) == 0) gs[grp] = (uint8_t)code;
 }
 
 void fq_launch_cas_scales(const uint16_t* W, float target, float* lambda, int N, int K, hipStream_t stream) {
-#ifndef FQW_CAS_LPR
-#define FQW_CAS_LPR 16
-#endif
-    // whole lines per workgroup where K / 64 workgroups are enough to cover half the chip (measured, N x K: 4096 x 11008
-    // 34.3 -> 19.1 us; 11008 x 4096, 64 workgroups: 35.1 -> 42.3, where the conversions to FP64 bound a compute unit)
-    if ((K % 8) == 0 && (reinterpret_cast<uintptr_t>(W) % 16) == 0 && 2 * ((K + 63) / 64) >= fq_device_cus()) {
-        hipLaunchKernelGGL(fq_cas_scales_wide_kernel, dim3((unsigned)((K + 63) / 64)), dim3(8 * FQW_CASW_ROWS), 0, stream, W, target, lambda, N, K);
+    if ((K % 8) == 0 && (reinterpret_cast<uintptr_t>(W) % 16) == 0) {
+        // channels per workgroup.  Whole lines where they give more than half the compute units a workgroup (N x K: 4096 x
+        // 11008 21.3 us; 32 channels 29.4, 16 channels 33.1), 32 channels from a third of them on (14336 x 8192: 58.1;
+        // 64 channels 62.4, 16 channels 81.7), else 16 (11008 x 4096: 33.6; 32 channels 39.7, 64 channels 44.5)
+        const int lines = (K + 63) / 64, rounds = (lines + 7) / 8;      // (64 channels = a 128-byte line of a row)
+        const int cus = fq_device_cus();
+        if (2 * lines > cus)
+            hipLaunchKernelGGL(fq_cas_scales_wide_kernel<8>, dim3((unsigned)(8 * rounds)), dim3(FQW_CASW_THREADS), 0, stream, W, target, lambda, N, K);
+        else if (3 * lines >= cus)
+            hipLaunchKernelGGL(fq_cas_scales_wide_kernel<4>, dim3((unsigned)(16 * rounds)), dim3(FQW_CASW_THREADS), 0, stream, W, target, lambda, N, K);
+        else
+            hipLaunchKernelGGL(fq_cas_scales_wide_kernel<2>, dim3((unsigned)(32 * rounds)), dim3(FQW_CASW_THREADS), 0, stream, W, target, lambda, N, K);
         return;
     }
     constexpr int CH = 2 * FQW_CAS_LPR;
-    hipLaunchKernelGGL(fq_cas_scales_kernel<FQW_CAS_LPR>, dim3((unsigned)((K + CH - 1) / CH)), dim3(FQW_CAS_THREADS), 0, stream, W, target, lambda, N, K);
+    hipLaunchKernelGGL(fq_cas_scales_kernel, dim3((unsigned)((K + CH - 1) / CH)), dim3(FQW_CAS_THREADS), 0, stream, W, target, lambda, N, K);
 }
 
 void fq_launch_pts_exponent(const uint16_t* W, const float* lambda, int* n_out, int N, int K, hipStream_t stream) {
     unsigned* stats = reinterpret_cast<unsigned*>(n_out) + 8;     // the caller's 64 bytes: [0] = n, [8..9] statistics
-    // about 512 workgroups' worth of threads (two per compute unit: few enough that their closing atomics stay cheap),
-    // as whole rows of K / 8 chunk columns
+    // about FQW_PTS_WGS workgroups' worth of threads, as whole rows of K / 8 chunk columns
     const int KC = K / 8;
-    int rows_par = (512 * 256 + KC - 1) / KC;
+    int rows_par = (FQW_PTS_WGS * FQW_PTS_THREADS + KC - 1) / KC;
     if (rows_par > N) rows_par = N;
-    const size_t blocks = ((size_t)KC * (size_t)rows_par + 255u) / 256u;
+    const size_t blocks = ((size_t)KC * (size_t)rows_par + FQW_PTS_THREADS - 1u) / FQW_PTS_THREADS;
     hipLaunchKernelGGL(fq_pts_init_kernel, dim3(1), dim3(64), 0, stream, stats);
-    hipLaunchKernelGGL(fq_pts_stats_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, W, lambda, stats, N, K, rows_par);
+    hipLaunchKernelGGL(fq_pts_stats_kernel, dim3((unsigned)blocks), dim3(FQW_PTS_THREADS), 0, stream, W, lambda, stats, N, K,
+                       rows_par);
     hipLaunchKernelGGL(fq_pts_resolve_kernel, dim3(1), dim3(64), 0, stream, stats, n_out);
 }
 
 void fq_launch_quantize_weights(const uint16_t* W, const float* lambda, int n_pts, bool sigma_rne, int8_t* q,
                                 uint8_t* gs, int N, int K, hipStream_t stream) {
     const size_t groups = (size_t)N * (size_t)(K / FQ_GROUP);
-    hipLaunchKernelGGL(fq_quantize_weights_kernel, dim3((unsigned)((groups + 15u) / 16u)), dim3(256), 0, stream, W, lambda,
+    hipLaunchKernelGGL(fq_quantize_weights_kernel, dim3((unsigned)((groups + 16u * FQW_QW_UNROLL - 1u) / (16u * FQW_QW_UNROLL))), dim3(256), 0, stream, W, lambda,
                        n_pts, sigma_rne ? 1 : 0, q, gs, groups, K);
 }

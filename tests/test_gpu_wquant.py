@@ -142,3 +142,54 @@ def test_full_size_gate_up_matrix(fq):
         nz = v[v > 0]
         return bool(np.all(nz * 2.0 ** m >= T)) or bool(np.any((v * 2.0 ** m >= 224) & (v * 2.0 ** m < 448)))
     assert stops(n) and not any(stops(m) for m in range(n))
+
+# (channels per workgroup: 64 from K = 16384 on, 32 from 8192, else 16, on a 256-unit device; a last line of 8 channels)
+@pytest.mark.parametrize("N,K", [(1, 8), (513, 72), (1025, 4104), (130, 8200), (40, 16392)])
+def test_cas_scales_of_whole_lines_and_remainders(fq, N, K):
+    """Row counts around a pass of the workgroup and channel counts around a 128-byte line, with subnormal, huge and zero
+    weights: the FP64 mean of every channel."""
+    Wb = workloads.draw_weights(N, K, seed=N + K, channel_spread=2.0)
+    Wb[:, 0] = 1                                               # the smallest bf16 subnormal throughout
+    Wb[:, 1] = 0x7F7F                                          # the largest bf16
+    Wb[:, 2] = 0x8000                                          # -0
+    Wb[0, 3::5] |= 0x8000
+    lam = fq.fq_cas_scales(to_gpu_bf16(Wb), 0.02).cpu().numpy()
+    mean = np.abs(oracle.bf16_bits_to_f64(Wb)).mean(axis=0)
+    with np.errstate(divide="ignore", over="ignore"):
+        want = np.where(mean == 0, 1.0, 0.02 / mean).astype(np.float32)
+    assert np.array_equal(lam, want) or np.max(np.abs(lam.view(np.int32).astype(np.int64) - want.view(np.int32))) <= 1
+
+
+@pytest.mark.parametrize("N,K", [(1, 128), (63, 128), (65, 384), (4097, 128)])
+def test_pts_exponent_counts_every_workgroup(fq, N, K):
+    """The workgroup that finishes last resolves n: the smallest non-zero and the largest element placed in every corner,
+    twice in a row into fresh scratch (whatever the memory held before)."""
+    Wb = np.full((N, K), 0x3F80, np.uint16)                    # 1.0 throughout
+    base = int(fq.fq_pts_exponent(to_gpu_bf16(Wb))[0])
+    assert base == oracle.pts_exponent(Wb)
+    for pos in [(0, 0), (0, K - 1), (N - 1, 0), (N - 1, K - 1), (N // 2, K // 2)]:
+        Wc = Wb.copy(); Wc[pos] = 0x43DF                       # 446: the largest bf16 below 7 * 2^6
+        for _ in range(2):
+            assert int(fq.fq_pts_exponent(to_gpu_bf16(Wc))[0]) == oracle.pts_exponent(Wc)
+
+
+@pytest.mark.parametrize("N,K,n_pts", [(1, 128, 0), (15, 640, 3), (67, 128, 126), (129, 384, 7)])
+def test_quantize_weights_at_the_edges_of_a_workgroup(fq, N, K, n_pts):
+    """Group counts around the 64 a workgroup takes, quotients on and beside the rounding boundaries, huge v * 2^n, zero
+    groups and groups whose scale casts to zero: codes and scales bit for bit."""
+    rng = np.random.default_rng(N * K)
+    Wb = workloads.draw_weights(N, K, seed=N, channel_spread=1.0)
+    g = Wb.reshape(-1, 128)
+    g[0] = 0
+    for i in range(g.shape[0]):
+        if i % 3 == 1:                                         # half-integer multiples of an E4M3 scale, one bf16 step around
+            step = np.float32(2.0) ** int(rng.integers(-6, 3)) * np.float32(rng.integers(8, 16)) / 8
+            x = workloads.f32_to_bf16_bits((rng.integers(-14, 15, 128) * step / 2).astype(np.float32))
+            x[0] = workloads.f32_to_bf16_bits(np.array([7 * step], np.float32))[0]
+            g[i] = np.where((x & 0x7FFF) > 0, x + rng.integers(-1, 2, 128).astype(np.uint16), x)
+        elif i % 7 == 2:
+            g[i] = 1                                           # scale casts to zero
+    for rne in (False, True):
+        q, gs = fq.fq_quantize_weights(to_gpu_bf16(Wb), None, n_pts, rne)
+        qr, gr = oracle.quantize_weights(Wb, None, n_pts, sigma_rne=rne)
+        assert np.array_equal(gs.cpu().numpy(), gr) and np.array_equal(q.cpu().numpy(), qr)
