@@ -288,11 +288,7 @@ int fq_quantize_weights(const uint16_t *W_bf16, const float *lambda, int n_pts, 
  *                    p_scale [H][R] FP32, v_scale [H][T], O_bf16 [H][R][128].  R <= 32, T >= 1.
  *                    Any T, ldp and alignment of P_fp8 and v_scale (a cache that grows by a token
  *                    per step has any length); rows in 16-byte steps save a load in ten.
- *   fq_kv4_output_ws the same with device scratch: fq_kv4_output_workspace_bytes(H,R,T) bytes, 16-byte
- *                    aligned (FQ_ERR_MEMORY if smaller; 0 or NULL: as fq_kv4_output).  With it, few heads
- *                    with long caches are cut into token slices, and a second kernel adds the
- *                    slices' FP32 sums in a fixed order (the last bits differ from the
- *                    unsliced sum's).
+ *                    (fireq_kv4_ws.h has the form with device scratch, for few heads with long caches.)
  * H <= 65535.  Status codes as above; a zero H, R (or T for the scores) is a successful no-op.
  */
 size_t fq_kv4_packed_bytes(int H, int T, int values);
@@ -304,10 +300,6 @@ int fq_kv4_scores(const uint8_t *Q_fp8, const float *q_scale, const uint8_t *K_p
 int fq_kv4_output(const uint8_t *P_fp8, const float *p_scale, const uint8_t *V_packed,
                   const uint8_t *v_scale, uint16_t *O_bf16, int H, int R, int T, int ldp,
                   void *stream);
-size_t fq_kv4_output_workspace_bytes(int H, int R, int T);
-int fq_kv4_output_ws(const uint8_t *P_fp8, const float *p_scale, const uint8_t *V_packed,
-                     const uint8_t *v_scale, uint16_t *O_bf16, int H, int R, int T, int ldp,
-                     void *workspace, size_t workspace_bytes, void *stream);
 
 /*
  * Diagnostics (used by the tests; no kernel is launched).

@@ -1,6 +1,7 @@
 // C entry points of the W4A8-FP library: argument validation, kernel choice, launch.
 // Declarations and the contract of every call are in include/fireq.h.
 #include "../../include/fireq.h"
+#include "../../include/fireq_kv4_ws.h"
 #include "fq_common.h"
 #include "fq_kernels.h"
 
