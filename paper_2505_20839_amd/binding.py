@@ -3,10 +3,16 @@
 Every step of the path runs in the HIP kernels of ``libfireq.so``; torch is used for device
 memory and the current stream.  There is no CPU fallback: if the library cannot be loaded or a
 tensor is not on the GPU, the call raises.
+
+The calls of a running model marshal their arguments in native code (``_fq_marshal.so``, see its source); whatever that
+does not take -- another kind of tensor, a wrong shape, an argument to be refused -- comes back as None and goes through
+the Python form below it, which decides and raises.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional, Tuple
 
@@ -17,6 +23,12 @@ from . import build as _build
 GROUP = 128
 
 _lib = None
+_marshal = None
+
+# the C functions the marshalling calls, in the order it expects them
+_MARSHALLED = ("fq_quantize_act", "fq_quantize_act_ws", "fq_packed_weight_bytes", "fq_w4a8_gemm_workspace_bytes", "fq_w4a8_gemm_ws",
+               "fq_w4a8_gemm_swiglu_ws", "fq_w4a8_gemm_add_ws", "fq_w4a8_gemm_swiglu_quant_ws", "fq_w4a8_linear_workspace_bytes",
+               "fq_w4a8_linear_ws", "fq_kv4_packed_bytes", "fq_kv4_scores", "fq_kv4_output_workspace_bytes", "fq_kv4_output_ws")
 
 
 class FireqError(RuntimeError):
@@ -101,6 +113,21 @@ def lib() -> ctypes.CDLL:
     L.fq_status_string.argtypes = [ci]
     _lib = L
     return L
+
+
+def marshal():
+    """The native marshalling, bound to the loaded library (built in-tree on first use if it was never built)."""
+    global _marshal
+    if _marshal is None:
+        if not os.path.exists(_build.MARSHAL_PATH):
+            _build.build_marshal()
+        loader = importlib.machinery.ExtensionFileLoader("_fq_marshal", _build.MARSHAL_PATH)
+        m = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fq_marshal", loader))
+        loader.exec_module(m)
+        L = lib()
+        m.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _MARSHALLED))
+        _marshal = m
+    return _marshal
 
 
 def status_string(status: int) -> str:
@@ -207,6 +234,11 @@ def fq_quantize_act(X: torch.Tensor, workspace: Optional[torch.Tensor] = None) -
 
     With `workspace` (a device tensor of fq_w4a8_gemm_workspace_bytes(M, N, K) bytes or more) the call is
     fq_quantize_act_ws, which also prepares that workspace for fq_w4a8_gemm(..., workspace_prepared=True)."""
+    r = (_marshal or marshal()).quantize_act(X, workspace)
+    if r is not None:
+        if type(r) is int:
+            raise FireqError(r, "fq_quantize_act")
+        return r
     X = _dev(X, torch.bfloat16, "X")
     M, K = X.shape
     A = torch.empty((M, K), dtype=torch.uint8, device=X.device)
@@ -230,6 +262,11 @@ def fq_w4a8_gemm(A: torch.Tensor, a_scale: torch.Tensor, Wq_packed: torch.Tensor
     Calls fq_w4a8_gemm_ws; `workspace` (a device tensor of at least
     fq_w4a8_gemm_workspace_bytes(M, N, K) bytes) is allocated here when not given;
     `workspace_prepared` says that fq_quantize_act(X, workspace) has filled it for this A."""
+    r = (_marshal or marshal()).gemm(A, a_scale, Wq_packed, w_gscale, w_tscale, N, out, workspace, workspace_prepared)
+    if r is not None:
+        if type(r) is int:
+            raise FireqError(r, "fq_w4a8_gemm_ws")
+        return r
     A = _dev(A, torch.uint8, "A")
     a_scale = _dev(a_scale, torch.float32, "a_scale")
     Wq_packed = _dev(Wq_packed, torch.uint8, "Wq_packed")
@@ -264,6 +301,11 @@ def fq_w4a8_gemm_swiglu(A: torch.Tensor, a_scale: torch.Tensor, Wq_packed: torch
                         workspace_prepared: bool = False) -> torch.Tensor:
     """H[M,N/2] (bf16) = SiLU(gate) * up of the W4A8-FP GEMM whose N weight rows interleave gate (even)
     and up (odd) channels.  Calls fq_w4a8_gemm_swiglu_ws; workspace handling as in fq_w4a8_gemm."""
+    r = (_marshal or marshal()).gemm_swiglu(A, a_scale, Wq_packed, w_gscale, w_tscale, N, out, workspace, workspace_prepared)
+    if r is not None:
+        if type(r) is int:
+            raise FireqError(r, "fq_w4a8_gemm_swiglu_ws")
+        return r
     A = _dev(A, torch.uint8, "A")
     a_scale = _dev(a_scale, torch.float32, "a_scale")
     Wq_packed = _dev(Wq_packed, torch.uint8, "Wq_packed")
@@ -299,6 +341,12 @@ def fq_w4a8_gemm_swiglu_quant(A: torch.Tensor, a_scale: torch.Tensor, Wq_packed:
     """(H bf16 [M,N/2], H as E4M3 codes [M,N/2], float32 [M] scales): fq_w4a8_gemm_swiglu whose output also leaves
     quantised for the next layer, as fq_quantize_act would give it.  Calls fq_w4a8_gemm_swiglu_quant_ws;
     `next_workspace` (fq_w4a8_gemm_workspace_bytes(M, N', N/2) bytes or more) is prepared for a GEMM on the codes."""
+    r = (_marshal or marshal()).gemm_swiglu_quant(A, a_scale, Wq_packed, w_gscale, w_tscale, N, out, workspace, workspace_prepared,
+                                                  next_workspace)
+    if r is not None:
+        if type(r) is int:
+            raise FireqError(r, "fq_w4a8_gemm_swiglu_quant_ws")
+        return r
     A = _dev(A, torch.uint8, "A")
     a_scale = _dev(a_scale, torch.float32, "a_scale")
     Wq_packed = _dev(Wq_packed, torch.uint8, "Wq_packed")
@@ -337,6 +385,11 @@ def fq_w4a8_gemm_add(A: torch.Tensor, a_scale: torch.Tensor, Wq_packed: torch.Te
                      workspace_prepared: bool = False) -> torch.Tensor:
     """Y[M,N] (bf16) = GEMM + residual, rounded once.  Calls fq_w4a8_gemm_add_ws; `out` may be
     `residual` itself (in-place update); workspace handling as in fq_w4a8_gemm."""
+    r = (_marshal or marshal()).gemm_add(A, a_scale, Wq_packed, w_gscale, w_tscale, N, out, workspace, workspace_prepared, residual)
+    if r is not None:
+        if type(r) is int:
+            raise FireqError(r, "fq_w4a8_gemm_add_ws")
+        return r
     A = _dev(A, torch.uint8, "A")
     a_scale = _dev(a_scale, torch.float32, "a_scale")
     Wq_packed = _dev(Wq_packed, torch.uint8, "Wq_packed")
@@ -373,6 +426,11 @@ def fq_w4a8_linear(X: torch.Tensor, Wq_packed: torch.Tensor, w_gscale: torch.Ten
                    out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Y[M,N] (bf16) of a whole linear layer from bf16 activations X[M,K] (quantiser + GEMM; one kernel
     for M <= 6 and K <= 4096).  Calls fq_w4a8_linear_ws; the workspace is allocated here when not given."""
+    r = (_marshal or marshal()).linear(X, Wq_packed, w_gscale, w_tscale, N, out, workspace)
+    if r is not None:
+        if type(r) is int:
+            raise FireqError(r, "fq_w4a8_linear_ws")
+        return r
     X = _dev(X, torch.bfloat16, "X")
     Wq_packed = _dev(Wq_packed, torch.uint8, "Wq_packed")
     w_gscale = _dev(w_gscale, torch.uint8, "w_gscale")
@@ -397,7 +455,8 @@ def fq_w4a8_linear(X: torch.Tensor, Wq_packed: torch.Tensor, w_gscale: torch.Ten
 
 
 def fq_w4a8_gemm_workspace_bytes(M: int, N: int, K: int) -> int:
-    return int(lib().fq_w4a8_gemm_workspace_bytes(M, N, K))
+    r = (_marshal or marshal()).gemm_workspace_bytes(M, N, K)
+    return int(lib().fq_w4a8_gemm_workspace_bytes(M, N, K)) if r is None else r
 
 
 def fq_w4a8_gemm_plan(M: int, N: int, K: int, cus: int = 0) -> dict:
@@ -477,6 +536,11 @@ def fq_kv4_unpack(packed: torch.Tensor, H: int, T: int, values: bool) -> torch.T
 def fq_kv4_scores(Q: torch.Tensor, q_scale: torch.Tensor, K_packed: torch.Tensor, k_scale: torch.Tensor,
                   out_scale: float) -> torch.Tensor:
     """S[H,R,T] (bf16): FP8 queries [H,R,128] against a packed INT4 key cache with E4M3 scales [H,T]."""
+    r = (_marshal or marshal()).kv4_scores(Q, q_scale, K_packed, k_scale, out_scale)
+    if r is not None:
+        if type(r) is int:
+            raise FireqError(r, "fq_kv4_scores")
+        return r
     Q = _dev(Q, torch.uint8, "Q"); q_scale = _dev(q_scale, torch.float32, "q_scale")
     K_packed = _dev(K_packed, torch.uint8, "K_packed"); k_scale = _dev(k_scale, torch.uint8, "k_scale")
     H, R, D = Q.shape
@@ -494,6 +558,11 @@ def fq_kv4_scores(Q: torch.Tensor, q_scale: torch.Tensor, K_packed: torch.Tensor
 
 def fq_kv4_output(P: torch.Tensor, p_scale: torch.Tensor, V_packed: torch.Tensor, v_scale: torch.Tensor) -> torch.Tensor:
     """O[H,R,128] (bf16): FP8 probabilities [H,R,T] against a packed INT4 value cache with E4M3 scales [H,T]."""
+    r = (_marshal or marshal()).kv4_output(P, p_scale, V_packed, v_scale)
+    if r is not None:
+        if type(r) is int:
+            raise FireqError(r, "fq_kv4_output")
+        return r
     P = _dev(P, torch.uint8, "P"); p_scale = _dev(p_scale, torch.float32, "p_scale")
     V_packed = _dev(V_packed, torch.uint8, "V_packed"); v_scale = _dev(v_scale, torch.uint8, "v_scale")
     H, R, ldp = P.shape

@@ -1,4 +1,5 @@
-"""Builds the HIP library in-tree: ``csrc/*.hip`` -> ``paper_2505_20839_amd/libfireq.so`` (gfx950)."""
+"""Builds the HIP library in-tree: ``csrc/*.hip`` -> ``paper_2505_20839_amd/libfireq.so`` (gfx950), and the binding's
+argument marshalling: ``csrc/fq_marshal.cpp`` -> ``paper_2505_20839_amd/_fq_marshal.so`` (host code, a Python extension)."""
 from __future__ import annotations
 
 import glob
@@ -9,6 +10,7 @@ import sys
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libfireq.so")
+MARSHAL_PATH = os.path.join(PKG_DIR, "_fq_marshal.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -42,5 +44,28 @@ def build_library(verbose: bool = False) -> str:
     return LIB_PATH
 
 
+def build_marshal() -> str:
+    """Compile the argument marshalling against the installed torch and Python.  Always recompiles."""
+    import sysconfig
+
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    tmp = MARSHAL_PATH + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-isystem", inc, "-isystem",
+           os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(rocm, "include"), os.path.join(CSRC, "fq_marshal.cpp"), "-o", tmp,
+           "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        if os.path.exists(tmp):
+            os.remove(tmp)
+        raise RuntimeError("g++ failed:\n" + res.stdout)
+    os.replace(tmp, MARSHAL_PATH)
+    return MARSHAL_PATH
+
+
 if __name__ == "__main__":
     print(build_library(verbose="-v" in sys.argv))
+    print(build_marshal())

@@ -1,0 +1,179 @@
+"""The native argument marshalling against the Python form of every call: the same results, exceptions and messages for
+everything a caller may pass (the native form declines what it does not take, and the Python form then decides)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+class _Declines:
+    """Stands in for the native module: declines every call."""
+
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+@pytest.fixture(scope="module")
+def fq():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU: torch.cuda.is_available() is False")
+    from paper_2505_20839_amd import binding
+    binding.lib()
+    return binding
+
+
+def _both(fq, name, make):
+    """The outcome of a call through the native and through the Python form: (outputs as a list) or (exception type, text).
+    `make` builds the arguments anew for each."""
+    got = []
+    for stub in (None, _Declines()):
+        native = fq.marshal()
+        try:
+            if stub is not None:
+                fq._marshal = stub
+            args, kw = make()
+            try:
+                r = getattr(fq, name)(*args, **kw)
+                torch.cuda.synchronize()
+                got.append([t.clone() for t in (r if isinstance(r, tuple) else (r,))])
+            except Exception as e:                             # noqa: BLE001 (compared below)
+                got.append((type(e), str(e)))
+        finally:
+            fq._marshal = native
+    return got
+
+
+def _same(fq, name, make, fails=None):
+    a, b = _both(fq, name, make)
+    if fails is not None:
+        assert isinstance(a, tuple) and isinstance(b, tuple), (name, a, b)
+        assert a == b and issubclass(a[0], fails), (name, a, b)
+    else:
+        assert isinstance(a, list) and isinstance(b, list) and len(a) == len(b), (name, a, b)
+        for x, y in zip(a, b):
+            assert x.dtype == y.dtype and x.shape == y.shape and x.device == y.device and torch.equal(x, y), name
+
+
+class _Sub(torch.Tensor):
+    pass
+
+
+def _layer(fq, N, K, seed=0):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    q = torch.randint(-8, 8, (N, K), generator=g, device="cuda", dtype=torch.int8)
+    gs = torch.randint(0x10, 0x30, (N, K // 128), generator=g, device="cuda", dtype=torch.uint8)
+    return fq.fq_pack_weights(q), gs
+
+
+def _x(M, K, seed=1):
+    return torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(seed), device="cuda").bfloat16()
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 64, 256), (7, 96, 512), (40, 128, 1024), (130, 264, 1024), (0, 64, 256)])
+def test_linear_layer_calls(fq, M, N, K):
+    w, gs = _layer(fq, N, K)
+    x = _x(M, K)
+    out = lambda: torch.empty((M, N), dtype=torch.bfloat16, device="cuda")   # noqa: E731
+    for n in (N, np.int64(N)):
+        _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 0.5, n), {}))
+    for ts in (2, np.float32(0.5), torch.tensor(0.25)):
+        _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, ts, N), {}))
+    _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 1.0, N), {"out": out()}))
+    _same(fq, "fq_w4a8_linear", lambda: ((x.as_subclass(_Sub), w, gs, 1.0, N), {}))
+    need = fq.fq_w4a8_linear_workspace_bytes(M, N, K)
+    if need:
+        _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 1.0, N), {"workspace": torch.empty(need, dtype=torch.uint8, device="cuda")}))
+        _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 1.0, N), {"workspace": torch.empty(need // 4 + 4, dtype=torch.float32, device="cuda")}))
+        _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 1.0, N), {"workspace": torch.empty(16, dtype=torch.uint8, device="cuda")}), fq.FireqError)
+    for bad, exc in [((x.float(), w, gs, 1.0, N), TypeError), ((x.cpu(), w, gs, 1.0, N), TypeError), ((None, w, gs, 1.0, N), TypeError),
+                     ((x, w, gs, 1.0, N + 32), fq.FireqError), ((x, w[:-16], gs, 1.0, N), fq.FireqError),
+                     ((x, w.to(torch.int8), gs, 1.0, N), TypeError), ((x, w, gs, None, N), TypeError)]:
+        _same(fq, "fq_w4a8_linear", lambda: (bad, {}), exc)
+    if M > 1:
+        _same(fq, "fq_w4a8_linear", lambda: ((_x(K, M).t(), w, gs, 1.0, N), {}), ValueError)
+        _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 1.0, N), {"out": out()[:-1]}), fq.FireqError)
+        _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 1.0, N), {"out": out().float()}), TypeError)
+
+
+@pytest.mark.parametrize("M,N,K", [(3, 64, 256), (40, 128, 1024), (130, 272, 1024)])
+def test_quantiser_and_gemm_calls(fq, M, N, K):
+    w, gs = _layer(fq, N, K)
+    x, res = _x(M, K), _x(M, N, 2)
+    need = fq.fq_w4a8_gemm_workspace_bytes(M, N, K)
+    ws = torch.empty(max(need, 16), dtype=torch.uint8, device="cuda")
+    _same(fq, "fq_quantize_act", lambda: ((x,), {}))
+    _same(fq, "fq_quantize_act", lambda: ((x, ws), {}))
+    _same(fq, "fq_quantize_act", lambda: ((x[:, :4].contiguous(),), {}), fq.FireqError)
+    _same(fq, "fq_quantize_act", lambda: ((x.half(),), {}), TypeError)
+    A, s = fq.fq_quantize_act(x, ws)
+    for name, extra in (("fq_w4a8_gemm", ()), ("fq_w4a8_gemm_swiglu", ()), ("fq_w4a8_gemm_add", (res,)), ("fq_w4a8_gemm_swiglu_quant", ())):
+        ok = (A, s, w, gs, 1.0, N) + extra
+        _same(fq, name, lambda: (ok, {}))
+        _same(fq, name, lambda: (ok, {"workspace": ws, "workspace_prepared": need > 0}))
+        _same(fq, name, lambda: (ok, {"workspace": ws}))
+        _same(fq, name, lambda: (ok, {"workspace_prepared": True}))
+        _same(fq, name, lambda: (ok, {"out": torch.empty((M, N if "swiglu" not in name else N // 2), dtype=torch.bfloat16, device="cuda")}))
+        _same(fq, name, lambda: (ok, {"out": torch.empty((M, 8), dtype=torch.bfloat16, device="cuda")}), fq.FireqError)
+        _same(fq, name, lambda: ((A, s[:-1], w, gs, 1.0, N) + extra, {}), fq.FireqError)
+        _same(fq, name, lambda: ((A, s.double(), w, gs, 1.0, N) + extra, {}), TypeError)
+        _same(fq, name, lambda: ((A, s, w, gs[:-1], 1.0, N) + extra, {}), fq.FireqError)
+        if need:
+            _same(fq, name, lambda: (ok, {"workspace": ws[:16]}), fq.FireqError)
+            if M * K > 4096:
+                _same(fq, name, lambda: ((A.view(-1)[8:8 + (M - 1) * K].view(M - 1, K), s[1:], w, gs, 1.0, N) + tuple(e[1:] for e in extra), {}), fq.FireqError)
+    _same(fq, "fq_w4a8_gemm_add", lambda: ((A, s, w, gs, 1.0, N, res[:, :-1]), {}), Exception)
+    inplace = lambda: (lambda r: ((A, s, w, gs, 1.0, N, r), {"out": r}))(res.clone())   # noqa: E731
+    _same(fq, "fq_w4a8_gemm_add", inplace)
+    _same(fq, "fq_w4a8_gemm_swiglu", lambda: ((A, s, w, gs, 1.0, N - 1), {}), fq.FireqError)
+
+
+@pytest.mark.parametrize("H,R,T,ldp", [(1, 1, 1, 1), (2, 4, 130, 144), (8, 3, 9000, 9000)])
+def test_attention_operand_calls(fq, H, R, T, ldp):
+    g = torch.Generator(device="cuda").manual_seed(T)
+    u8 = lambda *sh: torch.randint(0, 0x60, sh, generator=g, device="cuda", dtype=torch.uint8)   # noqa: E731
+    codes = torch.randint(-8, 8, (H, T, 128), generator=g, device="cuda", dtype=torch.int8)
+    kp, vp = fq.fq_kv4_pack(codes, False), fq.fq_kv4_pack(codes, True)
+    Q, P, sc, f = u8(H, R, 128), u8(H, R, ldp), u8(H, T), torch.rand((H, R), generator=g, device="cuda")
+    _same(fq, "fq_kv4_scores", lambda: ((Q, f, kp, sc, 0.1), {}))
+    _same(fq, "fq_kv4_output", lambda: ((P, f, vp, sc), {}))
+    for name, ok in (("fq_kv4_scores", (Q, f, kp, sc, 0.1)), ("fq_kv4_output", (P, f, vp, sc))):
+        _same(fq, name, lambda: ((ok[0].cpu(),) + ok[1:], {}), TypeError)
+        _same(fq, name, lambda: ((ok[0], ok[1].double()) + ok[2:], {}), TypeError)
+        _same(fq, name, lambda: ((ok[0], ok[1], ok[2][:-1]) + ok[3:], {}), fq.FireqError)
+        _same(fq, name, lambda: ((ok[0], torch.cat([ok[1], ok[1]], 1)) + ok[2:], {}), fq.FireqError)
+    many = 65 if R == 1 else 33
+    _same(fq, "fq_kv4_scores", lambda: ((u8(H, 65, 128), torch.rand((H, 65), device="cuda"), kp, sc, 0.1), {}), fq.FireqError)
+    _same(fq, "fq_kv4_output", lambda: ((u8(H, many, ldp), torch.rand((H, many), device="cuda"), vp, sc), {}), fq.FireqError)
+
+
+def test_another_stream_and_a_torch_function_mode(fq):
+    """The native form runs on the current stream; under an active torch-function mode the Python form runs (the mode sees
+    its calls)."""
+    from torch.overrides import TorchFunctionMode
+
+    class Sees(TorchFunctionMode):
+        def __init__(self):
+            super().__init__()
+            self.names = []
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            self.names.append(getattr(func, "__name__", ""))
+            return func(*args, **(kwargs or {}))
+
+    w, gs = _layer(fq, 64, 256)
+    x = _x(4, 256)
+    want = fq.fq_w4a8_linear(x, w, gs, 1.0, 64)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        big = torch.randn((4096, 4096), device="cuda") @ torch.randn((4096, 4096), device="cuda")   # keeps the stream busy
+        y = fq.fq_w4a8_linear((x + 0 * big[0, 0].bfloat16()), w, gs, 1.0, 64)
+    side.synchronize()
+    assert torch.equal(y, want)
+    mode = Sees()
+    with mode:
+        y = fq.fq_w4a8_linear(x, w, gs, 1.0, 64)
+    torch.cuda.synchronize()
+    assert torch.equal(y, want) and "empty" in mode.names
