@@ -30,9 +30,10 @@ __device__ __forceinline__ fq_v8i fqs_join(fq_v4i lo, fq_v4i hi) {
 // The output channels are dealt out evenly, in multiples of 8, to one workgroup per compute unit
 // (N = 14336 on 256 units: 56 channels each), so that every unit streams the same number of weight
 // bytes and the whole matrix is requested at once.  A workgroup of 8 waves covers its channels with
-// NSUB <= 4 sub-tiles of 16 channels (the last one may be partly masked); the waves split K into
+// NSUB <= 7 sub-tiles of 16 channels (the last one may be partly masked; with at most 4 a layer of 28672 channels took
+// 1.75 rounds of workgroups); the waves split K into
 // eight contiguous slices, so each activation byte is read once per workgroup and each weight byte
-// once overall.  A wave requests the packed weights of its first 4, 8 or 12 groups before it computes
+// once overall.  A wave requests the packed weights of its first 4, 8, 12 or 16 groups before it computes
 // anything; with K = 4096 that is its whole share.
 // Every load is a raw buffer load: masked lanes carry an out-of-range offset (they fetch nothing
 // and read zero), group steps travel in the scalar offset, and the code has no branches between
@@ -42,6 +43,7 @@ __device__ __forceinline__ fq_v8i fqs_join(fq_v4i lo, fq_v4i hi) {
 // ---------------------------------------------------------------------------------------------
 #define FQS16_THREADS 512
 #define FQS16_WAVES 8
+#define FQS16_MAXCOLS 112                                 // channels of a workgroup (7 sub-tiles: 56 KiB of partial sums in LDS)
 #define FQS16_FUSED_MAX_M 6                               // rows up to which quantising inside the GEMM kernel pays (<= waves)
 #define FQS16_OOB 0xFFFFFF00u                             // beyond any 32-bit buffer size
 // byte `i` (0..3, compile-time) of a word of E4M3 codes -> float
@@ -55,8 +57,8 @@ __device__ __forceinline__ float fq_e4m3_byte_to_float(unsigned w, int i) {
 // WORDS: every wave's slice starts at a multiple of 4 groups and the scale rows are word-aligned, so
 // they are one aligned word; otherwise the two aligned words around them are fetched and shifted
 // into place when they are used.
-// A wave keeps a ring of BATCH groups in flight (4, 8 or 12: the shortest that holds a wave's slice,
-// at most 48 bytes of packed weights per lane): it requests the first BATCH groups of its slice at
+// A wave keeps a ring of BATCH groups in flight (4, 8, 12 or 16: the shortest that holds a wave's slice,
+// as far as the registers go): it requests the first BATCH groups of its slice at
 // once and re-requests each slot, for the group BATCH further on, as soon as it has used it.  Loads
 // return in order, so the ring is consumed in the order it was requested.
 template <int NSUB, bool WORDS, int BATCH_>
@@ -318,15 +320,11 @@ void fq_gemm_small16_kernel(
 
 namespace {
 
-template <int NSUB, bool WORDS, int BATCH>
-void fq_launch_small16b(bool rounds, unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
+template <int NSUB, bool WORDS, bool ROUNDS, int BATCH>
+void fq_launch_small16b(unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
                         const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols, int swiglu, const uint16_t* R) {
-    if (rounds)
-        hipLaunchKernelGGL((fq_gemm_small16_kernel<NSUB, WORDS, true, BATCH>), dim3(grid), dim3(FQS16_THREADS), 0, stream,
-                           A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R, static_cast<float*>(nullptr));
-    else
-        hipLaunchKernelGGL((fq_gemm_small16_kernel<NSUB, WORDS, false, BATCH>), dim3(grid), dim3(FQS16_THREADS), 0, stream,
-                           A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R, static_cast<float*>(nullptr));
+    hipLaunchKernelGGL((fq_gemm_small16_kernel<NSUB, WORDS, ROUNDS, BATCH>), dim3(grid), dim3(FQS16_THREADS), 0, stream,
+                       A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R, static_cast<float*>(nullptr));
 }
 
 // The fused form (bf16 activations in, quantised by the kernel): slices of at most four groups per wave
@@ -347,18 +345,30 @@ bool fq_launch_linear16w(int per, unsigned grid, hipStream_t stream, const uint1
     return true;
 }
 
-// Ring depth: the shortest of 4, 8, 12 that holds a wave's slice of `per` groups, at most 12 / 8 / 4
-// groups for 1 / 2 / 3-4 sub-tiles (registers); longer slices go round the ring (ROUNDS).
+// Ring depth: the shortest of 4, 8, 12, 16 that holds a wave's slice of `per` groups, as far as 200 registers go (a slot
+// takes 8 for the activations and 4 per sub-tile: 16 / 12 / 8 / 4 groups for 1 / 2 / 3-4 / 5-7 sub-tiles); longer slices
+// go round a ring of 12 / 8 / 4 groups (ROUNDS), which exposes the latency of the refills: 16 x 4096 x 14336, 14 groups
+// per wave, 15.1 us round a ring of 12, 11.7 us with all of them requested at once.  5-7 sub-tiles are only taken
+// for slices of at most 4 groups (fqs_shape_of).
 template <int NSUB, bool WORDS>
 void fq_launch_small16w(int per, unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
                         const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols, int swiglu, const uint16_t* R) {
-    constexpr int CAP = NSUB == 1 ? 12 : (NSUB == 2 ? 8 : 4);
-    if (CAP >= 12 && per > 8)
-        fq_launch_small16b<NSUB, WORDS, CAP >= 12 ? 12 : CAP>(per > 12, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
-    else if (CAP >= 8 && per > 4)
-        fq_launch_small16b<NSUB, WORDS, CAP >= 8 ? 8 : CAP>(per > 8, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
-    else
-        fq_launch_small16b<NSUB, WORDS, 4>(per > 4, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+    constexpr int CAP = NSUB == 1 ? 16 : NSUB == 2 ? 12 : NSUB <= 4 ? 8 : 4, RING = NSUB == 1 ? 12 : NSUB == 2 ? 8 : 4;
+    if constexpr (NSUB <= 4) {
+        if (per > CAP)
+            return fq_launch_small16b<NSUB, WORDS, true, RING>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+        if (per > 4 && per > CAP - 4)
+            return fq_launch_small16b<NSUB, WORDS, false, CAP>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+        if constexpr (CAP >= 12) {
+            if (per > CAP - 8 && per > 4)
+                return fq_launch_small16b<NSUB, WORDS, false, CAP - 4>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+        }
+        if constexpr (CAP >= 16) {
+            if (per > 4)
+                return fq_launch_small16b<NSUB, WORDS, false, CAP - 8>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+        }
+    }
+    fq_launch_small16b<NSUB, WORDS, false, 4>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
 }
 
 template <int NSUB>
@@ -380,6 +390,8 @@ void fq_launch_small16(bool words, int per, unsigned grid, hipStream_t stream, c
 
 template <int MT, int NSUB>
 struct fqsm_ring {
+    // (deeper rings -- a whole slice of 4 groups at MT = 3 -- are no faster: 37 x 14336 x 4096 12.1 -> 12.7 us, 20 x 4096 x
+    // 11008 13.2 -> 15.7)
     static constexpr int BATCH = MT >= 3 ? 2 : (MT == 2 ? 4 : (NSUB <= 2 ? 8 : 4));
     fq_v4i bq[BATCH][NSUB];
     fq_v4i aq[BATCH][MT][2];
@@ -646,8 +658,9 @@ bool fq_launch_smallm_mt(int nsub, int per, unsigned grid, hipStream_t stream, c
 namespace {
 
 // How a small-M problem is cut up: channels per workgroup (an even share of N over the compute units,
-// a multiple of 8, at most 64), workgroups, groups per wave, sub-tiles of 16 channels, and whether the
-// scale bytes of four consecutive groups are one aligned word.
+// a multiple of 8, at most `max_cols`, or 64 where a wave's slice is longer than 4 groups; more channels than that go in
+// several even rounds: 16 x 28672 x 4096 15.0 us in 448 workgroups of 64 channels, 13.3 us in 256 of 112), workgroups, groups per wave,
+// sub-tiles of 16 channels, and whether the scale bytes of four consecutive groups are one aligned word.
 struct fqs_shape {
     int cols;
     unsigned grid;
@@ -655,14 +668,17 @@ struct fqs_shape {
     bool words;
 };
 
-fqs_shape fqs_shape_of(int N, int K, const uint8_t* gs) {
+fqs_shape fqs_shape_of(int N, int K, const uint8_t* gs, int max_cols) {
     const int cus = fq_device_cus();
     fqs_shape sh;
-    sh.cols = ((N + cus - 1) / cus + 7) & ~7;
-    sh.cols = sh.cols < 8 ? 8 : (sh.cols > 64 ? 64 : sh.cols);
-    sh.grid = (unsigned)((N + sh.cols - 1) / sh.cols);
     const int G = K / FQ_GROUP;
     sh.per = (G + FQS16_WAVES - 1) / FQS16_WAVES;
+    if (sh.per > 4 && max_cols > 64) max_cols = 64;
+    const int rounds = (int)(((long long)N + (long long)cus * max_cols - 1) / ((long long)cus * max_cols));
+    const long long wgs = (long long)rounds * cus;
+    sh.cols = (int)((N + wgs - 1) / wgs + 7) & ~7;
+    sh.cols = sh.cols < 8 ? 8 : (sh.cols > max_cols ? max_cols : sh.cols);
+    sh.grid = (unsigned)((N + sh.cols - 1) / sh.cols);
     sh.nsub = (sh.cols + 15) / 16;
     sh.words = (sh.per % 4 == 0) && (G % 4 == 0) && ((reinterpret_cast<uintptr_t>(gs) & 3) == 0);
     return sh;
@@ -677,7 +693,7 @@ bool fq_linear_small_serves(int M, int K) {
 bool fq_launch_linear_small(const uint16_t* X, float* a_scale_out, const uint8_t* wp, const uint8_t* gs, float tscale,
                             uint16_t* Y, int M, int N, int K, hipStream_t stream) {
     if (!fq_linear_small_serves(M, K)) return false;
-    const fqs_shape sh = fqs_shape_of(N, K, gs);
+    const fqs_shape sh = fqs_shape_of(N, K, gs, FQS16_MAXCOLS);
     switch (2 * sh.nsub + (sh.words ? 1 : 0)) {
         case 2: return fq_launch_linear16w<1, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
         case 3: return fq_launch_linear16w<1, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
@@ -686,14 +702,20 @@ bool fq_launch_linear_small(const uint16_t* X, float* a_scale_out, const uint8_t
         case 6: return fq_launch_linear16w<3, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
         case 7: return fq_launch_linear16w<3, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
         case 8: return fq_launch_linear16w<4, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        default: return fq_launch_linear16w<4, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 9: return fq_launch_linear16w<4, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 10: return fq_launch_linear16w<5, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 11: return fq_launch_linear16w<5, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 12: return fq_launch_linear16w<6, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 13: return fq_launch_linear16w<6, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 14: return fq_launch_linear16w<7, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        default: return fq_launch_linear16w<7, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
     }
 }
 
 bool fq_launch_gemm_small(const uint8_t* A, const float* a_scale, const uint8_t* wp, const uint8_t* gs,
                           float tscale, uint16_t* Y, int M, int N, int K, bool swiglu_epilogue, const uint16_t* R, hipStream_t stream) {
     const int swiglu = swiglu_epilogue ? 1 : 0;
-    const fqs_shape sh = fqs_shape_of(N, K, gs);
+    const fqs_shape sh = fqs_shape_of(N, K, gs, M <= 16 ? FQS16_MAXCOLS : FQSM_MAXCOLS);
     const int cols = sh.cols, per = sh.per, nsub = sh.nsub;
     const unsigned grid = sh.grid;
     if (M <= 16) {
@@ -702,7 +724,10 @@ bool fq_launch_gemm_small(const uint8_t* A, const float* a_scale, const uint8_t*
             case 1: fq_launch_small16<1>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
             case 2: fq_launch_small16<2>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
             case 3: fq_launch_small16<3>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
-            default: fq_launch_small16<4>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
+            case 4: fq_launch_small16<4>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
+            case 5: fq_launch_small16<5>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
+            case 6: fq_launch_small16<6>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
+            default: fq_launch_small16<7>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
         }
         return true;
     }

@@ -688,3 +688,34 @@ def test_table_mode_full_size_and_what_it_costs(fq):
     yl, ye = oracle.bf16_bits_to_f64(Yl[rows]), oracle.bf16_bits_to_f64(Ye[rows])
     rel_gpu = np.linalg.norm(yl - ye) / np.linalg.norm(ye)
     assert 0.01 < rel_oracle < 0.04 and abs(rel_gpu - rel_oracle) < 0.002, (rel_gpu, rel_oracle)
+
+
+# M <= 16: ring depths 4, 8, 12, 16 and a ring gone round (K), 1 to 7 sub-tiles of 16 channels per workgroup (N on a 256-unit
+# device, the last sub-tile partly masked), scale rows that are words and that are not; 16 < M <= 64: one request of the
+# whole slice and rings gone round, with 1 to 4 sub-tiles.
+SMALL_RING_SHAPES = [(16, 96, 14336), (3, 40, 16384), (5, 64, 17408), (16, 6144, 11008), (9, 8192, 6144), (2, 8192, 12800),
+                     (16, 14336, 8192), (7, 11008, 6272), (16, 16392, 8320), (16, 22016, 1024), (12, 24584, 512), (4, 28672, 640),
+                     (1, 30000, 256), (6, 28672, 4096), (37, 14336, 2048), (48, 11008, 1152), (64, 96, 4096), (33, 8192, 4224), (20, 4096, 8192)]
+
+
+@pytest.mark.parametrize("shape", SMALL_RING_SHAPES)
+def test_small_m_rings_and_sub_tiles(fq, shape):
+    """Every ring depth and sub-tile count of the M <= 64 kernels, plain and with the residual, on sampled channels (all of
+    the first and last workgroup's) against the oracle; the whole layer in one call gives the same bits."""
+    M, N, K = shape
+    d = workloads.draw(M, N, K, seed=M + N + K, outlier_frac=0.01, gs_lo=0.01, gs_hi=0.2)
+    packed, gs = fq.fq_pack_weights(_gpu(d["q"])), _gpu(d["gscale"])
+    X = to_gpu_bf16(d["X_bf16"])
+    A, s = fq.fq_quantize_act(X)
+    Rb = workloads.draw_residual(M, N, scale=workloads.RESIDUAL_SCALE, seed=N)
+    Y = fq.fq_w4a8_gemm(A, s, packed, gs, d["w_tscale"], N)
+    YR = fq.fq_w4a8_gemm_add(A, s, packed, gs, d["w_tscale"], N, to_gpu_bf16(Rb))
+    YL = fq.fq_w4a8_linear(X, packed, gs, d["w_tscale"], N)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, YL)
+    pick = np.unique(np.concatenate([np.arange(min(N, 128)), np.arange(max(0, N - 128), N), np.arange(0, N, 37)]))
+    A_ref, s_ref = A.cpu().numpy(), s.cpu().numpy()
+    Yr, B = oracle.w4a8_gemm(A_ref, s_ref, d["q"][pick], d["gscale"][pick], d["w_tscale"], want_bound=True)
+    check_gemm(bf16_bits_from_gpu(Y)[:, pick], Yr, B, "small %s" % (shape,), frobenius=M * len(pick) >= 4000)
+    Yr, B = oracle.w4a8_gemm_add(A_ref, s_ref, d["q"][pick], d["gscale"][pick], d["w_tscale"], Rb[:, pick], want_bound=True)
+    check_gemm(bf16_bits_from_gpu(YR)[:, pick], Yr, B, "small + residual %s" % (shape,), frobenius=M * len(pick) >= 4000)
