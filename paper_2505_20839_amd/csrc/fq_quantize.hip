@@ -13,20 +13,6 @@
 #include "fq_common.h"
 #include "fq_kernels.h"
 
-#define FQ_Q_THREADS 256
-#define FQ_Q_MAXCHUNK 8        // 16-byte chunks (8 bf16) a thread keeps in registers: K <= 16384
-
-__device__ __forceinline__ float fq_block_max(float v, float* red) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) red[wave] = v;
-    __syncthreads();
-    float r = red[0];
-#pragma unroll
-    for (int i = 1; i < FQ_Q_THREADS / 64; ++i) r = fmaxf(r, red[i]);
-    return r;
-}
 
 // Sum of the eight E4M3 values of two words of codes.
 __device__ __forceinline__ float fq_sum8(fq_v2i o) {
@@ -35,81 +21,97 @@ __device__ __forceinline__ float fq_sum8(fq_v2i o) {
     return ((a[0] + a[1]) + (b[0] + b[1])) + ((c[0] + c[1]) + (d[0] + d[1]));
 }
 
-// One workgroup per row.  The row is read once into registers when it fits (K <= 16384),
-// otherwise it is read a second time for the conversion pass.
+// WPR waves per row, up to CH chunks (of 16 bytes, 8 bf16) of it per thread in registers between the search for the
+// largest magnitude and the conversion, so that the row is read once; longer rows are read a second time (REREAD).
+// Bound by HBM (3 bytes per element).  What keeps it from there is how many rows a compute unit has under way: with
+// one wave per row (K <= 4096) no row waits at a barrier for its other waves.
+// Workgroups of max(4, WPR) waves.
 // ZP: also write, for every group of 128 codes of the row, the zero-point term the large-M GEMM
 // kernels take from their workspace: -2^-6 * (sum of the group's E4M3 values) as two fp16 terms,
 // laid out as that kernel reads it ([plane][group / 8][M rows][group % 8]; groups up to the next
 // multiple of 16 are zero).  Needs K % 128 == 0 and the row in registers.
 // KNOWN: the row's largest magnitude is not searched for but taken from a_scale[m], where the kernel that
 // produced X left it (the fused gate/up epilogue); the scale replaces it there.
-template <bool ZP, bool KNOWN = false>
-__global__ __launch_bounds__(FQ_Q_THREADS) void fq_quantize_kernel(const uint16_t* __restrict__ X,
+template <int WPR, int CH, bool ZP, bool KNOWN, bool REREAD>
+__global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(const uint16_t* __restrict__ X,
                                                                    uint8_t* __restrict__ A,
                                                                    float* __restrict__ a_scale, int K,
                                                                    uint16_t* __restrict__ planes, int M) {
-    __shared__ float red[FQ_Q_THREADS / 64];
-    __shared__ __attribute__((aligned(16))) uint16_t zrow[2][FQ_Q_THREADS * FQ_Q_MAXCHUNK / 16 + 16];   // [plane][group]
-    const int m = blockIdx.x;
-    const fq_v4i* x = reinterpret_cast<const fq_v4i*>(X + (size_t)m * K);
-    fq_v2i* a = reinterpret_cast<fq_v2i*>(A + (size_t)m * K);
+    static_assert(!(ZP && REREAD), "the zero-point terms are summed from registers");
+    constexpr int WAVES = WPR > 4 ? WPR : 4, ROWS = WAVES / WPR, T = 64 * WPR;
+    constexpr int MAXG = T * CH / 16 + 16;           // groups of a row, padded
+    __shared__ float red[WAVES];
+    __shared__ __attribute__((aligned(16))) uint16_t zrow[ZP ? ROWS : 1][2][ZP ? MAXG : 8];   // [row][plane][group]
+    const int row = (int)threadIdx.x / T, t = (int)threadIdx.x % T;
+    const int m = blockIdx.x * ROWS + row;
     if (ZP && M <= FQ_KSPLIT_MAX_M) {                     // the arrival counters behind the planes start at zero
         const int G = K >> 7, C2 = 2 * ((G + 15) >> 4);
         unsigned* counters = reinterpret_cast<unsigned*>(planes + (size_t)2 * C2 * M * 8);
-        for (int i = blockIdx.x * FQ_Q_THREADS + threadIdx.x; i < FQ_KSPLIT_COUNTERS; i += gridDim.x * FQ_Q_THREADS)
+        for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < FQ_KSPLIT_COUNTERS; i += gridDim.x * blockDim.x)
             counters[i] = 0u;
     }
+    const bool on = m < M;                                // (rows past M repeat the last one and store nothing)
     const int nchunk = K >> 3;
-    const bool in_regs = nchunk <= FQ_Q_THREADS * FQ_Q_MAXCHUNK;
-    fq_v4i keep[FQ_Q_MAXCHUNK];
+    const fq_v4i* x = reinterpret_cast<const fq_v4i*>(X + (size_t)(on ? m : M - 1) * K);
+    fq_v2i* a = reinterpret_cast<fq_v2i*>(A + (size_t)(on ? m : M - 1) * K);
+    fq_v4i keep[CH];
     float amax = 0.f;
-    if (in_regs) {
+    auto search = [&](fq_v4i v) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < FQ_Q_MAXCHUNK; ++i) {
-            int c = threadIdx.x + i * FQ_Q_THREADS;
+        for (int j = 0; j < 4; ++j) {
+            const unsigned w = (unsigned)v[j];
+            amax = fmaxf(amax, fmaxf(fabsf(fq_bf16_lo(w)), fabsf(fq_bf16_hi(w))));
+        }
+    };
+    if (!REREAD) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {               // all of the thread's chunks are requested before the first is used
+            // (past the row's end its last chunk again, which changes no maximum and is not stored: the branch is the
+            // same for the whole wave)
+            const int c = t + i * T < nchunk ? t + i * T : nchunk - 1;
             keep[i] = (fq_v4i){0, 0, 0, 0};
-            if (c < nchunk) {
-                keep[i] = x[c];
-                if (!KNOWN) {
+            if (CH <= 2 || i * T < nchunk) keep[i] = x[c];
+        }
+        if (!KNOWN) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        unsigned w = (unsigned)keep[i][j];
-                        amax = fmaxf(amax, fmaxf(fabsf(fq_bf16_lo(w)), fabsf(fq_bf16_hi(w))));
-                    }
-                }
-            }
+            for (int i = 0; i < CH; ++i) search(keep[i]);
         }
     } else {
-        for (int c = threadIdx.x; c < nchunk; c += FQ_Q_THREADS) {
-            fq_v4i v = x[c];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                unsigned w = (unsigned)v[j];
-                amax = fmaxf(amax, fmaxf(fabsf(fq_bf16_lo(w)), fabsf(fq_bf16_hi(w))));
-            }
-        }
+        for (int c = t; c < nchunk; c += T) search(x[c]);
     }
     if (KNOWN) {                                          // (read by one thread before anyone overwrites it below)
-        if (threadIdx.x == 0) red[0] = a_scale[m];
+        if (t == 0) red[row * WPR] = a_scale[on ? m : M - 1];
         __syncthreads();
-        amax = red[0];
+        amax = red[row * WPR];
     } else {
-        amax = fq_block_max(amax, red);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+        if (WPR > 1) {
+            if ((t & 63) == 0) red[row * WPR + (t >> 6)] = amax;
+            __syncthreads();
+            amax = red[row * WPR];
+#pragma unroll
+            for (int i = 1; i < WPR; ++i) amax = fmaxf(amax, red[row * WPR + i]);
+        }
     }
     const float s = (amax == 0.f) ? 1.0f : amax / 448.0f;
-    if (threadIdx.x == 0) a_scale[m] = s;
+    if (t == 0 && on) a_scale[m] = s;
     const float rcp = 1.0f / s;
-    // One choice of quotient per row (s is the same in every thread of the workgroup): the range the
+    // One choice of quotient per row (s is the same in every thread of a wave): the range the
     // short quotient was checked on, else the full division; straight-line code either way.
     auto convert = [&](auto fast_tag) __attribute__((always_inline)) {
-    constexpr bool FAST = decltype(fast_tag)::value;
-    if (in_regs) {
+        constexpr bool FAST = decltype(fast_tag)::value;
+        if (REREAD) {
+            for (int c = t; c < nchunk; c += T) a[c] = fq_quant8<FAST>(x[c], s, rcp);
+            return;
+        }
 #pragma unroll
-        for (int i = 0; i < FQ_Q_MAXCHUNK; ++i) {
-            int c = threadIdx.x + i * FQ_Q_THREADS;
+        for (int i = 0; i < CH; ++i) {
+            const int c = t + i * T;
+            if (CH > 2 && i * T >= nchunk) break;         // (the same for the whole wave)
             if (c < nchunk) {
                 const fq_v2i o = fq_quant8<FAST>(keep[i], s, rcp);
-                a[c] = o;
+                if (on) a[c] = o;
                 if (ZP) {
                     // a group is 16 consecutive chunks = 16 consecutive lanes (nchunk is a multiple of 16,
                     // so a group's lanes are all here or all absent)
@@ -118,52 +120,66 @@ __global__ __launch_bounds__(FQ_Q_THREADS) void fq_quantize_kernel(const uint16_
                     z += __shfl_xor(z, 2, 64);
                     z += __shfl_xor(z, 4, 64);
                     z += __shfl_xor(z, 8, 64);
-                    if ((threadIdx.x & 15) == 0) {
+                    if ((t & 15) == 0) {
                         z *= -0.015625f;
                         const _Float16 hi = (_Float16)z;                  // round to nearest even
                         const _Float16 lo = (_Float16)(z - (float)hi);    // the difference is exact in FP32
-                        zrow[0][c >> 4] = __builtin_bit_cast(uint16_t, hi);
-                        zrow[1][c >> 4] = __builtin_bit_cast(uint16_t, lo);
+                        zrow[row][0][c >> 4] = __builtin_bit_cast(uint16_t, hi);
+                        zrow[row][1][c >> 4] = __builtin_bit_cast(uint16_t, lo);
                     }
                 }
             }
         }
-        if (ZP) {
-            // padding groups are zero; then one 16-byte store per (plane, 8 groups) of this row
-            const int G = K >> 7, C2 = 2 * ((G + 15) >> 4);
-            for (int g = G + threadIdx.x; g < 8 * C2; g += FQ_Q_THREADS) zrow[0][g] = zrow[1][g] = 0;
-            __syncthreads();
-            for (int t = threadIdx.x; t < 2 * C2; t += FQ_Q_THREADS) {
-                const int plane = t / C2, unit = t - plane * C2;
-                const fq_v4i v = *reinterpret_cast<const fq_v4i*>(&zrow[plane][8 * unit]);
-                *reinterpret_cast<fq_v4i*>(planes + (((size_t)plane * C2 + unit) * M + m) * 8) = v;
-            }
-        }
-    } else {
-        for (int c = threadIdx.x; c < nchunk; c += FQ_Q_THREADS) a[c] = fq_quant8<FAST>(x[c], s, rcp);
-    }
     };
     if (__builtin_amdgcn_readfirstlane((int)fq_scale_is_fast(s))) convert(std::true_type());
     else convert(std::false_type());
+    if (ZP) {
+        // padding groups are zero; then one 16-byte store per (plane, 8 groups) of a row, rows of a workgroup side by side
+        const int G = K >> 7, C2 = 2 * ((G + 15) >> 4);
+        for (int g = G + t; g < 8 * C2; g += T) zrow[row][0][g] = zrow[row][1][g] = 0;
+        __syncthreads();
+        for (int i = threadIdx.x; i < 2 * C2 * ROWS; i += 64 * WAVES) {
+            const int r = i % ROWS, pu = i / ROWS, plane = pu / C2, unit = pu - plane * C2, mm = blockIdx.x * ROWS + r;
+            if (mm < M)
+                *reinterpret_cast<fq_v4i*>(planes + (((size_t)plane * C2 + unit) * M + mm) * 8) =
+                    *reinterpret_cast<const fq_v4i*>(&zrow[r][plane][8 * unit]);
+        }
+    }
 }
+
+namespace {
+
+// Waves per row.  Many rows: the fewest that hold a row in registers (4096 columns each; 8192 x 4096 with zero-point terms
+// 21.6 us, 28.1 with four).  Few rows: four, or sixteen for a handful of long rows, where the time of one row is the time
+// of the call (32 x 32016 5.7 us; 10.9 with four waves that read the row twice).
+template <bool ZP, bool KNOWN>
+void fq_launch_quantize_as(const uint16_t* X, uint8_t* A, float* a_scale, int M, int K, uint16_t* planes, hipStream_t stream) {
+#define FQ_QUANTIZE(WPR_, CH_, REREAD_) \
+    hipLaunchKernelGGL((fq_quantize_kernel<WPR_, CH_, ZP, KNOWN, REREAD_>), dim3((unsigned)((M + (WPR_ > 4 ? 1 : 4 / WPR_) - 1) / (WPR_ > 4 ? 1 : 4 / WPR_))), \
+                       dim3(WPR_ > 4 ? 64 * WPR_ : 256), 0, stream, X, A, a_scale, K, planes, M)
+    if (K > 16 * 4096) {
+        if constexpr (!ZP) FQ_QUANTIZE(16, 8, true);
+    } else if (K > 4 * 4096) FQ_QUANTIZE(16, 8, false);
+    else if (K > 4096 && M <= 64) FQ_QUANTIZE(16, 2, false);
+    else if (K <= 4096 && M <= 1536) FQ_QUANTIZE(4, 2, false);
+    else if (K > 2 * 4096 || M <= 512) FQ_QUANTIZE(4, 8, false);
+    else if (K > 4096) FQ_QUANTIZE(2, 8, false);
+    else FQ_QUANTIZE(1, 8, false);
+#undef FQ_QUANTIZE
+}
+
+}  // namespace
 
 void fq_launch_quantize(const uint16_t* X, uint8_t* A, float* a_scale, int M, int K, hipStream_t stream) {
-    hipLaunchKernelGGL(fq_quantize_kernel<false>, dim3((unsigned)M), dim3(FQ_Q_THREADS), 0, stream, X, A, a_scale, K,
-                       static_cast<uint16_t*>(nullptr), M);
+    fq_launch_quantize_as<false, false>(X, A, a_scale, M, K, nullptr, stream);
 }
 
-bool fq_quantize_can_write_zero_point(int K) {
-    return (K % FQ_GROUP) == 0 && (K >> 3) <= FQ_Q_THREADS * FQ_Q_MAXCHUNK;
-}
+bool fq_quantize_can_write_zero_point(int K) { return (K % FQ_GROUP) == 0 && K <= 16384; }
 
 void fq_launch_quantize_known(const uint16_t* X, uint8_t* A, float* a_scale, int M, int K, void* workspace,
                               hipStream_t stream) {
-    if (workspace)
-        hipLaunchKernelGGL((fq_quantize_kernel<true, true>), dim3((unsigned)M), dim3(FQ_Q_THREADS), 0, stream, X, A, a_scale,
-                           K, static_cast<uint16_t*>(workspace), M);
-    else
-        hipLaunchKernelGGL((fq_quantize_kernel<false, true>), dim3((unsigned)M), dim3(FQ_Q_THREADS), 0, stream, X, A, a_scale,
-                           K, static_cast<uint16_t*>(nullptr), M);
+    if (workspace) fq_launch_quantize_as<true, true>(X, A, a_scale, M, K, static_cast<uint16_t*>(workspace), stream);
+    else           fq_launch_quantize_as<false, true>(X, A, a_scale, M, K, nullptr, stream);
 }
 
 __global__ void fq_fill_zero_kernel(unsigned* __restrict__ p, int n) {
@@ -177,6 +193,5 @@ void fq_launch_fill_zero(unsigned* p, int n, hipStream_t stream) {
 
 void fq_launch_quantize_zp(const uint16_t* X, uint8_t* A, float* a_scale, int M, int K, void* workspace,
                            hipStream_t stream) {
-    hipLaunchKernelGGL(fq_quantize_kernel<true>, dim3((unsigned)M), dim3(FQ_Q_THREADS), 0, stream, X, A, a_scale, K,
-                       static_cast<uint16_t*>(workspace), M);
+    fq_launch_quantize_as<true, false>(X, A, a_scale, M, K, static_cast<uint16_t*>(workspace), stream);
 }

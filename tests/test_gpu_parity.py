@@ -719,3 +719,30 @@ def test_small_m_rings_and_sub_tiles(fq, shape):
     check_gemm(bf16_bits_from_gpu(Y)[:, pick], Yr, B, "small %s" % (shape,), frobenius=M * len(pick) >= 4000)
     Yr, B = oracle.w4a8_gemm_add(A_ref, s_ref, d["q"][pick], d["gscale"][pick], d["w_tscale"], Rb[:, pick], want_bound=True)
     check_gemm(bf16_bits_from_gpu(YR)[:, pick], Yr, B, "small + residual %s" % (shape,), frobenius=M * len(pick) >= 4000)
+
+
+# waves per row (1, 2, 4, 16) by K and M, the last chunk and the last rows of a workgroup partly there, rows in two passes
+@pytest.mark.parametrize("M,K", [(1, 8), (5, 4088), (1537, 4096), (1539, 136), (1601, 264), (65, 4104), (513, 8192), (514, 4224), (600, 8200), (64, 4104),
+                                 (3, 16384), (66, 16384), (2, 16392), (5, 65536), (2, 65544)])
+def test_quantizer_rows_of_every_split(fq, M, K):
+    """Codes and scales bit for bit, a zero row and a row whose largest element is its last one among them; with whole groups
+    also the prepared workspace: the GEMM on it gives what the GEMM that prepares its own gives."""
+    rng = np.random.default_rng(M * 7 + K)
+    Xb = workloads.f32_to_bf16_bits(rng.standard_normal((M, K)).astype(np.float32))
+    Xb[M // 2] = 0
+    Xb[M - 1, K - 1] = 0x4480                                  # 1024
+    A, s = fq.fq_quantize_act(to_gpu_bf16(Xb))
+    torch.cuda.synchronize()
+    A_ref, s_ref = oracle.quantize_act(Xb)
+    assert np.array_equal(s.cpu().numpy(), s_ref)
+    assert np.array_equal(A.cpu().numpy() & 0x7F, A_ref & 0x7F)
+    if K % 128 == 0 and M > 64:
+        N = 64
+        q = torch.from_numpy(rng.integers(-8, 8, (N, K), dtype=np.int8)).cuda()
+        gs = torch.from_numpy(rng.integers(1, 0x40, (N, K // 128)).astype(np.uint8)).cuda()
+        ws = torch.empty(fq.fq_w4a8_gemm_workspace_bytes(M, N, K), dtype=torch.uint8, device="cuda")
+        A2, s2 = fq.fq_quantize_act(to_gpu_bf16(Xb), workspace=ws)
+        assert torch.equal(A, A2) and torch.equal(s, s2)
+        packed = fq.fq_pack_weights(q)
+        Y = fq.fq_w4a8_gemm(A, s, packed, gs, 1.0, N, workspace=ws, workspace_prepared=True)
+        assert torch.equal(Y, fq.fq_w4a8_gemm(A, s, packed, gs, 1.0, N))
