@@ -23,8 +23,8 @@ __device__ __forceinline__ float fq_sum8(fq_v2i o) {
 
 // WPR waves per row, up to CH chunks (of 16 bytes, 8 bf16) of it per thread in registers between the search for the
 // largest magnitude and the conversion, so that the row is read once; longer rows are read a second time (REREAD).
-// Bound by HBM (3 bytes per element).  What keeps it from there is how many rows a compute unit has under way: with
-// one wave per row (K <= 4096) no row waits at a barrier for its other waves.
+// Bound by HBM (3 bytes per element); what keeps it from there is the latency of a row (load, maximum, conversion, store one
+// after the other) against the rows a compute unit has under way: fq_launch_quantize_as picks WPR and CH by that.
 // Workgroups of max(4, WPR) waves.
 // ZP: also write, for every group of 128 codes of the row, the zero-point term the large-M GEMM
 // kernels take from their workspace: -2^-6 * (sum of the group's E4M3 values) as two fp16 terms,
@@ -149,9 +149,11 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(c
 
 namespace {
 
-// Waves per row.  Many rows: the fewest that hold a row in registers (4096 columns each; 8192 x 4096 with zero-point terms
-// 21.6 us, 28.1 with four).  Few rows: four, or sixteen for a handful of long rows, where the time of one row is the time
-// of the call (32 x 32016 5.7 us; 10.9 with four waves that read the row twice).
+// Waves per row: enough that a thread holds two chunks, or four where rows are long and many (the row's latency is then
+// hidden by other rows, and fewer waves meet at its barrier).  Measured with zero-point terms, us: 2048 x 4096 8.2 with
+// <4, 2>, 9.7 with <1, 8>; 1000 x 7168 7.7 with <8, 2>, 8.3 <4, 4>, 8.9 <2, 8>, but 8192 x 8192 37.1, 35.0, 36.3;
+// 200 x 11008 4.8 with <16, 2>, 5.0 <8, 4>, 5.7 <4, 8>, but 2048 x 11008 17.9, 16.5, 17.1; 4096 x 1024 6.1 with <1, 4>,
+// 8.0 <4, 2>.  32 x 32016 (no such terms) 5.6 with <16, 8>; 10.9 with four waves that read the row twice.
 template <bool ZP, bool KNOWN>
 void fq_launch_quantize_as(const uint16_t* X, uint8_t* A, float* a_scale, int M, int K, uint16_t* planes, hipStream_t stream) {
 #define FQ_QUANTIZE(WPR_, CH_, REREAD_) \
@@ -160,11 +162,10 @@ void fq_launch_quantize_as(const uint16_t* X, uint8_t* A, float* a_scale, int M,
     if (K > 16 * 4096) {
         if constexpr (!ZP) FQ_QUANTIZE(16, 8, true);
     } else if (K > 4 * 4096) FQ_QUANTIZE(16, 8, false);
-    else if (K > 4096 && M <= 64) FQ_QUANTIZE(16, 2, false);
-    else if (K <= 4096 && M <= 1536) FQ_QUANTIZE(4, 2, false);
-    else if (K > 2 * 4096 || M <= 512) FQ_QUANTIZE(4, 8, false);
-    else if (K > 4096) FQ_QUANTIZE(2, 8, false);
-    else FQ_QUANTIZE(1, 8, false);
+    else if (K > 2 * 4096) { if (M <= 512) FQ_QUANTIZE(16, 2, false); else FQ_QUANTIZE(8, 4, false); }
+    else if (K > 4096) { if (M <= 4096) FQ_QUANTIZE(8, 2, false); else FQ_QUANTIZE(4, 4, false); }
+    else if (K > 2048 || M <= 1536) FQ_QUANTIZE(4, 2, false);
+    else FQ_QUANTIZE(1, 4, false);
 #undef FQ_QUANTIZE
 }
 
