@@ -66,7 +66,7 @@ GemmKernel choose_kernel(int M) {
     return k != GemmKernel::Auto ? k : (M <= 64 ? GemmKernel::Small : GemmKernel::Large);
 }
 
-// 0: the large-M kernel's own tiles; 1, 2: a shape of the K-split kernel (never with the fused gate/up epilogue).
+// 0: the large-M kernel's own tiles; 1, 2, 3: a shape of the K-split kernel (never with the fused gate/up epilogue).
 // Forcing "large" keeps the large-M kernel, forcing "ksplit" takes the K-split kernel wherever it can run.
 int ksplit_choice(int M, int N, int K, bool swiglu) {
     const GemmKernel k = forced_kernel();
@@ -192,7 +192,10 @@ int fq_w4a8_gemm_plan(int M, int N, int K, int cus, int* plan) {
         const int ks = f == GemmKernel::Large ? 0
                      : f == GemmKernel::KSplit ? ((K / FQ_GROUP >= 8) ? (M <= 512 ? 2 : 1) : 0)
                                                : fq_gemm_ksplit_choice(M, N, K, c);
-        if (ks != 0) {
+        if (f == GemmKernel::Auto && ks != 0 && (ks == 3 || M > FQ_KSPLIT_MAX_M)) {
+            plan[7] = ks - 1;                             // 1: 128 x 64, 2: 128 x 128 tiles of the K-split kernel
+            plan[5] = ((M + 127) / 128) * (ks == 2 ? (N + 63) / 64 : (N + 127) / 128);
+        } else if (ks != 0) {
             plan[0] = 3 + ks;
             plan[5] = ks == 1 ? ((M + 255) / 256) * ((N + 127) / 128) : ((M + 127) / 128) * ((N + 63) / 64);
             plan[6] = fq_gemm_ksplit_slices(ks, M, N, K, c);

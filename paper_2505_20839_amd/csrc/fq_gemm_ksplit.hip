@@ -1,18 +1,16 @@
 // W4A8-FP GEMM for problems with too few output tiles to fill the chip (Sec. 3.1.1; same arithmetic and
 // operand formats as fq_gemm_large.hip): a workgroup of 8 waves owns one tile of 32 * NMT rows x 32 * NW
 // channels and splits K over KS = 8 / NW groups of NW waves.  Each K split streams its own A tiles through
-// its own two LDS stages and its own packed weights (128 x 64 tiles: straight into registers, two groups
-// ahead -- a lane consumes exactly the 32 bytes it loads), with the main loop of the large-M kernel (two chained
-// v_mfma_f32_32x32x64_f8f6f4 per row tile and group, the group scale applied in FP32 to each group's
-// partial sum); the splits' partial tiles are then added through LDS, each wave taking over NMT / KS row
-// tiles, and the zero-point update and the epilogue finish those.  Two shapes are built:
-//     NMT = 8, NW = 4, KS = 2   256 x 128 tiles, K halved: for M > 128 when whole tiles of that size would
-//                               leave half the compute units idle (e.g. a down projection, N = 4096)
-//     NMT = 4, NW = 2, KS = 4   128 x 64 tiles, K quartered: for 64 < M <= 512 (batched decode, chunked
-//                               prefill), where 128-channel tiles are too few and the small-M kernels
-//                               re-read the activations once per compute unit from L2
+// its own two LDS stages and its own packed weights (128- and 64-row tiles: both through registers, several groups
+// ahead), with two chained v_mfma_f32_32x32x64_f8f6f4 per row tile and group and the group scale applied in FP32 to each
+// group's partial sum, as in the large-M kernel; the splits' partial tiles are then added through LDS, each wave taking
+// over NMT / KS row tiles, and the zero-point update and the epilogue finish those.  The shapes:
+//     NMT = 4, NW = 4, KS = 2   128 x 128 tiles, K halved: wherever these tiles fit one round of the compute units
+//     NMT = 4, NW = 2, KS = 4   128 x 64 tiles, K quartered: where even these do (batched decode, chunked prefill,
+//                               narrow layers)
 //     NMT = 2, NW = 2, KS = 4   64 x 64 tiles, the zero point through the matrix cores (no workspace): M just
 //                               below 64 with many channels, where the M <= 64 kernel is slowest
+//     NMT = 8, NW = 4, KS = 2   256 x 128 tiles, K halved, only on request (fq_test_force_kernel)
 // One workgroup per compute unit (64 to 160 KiB of LDS, two waves per SIMD).
 //
 // K slices: when even these tiles are fewer than the compute units, S workgroups share a tile, each taking a
@@ -112,7 +110,7 @@ void fq_gemm_ksplit_kernel(
     const __amdgpu_buffer_rsrc_t rsZ = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t*>(planes), 0, (int)((unsigned)ZU * (unsigned)M * 16u), 0x00020000);
     const unsigned abase = fql_a_lane_base(nw, lane, K, NT);
-    const uint8_t* gsrow = gs + (size_t)(n_ok ? n : N - 1) * G;
+    [[maybe_unused]] const uint8_t* gsrow = gs + (size_t)(n_ok ? n : N - 1) * G;
     // this workgroup's slice of the groups: [sb, se); this split's groups: [gb, ge); every split runs `gper`
     // steps, the surplus ones as ghosts with scale 0
     const int sper = (G + S - 1) / S;
@@ -142,101 +140,212 @@ void fq_gemm_ksplit_kernel(
 #pragma unroll
     for (int r = 0; r < 8; ++r) zpb[r] = (int)FQ_ZP_BYTES;
 
-    // ---- prologue ----
     fq_v4i* stages = lds + kw * (2 * cfg::STG);           // this split's two A stages
-    fq_v4i* wbuf = lds + KS * 2 * cfg::STG + wave * 256;  // this wave's two weight buffers
-    // (both A stages are free at the start: the second group's tile travels with the first instead of one step later)
-    fq_v4i wraw[2][2];                                    // (WREG) the packed weights of the next two groups
-    auto load_w = [&](int slot, int j) __attribute__((always_inline)) {
-        const unsigned off = wblk + (unsigned)gclamp(j) * 2048u;
-        wraw[slot][0] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsW, lane16 | ghost(j), off, 0));
-        wraw[slot][1] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsW, lane16 | ghost(j), off + 1024u, 0));
-    };
-    fql_issue_a<NT>(rsA, abase, m0, K, stages, nw, gclamp(0), ghost(0));
-    if (cfg::WREG) {
-        load_w(0, 0);
-        load_w(1, 1);
-    } else {
-        fql_issue_b(rsW, wbuf, lane16 | ghost(0), wblk + (unsigned)gclamp(0) * 2048u);
-        fql_issue_b(rsW, wbuf + 128, lane16 | ghost(1), wblk + (unsigned)gclamp(1) * 2048u);
-    }
-    fql_issue_a<NT>(rsA, abase, m0, K, stages + cfg::STG, nw, gclamp(1), ghost(1));
-    unsigned psb[2];
-    psb[0] = gsrow[gclamp(0)];
-    psb[1] = gsrow[gclamp(1)];
-    fq_v8i b0[2], b1[2];
-    float sc[2];
-    __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(0));
-    b0[0] = fq_unpack_chunk(cfg::WREG ? wraw[0][0] : wbuf[lane]);
-    b1[0] = fq_unpack_chunk(cfg::WREG ? wraw[0][1] : wbuf[64 + lane]);
-    sc[0] = gb < ge ? __builtin_amdgcn_cvt_f32_fp8((int)psb[0], 0) : 0.f;
-    b0[1] = b0[0]; b1[1] = b1[0]; sc[1] = 0.f;
-    __syncthreads();
-
     fq_v16f pprev = zero;
     float sprev = 0.f;
-    const int npairs = (gper + 1) >> 1;
-    fq_v8i an = fql_join(stages[o00], stages[o01]);
-    for (int p = 0; p < npairs; ++p) {
+    if constexpr (cfg::WREG) {
+        // ---- main loop, operands through registers ----
+        // A step (one group) of a workgroup is 16 matrix instructions per SIMD, 1024 cycles, and measured 2500 with all of
+        // its requests issued at its start: the 48 to 80 requests of the eight waves occupy the address path for 800 to 1300
+        // cycles, and no wave gets past its own to its next MFMA.  Spread over the step's MFMAs it is 2100 (200 x 4096 x 11008
+        // with two slices 27.5 -> 25.4 us, 512 x 4096 x 11008 40.3 -> 36.1; the compiler keeps transfers straight into
+        // LDS from being spread, so A goes through registers).  Without any loads a step takes 1650 cycles, without LDS
+        // reads as well 1150.  More groups in flight change nothing.
+        // A(g) sits in register set g % RA until the middle of step g - 1, when it goes to LDS stage g & 1; W(g) in slot
+        // g % 4 until it is unpacked during step g - 1; a word holds the group scales of four steps.
+        constexpr int RA = 2;
+        fq_v4i ra[RA][NT], wr[4][2];
+        auto load_a = [&](int set, int j, int i) __attribute__((always_inline)) {
+            unsigned ab = abase;
+            if (NT > 4) asm volatile("" : "+v"(ab));      // (opaque, or the offsets of all transfers stay in registers)
+            const unsigned v = (ab ^ ((i & 1) ? 64u : 0u)) + (unsigned)(m0 + 8 * i) * (unsigned)K;
+            ra[set][i] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsA, v | ghost(j), gclamp(j) * FQ_GROUP, 0));
+        };
+        auto load_w = [&](int slot, int j, int h) __attribute__((always_inline)) {
+            wr[slot][h] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(
+                rsW, lane16 | ghost(j), wblk + (unsigned)gclamp(j) * 2048u + 1024u * (unsigned)h, 0));
+        };
+        auto put_a = [&](int set, int stage, int i) __attribute__((always_inline)) {
+            stages[stage * cfg::STG + nw * (64 * NT) + lane + 64 * i] = ra[set][i];
+        };
+        // group scales: the word of steps 4 p .. 4 p + 3 from the aligned words around its bytes
+        const __amdgpu_buffer_rsrc_t rsG = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint8_t*>(gs), 0, (int)(((unsigned)N * (unsigned)G + 3u) & ~3u), 0x00020000);
+        const unsigned goff = (unsigned)(n_ok ? n : N - 1) * (unsigned)G + (unsigned)gb;
+        auto load_s = [&](int p) __attribute__((always_inline)) {
+            return __builtin_amdgcn_raw_buffer_load_b32(rsG, (goff & ~3u) + 4u * (unsigned)p, 0, 0);
+        };
+        unsigned sw0 = load_s(0), sw1 = load_s(1), sw2 = load_s(2);
+        // requested in the order of the steady state (the waits are timed for the shortest path into the loop)
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int j = 2 * p + u;                      // step of this split; group gb + j
-            const fq_v4i* cur = stages + u * cfg::STG;
-            if (j > 0) fql_issue_a<NT>(rsA, abase, m0, K, stages + (u ^ 1) * cfg::STG, nw, gclamp(j + 1), ghost(j + 1));
-            const unsigned qs = psb[u ^ 1];
-            // (WREG: slot u held group j, unpacked during the last step; the compiler times the wait for slot u ^ 1)
-            if (cfg::WREG) load_w(u, j + 2);
-            else           fql_issue_b(rsW, wbuf + u * 128, lane16 | ghost(j + 2), wblk + (unsigned)gclamp(j + 2) * 2048u);
-            psb[u] = gsrow[gclamp(j + 2)];
-            if (!cfg::WREG) __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(NT + 3));
-            const fq_v4i* nxt = wbuf + (u ^ 1) * 128 + lane;
-            const float s = sc[u];
-            fq_v4i q = cfg::WREG ? wraw[u ^ 1][0] : nxt[0];
-            fq_v16f pt;
-            __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < 4; ++i) {
+            if (i >= 4 - RA)
 #pragma unroll
-            for (int mt = 0; mt < NMT; ++mt) {
-                const int tp = (mt + NMT - 1) % NMT;
-                const float sp = (mt == 0) ? sprev : s;
+                for (int x = 0; x < NT; ++x) load_a(i - (4 - RA), i - (4 - RA), x);
+            load_w(i, i, 0);
+            load_w(i, i, 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        fq_v8i b0[2], b1[2];
+        b0[0] = fq_unpack_chunk(wr[0][0]);
+        b1[0] = fq_unpack_chunk(wr[0][1]);
+        b0[1] = b0[0]; b1[1] = b1[0];
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const fq_v8i ac = an;
-                    if (h == 0) {
-                        an = fql_join(cur[mt * 256 + o10], cur[mt * 256 + o11]);
-                    } else if (mt + 1 < NMT) {
-                        an = fql_join(cur[(mt + 1) * 256 + o00], cur[(mt + 1) * 256 + o01]);
+        for (int x = 0; x < NT; ++x) put_a(0, 0, x);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        fq_v8i an = fql_join(stages[o00], stages[o01]);
+        for (int p = 0; 4 * p < gper; ++p) {
+            const unsigned sw = __builtin_amdgcn_alignbyte(sw1, sw0, goff & 3u);
+            sw0 = sw1; sw1 = sw2;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int j = 4 * p + u;                  // step of this split; group gb + j
+                if (u > 0 && j >= gper) break;            // (the same for all splits)
+                const fq_v4i* cur = stages + (u & 1) * cfg::STG;
+                const float t = u == 0 ? __builtin_amdgcn_cvt_f32_fp8((int)sw, 0) : u == 1 ? __builtin_amdgcn_cvt_f32_fp8((int)sw, 1)
+                              : u == 2 ? __builtin_amdgcn_cvt_f32_fp8((int)sw, 2) : __builtin_amdgcn_cvt_f32_fp8((int)sw, 3);
+                const float s = gb + j < ge ? t : 0.f;
+                fq_v4i q = wr[(u + 1) & 3][0];
+                fq_v16f pt;
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int mt = 0; mt < NMT; ++mt) {
+                    const int tp = (mt + NMT - 1) % NMT;
+                    const float sp = (mt == 0) ? sprev : s;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        // The step's requests are spread over its MFMAs (see above).  A(j + 1) goes to the other stage (last read before the previous barrier) in the second half;
+                        // the barrier stands before the step's last MFMA, when all of its operands have been read, so
+                        // that this MFMA covers the next step's first reads.
+                        constexpr int SLOTS = 2 * NMT;
+                        const int sl = 2 * mt + h;
+#pragma unroll
+                        for (int x = 0; x < NT; ++x)
+                            if (x * SLOTS / NT == sl) load_a(u % RA, j + RA, x);
+                        if (sl == SLOTS / 2) load_w(u, j + 4, 0);
+                        if (sl == SLOTS - 2) load_w(u, j + 4, 1);
+                        if (u == 0 && sl == SLOTS - 1) sw2 = load_s(p + 3);
+#pragma unroll
+                        for (int x = 0; x < NT; ++x)
+                            if (SLOTS - 2 - x * (SLOTS / 2) / NT == sl) put_a((u + 1) % RA, (u & 1) ^ 1, x);
+                        const fq_v8i ac = an;
+                        if (h == 0) {
+                            an = fql_join(cur[mt * 256 + o10], cur[mt * 256 + o11]);
+                        } else if (mt + 1 < NMT) {
+                            an = fql_join(cur[(mt + 1) * 256 + o00], cur[(mt + 1) * 256 + o01]);
+                        } else {
+                            __builtin_amdgcn_sched_barrier(0);
+                            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                            const fq_v4i* nxs = stages + ((u & 1) ^ 1) * cfg::STG;
+                            an = fql_join(nxs[o00], nxs[o01]);
+                        }
+                        if (ZPM) pt = FQ_MFMA(ac, zpb, h == 0 ? zero : pt);   // -2^-6 * sum_k a_k in every column
+                        if (h == 0) pt = FQ_MFMA(ac, b0[u & 1], ZPM ? pt : zero);
+                        else        pt = FQ_MFMA(ac, b1[u & 1], pt);
+#pragma unroll
+                        for (int r = 8 * h; r < 8 * h + 8; ++r) acc[tp][r] = fmaf(sp, pprev[r], acc[tp][r]);
+#pragma unroll
+                        for (int e = 0; e < 8 / NMT; ++e) {
+                            const int slot = (8 / NMT) * mt + e;
+                            const unsigned w = (unsigned)q[slot & 3];
+                            const int ev = (int)((h == 0 ? w : (w >> 4)) & 0x0F0F0F0Fu);
+                            if (slot < 4) b0[(u & 1) ^ 1][4 * h + (slot & 3)] = ev;
+                            else          b1[(u & 1) ^ 1][4 * h + (slot & 3)] = ev;
+                        }
+                        if (mt == NMT / 2 - 1 && h == 1) q = wr[(u + 1) & 3][1];
+                        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x008, ZPM ? 2 : 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x020, 3, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x200, 4, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 24, 0);
+                        __builtin_amdgcn_sched_barrier(0);
                     }
-                    if (ZPM) pt = FQ_MFMA(ac, zpb, h == 0 ? zero : pt);   // -2^-6 * sum_k a_k in every column
-                    if (h == 0) pt = FQ_MFMA(ac, b0[u], ZPM ? pt : zero);
-                    else        pt = FQ_MFMA(ac, b1[u], pt);
-#pragma unroll
-                    for (int r = 8 * h; r < 8 * h + 8; ++r) acc[tp][r] = fmaf(sp, pprev[r], acc[tp][r]);
-#pragma unroll
-                    for (int e = 0; e < 8 / NMT; ++e) {
-                        const int slot = (8 / NMT) * mt + e;
-                        const unsigned w = (unsigned)q[slot & 3];
-                        const int ev = (int)((h == 0 ? w : (w >> 4)) & 0x0F0F0F0Fu);
-                        if (slot < 4) b0[u ^ 1][4 * h + (slot & 3)] = ev;
-                        else          b1[u ^ 1][4 * h + (slot & 3)] = ev;
-                    }
-                    if (mt == NMT / 2 - 1 && h == 1) q = cfg::WREG ? wraw[u ^ 1][1] : nxt[64];
-                    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x008, ZPM ? 2 : 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 24, 0);
-                    __builtin_amdgcn_sched_barrier(0);
+                    pprev = pt;
                 }
-                pprev = pt;
+                sprev = s;
             }
-            sprev = s;
-            {
-                const float t = __builtin_amdgcn_cvt_f32_fp8((int)qs, 0);
-                sc[u ^ 1] = (gb + j + 1 < ge) ? t : 0.f;
-            }
-            __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(3));
-            __syncthreads();
-            {
-                const fq_v4i* nxs = stages + (u ^ 1) * cfg::STG;
-                an = fql_join(nxs[o00], nxs[o01]);
+        }
+    } else {
+        // ---- prologue ----
+        fq_v4i* wbuf = lds + KS * 2 * cfg::STG + wave * 256;  // this wave's two weight buffers
+        // (both A stages are free at the start: the second group's tile travels with the first instead of one step later)
+        fql_issue_a<NT>(rsA, abase, m0, K, stages, nw, gclamp(0), ghost(0));
+        fql_issue_b(rsW, wbuf, lane16 | ghost(0), wblk + (unsigned)gclamp(0) * 2048u);
+        fql_issue_b(rsW, wbuf + 128, lane16 | ghost(1), wblk + (unsigned)gclamp(1) * 2048u);
+        fql_issue_a<NT>(rsA, abase, m0, K, stages + cfg::STG, nw, gclamp(1), ghost(1));
+        unsigned psb[2];
+        psb[0] = gsrow[gclamp(0)];
+        psb[1] = gsrow[gclamp(1)];
+        fq_v8i b0[2], b1[2];
+        float sc[2];
+        __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(0));
+        b0[0] = fq_unpack_chunk(wbuf[lane]);
+        b1[0] = fq_unpack_chunk(wbuf[64 + lane]);
+        sc[0] = gb < ge ? __builtin_amdgcn_cvt_f32_fp8((int)psb[0], 0) : 0.f;
+        b0[1] = b0[0]; b1[1] = b1[0]; sc[1] = 0.f;
+        __syncthreads();
+
+        const int npairs = (gper + 1) >> 1;
+        fq_v8i an = fql_join(stages[o00], stages[o01]);
+        for (int p = 0; p < npairs; ++p) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int j = 2 * p + u;                      // step of this split; group gb + j
+                const fq_v4i* cur = stages + u * cfg::STG;
+                if (j > 0) fql_issue_a<NT>(rsA, abase, m0, K, stages + (u ^ 1) * cfg::STG, nw, gclamp(j + 1), ghost(j + 1));
+                const unsigned qs = psb[u ^ 1];
+                fql_issue_b(rsW, wbuf + u * 128, lane16 | ghost(j + 2), wblk + (unsigned)gclamp(j + 2) * 2048u);
+                psb[u] = gsrow[gclamp(j + 2)];
+                __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(NT + 3));
+                const fq_v4i* nxt = wbuf + (u ^ 1) * 128 + lane;
+                const float s = sc[u];
+                fq_v4i q = nxt[0];
+                fq_v16f pt;
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int mt = 0; mt < NMT; ++mt) {
+                    const int tp = (mt + NMT - 1) % NMT;
+                    const float sp = (mt == 0) ? sprev : s;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const fq_v8i ac = an;
+                        if (h == 0) {
+                            an = fql_join(cur[mt * 256 + o10], cur[mt * 256 + o11]);
+                        } else if (mt + 1 < NMT) {
+                            an = fql_join(cur[(mt + 1) * 256 + o00], cur[(mt + 1) * 256 + o01]);
+                        }
+                        if (ZPM) pt = FQ_MFMA(ac, zpb, h == 0 ? zero : pt);   // -2^-6 * sum_k a_k in every column
+                        if (h == 0) pt = FQ_MFMA(ac, b0[u], ZPM ? pt : zero);
+                        else        pt = FQ_MFMA(ac, b1[u], pt);
+#pragma unroll
+                        for (int r = 8 * h; r < 8 * h + 8; ++r) acc[tp][r] = fmaf(sp, pprev[r], acc[tp][r]);
+#pragma unroll
+                        for (int e = 0; e < 8 / NMT; ++e) {
+                            const int slot = (8 / NMT) * mt + e;
+                            const unsigned w = (unsigned)q[slot & 3];
+                            const int ev = (int)((h == 0 ? w : (w >> 4)) & 0x0F0F0F0Fu);
+                            if (slot < 4) b0[u ^ 1][4 * h + (slot & 3)] = ev;
+                            else          b1[u ^ 1][4 * h + (slot & 3)] = ev;
+                        }
+                        if (mt == NMT / 2 - 1 && h == 1) q = nxt[64];
+                        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x008, ZPM ? 2 : 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 24, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    pprev = pt;
+                }
+                sprev = s;
+                {
+                    const float t = __builtin_amdgcn_cvt_f32_fp8((int)qs, 0);
+                    sc[u ^ 1] = (gb + j + 1 < ge) ? t : 0.f;
+                }
+                __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(3));
+                __syncthreads();
+                {
+                    const fq_v4i* nxs = stages + (u ^ 1) * cfg::STG;
+                    an = fql_join(nxs[o00], nxs[o01]);
+                }
             }
         }
     }
@@ -491,23 +600,21 @@ void fqk_launch(const uint8_t* A, const float* a_scale, const uint8_t* wp, const
 
 }  // namespace
 
-// Which shape of this kernel, if any, serves the problem better than the large-M kernel's own tiles:
-// 0 = none, 1 = 256 x 128 tiles with K halved, 2 = 128 x 64 tiles with K quartered.
-// Measured on MI355X (large-M kernel -> this kernel, prepared workspace): the 128 x 64 shape wins wherever its
-// tiles fit one round of the compute units -- M = 128, K = 4096: N = 4096 20.7 -> 14.0 us, N = 11008 21.5 -> 16.5,
-// N = 14336 23.6 -> 17.4; M = 128, N = 4096, K = 11008: 55.4 -> 21.7 (4 K slices); M = 512, N = 4096: K = 4096
-// 21.1 -> 16.4, K = 11008 55.5 -> 38.9; 8192 x 8192 at M = 256: 49.3 -> 29.9 -- and loses beyond one round
-// (M = 256, N = 11008: 23.4 -> 29.9; M = 512, N = 14336: 33.0 -> 59.4), except for a single row tile with a long K,
-// where two rounds still win (M = 128: 20480 x 5120 46.7 -> 43.7, 28672 x 8192 74.5 -> 63.3; at K = 4096 the two
-// are equal).  A step of a workgroup moves 80 KiB for 8 matrix instructions per wave and takes as long as that
-// transfer (1.2 us measured), so one compute unit cannot run more than one round of such tiles well.
-// The 256 x 128 shape brought nothing on the shapes tried (down projection 2048 x 4096 x 11008: 105 us
-// either way; 1024 x 4096 x 4096: 29.3 -> 37.1) and is not chosen automatically.
+// Which shape of this kernel, if any, serves the problem better than the large-M kernel's own tiles: 0 = none,
+// 2 = 128 x 64 tiles with K quartered, 3 = 128 x 128 tiles with K halved (1 = 256 x 128 tiles is never chosen).
+// A shape wins where its tiles fit one round of the compute units, the smaller one first; measured with a prepared
+// workspace, large-M kernel -> 128 x 128 -> 128 x 64, us: 256 x 14336 x 4096 25.8 -> 23.8 -> 31.3 (two rounds); 700 x 4096 x 4096
+// 23.7 -> 20.7 -> 29.5; 1000 x 4096 x 11008 58.8 -> 50.0 -> 69.5; 1024 x 4096 x 14336 75.2 -> 63.8 -> 85.7; 1500 x 2048 x
+// 8192 44.1 -> 34.7 -> 48.9; 1000 x 2048 x 4096 24.7 -> 19.8 -> 16.7; 1000 x 1024 x 8192 43.4 -> 32.1 -> 24.4; beyond one round
+// both lose (2048 x 4096 x 11008, 512 tiles: 89.1 -> 93.5; 512 x 14336 x 4096: 33.3 -> 39.2), except 128 x 64 tiles for
+// a single row tile with a long K, where two rounds still win (M = 128: 20480 x 5120 46.7 -> 43.7, 28672 x 8192
+// 74.5 -> 63.3 with an earlier form of the loop; at K = 4096 equal).
 int fq_gemm_ksplit_choice(int M, int N, int K, int cus) {
     const int G = K / FQ_GROUP;
-    if (M <= 64 || M > FQ_KSPLIT_MAX_M || G < 8) return 0;
-    const long long rounds = (M <= 128 && G >= 40) ? 2 : 1;
-    return (long long)((M + 127) / 128) * ((N + 63) / 64) <= rounds * cus ? 2 : 0;
+    if (M <= 64 || G < 8) return 0;
+    const long long rows = (M + 127) / 128, rounds = (M <= 128 && G >= 40) ? 2 : 1;
+    if (rows * ((N + 63) / 64) <= rounds * cus) return 2;
+    return rows * ((N + 127) / 128) <= cus ? 3 : 0;
 }
 
 // K slices of the 128 x 64 shape: as many as fill the compute units, each with at least two groups per K split
@@ -542,7 +649,8 @@ void fq_launch_gemm_ksplit(int choice, const uint8_t* A, const float* a_scale, c
     unsigned* counters = reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + plane_bytes);
     float* partials = reinterpret_cast<float*>(counters + FQ_KSPLIT_COUNTERS);
     const int S = fq_gemm_ksplit_slices(choice, M, N, K, fq_device_cus());
-    if (choice == 1) fqk_launch<8, 4, 2>(A, a_scale, wp, gs, tscale, Y, M, N, K, planes, R, 1, counters, partials, stream);
+    if (choice == 3) fqk_launch<4, 4, 2>(A, a_scale, wp, gs, tscale, Y, M, N, K, planes, R, 1, counters, partials, stream);
+    else if (choice == 1) fqk_launch<8, 4, 2>(A, a_scale, wp, gs, tscale, Y, M, N, K, planes, R, 1, counters, partials, stream);
     else             fqk_launch<4, 2, 4>(A, a_scale, wp, gs, tscale, Y, M, N, K, planes, R, S, counters, partials, stream);
 }
 

@@ -110,7 +110,7 @@ void fq_launch_kv4_output(const uint8_t* P, const float* p_scale, const uint8_t*
 
 // K-split kernel (fq_gemm_ksplit.hip): 8-wave workgroups that split K inside the workgroup, for problems with
 // too few tiles for the large-M kernel.  fq_gemm_ksplit_choice: 0 = not used for this shape, 1 = 256 x 128 tiles
-// with K halved, 2 = 128 x 64 tiles with K quartered.  Workspace and `prepared` as for fq_launch_gemm_large; no
+// with K halved (on request only), 2 = 128 x 64 tiles with K quartered, 3 = 128 x 128 tiles with K halved.  Workspace and `prepared` as for fq_launch_gemm_large; no
 // fused gate/up epilogue.
 int fq_gemm_ksplit_choice(int M, int N, int K, int cus);
 // K slices per tile (workgroups that share a tile and add their partial tiles through the workspace) and the

@@ -352,3 +352,44 @@ def test_a_prepared_workspace_serves_several_sliced_gemms(fq):
         assert np.array_equal(bf16_bits_from_gpu(Yg), bf16_bits_from_gpu(fresh)), N
         Y, B = oracle.w4a8_gemm(An, sn, d["q"], d["gscale"], d["w_tscale"], want_bound=True)
         check_gemm(bf16_bits_from_gpu(Yg), Y, B, "shared workspace, N = %d" % N)
+
+
+# (M, N, K) -> the tiles of the K-split kernel that serve it on a 256-unit device: 1 128 x 64, 2 128 x 128 (0: the large-M
+# kernel); even and ragged edges, K splits of equal and unequal length (10 and 11 groups), steps that are no multiple of 4
+SPLIT_TILE_SHAPES = [((600, 1024, 1024), 1), ((513, 200, 1408), 1), ((1000, 2040, 1280), 1), ((300, 8200, 1024), 2), ((257, 10000, 1152), 2),
+                     ((700, 4104, 1280), 2), ((1025, 3001, 1024), 2), ((1024, 4096, 1408), 2), ((2000, 2048, 1024), 2), ((130, 16384, 1024), 2)]
+
+
+@pytest.mark.parametrize("shape,tiles", SPLIT_TILE_SHAPES)
+def test_large_m_range_on_k_split_tiles(fq, shape, tiles):
+    """Problems of the large-M range whose 128-row tiles fit on the device at once: plain, with the residual and in place against
+    the oracle (all rows, sampled channels with both edges), and close to the large-M kernel's own tiles."""
+    import ctypes
+    M, N, K = shape
+    plan = (ctypes.c_int * 8)()
+    assert fq.lib().fq_w4a8_gemm_plan(M, N, K, 256, plan) == 0 and plan[0] == 3 and plan[7] == tiles
+    assert fq.fq_w4a8_gemm_workspace_bytes(M, N, K) == 2 * (2 * -(-(K // 128) // 16)) * M * 16 + (4096 if M <= 512 else 0)
+    d = _problem(shape, seed=M + N + K)
+    A, s = fq.fq_quantize_act(to_gpu_bf16(d["X_bf16"]))
+    packed, gs = fq.fq_pack_weights(_gpu(d["q"])), _gpu(d["gscale"])
+    Rb = workloads.draw_residual(M, N, scale=workloads.RESIDUAL_SCALE, seed=N)
+    R = to_gpu_bf16(Rb)
+    Y = fq.fq_w4a8_gemm(A, s, packed, gs, d["w_tscale"], N)
+    YR = fq.fq_w4a8_gemm_add(A, s, packed, gs, d["w_tscale"], N, R)
+    fq.fq_w4a8_gemm_add(A, s, packed, gs, d["w_tscale"], N, R, out=R)
+    fq.fq_test_force_kernel("large")
+    try:
+        YL = fq.fq_w4a8_gemm(A, s, packed, gs, d["w_tscale"], N)
+        torch.cuda.synchronize()
+    finally:
+        fq.fq_test_force_kernel(None)
+    assert torch.equal(YR, R)
+    pick = np.unique(np.concatenate([np.arange(min(N, 130)), np.arange(max(0, N - 130), N), np.arange(0, N, 61)]))
+    A_ref, s_ref = A.cpu().numpy(), s.cpu().numpy()
+    Yr, B = oracle.w4a8_gemm(A_ref, s_ref, d["q"][pick], d["gscale"][pick], d["w_tscale"], want_bound=True)
+    check_gemm(bf16_bits_from_gpu(Y)[:, pick], Yr, B, "split tiles %s" % (shape,))
+    # the same sums in another FP32 order: at most one bf16 step + 1e-4 of the terms' magnitudes apart
+    y, yl = oracle.bf16_bits_to_f64(bf16_bits_from_gpu(Y))[:, pick], oracle.bf16_bits_to_f64(bf16_bits_from_gpu(YL))[:, pick]
+    assert np.all(np.abs(y - yl) <= oracle.bf16_ulp_array(yl) + 1e-4 * B)
+    Yr, B = oracle.w4a8_gemm_add(A_ref, s_ref, d["q"][pick], d["gscale"][pick], d["w_tscale"], Rb[:, pick], want_bound=True)
+    check_gemm(bf16_bits_from_gpu(YR)[:, pick], Yr, B, "split tiles + residual %s" % (shape,))
