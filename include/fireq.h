@@ -314,7 +314,8 @@ int fq_kv4_output(const uint8_t *P_fp8, const float *p_scale, const uint8_t *V_p
  *     plan[1]  large-M kernel: whole tiles (256 rows x 128 channels) with nothing masked in their stores
  *     plan[2]  whole tiles with a ragged edge (masked whole-row stores) or N not a multiple of 8 (written
  *              element by element)
- *     plan[3], plan[4]  the same two counts for the 128-row half tiles of the last round
+ *     plan[3], plan[4]  the same two counts for the 128-row half tiles of the last round (each run as two items of 64
+ *                       rows where every XCD has few of them)
  *     plan[7]  0, or (with plan[0] = 3) the large-M range served by the K-split kernel on plan[5] tiles that all
  *              fit on the device at once: 1 128 x 64, 2 128 x 128 tiles (plan[1] .. plan[4] are 0 then)
  * fq_test_force_kernel: "simple", "small", "large" or "ksplit" makes every GEMM entry point use that kernel

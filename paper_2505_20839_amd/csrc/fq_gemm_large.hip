@@ -4,8 +4,8 @@
 // into a rounded FP8 table but applied exactly, in FP32, to each group's partial sum; all output
 // scaling is FP32 with a single rounding to bf16.
 //
-// Work split.  A workgroup of 4 waves owns one output tile of 256 (or 128) rows x 128 channels;
-// wave w owns 32 channels and all rows of the tile (NMT = 8 or 4 MFMA tiles of 32x32), so every
+// Work split.  A workgroup of 4 waves owns one output tile of 256 (or 128, 64) rows x 128 channels;
+// wave w owns 32 channels and all rows of the tile (NMT = 8, 4 or 2 MFMA tiles of 32x32), so every
 // weight is unpacked exactly once per workgroup and each unpacked operand is reused by all row tiles.
 // Two workgroups share a compute unit (80 KiB of LDS and one wave per SIMD each): the two waves of
 // a SIMD belong to different workgroups, so no barrier couples them, and each fills the other's
@@ -30,8 +30,8 @@
 // range of tiles in an order that walks panels of 4 row tiles, row tile fastest, so the workgroups
 // an XCD runs at one time cover a few row tiles x a few channel tiles and share them in its L2.
 // The tiles an XCD cannot fill a whole round of its slots with are cut into two 128-row halves (the
-// NMT = 4 variant, later workgroups of the same launch), so that the last round keeps all units busy
-// for half the time.
+// NMT = 4 variant, later workgroups of the same launch) or, where they are few, four quarters (NMT = 2), so that
+// the last round keeps more units busy for less time.
 #include <type_traits>
 #include "fq_common.h"
 #include "fq_kernels.h"
@@ -49,46 +49,49 @@
 
 namespace {
 
-// Tiles of XCD x: [lo, lo + count) of the row-tile-fastest order; the first `nfull` are run whole
-// by the first launch, the rest as halves by the second.
+// Tiles of XCD x: [lo, lo + count) of the row-tile-fastest order; the first `nfull` are run whole, each of the rest in
+// `parts` items of 256 / parts rows.
 struct fql_split {
-    int lo, nfull, nhalf;                                 // nhalf = number of 128-row items (2 per tile)
+    int lo, nfull, nitems;                                // nitems = number of items of the last round
 };
 
-__host__ __device__ inline fql_split fql_xcd_split(int x, int ntiles, int slots) {
+__host__ __device__ inline fql_split fql_xcd_split(int x, int ntiles, int slots, int parts) {
     const int base = ntiles / FQL_XCDS, rem = ntiles % FQL_XCDS;
     const int count = base + (x < rem ? 1 : 0);
     fql_split sp;
     sp.lo = x * base + (x < rem ? x : rem);
     const int r = count % slots;                          // tiles of the last, partial round
-    if (r > 0 && 2 * r <= slots) { sp.nfull = count - r; sp.nhalf = 2 * r; }
-    else                         { sp.nfull = count;     sp.nhalf = 0; }
+    if (r > 0 && 2 * r <= slots) { sp.nfull = count - r; sp.nitems = parts * r; }
+    else                         { sp.nfull = count;     sp.nitems = 0; }
     return sp;
 }
 
-// Which item workgroup `bid` of its kind (NMT = 8: whole tiles, NMT = 4: 128-row halves) runs: XCD
+// Quarters where at most one of them falls on a compute unit, on any XCD: a lone item costs what its rows take
+// (1500 x 11008 x 4096, a tile or two past a full round: 80.3 us with halves, 76.6 us with quarters; 2304 x 8192 x 4096: 80.8,
+// 77.5); two quarters on a compute unit take longer than the half that they replace, since each unpacks the same weights.
+inline int fql_tail_parts(int ntiles, int slots) {
+    const int r = ntiles / FQL_XCDS % slots, r1 = (ntiles / FQL_XCDS + 1) % slots;
+    const bool more = ntiles % FQL_XCDS != 0;             // (some XCDs have a tile more)
+    return 8 * r <= slots && (!more || 8 * r1 <= slots) ? 4 : 2;
+}
+
+// Which item workgroup `bid` of its kind (NMT = 8: whole tiles; NMT = 4, 2: halves and quarters) runs: XCD
 // x = bid % 8 (both kinds start at a multiple of 8 workgroups), j-th item of that XCD's list.  Tile
 // order: panels of `pm` row tiles; inside a panel row tile fastest, then channel tile.  False: no item
-// (past the end of the XCD's list, or a second half without rows).
+// (past the end of the XCD's list, or a part without rows).
 template <int NMT>
 __host__ __device__ inline bool fql_locate(unsigned bid, int M, int tiles_m, int tiles_n, int slots, int pm,
                                            int* m0, int* n0) {
     const int x = bid % FQL_XCDS, j = bid / FQL_XCDS;
-    const fql_split sp = fql_xcd_split(x, tiles_m * tiles_n, slots);
-    int t, half = 0;
-    if (NMT == 8) {
-        if (j >= sp.nfull) return false;
-        t = sp.lo + j;
-    } else {
-        if (j >= sp.nhalf) return false;
-        t = sp.lo + sp.nfull + (j >> 1);
-        half = j & 1;
-    }
+    constexpr int PARTS = 8 / NMT;
+    const fql_split sp = fql_xcd_split(x, tiles_m * tiles_n, slots, PARTS);
+    if (j >= (NMT == 8 ? sp.nfull : sp.nitems)) return false;
+    const int t = sp.lo + (NMT == 8 ? 0 : sp.nfull) + j / PARTS;
     const int per_panel = pm * tiles_n;
     const int panel = t / per_panel, rem = t - panel * per_panel;
     const int ph = tiles_m - panel * pm < pm ? tiles_m - panel * pm : pm;   // row tiles of this panel
     const int tn = rem / ph, tm = panel * pm + (rem - tn * ph);
-    *m0 = tm * FQL_BM + half * 128;
+    *m0 = tm * FQL_BM + (j % PARTS) * (32 * NMT);
     *n0 = tn * FQL_BN;
     return *m0 < M;
 }
@@ -145,7 +148,7 @@ __global__ __launch_bounds__(256) void fq_zero_point_kernel(const uint8_t* __res
     }
 }
 
-// One item: NMT row tiles of 32 rows (8, or 4 for the half tiles) x 128 channels.  `bid` counts the
+// One item: NMT row tiles of 32 rows (8, or 4 and 2 for the half and quarter tiles) x 128 channels.  `bid` counts the
 // workgroups of the item's kind.
 // LUT: the paper's table mode instead of the exact one.  The weights enter the matrix cores as
 // E4M3(q * sigma) (looked up in a per-group table that is built one group ahead), the products
@@ -297,7 +300,7 @@ __device__ __forceinline__ void fql_item(
                         for (int r = 8 * h; r < 8 * h + 8; ++r) acc[tp][r] = fmaf(sp, pprev[r], acc[tp][r]);
                     }
                     // a share of the next group's unpack: half a packed word per step with 8 row
-                    // tiles, a whole word's half twice with 4
+                    // tiles, two halves with 4, four with 2
 #pragma unroll
                     for (int e = 0; e < 8 / NMT; ++e) {
                         const int slot = (8 / NMT) * mt + e;                    // packed word 0..7
@@ -598,8 +601,9 @@ __device__ __forceinline__ void fql_item(
     }
 }
 
-// Workgroups [0, full_wgs) run whole tiles, the rest the half tiles of the tail round: one launch, so
-// the halves start as soon as the first compute units run out of whole tiles.
+// Workgroups [0, full_wgs) run whole tiles, the rest the halves or quarters (TAIL_NMT = 4 or 2) of the tail round: one launch, so
+// these start as soon as the first compute units run out of whole tiles.
+template <int TAIL_NMT>
 __global__ __launch_bounds__(FQL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void fq_gemm_large_kernel(
     const uint8_t* __restrict__ A, const float* __restrict__ a_scale, const uint8_t* __restrict__ wp,
@@ -611,11 +615,11 @@ void fq_gemm_large_kernel(
         fql_item<8>(lds, blockIdx.x, A, a_scale, wp, gs, tscale, Y, M, N, K, tiles_m, tiles_n, slots, pm, planes, swiglu, R,
                     rowmax);
     else
-        fql_item<4>(lds, blockIdx.x - full_wgs, A, a_scale, wp, gs, tscale, Y, M, N, K, tiles_m, tiles_n, slots, pm, planes,
-                    swiglu, R, rowmax);
+        fql_item<TAIL_NMT>(lds, blockIdx.x - full_wgs, A, a_scale, wp, gs, tscale, Y, M, N, K, tiles_m, tiles_n, slots, pm,
+                           planes, swiglu, R, rowmax);
 }
 
-// The table mode of the same items (no zero-point planes).
+// The table mode of the same items (no zero-point planes; halves only).
 __global__ __launch_bounds__(FQL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void fq_gemm_large_lut_kernel(
     const uint8_t* __restrict__ A, const float* __restrict__ a_scale, const uint8_t* __restrict__ wp,
@@ -644,12 +648,12 @@ void fq_gemm_large_plan(int M, int N, int cus, int out[4]) {
     const int pm = tiles_m < 4 ? tiles_m : 4;
     out[0] = out[1] = out[2] = out[3] = 0;
     for (int x = 0; x < FQL_XCDS; ++x) {
-        const fql_split sp = fql_xcd_split(x, tiles_m * tiles_n, slots);
+        const fql_split sp = fql_xcd_split(x, tiles_m * tiles_n, slots, 2);   // (quarters count as the half they make up)
         int m0, n0;
         for (int j = 0; j < sp.nfull; ++j)
             if (fql_locate<8>((unsigned)(j * FQL_XCDS + x), M, tiles_m, tiles_n, slots, pm, &m0, &n0))
                 ++out[(m0 + 256 <= M && n0 + FQL_BN <= N && (N & 7) == 0) ? 0 : 1];
-        for (int j = 0; j < sp.nhalf; ++j)
+        for (int j = 0; j < sp.nitems; ++j)
             if (fql_locate<4>((unsigned)(j * FQL_XCDS + x), M, tiles_m, tiles_n, slots, pm, &m0, &n0))
                 ++out[(m0 + 128 <= M && n0 + FQL_BN <= N && (N & 7) == 0) ? 2 : 3];
     }
@@ -665,7 +669,9 @@ void fq_launch_gemm_large(const uint8_t* A, const float* a_scale, const uint8_t*
                           bool swiglu, const uint16_t* R, hipStream_t stream, bool lut, unsigned* rowmax) {
     static fq_device_once attr_once;
     fq_once_per_device(attr_once, [] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_gemm_large_kernel),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_gemm_large_kernel<4>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, FQL_LDS_BYTES);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_gemm_large_kernel<2>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, FQL_LDS_BYTES);
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_gemm_large_lut_kernel),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, FQL_LDS_BYTES);
@@ -678,19 +684,20 @@ void fq_launch_gemm_large(const uint8_t* A, const float* a_scale, const uint8_t*
     if (slots < 1) slots = 1;
     int pm = 4;                                           // row tiles per panel: an XCD's 64 resident tiles then span
     if (pm > tiles_m) pm = tiles_m;                       // 4 row tiles x 16 channel tiles, 4 MiB of A and of W at K = 4096
-    int max_full = 0, max_half = 0;
+    const int parts = lut ? 2 : fql_tail_parts(tiles_m * tiles_n, slots);
+    int max_full = 0, max_items = 0;
     for (int x = 0; x < FQL_XCDS; ++x) {
-        const fql_split sp = fql_xcd_split(x, tiles_m * tiles_n, slots);
+        const fql_split sp = fql_xcd_split(x, tiles_m * tiles_n, slots, parts);
         max_full = sp.nfull > max_full ? sp.nfull : max_full;
-        max_half = sp.nhalf > max_half ? sp.nhalf : max_half;
+        max_items = sp.nitems > max_items ? sp.nitems : max_items;
     }
-    const unsigned full_wgs = (unsigned)(max_full * FQL_XCDS), half_wgs = (unsigned)(max_half * FQL_XCDS);
+    const unsigned full_wgs = (unsigned)(max_full * FQL_XCDS), tail_wgs = (unsigned)(max_items * FQL_XCDS);
     if (lut) {
-        hipLaunchKernelGGL(fq_gemm_large_lut_kernel, dim3(full_wgs + half_wgs), dim3(FQL_THREADS), FQL_LDS_BYTES, stream,
+        hipLaunchKernelGGL(fq_gemm_large_lut_kernel, dim3(full_wgs + tail_wgs), dim3(FQL_THREADS), FQL_LDS_BYTES, stream,
                            A, a_scale, wp, gs, tscale, Y, M, N, K, tiles_m, tiles_n, slots, pm, full_wgs, swiglu ? 1 : 0, R);
         return;
     }
-    hipLaunchKernelGGL(fq_gemm_large_kernel, dim3(full_wgs + half_wgs), dim3(FQL_THREADS), FQL_LDS_BYTES, stream,
+    hipLaunchKernelGGL(parts == 4 ? fq_gemm_large_kernel<2> : fq_gemm_large_kernel<4>, dim3(full_wgs + tail_wgs), dim3(FQL_THREADS), FQL_LDS_BYTES, stream,
                        A, a_scale, wp, gs, tscale, Y, M, N, K, tiles_m, tiles_n, slots, pm, planes, full_wgs,
                        swiglu ? 1 : 0, R, swiglu ? rowmax : nullptr);
 }

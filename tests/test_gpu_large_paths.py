@@ -393,3 +393,21 @@ def test_large_m_range_on_k_split_tiles(fq, shape, tiles):
     assert np.all(np.abs(y - yl) <= oracle.bf16_ulp_array(yl) + 1e-4 * B)
     Yr, B = oracle.w4a8_gemm_add(A_ref, s_ref, d["q"][pick], d["gscale"][pick], d["w_tscale"], Rb[:, pick], want_bound=True)
     check_gemm(bf16_bits_from_gpu(YR)[:, pick], Yr, B, "split tiles + residual %s" % (shape,))
+
+
+# the last round in halves (11 tiles on an XCD's 64 slots) and in quarters: 1 or 2 tiles behind a full round, with a ragged last row
+# tile (52 rows: the second to fourth quarter are empty) and a ragged channel edge; quarters alone, odd group counts, two
+# rounds of zero-point units
+TAIL_SHAPES = [(2048, 9600, 256), (2100, 7304, 384), (300, 2000, 4224), (459, 136, 128)]
+
+
+@pytest.mark.parametrize("shape", TAIL_SHAPES)
+def test_last_round_in_halves_and_quarters(fq, shape):
+    fq.fq_test_force_kernel("large")
+    try:
+        test_plain_gemm_every_element(fq, shape)
+        test_residual_every_element_and_in_place(fq, shape)
+        test_swiglu_every_element(fq, shape)
+        test_zero_activations_return_the_residual_bit_for_bit(fq, shape)
+    finally:
+        fq.fq_test_force_kernel(None)
