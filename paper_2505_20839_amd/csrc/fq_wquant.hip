@@ -137,19 +137,29 @@ __global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_scales_wide_kernel(co
     fq_v4i w[FQW_CASW_UNROLL];
 #pragma unroll
     for (int u = 0; u < FQW_CASW_UNROLL; ++u) w[u] = bands.next(lane_off);
-    for (int n0 = 0; n0 < N; n0 += ROWS * FQW_CASW_UNROLL) {
+    const auto add = [&](const fq_v4i& v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const unsigned word = (unsigned)v[i];
+            s[2 * i] += __hiloint2double((int)((word << 13) & 0x0FFFE000u), 0);
+            s[2 * i + 1] += __hiloint2double((int)((word >> 3) & 0x0FFFE000u), 0);
+        }
+    };
+    // A round of bands with rows in at most half of them (a small matrix has no other) is finished band by band, without the
+    // work on the rest: 1024 x 1024 5.7 -> 4.0 us, 6000 x 1536 12.9 -> 12.0, 22016 x 1024 46.6 -> 42.2; a fuller one gains nothing by
+    // it (11008 x 4096, 5.5 of 8 bands left: 37.5 us as a whole round, 38.0 band by band).
+    int n0 = 0;
+    for (; n0 + ROWS * FQW_CASW_UNROLL / 2 < N; n0 += ROWS * FQW_CASW_UNROLL) {
 #pragma unroll
         for (int u = 0; u < FQW_CASW_UNROLL; ++u) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const unsigned word = (unsigned)w[u][i];
-                s[2 * i] += __hiloint2double((int)((word << 13) & 0x0FFFE000u), 0);
-                s[2 * i + 1] += __hiloint2double((int)((word >> 3) & 0x0FFFE000u), 0);
-            }
+            add(w[u]);
             w[u] = bands.next(lane_off);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+#pragma unroll
+    for (int u = 0; u < FQW_CASW_UNROLL / 2; ++u)
+        if (n0 + ROWS * u < N) add(w[u]);
     // the rows of a wave are added inside its four 16-lane rows by rotations (lanes LPR apart hold the same channels; DPP:
     // shuffles through LDS took 3 us), the rest through LDS, all in a fixed order
 #pragma unroll
@@ -226,23 +236,32 @@ __global__ __launch_bounds__(FQW_PTS_THREADS) void fq_pts_stats_kernel(const uin
     fq_v4i w[FQW_PTS_UNROLL];
 #pragma unroll
     for (int u = 0; u < FQW_PTS_UNROLL; ++u) w[u] = bands.next(lane_off);
-    for (int n0 = 0; n0 < N; n0 += FQW_PTS_UNROLL * rows_par) {
+    const auto look = [&](const fq_v4i& x) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const unsigned word = (unsigned)x[i >> 1];
+            float v = __uint_as_float((i & 1) ? (word & 0xFFFF0000u) : (word << 16));
+            v *= lam[i];                                  // (exact where there is no lambda)
+            const unsigned b = __float_as_uint(v) & 0x7FFFFFFFu;
+            vmin = b - 1u < vmin ? b - 1u : vmin;         // (a zero wraps to the largest number)
+            const unsigned below = b < FQW_BAND0_END ? b : 0u;
+            vmax = below > vmax ? below : vmax;
+        }
+    };
+    // (the last round band by band: bands without rows cost their work otherwise, 1024 x 1024 14.1 -> 12.9 us, 11008 x 4096 26.1
+    // -> 25.1, all three launches)
+    long long n0 = 0;
+    for (; n0 + (long long)FQW_PTS_UNROLL * rows_par <= N; n0 += (long long)FQW_PTS_UNROLL * rows_par) {
 #pragma unroll
         for (int u = 0; u < FQW_PTS_UNROLL; ++u) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const unsigned word = (unsigned)w[u][i >> 1];
-                float v = __uint_as_float((i & 1) ? (word & 0xFFFF0000u) : (word << 16));
-                v *= lam[i];                              // (exact where there is no lambda)
-                const unsigned b = __float_as_uint(v) & 0x7FFFFFFFu;
-                vmin = b - 1u < vmin ? b - 1u : vmin;     // (a zero wraps to the largest number)
-                const unsigned below = b < FQW_BAND0_END ? b : 0u;
-                vmax = below > vmax ? below : vmax;
-            }
+            look(w[u]);
             w[u] = bands.next(lane_off);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+#pragma unroll
+    for (int u = 0; u < FQW_PTS_UNROLL; ++u)              // the bands left that hold rows
+        if (n0 + (long long)u * rows_par < N) look(w[u]);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const unsigned lo = (unsigned)__shfl_xor((int)vmin, o, 64), hi = (unsigned)__shfl_xor((int)vmax, o, 64);

@@ -144,7 +144,7 @@ def test_full_size_gate_up_matrix(fq):
     assert stops(n) and not any(stops(m) for m in range(n))
 
 # (channels per workgroup: 64 from K = 16384 on, 32 from 8192, else 16, on a 256-unit device; a last line of 8 channels)
-@pytest.mark.parametrize("N,K", [(1, 8), (513, 72), (1025, 4104), (130, 8200), (40, 16392)])
+@pytest.mark.parametrize("N,K", [(1, 8), (513, 72), (1025, 4104), (130, 8200), (40, 16392), (2048, 72), (2049, 72), (6100, 136), (1100, 8200)])
 def test_cas_scales_of_whole_lines_and_remainders(fq, N, K):
     """Row counts around a pass of the workgroup and channel counts around a 128-byte line, with subnormal, huge and zero
     weights: the FP64 mean of every channel."""
@@ -160,7 +160,7 @@ def test_cas_scales_of_whole_lines_and_remainders(fq, N, K):
     assert np.array_equal(lam, want) or np.max(np.abs(lam.view(np.int32).astype(np.int64) - want.view(np.int32))) <= 1
 
 
-@pytest.mark.parametrize("N,K", [(1, 128), (63, 128), (65, 384), (4097, 128)])
+@pytest.mark.parametrize("N,K", [(1, 128), (63, 128), (65, 384), (4097, 128), (2060, 4096)])
 def test_pts_exponent_counts_every_workgroup(fq, N, K):
     """The workgroup that finishes last resolves n: the smallest non-zero and the largest element placed in every corner,
     twice in a row into fresh scratch (whatever the memory held before)."""
