@@ -307,17 +307,16 @@ int fq_kv4_output(const uint8_t *P_fp8, const float *p_scale, const uint8_t *V_p
  * fq_w4a8_gemm_plan: how fq_w4a8_gemm_ws would run an M x N x K problem on a device with `cus`
  *   compute units (0 = the current device).  `plan` is HOST memory of 8 ints:
  *     plan[0]  kernel: 0 one-thread-per-output cross-check kernel, 1 the M <= 16 kernel, 2 the
- *              M <= 64 kernel, 3 the large-M kernel, 4 / 5 / 6 the K-split kernel with 256 x 128 /
- *              128 x 64 / 64 x 64 tiles (plain GEMM and residual form; the fused gate/up form
- *              always takes the large-M or the M <= 64 kernel), its number of tiles in plan[5] and
- *              the number of workgroups that share a tile along K in plan[6]
+ *              M <= 64 kernel, 3 the large-M kernel, 4 / 5 / 6 / 7 the K-split kernel with 256 x 128 /
+ *              128 x 64 / 64 x 64 / 128 x 128 tiles (plain GEMM and residual form; the fused gate/up
+ *              form always takes the large-M or the M <= 64 kernel), its number of tiles in plan[5]
+ *              and the number of workgroups that share a tile along K in plan[6]
  *     plan[1]  large-M kernel: whole tiles (256 rows x 128 channels) with nothing masked in their stores
  *     plan[2]  whole tiles with a ragged edge (masked whole-row stores) or N not a multiple of 8 (written
  *              element by element)
  *     plan[3], plan[4]  the same two counts for the 128-row half tiles of the last round (each run as two items of 64
  *                       rows where every XCD has few of them)
- *     plan[7]  0, or (with plan[0] = 3) the large-M range served by the K-split kernel on plan[5] tiles that all
- *              fit on the device at once: 1 128 x 64, 2 128 x 128 tiles (plan[1] .. plan[4] are 0 then)
+ *     plan[7]  0
  * fq_test_force_kernel: "simple", "small", "large" or "ksplit" makes every GEMM entry point use that kernel
  *   where it serves the shape; "" or NULL restores the choice by M.  The environment variable
  *   FQ_FORCE_KERNEL, read once when the library is loaded, sets the initial value.  Process-wide;

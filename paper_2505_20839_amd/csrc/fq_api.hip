@@ -192,12 +192,10 @@ int fq_w4a8_gemm_plan(int M, int N, int K, int cus, int* plan) {
         const int ks = f == GemmKernel::Large ? 0
                      : f == GemmKernel::KSplit ? ((K / FQ_GROUP >= 8) ? (M <= 512 ? 2 : 1) : 0)
                                                : fq_gemm_ksplit_choice(M, N, K, c);
-        if (f == GemmKernel::Auto && ks != 0 && (ks == 3 || M > FQ_KSPLIT_MAX_M)) {
-            plan[7] = ks - 1;                             // 1: 128 x 64, 2: 128 x 128 tiles of the K-split kernel
-            plan[5] = ((M + 127) / 128) * (ks == 2 ? (N + 63) / 64 : (N + 127) / 128);
-        } else if (ks != 0) {
-            plan[0] = 3 + ks;
-            plan[5] = ks == 1 ? ((M + 255) / 256) * ((N + 127) / 128) : ((M + 127) / 128) * ((N + 63) / 64);
+        if (ks != 0) {
+            const int bm = ks == 1 ? 256 : 128, bn = ks == 2 ? 64 : 128;
+            plan[0] = ks == 3 ? 7 : 3 + ks;
+            plan[5] = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
             plan[6] = fq_gemm_ksplit_slices(ks, M, N, K, c);
         } else {
             fq_gemm_large_plan(M, N, c, plan + 1);

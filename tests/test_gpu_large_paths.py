@@ -354,8 +354,7 @@ def test_a_prepared_workspace_serves_several_sliced_gemms(fq):
         check_gemm(bf16_bits_from_gpu(Yg), Y, B, "shared workspace, N = %d" % N)
 
 
-# (M, N, K) -> the tiles of the K-split kernel that serve it on a 256-unit device: 1 128 x 64, 2 128 x 128 (0: the large-M
-# kernel); even and ragged edges, K splits of equal and unequal length (10 and 11 groups), steps that are no multiple of 4
+# (M, N, K) -> the tiles of the K-split kernel that serve it on a 256-unit device: 1 128 x 64, 2 128 x 128; even and ragged edges, K splits of equal and unequal length (10 and 11 groups), steps that are no multiple of 4
 SPLIT_TILE_SHAPES = [((600, 1024, 1024), 1), ((513, 200, 1408), 1), ((1000, 2040, 1280), 1), ((300, 8200, 1024), 2), ((257, 10000, 1152), 2),
                      ((700, 4104, 1280), 2), ((1025, 3001, 1024), 2), ((1024, 4096, 1408), 2), ((2000, 2048, 1024), 2), ((130, 16384, 1024), 2)]
 
@@ -364,10 +363,10 @@ SPLIT_TILE_SHAPES = [((600, 1024, 1024), 1), ((513, 200, 1408), 1), ((1000, 2040
 def test_large_m_range_on_k_split_tiles(fq, shape, tiles):
     """Problems of the large-M range whose 128-row tiles fit on the device at once: plain, with the residual and in place against
     the oracle (all rows, sampled channels with both edges), and close to the large-M kernel's own tiles."""
-    import ctypes
     M, N, K = shape
-    plan = (ctypes.c_int * 8)()
-    assert fq.lib().fq_w4a8_gemm_plan(M, N, K, 256, plan) == 0 and plan[0] == 3 and plan[7] == tiles
+    plan = fq.fq_w4a8_gemm_plan(M, N, K, 256)
+    assert plan["kernel"] == ("ksplit128x64" if tiles == 1 else "ksplit128x128") and plan["ksplit_slices"] == 1
+    assert plan["ksplit_tiles"] == -(-M // 128) * -(-N // (64 * tiles))
     assert fq.fq_w4a8_gemm_workspace_bytes(M, N, K) == 2 * (2 * -(-(K // 128) // 16)) * M * 16 + (4096 if M <= 512 else 0)
     d = _problem(shape, seed=M + N + K)
     A, s = fq.fq_quantize_act(to_gpu_bf16(d["X_bf16"]))

@@ -28,12 +28,20 @@ def test_kernel_choice_follows_m_and_the_tile_count():
             if top:
                 assert p["ksplit_tiles"] == tiles64 and p["ksplit_slices"] == 1
         else:
-            tiles = -(-M // 128) * -(-N // 64)
+            # the K-split kernel wherever 128 x 64 tiles, or else 128 x 128 tiles, fit one round of the compute units
+            tiles64, tiles128 = -(-M // 128) * -(-N // 64), -(-M // 128) * -(-N // 128)
             rounds = 2 if (M <= 128 and K // 128 >= 40) else 1
-            want_ksplit = M <= 512 and K // 128 >= 8 and tiles <= rounds * CUS
-            assert (p["kernel"] == "ksplit128x64") == want_ksplit, (M, N, K, p)
-            if not want_ksplit:
-                assert p["kernel"] == "large", (M, N, K, p)
+            if K // 128 >= 8 and tiles64 <= rounds * CUS:
+                want, tiles = "ksplit128x64", tiles64
+            elif K // 128 >= 8 and tiles128 <= CUS:
+                want, tiles = "ksplit128x128", tiles128
+            else:
+                want, tiles = "large", 0
+            assert p["kernel"] == want and p["ksplit_tiles"] == tiles, (M, N, K, p)
+            if want == "large":
+                assert p["ksplit_slices"] == 0 and p["whole"] + p["whole_ragged"] + p["half"] + p["half_ragged"] > 0
+            elif want == "ksplit128x128" or M > 512:           # K slices: 128 x 64 tiles and M <= 512 only
+                assert p["ksplit_slices"] == 1
 
 
 def test_large_kernel_tiles_cover_the_problem_once():
@@ -78,8 +86,8 @@ def test_k_slices_fill_the_device_without_empty_slices():
             per = -(-G // S)
             assert per * (S - 1) < G                           # the last slice is not empty
         else:
-            # no further slice would fit, or K is too short to share
-            assert tiles * 2 > CUS or G // 8 < 2 or (-(-G // 2)) * 1 >= G
+            # no further slice would fit, K is too short to share, or the workspace has no counters
+            assert M > 512 or tiles * 2 > CUS or G // 8 < 2 or (-(-G // 2)) * 1 >= G
     assert seen_sliced > 50
 
 
