@@ -108,7 +108,9 @@ __global__ __launch_bounds__(FQW_CAS_THREADS) void fq_cas_scales_kernel(const ui
 // or four times, which used to cap this at 32 channels).  |bf16| becomes FP64 by its bits alone: shifted to the top of
 // the double's exponent and fraction it is the value times 2^-896, subnormals included (the double is subnormal
 // then, in the same steps), so an element costs two integer instructions and an FP64 addition, no conversion; all sums
-// carry that factor, which comes off exactly at the end.
+// carry that factor, which comes off exactly at the end.  Infinities and NaN go in as finite numbers of 2^128 and more that way:
+// a channel with a sum from there on is read once more for them (so that finite weights pay nothing for it), and its sum
+// becomes an infinity or a NaN, as FP64 addition would have made it.
 #define FQW_CASW_UNROLL 8
 #define FQW_CASW_THREADS 1024
 template <int CTRL>
@@ -173,14 +175,28 @@ __global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_scales_wide_kernel(co
         for (int i = 0; i < 8; ++i) part[4 * wave + (lane >> 4)][8 * (lane & 15) + i] = s[i];
     }
     __syncthreads();
-    if ((int)threadIdx.x < CH && k0 + (int)threadIdx.x < K) {
-        double t = 0.0;
+    if (wave != 0) return;
+    const bool mine = lane < CH && k0 + lane < K;         // (CH <= 64: the channels' sums are lanes of the first wave)
+    double t = 0.0;
+    if (mine) {
 #pragma unroll 16
-        for (int r = 0; r < 64; ++r) t += part[r][threadIdx.x];
+        for (int r = 0; r < 64; ++r) t += part[r][lane];
         t *= 0x1p+896;
-        lambda[k0 + threadIdx.x] =
-            t == 0.0 ? 1.0f : (float)((double)target / (t / (double)N));            // an all-zero channel keeps 1
     }
+    for (unsigned long long big = __ballot(mine && t >= 0x1p+128); big != 0; big &= big - 1) {
+        const int c = __ffsll(big) - 1;
+        bool inf = false, nan = false;
+        for (int n = lane; n < N; n += 64) {
+            const unsigned b = W[(size_t)n * K + k0 + c] & 0x7FFFu;
+            inf |= b == 0x7F80u;
+            nan |= b > 0x7F80u;
+        }
+        const bool any_inf = __ballot(inf) != 0, any_nan = __ballot(nan) != 0;
+        if (lane == c) t = any_nan ? __builtin_nan("") : any_inf ? __builtin_inf() : t;
+    }
+    if (mine)
+        lambda[k0 + lane] =
+            t == 0.0 ? 1.0f : (float)((double)target / (t / (double)N));            // an all-zero channel keeps 1
 }
 
 // ---- per-tensor scaling: statistics, then the choice of n --------------------------------------------

@@ -193,3 +193,21 @@ def test_quantize_weights_at_the_edges_of_a_workgroup(fq, N, K, n_pts):
         q, gs = fq.fq_quantize_weights(to_gpu_bf16(Wb), None, n_pts, rne)
         qr, gr = oracle.quantize_weights(Wb, None, n_pts, sigma_rne=rne)
         assert np.array_equal(gs.cpu().numpy(), gr) and np.array_equal(q.cpu().numpy(), qr)
+
+
+@pytest.mark.parametrize("N,K", [(5, 72), (700, 72), (129, 8208), (70, 16392), (3, 75)])
+def test_cas_scales_of_channels_that_are_not_finite(fq, N, K):
+    """A NaN anywhere in a channel gives a NaN scale, an infinity a scale of 0, in every form of the kernel (K odd: the one
+    without whole 16-byte steps); the other channels, sums beyond 2^128 of finite weights among them, keep their means."""
+    Wb = workloads.draw_weights(N, K, seed=N + K)
+    nan, inf = [0, 9, K - 1], [1, 17, K - 3]
+    Wb[N - 1, nan] = [0x7F81, 0xFFC0, 0x7FFF]
+    Wb[N // 2, inf] = [0x7F80, 0xFF80, 0x7F80]
+    Wb[0, 9] = 0x7F80                                          # NaN and infinity in one channel
+    Wb[:, 5] = 0x7F7F
+    lam = fq.fq_cas_scales(to_gpu_bf16(Wb), 0.02).cpu().numpy()
+    assert np.isnan(lam[nan]).all() and (lam[inf] == 0).all()
+    rest = np.setdiff1d(np.arange(K), nan + inf)
+    mean = np.abs(oracle.bf16_bits_to_f64(Wb[:, rest])).mean(axis=0)
+    want = (0.02 / mean).astype(np.float32)
+    assert np.max(np.abs(lam[rest].view(np.int32).astype(np.int64) - want.view(np.int32))) <= 1
