@@ -388,7 +388,8 @@ __global__ __launch_bounds__(256) void fq_quantize_weights_kernel(const uint16_t
 }
 
 void fq_launch_cas_scales(const uint16_t* W, float target, float* lambda, int N, int K, hipStream_t stream) {
-    if ((K % 8) == 0 && (reinterpret_cast<uintptr_t>(W) % 16) == 0) {
+    // (a band of rows is addressed through 32-bit offsets: at most 128 rows where K is past 8192)
+    if ((K % 8) == 0 && (reinterpret_cast<uintptr_t>(W) % 16) == 0 && (long long)K * (128 * 2) < 0xFFFFFF00ll) {
         // channels per workgroup.  Whole lines where they give more than half the compute units a workgroup (N x K: 4096 x
         // 11008 21.3 us; 32 channels 29.4, 16 channels 33.1), 32 channels from a third of them on (14336 x 8192: 58.1;
         // 64 channels 62.4, 16 channels 81.7), else 16 (11008 x 4096: 33.6; 32 channels 39.7, 64 channels 44.5)

@@ -211,3 +211,14 @@ def test_cas_scales_of_channels_that_are_not_finite(fq, N, K):
     mean = np.abs(oracle.bf16_bits_to_f64(Wb[:, rest])).mean(axis=0)
     want = (0.02 / mean).astype(np.float32)
     assert np.max(np.abs(lam[rest].view(np.int32).astype(np.int64) - want.view(np.int32))) <= 1
+
+
+@pytest.mark.parametrize("N,K", [(1, 1 << 25), (2, (17 << 20) + 8)])
+def test_cas_scales_of_rows_beyond_32_bit_band_offsets(fq, N, K):
+    """Rows so long that the 128 rows a workgroup reads side by side span 4 GiB and more: every row counts once (K past 2^24: offsets
+    that wrapped would read the first rows again in the place of rows past N)."""
+    W = torch.full((N, K), 0.5, dtype=torch.bfloat16, device="cuda")
+    W[:, -1] = 2.0
+    lam = fq.fq_cas_scales(W, 0.25)
+    torch.cuda.synchronize()
+    assert bool((lam[:-1] == 0.5).all()) and float(lam[-1]) == 0.125
