@@ -6,7 +6,7 @@ tensor is not on the GPU, the call raises.
 
 The calls of a running model marshal their arguments in native code (``_fq_marshal.so``, see its source); whatever that
 does not take -- another kind of tensor, a wrong shape, an argument to be refused -- comes back as None and goes through
-the Python form below it, which decides and raises.
+the Python form below it, which decides and raises.  Without that extension every call takes its Python form.
 """
 from __future__ import annotations
 
@@ -14,6 +14,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -115,17 +116,34 @@ def lib() -> ctypes.CDLL:
     return L
 
 
+class _PythonForms:
+    """In the place of the native marshalling where there is none: declines every call."""
+
+    def __getattr__(self, name):
+        return _decline
+
+
+def _decline(*args):
+    return None
+
+
 def marshal():
-    """The native marshalling, bound to the loaded library (built in-tree on first use if it was never built)."""
+    """The native marshalling, bound to the loaded library (built in-tree on first use if it was never built).  Where it can
+    be neither built nor loaded (it needs a C++ compiler and the headers of torch and Python, the library itself does not),
+    a warning is given once and every call takes its Python form."""
     global _marshal
     if _marshal is None:
-        if not os.path.exists(_build.MARSHAL_PATH):
-            _build.build_marshal()
-        loader = importlib.machinery.ExtensionFileLoader("_fq_marshal", _build.MARSHAL_PATH)
-        m = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fq_marshal", loader))
-        loader.exec_module(m)
         L = lib()
-        m.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _MARSHALLED))
+        try:
+            if not os.path.exists(_build.MARSHAL_PATH):
+                _build.build_marshal()
+            loader = importlib.machinery.ExtensionFileLoader("_fq_marshal", _build.MARSHAL_PATH)
+            m = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fq_marshal", loader))
+            loader.exec_module(m)
+            m.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _MARSHALLED))
+        except Exception as e:
+            warnings.warn("calls are marshalled in Python (about 6 us more each): " + str(e), RuntimeWarning, stacklevel=3)
+            m = _PythonForms()
         _marshal = m
     return _marshal
 
