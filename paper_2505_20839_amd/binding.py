@@ -4,7 +4,7 @@ Every step of the path runs in the HIP kernels of ``libfireq.so``; torch is used
 memory and the current stream.  There is no CPU fallback: if the library cannot be loaded or a
 tensor is not on the GPU, the call raises.
 
-The calls of a running model marshal their arguments in native code (``_fq_marshal.so``, see its source); whatever that
+The calls of a running model marshal their arguments in native code (``_fq_marshal-*.so``, see its source); whatever that
 does not take -- another kind of tensor, a wrong shape, an argument to be refused -- comes back as None and goes through
 the Python form below it, which decides and raises.  Without that extension every call takes its Python form.
 """
@@ -128,16 +128,17 @@ def _decline(*args):
 
 
 def marshal():
-    """The native marshalling, bound to the loaded library (built in-tree on first use if it was never built).  Where it can
-    be neither built nor loaded (it needs a C++ compiler and the headers of torch and Python, the library itself does not),
-    a warning is given once and every call takes its Python form."""
+    """The native marshalling, bound to the loaded library (built in-tree on first use if it was never built from these
+    sources for this torch and Python).  Where it can be neither built nor loaded (it needs a C++ compiler and the headers of
+    torch and Python, the library itself does not), a warning is given once and every call takes its Python form."""
     global _marshal
     if _marshal is None:
         L = lib()
         try:
-            if not os.path.exists(_build.MARSHAL_PATH):
+            path = _build.marshal_path()
+            if not os.path.exists(path):
                 _build.build_marshal()
-            loader = importlib.machinery.ExtensionFileLoader("_fq_marshal", _build.MARSHAL_PATH)
+            loader = importlib.machinery.ExtensionFileLoader("_fq_marshal", path)
             m = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fq_marshal", loader))
             loader.exec_module(m)
             m.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _MARSHALLED))
