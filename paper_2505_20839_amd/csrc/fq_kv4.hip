@@ -84,6 +84,8 @@ __global__ __launch_bounds__(256) void fqk_pack_values_kernel(const int8_t* __re
             own[p ^ ((p >> 4) & 7)] = out[i];
         }
     }
+    // (other lanes' chunks are read back: the wave's own LDS accesses stay in order, which the fence holds the compiler to)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     uint8_t* dst = packed + (size_t)blockIdx.y * fqk_value_bytes(T) + (size_t)g * 2048u;
 #pragma unroll
