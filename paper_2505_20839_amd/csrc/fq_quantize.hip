@@ -149,21 +149,35 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(c
 
 namespace {
 
-// Waves per row: enough that a thread holds two chunks, or four where rows are long and many (the row's latency is then
-// hidden by other rows, and fewer waves meet at its barrier).  Measured with zero-point terms, us: 2048 x 4096 8.2 with
-// <4, 2>, 9.7 with <1, 8>; 1000 x 7168 7.7 with <8, 2>, 8.3 <4, 4>, 8.9 <2, 8>, but 8192 x 8192 37.1, 35.0, 36.3;
-// 200 x 11008 4.8 with <16, 2>, 5.0 <8, 4>, 5.7 <4, 8>, but 2048 x 11008 17.9, 16.5, 17.1; 4096 x 1024 6.1 with <1, 4>,
-// 8.0 <4, 2>.  32 x 32016 (no such terms) 5.6 with <16, 8>; 10.9 with four waves that read the row twice.
+// Waves per row and chunks per thread: few rows take many waves with two chunks each (a row's latency is all there is); many
+// rows fewer waves with more (other rows hide the latency, fewer waves meet at a barrier), as long as the last chunk of every
+// thread is not mostly empty.  One process, alternating; us without / with zero-point terms, one workgroup of 4 waves with up to
+// 8 chunks for every row (the former form) | the choice here | its neighbours:
+//     1536 x 2048   4.1 / 4.7 | <4, 2> 3.8 / 4.4; <1, 4> 3.7 / 4.7.    2048 x 2048   4.7 / 5.6 | <1, 4> 4.0 / 4.9; <4, 2> 4.4 / 5.1
+//     512 x 4224    3.6 / 4.6 | <8, 2> 3.3 / 4.0; <4, 3> 3.3 / 4.3.    640 x 4224    3.8 / 4.9 | <4, 3> 3.6 / 4.6; <8, 2> 3.9 / 4.7
+//     2048 x 4224   6.5 / 8.1 | <4, 3> 6.3 / 7.9; <8, 2> 7.1 / 8.7.    5120 x 6144   17.4 / 19.9 | <4, 3> 16.2 / 18.0; <8, 2> 16.4 / 18.9
+//     2048 x 8192   10.4 / 12.9 | <8, 2> 9.8 / 11.7.                   8192 x 8192   32.8 / 36.6 | <8, 2> 30.3 / 33.4
+//     256 x 8320    3.9 / 5.2 | <16, 2> 3.4 / 4.1; <4, 6> 3.5 / 4.7.   400 x 8320    4.3 / 5.8 | <4, 6> 4.1 / 5.4; <16, 2> 4.5 / 5.5
+//     1536 x 8320   8.1 / 10.5 | <4, 6> 8.2 / 10.5; <8, 4> 9.1 / 10.6. 1024 x 9600   6.7 / 8.5 | <4, 6> 6.3 / 8.1; <8, 4> 7.1 / 8.2
+//     400 x 11008   4.9 / 6.5 | <16, 2> 4.8 / 5.8; <8, 4> 4.5 / 5.6.   1024 x 11008  7.7 / 9.8 | <8, 4> 7.7 / 9.1; <16, 2> 8.2 / 9.8
+//     512 x 16384   6.2 / 8.1 | <16, 2> 5.7 / 6.9; <8, 4> 5.5 / 6.9.   4096 x 16384  34.7 / 40.5 | <8, 4> 32.0 / 34.7; <16, 2> 31.0 / 35.5
+//     1024 x 16512  12.6 | <16, 4> 11.7; <16, 8> 17.5.                 2048 x 32768 49.2 | <16, 4> 32.6; <16, 8> 40.6
+//     512 x 40960   19.9 | <16, 8> 15.9 (rows read twice by 16 waves: 14.6).  Longer rows do not fit and are read twice.
 template <bool ZP, bool KNOWN>
 void fq_launch_quantize_as(const uint16_t* X, uint8_t* A, float* a_scale, int M, int K, uint16_t* planes, hipStream_t stream) {
 #define FQ_QUANTIZE(WPR_, CH_, REREAD_) \
     hipLaunchKernelGGL((fq_quantize_kernel<WPR_, CH_, ZP, KNOWN, REREAD_>), dim3((unsigned)((M + (WPR_ > 4 ? 1 : 4 / WPR_) - 1) / (WPR_ > 4 ? 1 : 4 / WPR_))), \
                        dim3(WPR_ > 4 ? 64 * WPR_ : 256), 0, stream, X, A, a_scale, K, planes, M)
-    if (K > 16 * 4096) {
-        if constexpr (!ZP) FQ_QUANTIZE(16, 8, true);
-    } else if (K > 4 * 4096) FQ_QUANTIZE(16, 8, false);
-    else if (K > 2 * 4096) { if (M <= 512) FQ_QUANTIZE(16, 2, false); else FQ_QUANTIZE(8, 4, false); }
-    else if (K > 4096) { if (M <= 4096) FQ_QUANTIZE(8, 2, false); else FQ_QUANTIZE(4, 4, false); }
+    if (K > 4 * 4096) {
+        if constexpr (!ZP) {                              // (no zero-point terms for rows this long)
+            if (K > 16 * 4096) FQ_QUANTIZE(16, 8, true);
+            else if (K > 8 * 4096) FQ_QUANTIZE(16, 8, false);
+            else FQ_QUANTIZE(16, 4, false);
+        }
+    } else if (K > 10240) { if (M <= 512) FQ_QUANTIZE(16, 2, false); else FQ_QUANTIZE(8, 4, false); }
+    else if (K > 2 * 4096) { if (M <= 256) FQ_QUANTIZE(16, 2, false); else FQ_QUANTIZE(4, 6, false); }
+    else if (K > 6144 || (K > 4096 && M <= 512)) FQ_QUANTIZE(8, 2, false);
+    else if (K > 4096) FQ_QUANTIZE(4, 3, false);
     else if (K > 2048 || M <= 1536) FQ_QUANTIZE(4, 2, false);
     else FQ_QUANTIZE(1, 4, false);
 #undef FQ_QUANTIZE

@@ -721,9 +721,12 @@ def test_small_m_rings_and_sub_tiles(fq, shape):
     check_gemm(bf16_bits_from_gpu(YR)[:, pick], Yr, B, "small + residual %s" % (shape,), frobenius=M * len(pick) >= 4000)
 
 
-# waves per row (1, 2, 4, 16) by K and M, the last chunk and the last rows of a workgroup partly there, rows in two passes
+# waves per row (1, 4, 8, 16) and chunks per thread (2, 3, 4, 6, 8) by K and M, at both ends of each range, the last chunk and
+# the last rows of a workgroup partly there, rows in two passes
 @pytest.mark.parametrize("M,K", [(1, 8), (5, 4088), (1537, 4096), (1539, 136), (1601, 264), (65, 4104), (513, 8192), (514, 4224), (600, 8200), (64, 4104),
-                                 (3, 16384), (66, 16384), (2, 16392), (5, 65536), (2, 65544)])
+                                 (3, 16384), (66, 16384), (2, 16392), (5, 65536), (2, 65544),
+                                 (513, 4104), (4097, 6144), (512, 6144), (4099, 6272), (4097, 8192), (256, 8320), (257, 8320), (300, 10240), (513, 10368),
+                                 (3, 32768), (300, 16640), (2, 32776)])
 def test_quantizer_rows_of_every_split(fq, M, K):
     """Codes and scales bit for bit, a zero row and a row whose largest element is its last one among them; with whole groups
     also the prepared workspace: the GEMM on it gives what the GEMM that prepares its own gives."""
