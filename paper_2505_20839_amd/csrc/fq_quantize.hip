@@ -76,7 +76,7 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(c
 #pragma unroll
             for (int i = 0; i < CH; ++i) search(keep[i]);
         }
-    } else {
+    } else if (!KNOWN) {
         for (int c = t; c < nchunk; c += T) search(x[c]);
     }
     if (KNOWN) {                                          // (read by one thread before anyone overwrites it below)
