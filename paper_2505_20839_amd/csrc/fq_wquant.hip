@@ -34,7 +34,8 @@ __device__ __forceinline__ int fqw_log2_over_7(unsigned bits) {
 // Consecutive bands of `step` rows of W, one 16-byte load per lane each (`lane_off`: the lane's bytes inside a band): a wave
 // keeps a ring of them in flight and asks for the next band as soon as it has used one, so that the reading never
 // pauses (workgroups that fetch a batch, work on it and fetch the next do so in step, and the memory idles in between:
-// 11008 x 4096 channel means: 37.9 instead of 34.1 us).  Rows past N lie behind the descriptor's range and read as zeros.
+// 11008 x 4096 channel means from memory 40.2 us in batches, 38.1 as a ring).  Rows past N lie behind the descriptor's range and
+// read as zeros.
 struct fqw_bands {
     const uint16_t* p;
     long long left;                                       // bytes from p to the end of W
@@ -119,7 +120,7 @@ __device__ __forceinline__ double fqw_dpp_f64(double v) {
                             __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false));
 }
 
-template <int LPR>
+template <int LPR, bool STREAM>
 __global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_scales_wide_kernel(const uint16_t* __restrict__ W, float target,
                                                                               float* __restrict__ lambda, int N, int K) {
     constexpr int ROWS = FQW_CASW_THREADS / LPR, CH = 8 * LPR, SHARE = 8 / LPR;
@@ -134,11 +135,7 @@ __global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_scales_wide_kernel(co
     double s[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) s[i] = 0.0;
-    fqw_bands bands(W, N, K, k0, ROWS);
-    const unsigned lane_off = on ? (unsigned)sub * (unsigned)K * 2u + 16u * (threadIdx.x % LPR) : FQW_OOB;
     fq_v4i w[FQW_CASW_UNROLL];
-#pragma unroll
-    for (int u = 0; u < FQW_CASW_UNROLL; ++u) w[u] = bands.next(lane_off);
     const auto add = [&](const fq_v4i& v) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -147,21 +144,45 @@ __global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_scales_wide_kernel(co
             s[2 * i + 1] += __hiloint2double((int)((word >> 3) & 0x0FFFE000u), 0);
         }
     };
-    // A round of bands with rows in at most half of them (a small matrix has no other) is finished band by band, without the
-    // work on the rest: 1024 x 1024 5.7 -> 4.0 us, 6000 x 1536 12.9 -> 12.0, 22016 x 1024 46.6 -> 42.2; a fuller one gains nothing by
-    // it (11008 x 4096, 5.5 of 8 bands left: 37.5 us as a whole round, 38.0 band by band).
-    int n0 = 0;
-    for (; n0 + ROWS * FQW_CASW_UNROLL / 2 < N; n0 += ROWS * FQW_CASW_UNROLL) {
+    if constexpr (LPR == 8) {
+        // Whole lines per workgroup and a long row stride: all workgroups fetch a batch of bands at a time, which keeps them on
+        // the same rows of W.  The ring below lets them drift apart, and memory then serves rows 22 to 57 KB apart at random:
+        // 11008 x 22016 115 us in batches, 133 as a ring; 4096 x 11008, from memory, 20.5 -> 21.2 -> 21.9 (nontemporal batches,
+        // these, ring), where the cached lines save the next pass over W more.
+        for (int n0 = sub; n0 < N; n0 += ROWS * FQW_CASW_UNROLL) {
 #pragma unroll
-        for (int u = 0; u < FQW_CASW_UNROLL; ++u) {
-            add(w[u]);
-            w[u] = bands.next(lane_off);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int u = 0; u < FQW_CASW_UNROLL; ++u) {
+                const int n = n0 + ROWS * u;
+                w[u] = (fq_v4i){0, 0, 0, 0};
+                if (n < N && on) {
+                    const fq_v4i* src = reinterpret_cast<const fq_v4i*>(W + (size_t)n * K + k);
+                    w[u] = STREAM ? __builtin_nontemporal_load(src) : *src;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < FQW_CASW_UNROLL; ++u) add(w[u]);
         }
-    }
+    } else {
+        fqw_bands bands(W, N, K, k0, ROWS);
+        const unsigned lane_off = on ? (unsigned)sub * (unsigned)K * 2u + 16u * (threadIdx.x % LPR) : FQW_OOB;
 #pragma unroll
-    for (int u = 0; u < FQW_CASW_UNROLL / 2; ++u)
-        if (n0 + ROWS * u < N) add(w[u]);
+        for (int u = 0; u < FQW_CASW_UNROLL; ++u) w[u] = bands.next(lane_off);
+        // A round of bands with rows in at most half of them (a small matrix has no other) is finished band by band, without the
+        // work on the rest: 1024 x 1024 5.7 -> 4.0 us, 6000 x 1536 12.9 -> 12.0, 22016 x 1024 46.6 -> 42.2; a fuller one gains nothing by
+        // it (11008 x 4096, from memory, 5.5 of 8 bands left: 37.5 us as a whole round, 38.0 band by band).
+        int n0 = 0;
+        for (; n0 + ROWS * FQW_CASW_UNROLL / 2 < N; n0 += ROWS * FQW_CASW_UNROLL) {
+#pragma unroll
+            for (int u = 0; u < FQW_CASW_UNROLL; ++u) {
+                add(w[u]);
+                w[u] = bands.next(lane_off);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < FQW_CASW_UNROLL / 2; ++u)
+            if (n0 + ROWS * u < N) add(w[u]);
+    }
     // the rows of a wave are added inside its four 16-lane rows by rotations (lanes LPR apart hold the same channels; DPP:
     // shuffles through LDS took 3 us), the rest through LDS, all in a fixed order
 #pragma unroll
@@ -387,20 +408,28 @@ __global__ __launch_bounds__(256) void fq_quantize_weights_kernel(const uint16_t
     }
 }
 
+namespace {
+
+// W is larger than the last-level cache (256 MiB): read once from end to end, nothing of it is left for the next pass.
+bool fqw_past_cache(int N, int K) { return (long long)N * K * 2 > (256ll << 20); }
+
+}  // namespace
+
 void fq_launch_cas_scales(const uint16_t* W, float target, float* lambda, int N, int K, hipStream_t stream) {
-    // (a band of rows is addressed through 32-bit offsets: at most 128 rows where K is past 8192)
-    if ((K % 8) == 0 && (reinterpret_cast<uintptr_t>(W) % 16) == 0 && (long long)K * (128 * 2) < 0xFFFFFF00ll) {
-        // channels per workgroup.  Whole lines where they give more than half the compute units a workgroup (N x K: 4096 x
-        // 11008 21.3 us; 32 channels 29.4, 16 channels 33.1), 32 channels from a third of them on (14336 x 8192: 58.1;
-        // 64 channels 62.4, 16 channels 81.7), else 16 (11008 x 4096: 33.6; 32 channels 39.7, 64 channels 44.5)
+    if ((K % 8) == 0 && (reinterpret_cast<uintptr_t>(W) % 16) == 0) {
+        // channels per workgroup: the fewest that take no second round of workgroups (N x K, in cache: 11008 x 4096 with 16 channels
+        // 22.9 us, 32 24.4, 64 28.2; 11008 x 5120, 320 workgroups of 16: 42.9, 32 28.6, 64 34.0; 14336 x 8192 with 32 47.1, 64 46.3;
+        // 4096 x 11008 with 64 18.4, 32 21.8).  A matrix larger than the last-level cache is read nontemporally.
         const int lines = (K + 63) / 64, rounds = (lines + 7) / 8;      // (64 channels = a 128-byte line of a row)
         const int cus = fq_device_cus();
-        if (2 * lines > cus)
-            hipLaunchKernelGGL(fq_cas_scales_wide_kernel<8>, dim3((unsigned)(8 * rounds)), dim3(FQW_CASW_THREADS), 0, stream, W, target, lambda, N, K);
-        else if (3 * lines >= cus)
-            hipLaunchKernelGGL(fq_cas_scales_wide_kernel<4>, dim3((unsigned)(16 * rounds)), dim3(FQW_CASW_THREADS), 0, stream, W, target, lambda, N, K);
-        else
-            hipLaunchKernelGGL(fq_cas_scales_wide_kernel<2>, dim3((unsigned)(32 * rounds)), dim3(FQW_CASW_THREADS), 0, stream, W, target, lambda, N, K);
+#define FQW_CASW(LPR_, STREAM_, GRID_) \
+        hipLaunchKernelGGL((fq_cas_scales_wide_kernel<LPR_, STREAM_>), dim3((unsigned)(GRID_)), dim3(FQW_CASW_THREADS), 0, stream, W, target, lambda, N, K)
+        if (2 * lines > cus) {
+            if (fqw_past_cache(N, K)) FQW_CASW(8, true, 8 * rounds);
+            else                      FQW_CASW(8, false, 8 * rounds);
+        } else if (4 * lines > cus) FQW_CASW(4, false, 16 * rounds);
+        else                        FQW_CASW(2, false, 32 * rounds);
+#undef FQW_CASW
         return;
     }
     constexpr int CH = 2 * FQW_CAS_LPR;
