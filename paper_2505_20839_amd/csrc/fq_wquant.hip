@@ -42,12 +42,13 @@ struct fqw_bands {
     long long band;                                       // bytes of a band
     __device__ __forceinline__ fqw_bands(const uint16_t* W, int N, int K, int k0, int step)
         : p(W + k0), left(((long long)N * K - k0) * 2), band((long long)step * K * 2) {}
+    template <int POLICY = 0>                             // cache policy of the load (2: nontemporal)
     __device__ __forceinline__ fq_v4i next(unsigned lane_off) {
         const long long n = left < 0 ? 0 : left < 0xFFFFFF00ll ? left : 0xFFFFFF00ll;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, (int)(unsigned)n, 0x00020000);
         p += band / 2;
         left -= band;
-        return __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, lane_off, 0, 0));
+        return __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, lane_off, 0, POLICY));
     }
 };
 #define FQW_OOB 0xFFFFFFF0u                               // an offset behind any range
@@ -253,17 +254,20 @@ __device__ __forceinline__ int fqw_pts_resolve(unsigned vmin, unsigned vmax) {
 // and close with two atomics each, which queue up (11008 x 4096, all three launches: 24.8 us with 256 workgroups of
 // 1024 threads, 29.0 with 512 of 512, 43.9 with 1024 of 256; counting the workgroups in, so that the last one resolves n
 // and the third launch goes, cost 12 us more than that launch; 37 us with 512 workgroups that fetch four rows at a time).
+// A small matrix (at most 32 such workgroups) takes workgroups of 256, which start and fold sooner; STREAM: a matrix
+// larger than the last-level cache is read nontemporally (fq_launch_pts_exponent has the figures).
 #define FQW_PTS_UNROLL 6
 #define FQW_PTS_THREADS 1024
 #define FQW_PTS_WGS 256
-__global__ __launch_bounds__(FQW_PTS_THREADS) void fq_pts_stats_kernel(const uint16_t* __restrict__ W,
+template <int THREADS, bool STREAM>
+__global__ __launch_bounds__(THREADS) void fq_pts_stats_kernel(const uint16_t* __restrict__ W,
                                                            const float* __restrict__ lambda,
                                                            unsigned* __restrict__ stats,
                                                            int N, int K, int rows_par) {
-    __shared__ unsigned red[FQW_PTS_THREADS / 64][2];
+    __shared__ unsigned red[THREADS / 64][2];
     unsigned vmin = 0xFFFFFFFFu, vmax = 0u;               // vmin: the smallest non-zero pattern minus 1
     const int KC = K / 8;
-    const unsigned t = blockIdx.x * (unsigned)FQW_PTS_THREADS + threadIdx.x;
+    const unsigned t = blockIdx.x * (unsigned)THREADS + threadIdx.x;
     const int r0 = (int)(t / (unsigned)KC), cc = (int)(t % (unsigned)KC);
     float lam[8];
 #pragma unroll
@@ -272,7 +276,7 @@ __global__ __launch_bounds__(FQW_PTS_THREADS) void fq_pts_stats_kernel(const uin
     const unsigned lane_off = r0 < rows_par ? (unsigned)r0 * (unsigned)K * 2u + 16u * (unsigned)cc : FQW_OOB;
     fq_v4i w[FQW_PTS_UNROLL];
 #pragma unroll
-    for (int u = 0; u < FQW_PTS_UNROLL; ++u) w[u] = bands.next(lane_off);
+    for (int u = 0; u < FQW_PTS_UNROLL; ++u) w[u] = bands.template next<STREAM ? 2 : 0>(lane_off);
     const auto look = [&](const fq_v4i& x) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -292,7 +296,7 @@ __global__ __launch_bounds__(FQW_PTS_THREADS) void fq_pts_stats_kernel(const uin
 #pragma unroll
         for (int u = 0; u < FQW_PTS_UNROLL; ++u) {
             look(w[u]);
-            w[u] = bands.next(lane_off);
+            w[u] = bands.template next<STREAM ? 2 : 0>(lane_off);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -313,7 +317,7 @@ __global__ __launch_bounds__(FQW_PTS_THREADS) void fq_pts_stats_kernel(const uin
     if (threadIdx.x == 0) {
         unsigned m0 = red[0][0], m1 = red[0][1];
 #pragma unroll
-        for (int w = 1; w < FQW_PTS_THREADS / 64; ++w) {
+        for (int w = 1; w < THREADS / 64; ++w) {
             m0 = red[w][0] < m0 ? red[w][0] : m0;
             m1 = red[w][1] > m1 ? red[w][1] : m1;
         }
@@ -438,14 +442,24 @@ void fq_launch_cas_scales(const uint16_t* W, float target, float* lambda, int N,
 
 void fq_launch_pts_exponent(const uint16_t* W, const float* lambda, int* n_out, int N, int K, hipStream_t stream) {
     unsigned* stats = reinterpret_cast<unsigned*>(n_out) + 8;     // the caller's 64 bytes: [0] = n, [8..9] statistics
-    // about FQW_PTS_WGS workgroups' worth of threads, as whole rows of K / 8 chunk columns
+    // at most FQW_PTS_WGS workgroups' worth of threads, as whole rows of K / 8 chunk columns, with the same number of rows each.
+    // One workgroup more than that (the number of rows rounded up, as it used to be) has to share a compute unit: 11008 x
+    // 11008, 257 workgroups, 62 us, with 256 41; 256 x 11008 19.0, 13.7.
     const int KC = K / 8;
-    int rows_par = (FQW_PTS_WGS * FQW_PTS_THREADS + KC - 1) / KC;
-    if (rows_par > N) rows_par = N;
-    const size_t blocks = ((size_t)KC * (size_t)rows_par + FQW_PTS_THREADS - 1u) / FQW_PTS_THREADS;
+    int rows_par = FQW_PTS_WGS * FQW_PTS_THREADS / KC;
+    if (rows_par < 1) rows_par = 1;
+    const int passes = (N + rows_par - 1) / rows_par;
+    rows_par = (N + passes - 1) / passes;
+    const size_t threads = (size_t)KC * (size_t)rows_par;
     hipLaunchKernelGGL(fq_pts_init_kernel, dim3(1), dim3(64), 0, stream, stats);
-    hipLaunchKernelGGL(fq_pts_stats_kernel, dim3((unsigned)blocks), dim3(FQW_PTS_THREADS), 0, stream, W, lambda, stats, N, K,
-                       rows_par);
+#define FQW_PTS(THREADS_, STREAM_) \
+    hipLaunchKernelGGL((fq_pts_stats_kernel<THREADS_, STREAM_>), dim3((unsigned)((threads + THREADS_ - 1u) / THREADS_)), dim3(THREADS_), 0, stream, \
+                       W, lambda, stats, N, K, rows_par)
+    // (64 x 128 10.0 us with workgroups of 1024, 7.3 with 256; 64 x 4096, 32 of 1024: 10.8, 9.6; 64 x 8192: 11.4, 13)
+    if (threads <= 32u * FQW_PTS_THREADS) FQW_PTS(256, false);
+    else if (fqw_past_cache(N, K)) FQW_PTS(FQW_PTS_THREADS, true);
+    else FQW_PTS(FQW_PTS_THREADS, false);
+#undef FQW_PTS
     hipLaunchKernelGGL(fq_pts_resolve_kernel, dim3(1), dim3(64), 0, stream, stats, n_out);
 }
 

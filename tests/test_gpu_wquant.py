@@ -160,10 +160,11 @@ def test_cas_scales_of_whole_lines_and_remainders(fq, N, K):
     assert np.array_equal(lam, want) or np.max(np.abs(lam.view(np.int32).astype(np.int64) - want.view(np.int32))) <= 1
 
 
-@pytest.mark.parametrize("N,K", [(1, 128), (63, 128), (65, 384), (4097, 128), (2060, 4096)])
+# (workgroups of 256 threads up to 32768 threads, of 1024 beyond; one pass over the rows and several, a last one that is shorter)
+@pytest.mark.parametrize("N,K", [(1, 128), (63, 128), (65, 384), (4097, 128), (2060, 4096), (64, 4096), (65, 4096), (191, 11008), (400, 11008)])
 def test_pts_exponent_counts_every_workgroup(fq, N, K):
-    """The workgroup that finishes last resolves n: the smallest non-zero and the largest element placed in every corner,
-    twice in a row into fresh scratch (whatever the memory held before)."""
+    """Every workgroup's rows count: the smallest non-zero and the largest element placed in every corner, twice in a row into
+    fresh scratch (whatever the memory held before)."""
     Wb = np.full((N, K), 0x3F80, np.uint16)                    # 1.0 throughout
     base = int(fq.fq_pts_exponent(to_gpu_bf16(Wb))[0])
     assert base == oracle.pts_exponent(Wb)
