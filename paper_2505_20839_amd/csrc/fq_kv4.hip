@@ -231,8 +231,11 @@ __global__ __launch_bounds__(256) void fq_kv4_scores_kernel(
 // A wave keeps DEPTH groups in flight: what bounds a long cache is the latency of a group's loads times the groups a
 // wave takes one after the other (8 heads x 32001 tokens: 394 us with byte loads and one block of 32 tokens ahead, 26.7
 // us in this form on one workgroup per head and tile).
-// ALIGNED: rows of P and of the scales start at multiples of 16 bytes and T is one (16-byte loads as they are).
-// Otherwise -- a cache that grows by a token per step has any length -- the aligned words around the 32 bytes are
+// CROWD: there are workgroups enough for two and more on every compute unit, and what counts is that they fit: at most 128
+// registers, two groups in flight with up to 16 rows, one with up to 32 (256 heads x 32 rows x 2048 tokens 16.1 us with a ring of two,
+// 160 registers and so one workgroup per compute unit; 12.3 in this form).
+// ALIGNED: rows of P and of the scales start at multiples of 16 bytes and T is one (16-byte loads as they are; the steps past T
+// are not fetched).  Otherwise -- a cache that grows by a token per step has any length -- the aligned words around the 32 bytes are
 // fetched (one more 4-byte load each) and shifted into place; what lies past T in the last group is cleared, in the
 // scales and in the codes, since neither the next row's bytes nor a padding's need be finite numbers.
 //
@@ -291,8 +294,9 @@ __global__ __launch_bounds__(256) void fqk_output_combine_kernel(const float* __
 
 // Rows r0 .. r0 + rows - 1 (at most 16 * MT) of the R query rows of every head; SPLIT: the token groups of slice blockIdx.z,
 // `gper` of them.
-template <int MT, int DT, int NW, int DEPTH, bool ALIGNED, bool SPLIT>
-__global__ __launch_bounds__(64 * NW) void fq_kv4_output_kernel(
+template <int MT, int DT, int NW, int DEPTH, bool ALIGNED, bool SPLIT, bool CROWD>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CROWD ? 4 : 1)))
+void fq_kv4_output_kernel(
     const uint8_t* __restrict__ P, const float* __restrict__ p_scale, const uint8_t* __restrict__ vp,
     const uint8_t* __restrict__ vs, uint16_t* __restrict__ O, float* __restrict__ part, int R, int r0, int rows, int T, int ldp,
     int gper) {
@@ -340,10 +344,12 @@ __global__ __launch_bounds__(64 * NW) void fq_kv4_output_kernel(
                    (unsigned)((kq & 1) * 32 + (dim & 31)) * 16u;
     }
     struct fqk_raw { fq_v4i vq[DT]; unsigned ws[NWD]; unsigned wp[MT][NWD]; };
-    auto fetch32 = [&](__amdgpu_buffer_rsrc_t rs, unsigned off, bool on, unsigned (&w)[NWD]) __attribute__((always_inline)) {
-        const unsigned o = on ? (off & ~3u) : FQK_OOB;    // (steps in the per-lane offset: the range check sees only that)
+    // 32 bytes from `off` on, of which the first `nv` are valid (none if nv <= 0).  ALIGNED: nv is a multiple of 16, and the
+    // 16-byte steps past it read zeros
+    auto fetch32 = [&](__amdgpu_buffer_rsrc_t rs, unsigned off, int nv, unsigned (&w)[NWD]) __attribute__((always_inline)) {
+        const unsigned o = nv > 0 ? (off & ~3u) : FQK_OOB;   // (steps in the per-lane offset: the range check sees only that)
         const fq_v4i lo = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0));
-        const fq_v4i hi = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, o + 16u, 0, 0));
+        const fq_v4i hi = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, !ALIGNED || nv > 16 ? o + 16u : FQK_OOB, 0, 0));
 #pragma unroll
         for (int i = 0; i < 4; ++i) { w[i] = (unsigned)lo[i]; w[4 + i] = (unsigned)hi[i]; }
         if (!ALIGNED) w[NWD - 1] = __builtin_amdgcn_raw_buffer_load_b32(rs, o + 32u, 0, 0);
@@ -355,10 +361,10 @@ __global__ __launch_bounds__(64 * NW) void fq_kv4_output_kernel(
             raw.vq[d] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(
                 rsV, (vlane[d] + (unsigned)g * 2048u) | dead, 0, 2));
         // (32 tokens that start past T hold nothing: not fetched)
-        const bool in = g < g_end && 128 * g + 32 * kq < T;
-        fetch32(rsS, srow + 128u * (unsigned)g, in, raw.ws);
+        const int nv = g < g_end ? T - (128 * g + 32 * kq) : 0;
+        fetch32(rsS, srow + 128u * (unsigned)g, nv, raw.ws);
 #pragma unroll
-        for (int m = 0; m < MT; ++m) fetch32(rsP, prow[m] + 128u * (unsigned)g, in, raw.wp[m]);
+        for (int m = 0; m < MT; ++m) fetch32(rsP, prow[m] + 128u * (unsigned)g, nv, raw.wp[m]);
     };
     // the 8 words of 32 bytes as fetched -> the bytes themselves; `nv` of them are valid
     auto settle = [&](unsigned (&w)[NWD], unsigned off, int nv, bool ragged) __attribute__((always_inline)) {
@@ -375,7 +381,7 @@ __global__ __launch_bounds__(64 * NW) void fq_kv4_output_kernel(
         }
     };
     auto work = [&](int g, fqk_raw& cur) __attribute__((always_inline)) {
-        const bool ragged = g == G - 1 && (T & 127) != 0;
+        const bool ragged = !ALIGNED && g == G - 1 && (T & 127) != 0;
         const int nv = T - (128 * g + 32 * kq);
         settle(cur.ws, srow, nv, ragged);
 #pragma unroll
@@ -426,23 +432,48 @@ __global__ __launch_bounds__(64 * NW) void fq_kv4_output_kernel(
             }
         }
     };
-    fqk_raw ring[DEPTH];
-#pragma unroll
-    for (int i = 0; i < DEPTH; ++i) fetch(g_begin + wave + i * NW, ring[i]);
-    __builtin_amdgcn_sched_barrier(0);                    // all requests go out before any arithmetic
-    int g = g_begin + wave;
-    for (; g + (DEPTH - 1) * NW < g_end; g += DEPTH * NW) {   // whole rounds of the ring
-#pragma unroll
-        for (int i = 0; i < DEPTH; ++i) {
-            work(g + i * NW, ring[i]);
+    if constexpr (CROWD && MT == 1) {
+        fqk_raw cur, nxt;
+        fetch(g_begin + wave, cur);
+        for (int g = g_begin + wave; g < g_end; g += NW) {
+            fetch(g + NW, nxt);
             __builtin_amdgcn_sched_barrier(0);
-            fetch(g + (i + DEPTH) * NW, ring[i]);
+            work(g, cur);
+            g += NW;
+            if (g >= g_end) break;
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(g + NW, cur);
+            __builtin_amdgcn_sched_barrier(0);
+            work(g, nxt);
             __builtin_amdgcn_sched_barrier(0);
         }
+    } else if constexpr (CROWD) {
+        fqk_raw cur;
+        for (int g = g_begin + wave; g < g_end; g += NW) {
+            fetch(g, cur);
+            __builtin_amdgcn_sched_barrier(0);
+            work(g, cur);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        fqk_raw ring[DEPTH];
+    #pragma unroll
+        for (int i = 0; i < DEPTH; ++i) fetch(g_begin + wave + i * NW, ring[i]);
+        __builtin_amdgcn_sched_barrier(0);                    // all requests go out before any arithmetic
+        int g = g_begin + wave;
+        for (; g + (DEPTH - 1) * NW < g_end; g += DEPTH * NW) {   // whole rounds of the ring
+    #pragma unroll
+            for (int i = 0; i < DEPTH; ++i) {
+                work(g + i * NW, ring[i]);
+                __builtin_amdgcn_sched_barrier(0);
+                fetch(g + (i + DEPTH) * NW, ring[i]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    #pragma unroll
+        for (int i = 0; i < DEPTH - 1; ++i)                   // the last, partial one
+            if (g + i * NW < g_end) work(g + i * NW, ring[i]);
     }
-#pragma unroll
-    for (int i = 0; i < DEPTH - 1; ++i)                   // the last, partial one
-        if (g + i * NW < g_end) work(g + i * NW, ring[i]);
     fqk_output_finish<MT, DT, NW, SPLIT>(acc, red, p_scale, O, part, h, d0, R, r0, rows);
 }
 
@@ -483,28 +514,41 @@ void fq_launch_kv4_scores(const uint8_t* Q, const float* q_scale, const uint8_t*
 
 namespace {
 
-template <int MT, int DT, int NW, int DEPTH, bool ALIGNED, bool SPLIT>
+template <int MT, int DT, int NW, int DEPTH, bool ALIGNED, bool SPLIT, bool CROWD = false>
 void fqk_launch_output(const uint8_t* P, const float* p_scale, const uint8_t* vp, const uint8_t* vs, uint16_t* O, float* part,
                        int H, int R, int r0, int rows, int T, int ldp, int slices, int gper, hipStream_t stream) {
     constexpr size_t lds = (size_t)NW * MT * (DT + 1) * 4 * 64 * sizeof(float);
     static fq_device_once attr_once;                      // (one per template instance)
     fq_once_per_device(attr_once, [] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_kv4_output_kernel<MT, DT, NW, DEPTH, ALIGNED, SPLIT>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_kv4_output_kernel<MT, DT, NW, DEPTH, ALIGNED, SPLIT, CROWD>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
-    hipLaunchKernelGGL((fq_kv4_output_kernel<MT, DT, NW, DEPTH, ALIGNED, SPLIT>), dim3((unsigned)H, 8 / DT, (unsigned)slices),
+    hipLaunchKernelGGL((fq_kv4_output_kernel<MT, DT, NW, DEPTH, ALIGNED, SPLIT, CROWD>), dim3((unsigned)H, 8 / DT, (unsigned)slices),
                        dim3(64 * NW), lds, stream, P, p_scale, vp, vs, O, part, R, r0, rows, T, ldp, gper);
 }
 
 template <int MT, bool ALIGNED>
 void fqk_launch_output_dt(int dt, const uint8_t* P, const float* p_scale, const uint8_t* vp, const uint8_t* vs, uint16_t* O, float* part,
                           int H, int R, int r0, int rows, int T, int ldp, int slices, int gper, hipStream_t stream) {
-    if (slices > 1)   fqk_launch_output<MT, 4, 8, 2, ALIGNED, true>(P, p_scale, vp, vs, O, part, H, R, r0, rows, T, ldp, slices, gper, stream);
-    else if (dt == 4) fqk_launch_output<MT, 4, 8, 2, ALIGNED, false>(P, p_scale, vp, vs, O, nullptr, H, R, r0, rows, T, ldp, 1, 0, stream);
-    else if (dt == 2) fqk_launch_output<MT, 2, 8, 2, ALIGNED, false>(P, p_scale, vp, vs, O, nullptr, H, R, r0, rows, T, ldp, 1, 0, stream);
-    // (up to 32 groups: four per wave of 8, all requested at once; 8 heads x 2048 tokens 4.5 us, 5.6 with 16 waves)
-    else if (T <= 4096) fqk_launch_output<MT, 1, 8, 4, ALIGNED, false>(P, p_scale, vp, vs, O, nullptr, H, R, r0, rows, T, ldp, 1, 0, stream);
-    else              fqk_launch_output<MT, 1, 16, (MT == 1 ? 3 : 2), ALIGNED, false>(P, p_scale, vp, vs, O, nullptr, H, R, r0, rows, T, ldp, 1, 0, stream);
+#define FQK_OUT(DT_, NW_, DEPTH_, CROWD_) \
+    fqk_launch_output<MT, DT_, NW_, DEPTH_, ALIGNED, false, CROWD_>(P, p_scale, vp, vs, O, nullptr, H, R, r0, rows, T, ldp, 1, 0, stream)
+    if (slices > 1) fqk_launch_output<MT, 4, 8, 2, ALIGNED, true>(P, p_scale, vp, vs, O, part, H, R, r0, rows, T, ldp, slices, gper, stream);
+    // more than a workgroup per compute unit (rows in 16-byte steps; without, the form has no advantage): 256 heads x 4 rows x 4096
+    // tokens 14.4 us with the ring, 13.9; x 24 rows 21.7, 19.6; 512 heads x 24 rows x 2048 tokens 29.4, 22.8
+    else if (ALIGNED && dt == 4 && 2 * H > fq_device_cus() && (MT == 2 || T > 1024)) FQK_OUT(4, 8, 2, ALIGNED);
+    // a group per wave at most, nothing to keep in flight behind it (8 heads x 4 rows x 128 tokens 2.65 us with a ring of four, 2.38; x
+    // 1000 3.7, 2.95); with 4 tiles and 32 rows in 16-byte steps the ring is as good and takes fewer registers
+    else if (T <= 1024) {
+        if (dt == 4) FQK_OUT(4, 8, (MT == 2 && ALIGNED ? 2 : 1), false);
+        else if (dt == 2) FQK_OUT(2, 8, 1, false);
+        else FQK_OUT(1, 8, 1, false);
+    } else if (dt == 4) FQK_OUT(4, 8, 2, false);
+    else if (dt == 2) FQK_OUT(2, 8, 2, false);
+    // (8 heads x 4 rows x 4096 tokens 4.45 us with a ring of two, 4.95 with four; x 32 rows 7.0, 8.1; 16 waves instead: 8 x 4 x 2048
+    // 5.6 us against 3.3)
+    else if (T <= 4096) FQK_OUT(1, 8, 2, false);
+    else FQK_OUT(1, 16, (MT == 1 ? 3 : 2), false);
+#undef FQK_OUT
 }
 
 // Dimension tiles per workgroup without slices: the most (of 4) that still give a workgroup per compute unit.  Every

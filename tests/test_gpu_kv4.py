@@ -88,6 +88,10 @@ def test_outputs_match_the_oracle(fq, H, R, T):
 
 @pytest.mark.parametrize("H,R,T,ldp,skew", [(1, 1, 1, 1, 0), (3, 4, 31, 33, 1), (2, 16, 127, 131, 2), (2, 5, 129, 129, 3),
                                             (9, 17, 2001, 2008, 0), (70, 2, 1153, 1168, 4), (260, 4, 385, 390, 1), (8, 4, 8191, 8192, 0),
+                                            # rows in 16-byte steps, many heads: several workgroups per compute unit, up to 16 and 32 rows,
+                                            # waves with no, one, an even and an odd number of groups; the same for few heads
+                                            (130, 3, 1040, 1040, 0), (131, 16, 2064, 2064, 0), (129, 17, 144, 144, 0), (132, 32, 1936, 1952, 0),
+                                            (130, 20, 3104, 3104, 0), (6, 17, 1024, 1024, 0), (70, 18, 512, 528, 0), (3, 31, 4080, 4080, 0), (129, 32, 1000, 1007, 3),
                                             # few heads, long caches: token slices (the last one shorter, a last group of 1 token)
                                             (1, 3, 9000, 9000, 0), (5, 20, 8833, 8840, 2), (64, 1, 12400, 12400, 0)])
 def test_outputs_of_caches_of_any_length_and_alignment(fq, H, R, T, ldp, skew):
