@@ -126,11 +126,12 @@ __device__ __forceinline__ fq_v8i fqk_join(fq_v4i lo, fq_v4i hi) {
 // A lane ends up with 4 rows x 1 token; the four lanes of a quad hold the same rows of four neighbouring tokens, and a
 // 4 x 4 transpose of bf16 pairs inside the quad (two DPP exchanges) leaves each lane with one row x four tokens = one
 // 8-byte store instead of four 2-byte ones, which cost the address path four times as much.  Rows of S start at any
-// multiple of 2 bytes (T is whatever the cache has grown to), so the store is one of 2-byte alignment; the last, partial
-// quad of a row is written token by token.
+// multiple of 2 bytes (T is whatever the cache has grown to): STORE 0, rows in 8-byte steps; 1, 8-byte stores of 2-byte
+// alignment, the last, partial quad of a row token by token; 2, 2-byte stores without the transpose, where the memory side pays
+// more for split lines than the address path saves (fq_launch_kv4_scores says where).
 #define FQK_S_NSUB 4
 typedef int fqk_v2i_a2 __attribute__((ext_vector_type(2), aligned(2)));
-template <int MT>
+template <int MT, int STORE>
 __global__ __launch_bounds__(256) void fq_kv4_scores_kernel(
     const uint8_t* __restrict__ Q, const float* __restrict__ q_scale, const uint8_t* __restrict__ kp,
     const uint8_t* __restrict__ ks, float out_scale, uint16_t* __restrict__ S, int R, int T) {
@@ -186,6 +187,17 @@ __global__ __launch_bounds__(256) void fq_kv4_scores_kernel(
 #pragma unroll
         for (int m = 0; m < MT; ++m) {
             const fq_v4f p = FQ_MFMA16(a[m], b, c0[m]);
+            if constexpr (STORE == 2) {
+                const int t = t_first + 16 * j + r16;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int orow = 16 * m + 4 * kq + i;
+                    const fq_v2f pr = {(sig[j] * p[i]) * rs[m][i], 0.f};
+                    if (orow < R && t < T)
+                        S[((size_t)h * R + orow) * T + t] = __builtin_bit_cast(unsigned short, __builtin_convertvector(pr, fq_v2bf)[0]);
+                }
+                continue;
+            }
             const fq_v2f pr0 = {(sig[j] * p[0]) * rs[m][0], (sig[j] * p[1]) * rs[m][1]};
             const fq_v2f pr1 = {(sig[j] * p[2]) * rs[m][2], (sig[j] * p[3]) * rs[m][3]};
             const unsigned pk0 = __builtin_bit_cast(unsigned, __builtin_convertvector(pr0, fq_v2bf));   // rows 0, 1
@@ -203,7 +215,9 @@ __global__ __launch_bounds__(256) void fq_kv4_scores_kernel(
             const int t4 = t_first + 16 * j + (r16 & 12);
             if (orow < R && t4 < T) {
                 uint16_t* dst = S + ((size_t)h * R + orow) * T + t4;
-                if (t4 + 4 <= T) {
+                if (STORE == 0) {
+                    *reinterpret_cast<fq_v2i*>(dst) = out;
+                } else if (t4 + 4 <= T) {
                     *reinterpret_cast<fqk_v2i_a2*>(dst) = out;
                 } else {
 #pragma unroll
@@ -501,8 +515,17 @@ void fq_launch_kv4_unpack(const uint8_t* packed, int8_t* codes, int H, int T, bo
 void fq_launch_kv4_scores(const uint8_t* Q, const float* q_scale, const uint8_t* kp, const uint8_t* ks, float out_scale,
                           uint16_t* S, int H, int R, int T, hipStream_t stream) {
     const dim3 grid((unsigned)((T + 4 * FQK_S_NSUB * 16 - 1) / (4 * FQK_S_NSUB * 16)), (unsigned)H);
+    // rows in 8-byte steps; else, by rows at odd multiples of 2 bytes or even ones (128 heads, T = 4095 and 8190, 8-byte / 2-byte
+    // stores, us: 4 rows 8.3 / 9.1 and 14.7 / 16.8; 8 rows 10.7 / 10.3 and 17.9 / 19.5; 16 rows 15.8 / 13.9 and 25.3 / 25.2; 24 rows
+    // 23.6 / 19.1 and 33.4 / 33.9; 64 rows 46.5 / 40.8 and 78.1 / 72.1)
+    const uintptr_t at = reinterpret_cast<uintptr_t>(S);
+    const int store = (T % 4) == 0 && (at % 8) == 0 ? 0 : R > ((T & 1) != 0 || (at & 2u) != 0 ? 4 : 32) ? 2 : 1;
 #define FQK_SCORES(MT_) \
-    hipLaunchKernelGGL(fq_kv4_scores_kernel<MT_>, grid, dim3(256), 0, stream, Q, q_scale, kp, ks, out_scale, S, R, T)
+    do { \
+        if (store == 0)      hipLaunchKernelGGL((fq_kv4_scores_kernel<MT_, 0>), grid, dim3(256), 0, stream, Q, q_scale, kp, ks, out_scale, S, R, T); \
+        else if (store == 1) hipLaunchKernelGGL((fq_kv4_scores_kernel<MT_, 1>), grid, dim3(256), 0, stream, Q, q_scale, kp, ks, out_scale, S, R, T); \
+        else                 hipLaunchKernelGGL((fq_kv4_scores_kernel<MT_, 2>), grid, dim3(256), 0, stream, Q, q_scale, kp, ks, out_scale, S, R, T); \
+    } while (0)
     switch ((R + 15) / 16) {
         case 1: FQK_SCORES(1); break;
         case 2: FQK_SCORES(2); break;

@@ -122,9 +122,10 @@ def test_outputs_of_caches_of_any_length_and_alignment(fq, H, R, T, ldp, skew):
                "output without scratch %s" % ((H, R, T, ldp, skew),), frobenius=False)
 
 
-@pytest.mark.parametrize("H,R,T", [(2, 4, 1), (3, 3, 5), (1, 33, 255), (4, 7, 1022), (2, 16, 4097)])
+@pytest.mark.parametrize("H,R,T", [(2, 4, 1), (3, 3, 5), (1, 33, 255), (4, 7, 1022), (2, 16, 4097), (1, 32, 510), (1, 33, 510), (2, 50, 68), (1, 64, 1020)])
 def test_scores_of_rows_at_odd_addresses(fq, H, R, T):
-    """Rows of S that start at odd multiples of 2 bytes: every element, and nothing written before or behind the array."""
+    """Rows of S that start at odd multiples of 2 bytes, at even ones and in 8-byte steps, on each of the forms of the store:
+    every element, and nothing written before or behind the array."""
     rng = np.random.default_rng(H + R + T)
     Q = _codes(rng, (H, R, 128)); Kq = rng.integers(-8, 8, (H, T, 128), dtype=np.int8)
     ks = _codes(rng, (H, T), top=0x50); qs = rng.uniform(0.01, 2, (H, R)).astype(np.float32)
