@@ -96,6 +96,20 @@ __global__ __launch_bounds__(256) void fqk_pack_values_kernel(const int8_t* __re
     }
 }
 
+// The same with a thread per packed byte, for a few groups (fq_launch_kv4_pack): bound by latency, which is that of two byte
+// loads here and of 32 loads, a transposition and a change of lanes there.
+__global__ __launch_bounds__(256) void fqk_pack_values_few_kernel(const int8_t* __restrict__ codes, uint8_t* __restrict__ packed,
+                                                                  int T, int G) {
+    const unsigned idx = blockIdx.x * 256u + threadIdx.x; // byte of the head's cache, a whole number of workgroups
+    const int8_t* src = codes + (size_t)blockIdx.y * T * FQK_HEAD;
+    const int blk = (int)(idx >> 11), in = (int)(idx & 2047u), lane = (in >> 4) & 63;
+    const int n = (blk / G) * 32 + (lane & 31);           // dimension
+    const int t = (blk % G) * 128 + 64 * (in >> 10) + 32 * (lane >> 5) + (in & 15);   // low nibble; the high one: 16 tokens on
+    const unsigned lo = t < T ? fq_code_from_q(src[(size_t)t * FQK_HEAD + n]) : 8u;
+    const unsigned hi = t + 16 < T ? fq_code_from_q(src[(size_t)(t + 16) * FQK_HEAD + n]) : 8u;
+    packed[(size_t)blockIdx.y * fqk_value_bytes(T) + idx] = (uint8_t)(lo | (hi << 4));
+}
+
 template <bool VALUES>
 __global__ __launch_bounds__(256) void fqk_unpack_kernel(const uint8_t* __restrict__ packed, int8_t* __restrict__ codes,
                                                          int T, size_t per_head) {
@@ -502,6 +516,12 @@ void fq_launch_kv4_pack(const int8_t* codes, uint8_t* packed, int H, int T, bool
         return;
     }
     const int G = (T + 127) / 128;
+    // few groups: 8 heads x 333 tokens (24 groups) 2.4 us with a thread per byte, 3.1 with a wave per group; 8 x 512 (32) 2.6, 3.1; 32
+    // x 100 2.65, 2.8; 8 x 1000 (64) 3.5, 3.3
+    if ((long long)H * G <= 32) {
+        hipLaunchKernelGGL(fqk_pack_values_few_kernel, dim3((unsigned)G * 32u, (unsigned)H), dim3(256), 0, stream, codes, packed, T, G);
+        return;
+    }
     hipLaunchKernelGGL(fqk_pack_values_kernel, dim3((unsigned)(G + 3) / 4u, (unsigned)H), dim3(256), 0, stream, codes, packed, T, G);
 }
 

@@ -86,6 +86,18 @@ def test_outputs_match_the_oracle(fq, H, R, T):
                "output %s" % ((H, R, T),), frobenius=False)   # (token 0 carries the largest scale and most of the norm)
 
 
+@pytest.mark.parametrize("H,T", [(33, 1), (33, 128), (17, 129), (9, 500), (2, 4095), (3, 4097)])
+def test_value_caches_of_few_and_many_groups_are_packed_alike(fq, H, T):
+    """Up to 32 groups of 128 tokens are packed by another kernel than more of them: all heads at once and head by head, byte for
+    byte, the padding past T included."""
+    rng = np.random.default_rng(H * T)
+    codes = _gpu(rng.integers(-8, 8, (H, T, 128), dtype=np.int8))
+    assert H * -(-T // 128) > 32 >= -(-T // 128) or T > 4096
+    whole = fq.fq_kv4_pack(codes, True)
+    assert torch.equal(whole, torch.cat([fq.fq_kv4_pack(codes[h:h + 1], True) for h in range(H)]))
+    assert torch.equal(fq.fq_kv4_unpack(whole, H, T, True), codes)
+
+
 @pytest.mark.parametrize("H,R,T,ldp,skew", [(1, 1, 1, 1, 0), (3, 4, 31, 33, 1), (2, 16, 127, 131, 2), (2, 5, 129, 129, 3),
                                             (9, 17, 2001, 2008, 0), (70, 2, 1153, 1168, 4), (260, 4, 385, 390, 1), (8, 4, 8191, 8192, 0),
                                             # rows in 16-byte steps, many heads: several workgroups per compute unit, up to 16 and 32 rows,
