@@ -336,25 +336,25 @@ __global__ void fq_pts_resolve_kernel(const unsigned* __restrict__ stats, int* _
 
 // ---- group-wise INT4 quantisation ------------------------------------------------------------------
 // 16 lanes per group of 128 weights (8 neighbouring weights = 16 bytes per lane): a wave quantises four groups at a time,
-// FQW_QW_UNROLL times, all of them requested before the first is worked on (11008 x 4096: 37.6 us with a division per
+// UNROLL times, all of them requested before the first is worked on (11008 x 4096: 37.6 us with a division per
 // weight, 32.9 / 30.9 / 32.8 with 1 / 2 / 4 at a time).  Bound by HBM (3 bytes per weight) once
 // the quotient is short: a full IEEE division per weight (about eleven instructions) made it VALU bound.  With r = the
 // correctly rounded 1 / sigma8 (one division per group), q0 = v * r, the exact residual e = fma(-q0, sigma8, v) and
 // q1 = fma(e, r, q0), rint(q1) equals rint of the IEEE quotient for every FP32 v and every E4M3 sigma8 (a host program
 // checks all of them; sigma8 has four significant bits, and a power of two moves nothing).  v is cut to
 // +-16 sigma8 first, which changes no code (they end at -8 and 7) and keeps the residual finite.
-#define FQW_QW_UNROLL 2
+template <int UNROLL>
 __global__ __launch_bounds__(256) void fq_quantize_weights_kernel(const uint16_t* __restrict__ W,
                                                                   const float* __restrict__ lambda, int n_pts,
                                                                   int sigma_rne, int8_t* __restrict__ q,
                                                                   uint8_t* __restrict__ gs, size_t groups, int K) {
-    const size_t grp0 = (size_t)blockIdx.x * (16u * FQW_QW_UNROLL) + (threadIdx.x >> 4);
+    const size_t grp0 = (size_t)blockIdx.x * (16u * UNROLL) + (threadIdx.x >> 4);
     const float p2n = __uint_as_float((unsigned)(n_pts + 127) << 23);    // 2^n, 0 <= n <= 126
     const int sub = threadIdx.x & 15;
-    fq_v4i w[FQW_QW_UNROLL];
-    fq_v4f l0[FQW_QW_UNROLL], l1[FQW_QW_UNROLL];
+    fq_v4i w[UNROLL];
+    fq_v4f l0[UNROLL], l1[UNROLL];
 #pragma unroll
-    for (int u = 0; u < FQW_QW_UNROLL; ++u) {
+    for (int u = 0; u < UNROLL; ++u) {
         const size_t grp = grp0 + 16u * u < groups ? grp0 + 16u * u : groups - 1;   // (past the end: repeated, not stored)
         const size_t e0 = grp * FQ_GROUP + 8 * sub;       // K is a multiple of 128: a group never straddles rows
         w[u] = *reinterpret_cast<const fq_v4i*>(W + e0);
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(256) void fq_quantize_weights_kernel(const uint16_t
         }
     }
 #pragma unroll
-    for (int u = 0; u < FQW_QW_UNROLL; ++u) {
+    for (int u = 0; u < UNROLL; ++u) {
         const size_t grp = grp0 + 16u * u;
         float v[8];
 #pragma unroll
@@ -466,6 +466,12 @@ void fq_launch_pts_exponent(const uint16_t* W, const float* lambda, int* n_out, 
 void fq_launch_quantize_weights(const uint16_t* W, const float* lambda, int n_pts, bool sigma_rne, int8_t* q,
                                 uint8_t* gs, int N, int K, hipStream_t stream) {
     const size_t groups = (size_t)N * (size_t)(K / FQ_GROUP);
-    hipLaunchKernelGGL(fq_quantize_weights_kernel, dim3((unsigned)((groups + 16u * FQW_QW_UNROLL - 1u) / (16u * FQW_QW_UNROLL))), dim3(256), 0, stream, W, lambda,
-                       n_pts, sigma_rne ? 1 : 0, q, gs, groups, K);
+#define FQW_QUANTIZE(U_) \
+    hipLaunchKernelGGL((fq_quantize_weights_kernel<U_>), dim3((unsigned)((groups + 16u * U_ - 1u) / (16u * U_))), dim3(256), 0, stream, W, lambda, \
+                       n_pts, sigma_rne ? 1 : 0, q, gs, groups, K)
+    // one group at a time where that takes at most four workgroups per compute unit: a second one only adds its latency (512 x 1024,
+    // 4096 groups: 3.2 us with two, 2.6 with one; 512 x 4096, 16384 groups: 3.8, 3.3; 1024 x 4096: 5.0, 5.1)
+    if (groups <= 16384u) FQW_QUANTIZE(1);
+    else FQW_QUANTIZE(2);
+#undef FQW_QUANTIZE
 }

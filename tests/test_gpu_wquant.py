@@ -174,9 +174,10 @@ def test_pts_exponent_counts_every_workgroup(fq, N, K):
             assert int(fq.fq_pts_exponent(to_gpu_bf16(Wc))[0]) == oracle.pts_exponent(Wc)
 
 
-@pytest.mark.parametrize("N,K,n_pts", [(1, 128, 0), (15, 640, 3), (67, 128, 126), (129, 384, 7)])
+@pytest.mark.parametrize("N,K,n_pts", [(1, 128, 0), (15, 128, 1), (16, 128, 2), (17, 128, 0), (15, 640, 3), (67, 128, 126), (129, 384, 7),
+                                       (128, 16384, 5), (1489, 1408, 4), (512, 4224, 0), (16417, 128, 2)])
 def test_quantize_weights_at_the_edges_of_a_workgroup(fq, N, K, n_pts):
-    """Group counts around the 64 a workgroup takes, quotients on and beside the rounding boundaries, huge v * 2^n, zero
+    """Group counts around the 16 a workgroup takes of a small matrix (up to 16384 groups) and the 32 of a larger one, quotients on and beside the rounding boundaries, huge v * 2^n, zero
     groups and groups whose scale casts to zero: codes and scales bit for bit."""
     rng = np.random.default_rng(N * K)
     Wb = workloads.draw_weights(N, K, seed=N, channel_spread=1.0)
