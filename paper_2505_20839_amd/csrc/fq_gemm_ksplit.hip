@@ -609,12 +609,16 @@ void fqk_launch(const uint8_t* A, const float* a_scale, const uint8_t* wp, const
 // both lose (2048 x 4096 x 11008, 512 tiles: 89.1 -> 93.5; 512 x 14336 x 4096: 33.3 -> 39.2), except 128 x 64 tiles for
 // a single row tile with a long K, where two rounds still win (M = 128: 20480 x 5120 46.7 -> 43.7, 28672 x 8192
 // 74.5 -> 63.3 with an earlier form of the loop; at K = 4096 equal).
+// With a short K the large-M kernel is the better one where its 128-row halves are one round too (GEMM alone, large-M -> 128 x 128: 256
+// x 11008 x 1024 9.7 -> 10.6 us, 512 x 6144 x 1024 9.8 -> 10.6, 200 x 8200 x 1536 11.0 -> 11.7, 1280 x 3000 x 1024 10.3 -> 11.2; at K =
+// 2048 equal within 1 %, 256 x 14336 x 3072 18.3 -> 17.8); two rounds of halves lose at any K (300 x 8200 x 1024 11.4 -> 10.6).
 int fq_gemm_ksplit_choice(int M, int N, int K, int cus) {
     const int G = K / FQ_GROUP;
     if (M <= 64 || G < 8) return 0;
     const long long rows = (M + 127) / 128, rounds = (M <= 128 && G >= 40) ? 2 : 1;
     if (rows * ((N + 63) / 64) <= rounds * cus) return 2;
-    return rows * ((N + 127) / 128) <= cus ? 3 : 0;
+    const long long cols = (N + 127) / 128, halves = 2 * (long long)((M + 255) / 256) * cols;
+    return rows * cols <= cus && (G >= 16 || halves > cus) ? 3 : 0;
 }
 
 // K slices of the 128 x 64 shape: as many as fill the compute units, each with at least two groups per K split

@@ -354,9 +354,11 @@ def test_a_prepared_workspace_serves_several_sliced_gemms(fq):
         check_gemm(bf16_bits_from_gpu(Yg), Y, B, "shared workspace, N = %d" % N)
 
 
-# (M, N, K) -> the tiles of the K-split kernel that serve it on a 256-unit device: 1 128 x 64, 2 128 x 128; even and ragged edges, K splits of equal and unequal length (10 and 11 groups), steps that are no multiple of 4
+# (M, N, K) -> the tiles of the K-split kernel that serve it on a 256-unit device: 1 128 x 64, 2 128 x 128; even and ragged
+# edges, K splits of equal and unequal length (9, 10, 11, 17 and 19 groups), steps that are no multiple of 4
 SPLIT_TILE_SHAPES = [((600, 1024, 1024), 1), ((513, 200, 1408), 1), ((1000, 2040, 1280), 1), ((300, 8200, 1024), 2), ((257, 10000, 1152), 2),
-                     ((700, 4104, 1280), 2), ((1025, 3001, 1024), 2), ((1024, 4096, 1408), 2), ((2000, 2048, 1024), 2), ((130, 16384, 1024), 2)]
+                     ((700, 4104, 2048), 2), ((1025, 3001, 2176), 2), ((1024, 4096, 2432), 2), ((2000, 2048, 2048), 2), ((130, 16384, 2048), 2),
+                     ((128, 22016, 1024), 2), ((513, 6144, 1280), 2)]
 
 
 @pytest.mark.parametrize("shape,tiles", SPLIT_TILE_SHAPES)

@@ -8,7 +8,7 @@ from paper_2505_20839_amd import binding
 CUS = 256
 MS = [1, 16, 17, 56, 57, 64, 65, 100, 128, 129, 192, 256, 300, 384, 512, 513, 1024, 2048, 8192]
 NS = [32, 64, 96, 200, 512, 1000, 4096, 6144, 8192, 11008, 14336, 16384, 16448, 22016, 28672]
-KS = [128, 256, 1024, 1408, 4096, 5120, 8192, 11008, 16384]
+KS = [128, 256, 1024, 1408, 1920, 2048, 4096, 5120, 8192, 11008, 16384]
 
 
 def _plan(M, N, K):
@@ -28,12 +28,13 @@ def test_kernel_choice_follows_m_and_the_tile_count():
             if top:
                 assert p["ksplit_tiles"] == tiles64 and p["ksplit_slices"] == 1
         else:
-            # the K-split kernel wherever 128 x 64 tiles, or else 128 x 128 tiles, fit one round of the compute units
+            # the K-split kernel wherever 128 x 64 tiles, or else 128 x 128 tiles, fit one round of the compute units (the latter
+            # with K below 2048 only where the large-M kernel's halves do not)
             tiles64, tiles128 = -(-M // 128) * -(-N // 64), -(-M // 128) * -(-N // 128)
             rounds = 2 if (M <= 128 and K // 128 >= 40) else 1
             if K // 128 >= 8 and tiles64 <= rounds * CUS:
                 want, tiles = "ksplit128x64", tiles64
-            elif K // 128 >= 8 and tiles128 <= CUS:
+            elif tiles128 <= CUS and (K >= 2048 or (K >= 1024 and 2 * -(-M // 256) * -(-N // 128) > CUS)):
                 want, tiles = "ksplit128x128", tiles128
             else:
                 want, tiles = "large", 0
