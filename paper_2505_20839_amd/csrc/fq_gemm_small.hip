@@ -659,8 +659,9 @@ namespace {
 
 // How a small-M problem is cut up: channels per workgroup (an even share of N over the compute units,
 // a multiple of 8, at most `max_cols`, or 64 where a wave's slice is longer than 4 groups; more channels than that go in
-// several even rounds: 16 x 28672 x 4096 15.0 us in 448 workgroups of 64 channels, 13.3 us in 256 of 112), workgroups, groups per wave,
-// sub-tiles of 16 channels, and whether the scale bytes of four consecutive groups are one aligned word.
+// several even rounds: 16 x 28672 x 4096 15.0 us in 448 workgroups of 64 channels, 13.3 us in 256 of 112; 64 x 18432 x 4096 27.0 us in
+// 288 of 64, 25.3 in 461 of 40.  With more than 16 rows an even round of 49 to 63 channels has as many sub-tiles as one of 64 and more
+// workgroups: 64 stay, 64 x 28672 x 4096 with the residual 30.7 us, in 512 of 56 32.3), workgroups, groups per wave, sub-tiles of 16 channels, and whether the scale bytes of four consecutive groups are one aligned word.
 struct fqs_shape {
     int cols;
     unsigned grid;
@@ -668,7 +669,7 @@ struct fqs_shape {
     bool words;
 };
 
-fqs_shape fqs_shape_of(int N, int K, const uint8_t* gs, int max_cols) {
+fqs_shape fqs_shape_of(int M, int N, int K, const uint8_t* gs, int max_cols) {
     const int cus = fq_device_cus();
     fqs_shape sh;
     const int G = K / FQ_GROUP;
@@ -678,6 +679,7 @@ fqs_shape fqs_shape_of(int N, int K, const uint8_t* gs, int max_cols) {
     const long long wgs = (long long)rounds * cus;
     sh.cols = (int)((N + wgs - 1) / wgs + 7) & ~7;
     sh.cols = sh.cols < 8 ? 8 : (sh.cols > max_cols ? max_cols : sh.cols);
+    if (M > 16 && rounds > 1 && sh.cols > max_cols - 16) sh.cols = max_cols;
     sh.grid = (unsigned)((N + sh.cols - 1) / sh.cols);
     sh.nsub = (sh.cols + 15) / 16;
     sh.words = (sh.per % 4 == 0) && (G % 4 == 0) && ((reinterpret_cast<uintptr_t>(gs) & 3) == 0);
@@ -693,7 +695,7 @@ bool fq_linear_small_serves(int M, int K) {
 bool fq_launch_linear_small(const uint16_t* X, float* a_scale_out, const uint8_t* wp, const uint8_t* gs, float tscale,
                             uint16_t* Y, int M, int N, int K, hipStream_t stream) {
     if (!fq_linear_small_serves(M, K)) return false;
-    const fqs_shape sh = fqs_shape_of(N, K, gs, FQS16_MAXCOLS);
+    const fqs_shape sh = fqs_shape_of(M, N, K, gs, FQS16_MAXCOLS);
     switch (2 * sh.nsub + (sh.words ? 1 : 0)) {
         case 2: return fq_launch_linear16w<1, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
         case 3: return fq_launch_linear16w<1, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
@@ -715,7 +717,7 @@ bool fq_launch_linear_small(const uint16_t* X, float* a_scale_out, const uint8_t
 bool fq_launch_gemm_small(const uint8_t* A, const float* a_scale, const uint8_t* wp, const uint8_t* gs,
                           float tscale, uint16_t* Y, int M, int N, int K, bool swiglu_epilogue, const uint16_t* R, hipStream_t stream) {
     const int swiglu = swiglu_epilogue ? 1 : 0;
-    const fqs_shape sh = fqs_shape_of(N, K, gs, M <= 16 ? FQS16_MAXCOLS : FQSM_MAXCOLS);
+    const fqs_shape sh = fqs_shape_of(M, N, K, gs, M <= 16 ? FQS16_MAXCOLS : FQSM_MAXCOLS);
     const int cols = sh.cols, per = sh.per, nsub = sh.nsub;
     const unsigned grid = sh.grid;
     if (M <= 16) {

@@ -695,7 +695,7 @@ def test_table_mode_full_size_and_what_it_costs(fq):
 # whole slice and rings gone round, with 1 to 4 sub-tiles.
 SMALL_RING_SHAPES = [(16, 96, 14336), (3, 40, 16384), (5, 64, 17408), (16, 6144, 11008), (9, 8192, 6144), (2, 8192, 12800),
                      (16, 14336, 8192), (7, 11008, 6272), (16, 16392, 8320), (16, 22016, 1024), (12, 24584, 512), (4, 28672, 640),
-                     (1, 30000, 256), (6, 28672, 4096), (37, 14336, 2048), (48, 11008, 1152), (64, 96, 4096), (33, 8192, 4224), (20, 4096, 8192)]
+                     (1, 30000, 256), (6, 28672, 4096), (37, 14336, 2048), (48, 11008, 1152), (64, 96, 4096), (33, 8192, 4224), (20, 4096, 8192), (40, 28680, 512), (17, 18440, 640)]
 
 
 @pytest.mark.parametrize("shape", SMALL_RING_SHAPES)
