@@ -137,3 +137,24 @@ def test_bad_arguments_are_rejected_without_a_launch():
     assert L.fq_pack_weights(null, null, 0, 128, null) == 0
     assert L.fq_unpack_weights(p, null, 8, 128, null) == -1
     assert L.fq_unpack_weights(p, p, 8, 64, null) == -2
+
+
+def test_output_product_with_scratch_is_exported_and_checks_its_scratch():
+    """The entry points of fireq_kv4_ws.h: declared, exported, sized (256 compute units assumed without a GPU), and refused with too
+    little or misaligned scratch where the product is cut into token slices; scratch that is not needed is not looked at."""
+    src = re.sub(r"/\*.*?\*/", "", open(os.path.join(os.path.dirname(HEADER), "fireq_kv4_ws.h")).read(), flags=re.S)
+    names = sorted(set(re.findall(r"\b(fq_[a-z0-9_]+)\s*\(", src)))
+    assert names == ["fq_kv4_output_workspace_bytes", "fq_kv4_output_ws"]
+    L = binding.lib()
+    for name in names:
+        assert hasattr(L, name), name
+    p, odd, null = ctypes.c_void_p(0x1000), ctypes.c_void_p(0x1008), ctypes.c_void_p(0)
+    need = L.fq_kv4_output_workspace_bytes(8, 4, 32001)
+    assert need == 16 * 8 * 4 * 128 * 4                       # 16 slices of FP32 sums
+    assert L.fq_kv4_output_workspace_bytes(256, 4, 32001) == 0 and L.fq_kv4_output_workspace_bytes(8, 4, 512) == 0
+    for bad in ((0, 4, 32001), (8, 0, 32001), (8, 4, 0), (8, 33, 32001), (-1, 4, 4096)):
+        assert L.fq_kv4_output_workspace_bytes(*bad) == 0
+    call = lambda ws, n, H=8, R=4, T=32001, ldp=32001, v=p: L.fq_kv4_output_ws(p, p, v, p, p, H, R, T, ldp, ws, ctypes.c_size_t(n), null)   # noqa: E731
+    assert call(p, need - 1) == -5 and call(odd, need) == -3
+    assert call(p, need, R=33) == -2 and call(p, need, ldp=32000) == -2 and call(p, need, T=0) == -2 and call(p, need, v=odd) == -3
+    assert call(p, need, v=null) == -1 and call(null, 0, H=0) == 0 and call(null, 0, R=0) == 0
