@@ -60,6 +60,35 @@ def test_codes_and_scales_are_those_of_the_quantiser_on_the_same_h(fq, shape):
     check_gemm(Hb, Ho, B, "gate/up + quantised output %s" % (shape,))
 
 
+# one shape per form of the quantiser that takes the row maxima from the GEMM (the output's rows are N/2 long), and one more
+# at the form's edge; the last three are too long for zero-point terms
+KNOWN_ROWS = [(1601, 528), (2050, 4096), (300, 4096), (1536, 512), (600, 8448), (2050, 12288), (300, 8448), (130, 16384),
+              (200, 16640), (260, 16640), (258, 20480), (130, 20736), (514, 20736), (513, 32768), (300, 33024), (65, 65792), (66, 131584)]
+
+
+@pytest.mark.parametrize("M,N", KNOWN_ROWS)
+def test_every_form_of_the_quantiser_of_known_rows(fq, M, N):
+    """Codes and scales are those of the quantiser that searches the row, for ragged row counts, with and without the
+    zero-point terms of the next layer; those terms are what that quantiser writes into a workspace."""
+    K, Kn = 128, N // 2
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    A, s = fq.fq_quantize_act(torch.randn((M, K), generator=g, device="cuda").bfloat16())
+    w = fq.fq_pack_weights(torch.randint(-8, 8, (N, K), generator=g, device="cuda", dtype=torch.int8))
+    gs = torch.randint(0x20, 0x38, (N, K // 128), generator=g, device="cuda", dtype=torch.uint8)
+    need = fq.fq_w4a8_gemm_workspace_bytes(M, 256, Kn) if Kn % 128 == 0 and Kn <= 16384 else 0
+    H, C, hs = fq.fq_w4a8_gemm_swiglu_quant(A, s, w, gs, 0.03125, N)
+    C_ref, s_ref = fq.fq_quantize_act(H)
+    torch.cuda.synchronize()
+    assert torch.equal(C, C_ref) and torch.equal(hs, s_ref)
+    if need:
+        ws, ws_ref = (torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda") for _ in range(2))
+        H, C, hs = fq.fq_w4a8_gemm_swiglu_quant(A, s, w, gs, 0.03125, N, next_workspace=ws)
+        C2, s2 = fq.fq_quantize_act(H, ws_ref)
+        torch.cuda.synchronize()
+        assert torch.equal(C, C_ref) and torch.equal(hs, s_ref) and torch.equal(C2, C_ref) and torch.equal(s2, s_ref)
+        assert torch.equal(ws, ws_ref)
+
+
 def test_two_calls_in_a_row_leave_nothing_behind(fq):
     """The row maxima live in the scale array between the two kernels of a call: a second call with other operands
     (smaller magnitudes) into the same arrays must not see the first call's maxima."""

@@ -105,7 +105,8 @@ def test_value_caches_of_few_and_many_groups_are_packed_alike(fq, H, T):
                                             (130, 3, 1040, 1040, 0), (131, 16, 2064, 2064, 0), (129, 17, 144, 144, 0), (132, 32, 1936, 1952, 0),
                                             (130, 20, 3104, 3104, 0), (6, 17, 1024, 1024, 0), (70, 18, 512, 528, 0), (3, 31, 4080, 4080, 0), (129, 32, 1000, 1007, 3),
                                             # few heads, long caches: token slices (the last one shorter, a last group of 1 token)
-                                            (1, 3, 9000, 9000, 0), (5, 20, 8833, 8840, 2), (64, 1, 12400, 12400, 0)])
+                                            (1, 3, 9000, 9000, 0), (5, 20, 8833, 8840, 2), (64, 1, 12400, 12400, 0),
+                                            (4, 20, 8832, 8832, 0), (2, 32, 12288, 12304, 0)])
 def test_outputs_of_caches_of_any_length_and_alignment(fq, H, R, T, ldp, skew):
     """Token counts, row strides and base addresses that are multiples of nothing, on every number of dimension tiles per
     workgroup: what lies behind the T codes of a row (here NaN codes) and behind the scales must not enter a sum."""
@@ -123,7 +124,9 @@ def test_outputs_of_caches_of_any_length_and_alignment(fq, H, R, T, ldp, skew):
     O1 = torch.empty_like(O)
     assert fq.lib().fq_kv4_output(Pd.data_ptr(), pd.data_ptr(), vp.data_ptr(), vd.data_ptr(), O1.data_ptr(), H, R, T, ldp,
                                   torch.cuda.current_stream().cuda_stream) == 0
+    again = fq.fq_kv4_output(Pd, pd, vp, vd)
     torch.cuda.synchronize()
+    assert torch.equal(O, again), "not deterministic"
     assert (fq.lib().fq_kv4_output_workspace_bytes(H, R, T) > 0) == (T > 8000)
     if T < 8000:
         assert torch.equal(O, O1)
@@ -132,6 +135,23 @@ def test_outputs_of_caches_of_any_length_and_alignment(fq, H, R, T, ldp, skew):
                "output %s" % ((H, R, T, ldp, skew),), frobenius=False)
     check_gemm(bf16_bits_from_gpu(O1).reshape(H * R, 128), Or.reshape(H * R, 128), B.reshape(H * R, 128),
                "output without scratch %s" % ((H, R, T, ldp, skew),), frobenius=False)
+
+
+@pytest.mark.parametrize("T,ldp", [(200, 1500000001), (9000, 2147483521)])
+def test_outputs_of_probability_rows_beyond_32_bit_offsets(fq, T, ldp):
+    """Rows of P so far apart that a head's rows span more than 4 GiB are taken a few at a time (two of the three, or each by itself),
+    without and with token slices."""
+    R = 3
+    rng = np.random.default_rng(T)
+    P = torch.empty((1, R, ldp), dtype=torch.uint8, device="cuda")
+    codes = _codes(rng, (1, R, T), top=0x70, signed=False)
+    P[:, :, :T] = _gpu(codes)
+    Vq = rng.integers(-8, 8, (1, T, 128), dtype=np.int8)
+    vs = _codes(rng, (1, T), top=0x50); ps = rng.uniform(0.001, 0.1, (1, R)).astype(np.float32)
+    O = fq.fq_kv4_output(P, _gpu(ps), fq.fq_kv4_pack(_gpu(Vq), True), _gpu(vs))
+    torch.cuda.synchronize()
+    Or, B = oracle.kv4_output(codes, ps, Vq, vs, want_bound=True)
+    check_gemm(bf16_bits_from_gpu(O).reshape(R, 128), Or.reshape(R, 128), B.reshape(R, 128), "output, rows %d apart" % ldp, frobenius=False)
 
 
 @pytest.mark.parametrize("H,R,T", [(2, 4, 1), (3, 3, 5), (1, 33, 255), (4, 7, 1022), (2, 16, 4097), (1, 32, 510), (1, 33, 510), (2, 50, 68), (1, 64, 1020)])

@@ -21,18 +21,19 @@ def fq():
         pytest.fail("GPU tests need a GPU: torch.cuda.is_available() is False")
     from paper_2505_20839_amd import binding
     binding.lib()
+    assert isinstance(binding.marshal(), type(np)), "the native marshalling module did not load"
     return binding
 
 
 def _both(fq, name, make):
-    """The outcome of a call through the native and through the Python form: (outputs as a list) or (exception type, text).
-    `make` builds the arguments anew for each."""
+    """The outcome of a call through the native and through the Python form: (outputs as a list) or (exception type, text);
+    then whether the native form took it.  `make` builds the arguments anew for each."""
     got = []
-    for stub in (None, _Declines()):
+    sees = _Sees(fq.marshal())
+    for stub in (sees, _Declines()):
         native = fq.marshal()
         try:
-            if stub is not None:
-                fq._marshal = stub
+            fq._marshal = stub
             args, kw = make()
             try:
                 r = getattr(fq, name)(*args, **kw)
@@ -42,11 +43,27 @@ def _both(fq, name, make):
                 got.append((type(e), str(e)))
         finally:
             fq._marshal = native
-    return got
+    return got + [sees.taken]
 
 
-def _same(fq, name, make, fails=None):
-    a, b = _both(fq, name, make)
+class _Sees:
+    """Stands in for the native module: passes every call on, and notes whether it was taken or declined."""
+
+    def __init__(self, native):
+        self.native, self.taken = native, []
+
+    def __getattr__(self, name):
+        def call(*a):
+            r = getattr(self.native, name)(*a)
+            self.taken.append(r is not None)
+            return r
+        return call
+
+
+def _same(fq, name, make, fails=None, native=None):
+    """`native`: True where the native module must take the call itself, False where it must decline."""
+    a, b, taken = _both(fq, name, make)
+    assert native is None or taken == [native], (name, taken)
     if fails is not None:
         assert isinstance(a, tuple) and isinstance(b, tuple), (name, a, b)
         assert a == b and issubclass(a[0], fails), (name, a, b)
@@ -77,14 +94,14 @@ def test_linear_layer_calls(fq, M, N, K):
     x = _x(M, K)
     out = lambda: torch.empty((M, N), dtype=torch.bfloat16, device="cuda")   # noqa: E731
     for n in (N, np.int64(N)):
-        _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 0.5, n), {}))
+        _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 0.5, n), {}), native=n is N and M > 0)
     for ts in (2, np.float32(0.5), torch.tensor(0.25)):
-        _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, ts, N), {}))
-    _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 1.0, N), {"out": out()}))
-    _same(fq, "fq_w4a8_linear", lambda: ((x.as_subclass(_Sub), w, gs, 1.0, N), {}))
+        _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, ts, N), {}), native=type(ts) is int and M > 0)
+    _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 1.0, N), {"out": out()}), native=M > 0)
+    _same(fq, "fq_w4a8_linear", lambda: ((x.as_subclass(_Sub), w, gs, 1.0, N), {}), native=False)
     need = fq.fq_w4a8_linear_workspace_bytes(M, N, K)
     if need:
-        _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 1.0, N), {"workspace": torch.empty(need, dtype=torch.uint8, device="cuda")}))
+        _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 1.0, N), {"workspace": torch.empty(need, dtype=torch.uint8, device="cuda")}), native=True)
         _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 1.0, N), {"workspace": torch.empty(need // 4 + 4, dtype=torch.float32, device="cuda")}))
         _same(fq, "fq_w4a8_linear", lambda: ((x, w, gs, 1.0, N), {"workspace": torch.empty(16, dtype=torch.uint8, device="cuda")}), fq.FireqError)
     for bad, exc in [((x.float(), w, gs, 1.0, N), TypeError), ((x.cpu(), w, gs, 1.0, N), TypeError), ((None, w, gs, 1.0, N), TypeError),
@@ -103,18 +120,18 @@ def test_quantiser_and_gemm_calls(fq, M, N, K):
     x, res = _x(M, K), _x(M, N, 2)
     need = fq.fq_w4a8_gemm_workspace_bytes(M, N, K)
     ws = torch.empty(max(need, 16), dtype=torch.uint8, device="cuda")
-    _same(fq, "fq_quantize_act", lambda: ((x,), {}))
-    _same(fq, "fq_quantize_act", lambda: ((x, ws), {}))
+    _same(fq, "fq_quantize_act", lambda: ((x,), {}), native=True)
+    _same(fq, "fq_quantize_act", lambda: ((x, ws), {}), native=True)
     _same(fq, "fq_quantize_act", lambda: ((x[:, :4].contiguous(),), {}), fq.FireqError)
     _same(fq, "fq_quantize_act", lambda: ((x.half(),), {}), TypeError)
     A, s = fq.fq_quantize_act(x, ws)
     for name, extra in (("fq_w4a8_gemm", ()), ("fq_w4a8_gemm_swiglu", ()), ("fq_w4a8_gemm_add", (res,)), ("fq_w4a8_gemm_swiglu_quant", ())):
         ok = (A, s, w, gs, 1.0, N) + extra
-        _same(fq, name, lambda: (ok, {}))
-        _same(fq, name, lambda: (ok, {"workspace": ws, "workspace_prepared": need > 0}))
-        _same(fq, name, lambda: (ok, {"workspace": ws}))
-        _same(fq, name, lambda: (ok, {"workspace_prepared": True}))
-        _same(fq, name, lambda: (ok, {"out": torch.empty((M, N if "swiglu" not in name else N // 2), dtype=torch.bfloat16, device="cuda")}))
+        _same(fq, name, lambda: (ok, {}), native=True)
+        _same(fq, name, lambda: (ok, {"workspace": ws, "workspace_prepared": need > 0}), native=True)
+        _same(fq, name, lambda: (ok, {"workspace": ws}), native=True)
+        _same(fq, name, lambda: (ok, {"workspace_prepared": True}), native=True)
+        _same(fq, name, lambda: (ok, {"out": torch.empty((M, N if "swiglu" not in name else N // 2), dtype=torch.bfloat16, device="cuda")}), native=True)
         _same(fq, name, lambda: (ok, {"out": torch.empty((M, 8), dtype=torch.bfloat16, device="cuda")}), fq.FireqError)
         _same(fq, name, lambda: ((A, s[:-1], w, gs, 1.0, N) + extra, {}), fq.FireqError)
         _same(fq, name, lambda: ((A, s.double(), w, gs, 1.0, N) + extra, {}), TypeError)
@@ -125,7 +142,7 @@ def test_quantiser_and_gemm_calls(fq, M, N, K):
                 _same(fq, name, lambda: ((A.view(-1)[8:8 + (M - 1) * K].view(M - 1, K), s[1:], w, gs, 1.0, N) + tuple(e[1:] for e in extra), {}), fq.FireqError)
     _same(fq, "fq_w4a8_gemm_add", lambda: ((A, s, w, gs, 1.0, N, res[:, :-1]), {}), Exception)
     inplace = lambda: (lambda r: ((A, s, w, gs, 1.0, N, r), {"out": r}))(res.clone())   # noqa: E731
-    _same(fq, "fq_w4a8_gemm_add", inplace)
+    _same(fq, "fq_w4a8_gemm_add", inplace, native=True)
     _same(fq, "fq_w4a8_gemm_swiglu", lambda: ((A, s, w, gs, 1.0, N - 1), {}), fq.FireqError)
 
 
@@ -136,8 +153,8 @@ def test_attention_operand_calls(fq, H, R, T, ldp):
     codes = torch.randint(-8, 8, (H, T, 128), generator=g, device="cuda", dtype=torch.int8)
     kp, vp = fq.fq_kv4_pack(codes, False), fq.fq_kv4_pack(codes, True)
     Q, P, sc, f = u8(H, R, 128), u8(H, R, ldp), u8(H, T), torch.rand((H, R), generator=g, device="cuda")
-    _same(fq, "fq_kv4_scores", lambda: ((Q, f, kp, sc, 0.1), {}))
-    _same(fq, "fq_kv4_output", lambda: ((P, f, vp, sc), {}))
+    _same(fq, "fq_kv4_scores", lambda: ((Q, f, kp, sc, 0.1), {}), native=True)
+    _same(fq, "fq_kv4_output", lambda: ((P, f, vp, sc), {}), native=True)
     for name, ok in (("fq_kv4_scores", (Q, f, kp, sc, 0.1)), ("fq_kv4_output", (P, f, vp, sc))):
         _same(fq, name, lambda: ((ok[0].cpu(),) + ok[1:], {}), TypeError)
         _same(fq, name, lambda: ((ok[0], ok[1].double()) + ok[2:], {}), TypeError)
@@ -174,6 +191,7 @@ def test_another_stream_and_a_torch_function_mode(fq):
     assert torch.equal(y, want)
     mode = Sees()
     with mode:
+        assert fq.marshal().linear(x, w, gs, 1.0, 64, None, None) is None
         y = fq.fq_w4a8_linear(x, w, gs, 1.0, 64)
     torch.cuda.synchronize()
     assert torch.equal(y, want) and "empty" in mode.names
