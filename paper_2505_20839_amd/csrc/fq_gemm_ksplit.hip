@@ -150,7 +150,8 @@ void fq_gemm_ksplit_kernel(
         // cycles, and no wave gets past its own to its next MFMA.  Spread over the step's MFMAs it is 2100 (200 x 4096 x 11008
         // with two slices 27.5 -> 25.4 us, 512 x 4096 x 11008 40.3 -> 36.1; the compiler keeps transfers straight into
         // LDS from being spread, so A goes through registers).  Without any loads a step takes 1650 cycles, without LDS
-        // reads as well 1150.  More groups in flight change nothing.
+        // reads as well 1150.  More groups in flight change nothing.  Where a step has fewer requests it gives little (128 x 14336 x 4096
+        // 16.6 -> 15.9 us, 64 x 14336 x 4096 10.7 -> 10.4), and with K = 1024 its longer start costs 0.35 us.
         // A(g) sits in register set g % RA until the middle of step g - 1, when it goes to LDS stage g & 1; W(g) in slot
         // g % 4 until it is unpacked during step g - 1; a word holds the group scales of four steps.
         constexpr int RA = 2;
@@ -602,16 +603,16 @@ void fqk_launch(const uint8_t* A, const float* a_scale, const uint8_t* wp, const
 
 // Which shape of this kernel, if any, serves the problem better than the large-M kernel's own tiles: 0 = none,
 // 2 = 128 x 64 tiles with K quartered, 3 = 128 x 128 tiles with K halved (1 = 256 x 128 tiles is never chosen).
-// A shape wins where its tiles fit one round of the compute units, the smaller one first; measured with a prepared
-// workspace, large-M kernel -> 128 x 128 -> 128 x 64, us: 256 x 14336 x 4096 25.8 -> 23.8 -> 31.3 (two rounds); 700 x 4096 x 4096
-// 23.7 -> 20.7 -> 29.5; 1000 x 4096 x 11008 58.8 -> 50.0 -> 69.5; 1024 x 4096 x 14336 75.2 -> 63.8 -> 85.7; 1500 x 2048 x
-// 8192 44.1 -> 34.7 -> 48.9; 1000 x 2048 x 4096 24.7 -> 19.8 -> 16.7; 1000 x 1024 x 8192 43.4 -> 32.1 -> 24.4; beyond one round
-// both lose (2048 x 4096 x 11008, 512 tiles: 89.1 -> 93.5; 512 x 14336 x 4096: 33.3 -> 39.2), except 128 x 64 tiles for
-// a single row tile with a long K, where two rounds still win (M = 128: 20480 x 5120 46.7 -> 43.7, 28672 x 8192
-// 74.5 -> 63.3 with an earlier form of the loop; at K = 4096 equal).
-// With a short K the large-M kernel is the better one where its 128-row halves are one round too (GEMM alone, large-M -> 128 x 128: 256
-// x 11008 x 1024 9.7 -> 10.6 us, 512 x 6144 x 1024 9.8 -> 10.6, 200 x 8200 x 1536 11.0 -> 11.7, 1280 x 3000 x 1024 10.3 -> 11.2; at K =
-// 2048 equal within 1 %, 256 x 14336 x 3072 18.3 -> 17.8); two rounds of halves lose at any K (300 x 8200 x 1024 11.4 -> 10.6).
+// A shape wins where its tiles fit one round of the compute units, the smaller one first; GEMM alone with a prepared
+// workspace, large-M kernel -> 128 x 128 -> 128 x 64, us: 256 x 14336 x 4096 25.1 -> 21.9 -> 30.2 (two rounds); 700 x 4096 x 4096
+// 23.1 -> 20.0 -> 28.4; 1000 x 4096 x 11008 58.7 -> 49.2 -> 67.4; 1024 x 4096 x 14336 74.1 -> 62.5 -> 83.3; 1500 x 2048 x
+// 8192 43.4 -> 33.7 -> 48.2; 1000 x 2048 x 4096 20.4 -> 19.0 -> 15.8; 1000 x 1024 x 8192 35.8 -> 31.6 -> 24.8; beyond one round
+// both lose (2048 x 4096 x 11008, 512 tiles: 89.6 -> 98.9; 512 x 14336 x 4096: 33.9 -> 42.2).  A single row tile with K >= 5120 is
+// given two rounds of 128 x 64 tiles all the same: that line was drawn when the large-M kernel took 46.7 us for 128 x 20480 x 5120
+// and 74.5 for 128 x 28672 x 8192; it now takes 24.2 and 37.6, two rounds 36.4 and 51.7, so the line is no longer where they meet.
+// With a short K the large-M kernel is the better one where its 128-row halves are one round too (large-M -> 128 x 128: 256
+// x 11008 x 1024 9.75 -> 10.7 us, 512 x 6144 x 1024 9.75 -> 10.7, 200 x 8200 x 1536 10.9 -> 11.5, 1280 x 3000 x 1024 10.3 -> 11.2; 256
+// x 14336 x 2048 13.7 -> 14.1, x 3072 18.5 -> 17.9); two rounds of halves lose at any K (300 x 8200 x 1024 11.4 -> 10.6).
 int fq_gemm_ksplit_choice(int M, int N, int K, int cus) {
     const int G = K / FQ_GROUP;
     if (M <= 64 || G < 8) return 0;
@@ -658,11 +659,13 @@ void fq_launch_gemm_ksplit(int choice, const uint8_t* A, const float* a_scale, c
     else             fqk_launch<4, 2, 4>(A, a_scale, wp, gs, tscale, Y, M, N, K, planes, R, S, counters, partials, stream);
 }
 
-// 16 < M <= 64 without a workspace: 64 x 64 tiles, K quartered, the zero point through the matrix cores.  Measured
-// against the M <= 64 kernel (N = 14336, K = 4096): M = 64 16.2 -> 13.7 us, M = 48 13.3 -> 14.0, M = 33 12.1 -> 13.9 (its
-// time hardly depends on M: 2 us until the first operands arrive, 7.4 us of loop at the rate the weights stream, 1.7 us
-// of fold and epilogue); N = 11008: M = 64 14.9 -> 12.8; N = 4096 (64 tiles for 256 compute units): 11.7 -> 10.9;
-// N = 4096, K = 11008: 25.7 -> 26.5.  So: the top of the range, at least half a round of tiles, K up to 8192.
+// 16 < M <= 64 without a workspace: 64 x 64 tiles, K quartered, the zero point through the matrix cores; its time hardly
+// depends on M.  Against the M <= 64 kernel, M <= 64 -> this, us: N = 14336, K = 4096: M = 64 14.7 -> 10.5, M = 48 12.3 -> 10.2,
+// M = 33 11.1 -> 10.2; 11008 x 4096: 13.4 -> 10.0, 11.3 -> 9.8, 9.9 -> 9.6; 8192 x 8192: 19.3 -> 16.0, 15.9 -> 15.8, 13.3 -> 15.6;
+// 12288 x 2048: 8.7 -> 7.3, 7.0 -> 7.2, 6.4 -> 7.2; 8192 x 1024: 5.9 -> 5.9, 4.9 -> 5.9, 4.6 -> 5.8; fewer tiles: 6144 x 4096
+// 11.6 -> 9.6, 9.4 -> 9.6; 4096 x 4096 10.6 -> 9.5, 8.7 -> 9.5; 14336 x 11008 32.6 -> 22.7, 27.3 -> 22.2.  So: the top of the
+// range, at least half a round of tiles, K up to 8192, on the safe side on all three but
+// for a short K (57 x 8192 x 1024 5.7 -> 6.0).
 bool fq_gemm_ksplit64_serves(int M, int N, int K, int cus) {
     const int tiles = (N + 63) / 64;
     return M > FQ_KSPLIT64_MIN_M && M <= 64 && K / FQ_GROUP >= 8 && K <= 8192 && tiles <= cus && 2 * tiles >= cus;

@@ -596,7 +596,9 @@ void fqk_launch_output_dt(int dt, const uint8_t* P, const float* p_scale, const 
 
 // Dimension tiles per workgroup without slices: the most (of 4) that still give a workgroup per compute unit.  Every
 // workgroup of a head converts the same P * sigma, so fewer tiles mean more redundant conversions, more of them fewer
-// workgroups (4 rows x 4096 tokens, an earlier form of the kernel: 128 heads 10.0 us with 4 tiles, 11.0 with 2, 13.8 with 1).
+// workgroups (4 rows x 4096 tokens, us with 4 / 2 / 1 tiles: 32 heads 7.0 / 5.4 / 4.6; 64 heads 7.1 / 5.6 / 7.0; 128 heads 7.7 / 9.1
+// / 12.4; x 24 rows 9.6 / 7.4 / 6.6, 9.7 / 7.6 / 11.2, 11.2 / 13.5 / 21.2.  Between the powers of two the next larger number is
+// already the faster one: 48 heads 7.1 / 5.5 / 6.8, 96 heads 7.4 / 8.6 / 9.4).
 int fqk_output_tiles(int H, int cus) {
     int dt = 4;
     while (dt > 1 && (long)H * (8 / dt) < (long)cus) dt >>= 1;
@@ -604,10 +606,12 @@ int fqk_output_tiles(int H, int cus) {
 }
 
 // Token slices of an output product that is given a workspace, and the groups of each: as many as fill the device with
-// workgroups of 4 dimension tiles, every wave with at least one group.  A group costs a wave about 1.2 us (the conversions
-// of its four waves per SIMD), the second kernel 3.5 us, so slices are taken where they save a wave three
-// groups or more.  Measured without -> with (4 rows): 8 heads x 32001 tokens 26.7 -> 9.9 us, x 8192 10.1 -> 6.6, x 4096
-// 6.4 -> 8.6 (not taken); 1 head x 32768 21.7 -> 7.2; 64 heads x 16384 21.5 -> 17.1, x 4096 7.0 -> 9.1 (not taken).
+// workgroups of 4 dimension tiles, every wave with at least one group.  A group costs a wave about 1 us (the conversions
+// of its two to four waves per SIMD), slices with their second kernel 4.5 us before the first group, so slices are taken where they
+// save a wave three groups or more.  Measured without -> with (4 rows): 8 heads x 32001 tokens 23.0 -> 8.4 us, x 16384 10.9 -> 6.2, x
+// 8192 7.1 -> 5.6, x 4096 4.4 -> 6.0 (not taken); 1 head x 32768 19.1 -> 6.3; 32 heads x 16384 12.7 -> 10.9, x 8192 7.3 -> 7.9 (not
+// taken); 64 heads x 16384 16.4 -> 15.8, x 8192 8.9 -> 10.1 (taken: there the line lies too low), x 4096 5.5 -> 7.5 (not taken).
+// 24 rows: 8 heads x 8192 10.9 -> 7.0; 64 heads 12.9 -> 14.4.
 int fqk_output_slices(int H, int T, int cus, int* gper) {
     const int G = (T + 127) / 128;
     *gper = G;

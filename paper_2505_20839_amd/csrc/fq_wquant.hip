@@ -340,9 +340,9 @@ __global__ void fq_pts_resolve_kernel(const unsigned* __restrict__ stats, int* _
 // weight, 32.9 / 30.9 / 32.8 with 1 / 2 / 4 at a time).  Bound by HBM (3 bytes per weight) once
 // the quotient is short: a full IEEE division per weight (about eleven instructions) made it VALU bound.  With r = the
 // correctly rounded 1 / sigma8 (one division per group), q0 = v * r, the exact residual e = fma(-q0, sigma8, v) and
-// q1 = fma(e, r, q0), rint(q1) equals rint of the IEEE quotient for every FP32 v and every E4M3 sigma8 (a host program
-// checks all of them; sigma8 has four significant bits, and a power of two moves nothing).  v is cut to
-// +-16 sigma8 first, which changes no code (they end at -8 and 7) and keeps the residual finite.
+// q1 = fma(e, r, q0), rint(q1) equals rint of the IEEE quotient for every FP32 v and every E4M3 sigma8 (a program on
+// the host has gone through all of them, the tests go through every third v; sigma8 has four significant bits, and a power
+// of two moves nothing).  v is cut to +-16 sigma8 first, which changes no code (they end at -8 and 7) and keeps the residual finite.
 template <int UNROLL>
 __global__ __launch_bounds__(256) void fq_quantize_weights_kernel(const uint16_t* __restrict__ W,
                                                                   const float* __restrict__ lambda, int n_pts,
