@@ -235,7 +235,8 @@ int fq_w4a8_linear_ws(const uint16_t *X_bf16, const uint8_t *Wq_packed, const ui
  *
  * fq_cas_scales -- channel-wise absmean scaling (Sec. 3.1.2, Def. 3.1):
  *   lambda[k] = target / ((1/N) * sum_n |W[n,k]|), FP64 sums, result rounded to FP32; a channel
- *   that is zero throughout keeps lambda = 1.  lambda is [K] FP32 (output); target > 0.  The
+ *   that is zero throughout keeps lambda = 1, one with an infinite weight gets 0, one with a NaN
+ *   gets NaN.  lambda is [K] FP32 (output); target > 0.  The
  *   caller merges 1/lambda into whatever produces the layer's input, as the paper does.
  *
  * fq_pts_exponent -- per-tensor scaling (Def. 3.2, App. C.1): the smallest n >= 0 such that

@@ -150,7 +150,7 @@ void fq_gemm_ksplit_kernel(
         // cycles, and no wave gets past its own to its next MFMA.  Spread over the step's MFMAs it is 2100 (200 x 4096 x 11008
         // with two slices 27.5 -> 25.4 us, 512 x 4096 x 11008 40.3 -> 36.1; the compiler keeps transfers straight into
         // LDS from being spread, so A goes through registers).  Without any loads a step takes 1650 cycles, without LDS
-        // reads as well 1150.  More groups in flight change nothing.  Where a step has fewer requests it gives little (128 x 14336 x 4096
+        // reads as well 1150 (all three from copies of the loop without them).  More groups in flight change nothing.  Where a step has fewer requests it gives little (128 x 14336 x 4096
         // 16.6 -> 15.9 us, 64 x 14336 x 4096 10.7 -> 10.4), and with K = 1024 its longer start costs 0.35 us.
         // A(g) sits in register set g % RA until the middle of step g - 1, when it goes to LDS stage g & 1; W(g) in slot
         // g % 4 until it is unpacked during step g - 1; a word holds the group scales of four steps.

@@ -172,12 +172,17 @@ def test_pts_exponent_counts_every_workgroup(fq, N, K):
         Wc = Wb.copy(); Wc[pos] = 0x43DF                       # 446: the largest bf16 below 7 * 2^6
         for _ in range(2):
             assert int(fq.fq_pts_exponent(to_gpu_bf16(Wc))[0]) == oracle.pts_exponent(Wc)
+        # where that one element decides: 2^-12 among ones (condition 1: n = 6), 446 among 2^-20 (condition 2: n = 0, not 14)
+        for rest, one, n in ((0x3F80, 0x3980, 6), (0x3580, 0x43DF, 0)):
+            Wc = np.full((N, K), rest, np.uint16); Wc[pos] = one
+            assert int(fq.fq_pts_exponent(to_gpu_bf16(Wc))[0]) == n and (N * K > 1 << 15 or oracle.pts_exponent(Wc) == n)
 
 
 @pytest.mark.parametrize("N,K,n_pts", [(1, 128, 0), (15, 128, 1), (16, 128, 2), (17, 128, 0), (15, 640, 3), (67, 128, 126), (129, 384, 7),
                                        (128, 16384, 5), (1489, 1408, 4), (512, 4224, 0), (16417, 128, 2)])
 def test_quantize_weights_at_the_edges_of_a_workgroup(fq, N, K, n_pts):
-    """Group counts around the 16 a workgroup takes of a small matrix (up to 16384 groups) and the 32 of a larger one, quotients on and beside the rounding boundaries, huge v * 2^n, zero
+    """Group counts around the 16 a workgroup takes of a small matrix (up to 16384 groups) and the 32 of a larger one, quotients on
+    and beside the rounding boundaries, huge v * 2^n, zero
     groups and groups whose scale casts to zero: codes and scales bit for bit."""
     rng = np.random.default_rng(N * K)
     Wb = workloads.draw_weights(N, K, seed=N, channel_spread=1.0)
