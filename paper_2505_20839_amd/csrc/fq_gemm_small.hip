@@ -8,7 +8,7 @@
 // Work split (both kernels).  The output channels are dealt out evenly to one workgroup per compute
 // unit; its 8 waves split K into contiguous slices of groups, so every weight byte is read once
 // overall and every activation byte once per workgroup; the partial sums of the waves are added
-// through LDS.  Activations are tiny (M x K bytes) and come straight from L2 in MFMA operand order.
+// through LDS.  Activations (M x K bytes) come from L2, a few rows straight in MFMA operand order, more in whole pieces of rows.
 #include <cstdlib>
 #include <type_traits>
 #include "fq_common.h"
@@ -21,6 +21,35 @@ __device__ __forceinline__ fq_v8i fqs_join(fq_v4i lo, fq_v4i hi) {
     r[0] = lo[0]; r[1] = lo[1]; r[2] = lo[2]; r[3] = lo[3];
     r[4] = hi[0]; r[5] = hi[1]; r[6] = hi[2]; r[7] = hi[3];
     return r;
+}
+
+// Activations of one group of 16 rows, on their way to an operand of the 16x16x128 MFMA.  The operand of lane 16*kq + r
+// is 32 bytes of row r: neighbouring lanes hold different rows, so a wave that loads it as such touches 64 places of 16
+// bytes, each of which takes the address path as long as four lanes that share 64 bytes.  So lane 4*r + c loads bytes
+// 16*c .. of each 64-byte half of row r (two loads), and the halves change lanes through LDS: 2 KiB per wave, row-major,
+// 16-byte slot x of row r at x ^ fqs_swizzle(r / 2), which spreads writes and reads over the banks.  The buffer is the wave's
+// own and a wave's LDS accesses keep their order: no barrier, and one buffer is enough for any number of groups in a row.
+__device__ __forceinline__ int fqs_swizzle(int h) { return h ^ ((h & 2) << 1); }
+
+struct fqs_turn {
+    int wr, rd;                                           // this lane's chunk in a row tile: to write (first half) and to read
+    __device__ __forceinline__ fqs_turn(int lane) {
+        const int rw = lane >> 2, rr = lane & 15;
+        wr = 8 * rw + ((lane & 3) ^ fqs_swizzle(rw >> 1));
+        rd = 8 * rr + ((2 * (lane >> 4)) ^ fqs_swizzle(rr >> 1));
+    }
+    __device__ __forceinline__ void operator()(fq_v4i* buf, fq_v4i (&half)[2]) const {   // the two halves as loaded -> the operand
+        buf[wr] = half[0];
+        buf[wr ^ 4] = half[1];
+        half[0] = buf[rd];
+        half[1] = buf[rd ^ 1];
+    }
+};
+
+// Byte offset of lane 4*r + c's chunk in the first half of group 0, row m0 + r; rows past M are requested out of range.
+__device__ __forceinline__ unsigned fqs_a_offset(int lane, int m0, int M, int K, unsigned oob) {
+    const int m = m0 + (lane >> 2);
+    return m < M ? (unsigned)m * (unsigned)K + (unsigned)(lane & 3) * 16u : oob;
 }
 
 }  // namespace
@@ -45,6 +74,10 @@ __device__ __forceinline__ fq_v8i fqs_join(fq_v4i lo, fq_v4i hi) {
 #define FQS16_WAVES 8
 #define FQS16_MAXCOLS 112                                 // channels of a workgroup (7 sub-tiles: 56 KiB of partial sums in LDS)
 #define FQS16_FUSED_MAX_M 6                               // rows up to which quantising inside the GEMM kernel pays (<= waves)
+// Rows from which the activations are loaded in whole 64-byte pieces and turned (fqs_turn); with fewer, most lanes of the
+// direct form repeat a row at no cost and the way through LDS is not worth it (us, turned / direct, N = 4096, K = 14336:
+// M = 2 8.8 / 8.3, 8 9.0 / 9.3, 10 8.9 / 9.3, 16 10.0 / 10.9; N = 6144, K = 4096: 16 4.6 / 5.2).
+#define FQS16_TURN_MIN_M 9
 #define FQS16_OOB 0xFFFFFF00u                             // beyond any 32-bit buffer size
 // byte `i` (0..3, compile-time) of a word of E4M3 codes -> float
 __device__ __forceinline__ float fq_e4m3_byte_to_float(unsigned w, int i) {
@@ -53,60 +86,71 @@ __device__ __forceinline__ float fq_e4m3_byte_to_float(unsigned w, int i) {
 }
 #define FQ_MFMA16(a, b, c) __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4((a), (b), (c), 0, 0, 0, 0, 0, 0)
 
-// The four scale bytes of a channel that go with four consecutive slots are fetched as words.
-// WORDS: every wave's slice starts at a multiple of 4 groups and the scale rows are word-aligned, so
-// they are one aligned word; otherwise the two aligned words around them are fetched and shifted
-// into place when they are used.
+// The four scale bytes of a channel that go with four consecutive slots are one 8-byte load, the two aligned words around
+// them, shifted into place when they are used.  Lane quarter kq fetches them for sub-tile kq (of four) and lane exchanges
+// hand them to the other quarters: every channel's scales are a place of their own, a turn of the address path for each lane
+// that asks, and with every lane asking for every sub-tile (twice where rows of scales are not whole words) it took more
+// turns for them than for the weights (16 x 14336 x 4096 7.5 -> 7.3 us, 16 x 4096 x 14336 10.2 -> 9.95, 1 x 4096 x 14336 8.1 -> 7.8).
 // A wave keeps a ring of BATCH groups in flight (4, 8, 12 or 16: the shortest that holds a wave's slice,
 // as far as the registers go): it requests the first BATCH groups of its slice at
 // once and re-requests each slot, for the group BATCH further on, as soon as it has used it.  Loads
 // return in order, so the ring is consumed in the order it was requested.
-template <int NSUB, bool WORDS, int BATCH_>
+typedef unsigned fqs_v2u __attribute__((ext_vector_type(2)));
+
+template <int NSUB, int BATCH_>
 struct fqs16_ring {
     static constexpr int BATCH = BATCH_;
     static_assert(BATCH % 4 == 0, "scale words cover four slots");
     fq_v4i bq[BATCH][NSUB];
     fq_v4i aq[BATCH][2];
-    unsigned sq[BATCH / 4][NSUB][WORDS ? 1 : 2];          // scale words of four slots
+    static constexpr int NSC = (NSUB + 3) / 4;            // scale loads of four slots: four sub-tiles each
+    fqs_v2u sq[BATCH / 4][NSC];
 
     // request group g into slot i; groups at or past g_end request nothing and read as zeros
     // (LOAD_A = false: the activations of the slot come from elsewhere)
-    template <bool LOAD_A = true>
+    template <bool LOAD_A, bool TURN>
     __device__ __forceinline__ void issue(int i, __amdgpu_buffer_rsrc_t rsA, __amdgpu_buffer_rsrc_t rsW,
                                           __amdgpu_buffer_rsrc_t rsG, unsigned aoff, const unsigned (&woff)[NSUB],
-                                          const unsigned (&goff)[NSUB], int g, int g_end) {
+                                          const unsigned (&goff)[NSC], int g, int g_end) {
         const unsigned dead = g < g_end ? 0u : FQS16_OOB;
         if (i % 4 == 0) {
 #pragma unroll
-            for (int j = 0; j < NSUB; ++j) {
-                if (WORDS) {
-                    sq[i / 4][j][0] = __builtin_amdgcn_raw_buffer_load_b32(rsG, goff[j] | dead, g, 0);
-                } else {
-                    const unsigned base = ((goff[j] + (unsigned)g) & ~3u) | dead;
-                    sq[i / 4][j][0] = __builtin_amdgcn_raw_buffer_load_b32(rsG, base, 0, 0);
-                    sq[i / 4][j][WORDS ? 0 : 1] = __builtin_amdgcn_raw_buffer_load_b32(rsG, base, 4, 0);
-                }
-            }
+            for (int j = 0; j < NSC; ++j)
+                sq[i / 4][j] = __builtin_bit_cast(fqs_v2u, __builtin_amdgcn_raw_buffer_load_b64(
+                    rsG, ((goff[j] + (unsigned)g) & ~3u) | dead, 0, 0));
         }
-        if (LOAD_A) {
+        if (LOAD_A) {                                     // (the halves of a group's 128 bytes to be turned, or of the lane's 32)
             aq[i][0] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsA, aoff | dead, g * FQ_GROUP, 0));
-            aq[i][1] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsA, (aoff + 16u) | dead, g * FQ_GROUP, 0));
+            aq[i][1] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsA, aoff | dead, g * FQ_GROUP + (TURN ? 64 : 16), 0));
         }
 #pragma unroll
         for (int j = 0; j < NSUB; ++j)                    // streamed once: non-temporal
             bq[i][j] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsW, woff[j] | dead, g * 2048, 2));
     }
 
-    // the scale word of slots i .. i + 3 (i a multiple of 4) of sub-tile j, whose first slot holds group g
-    __device__ __forceinline__ unsigned scale_word(int i, int j, unsigned goff_j, int g) const {
-        if (WORDS) return sq[i / 4][j][0];
-        return __builtin_amdgcn_alignbyte(sq[i / 4][j][WORDS ? 0 : 1], sq[i / 4][j][0], (goff_j + (unsigned)g) & 3u);
+    // the scale words of slots i .. i + 3 (i a multiple of 4, group g its first) of every sub-tile; bytes of groups at or
+    // past g_end, whatever they are, are cleared
+    __device__ __forceinline__ void scale_words(int i, const unsigned (&goff)[NSC], int g, int g_end, unsigned (&sw)[NSUB]) const {
+        const int nv = g_end - g;
+        const unsigned keep = nv >= 4 ? ~0u : (nv <= 0 ? 0u : (1u << (8 * nv)) - 1u);
+#pragma unroll
+        for (int j = 0; j < NSC; ++j) {
+            const unsigned w = __builtin_amdgcn_alignbyte(sq[i / 4][j][1], sq[i / 4][j][0], (goff[j] + (unsigned)g) & 3u) & keep;
+            const auto h = __builtin_amdgcn_permlane32_swap(w, w, false, false);          // quarters 0 1 0 1 and 2 3 2 3
+            const auto lo = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);   // 0 0 0 0 and 1 1 1 1
+            sw[4 * j] = lo[0];
+            if (4 * j + 1 < NSUB) sw[4 * j + 1] = lo[1];
+            if (4 * j + 2 < NSUB) {
+                const auto hi = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+                sw[4 * j + 2] = hi[0];
+                if (4 * j + 3 < NSUB) sw[4 * j + 3] = hi[1];
+            }
+        }
     }
 
-    // slot i -> accumulators (a dead group is all zeros and adds nothing: `live` also keeps whatever
-    // byte sits where its scale would be out of the sum); `sw` is the slot's scale word, read before
-    // the slot group's first slot may be re-requested
-    __device__ __forceinline__ void compute(int i, fq_v4f (&acc)[NSUB], const unsigned (&sw)[NSUB], bool live) const {
+    // slot i -> accumulators (a dead group is all zeros, its scale too, and adds nothing); `sw`: the slot's scale words, read
+    // before the slot group's first slot may be re-requested
+    __device__ __forceinline__ void compute(int i, fq_v4f (&acc)[NSUB], const unsigned (&sw)[NSUB]) const {
         const fq_v4f zero4 = {0.f, 0.f, 0.f, 0.f};
         const fq_v8i a = fqs_join(aq[i][0], aq[i][1]);
         fq_v8i zp;
@@ -116,8 +160,7 @@ struct fqs16_ring {
 #pragma unroll
         for (int j = 0; j < NSUB; ++j) {
             const fq_v8i b = fq_unpack_chunk(bq[i][j]);
-            // (WORDS: a dead slot's word was not fetched at all and reads as zero)
-            const float s = (WORDS || live) ? fq_e4m3_byte_to_float(sw[j], i % 4) : 0.f;
+            const float s = fq_e4m3_byte_to_float(sw[j], i % 4);
             const fq_v4f p = FQ_MFMA16(a, b, c0);
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[j][r] = fmaf(s, p[r], acc[j][r]);
@@ -135,16 +178,17 @@ struct fqs16_ring {
 // 10.1 at M = 4, 10.5 against 10.3 at M = 8: the conversion is some ten instructions per element, on
 // every compute unit).  `a_scale` is not read;
 // `a_scale_out` (may be NULL) receives the row scales.  Dynamic LDS: 8 * (K + 16) bytes.
-template <int NSUB, bool WORDS, bool ROUNDS, int BATCH_, bool FUSEDQ = false>
+template <int NSUB, bool ROUNDS, int BATCH_, bool TURN, bool FUSEDQ = false>
 __global__ __launch_bounds__(FQS16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void fq_gemm_small16_kernel(
     const uint8_t* __restrict__ A, const float* __restrict__ a_scale, const uint8_t* __restrict__ wp,
     const uint8_t* __restrict__ gs, float tscale, uint16_t* Y, int M, int N, int K, int cols,
     int swiglu, const uint16_t* R, float* __restrict__ a_scale_out) {
     static_assert(!(FUSEDQ && ROUNDS), "the fused form serves K <= 4096: a slice is at most four groups");
-    typedef fqs16_ring<NSUB, WORDS, BATCH_> ring_t;
+    typedef fqs16_ring<NSUB, BATCH_> ring_t;
     constexpr int BATCH = ring_t::BATCH;
     __shared__ float red[FQS16_WAVES][NSUB][4][64];
+    __shared__ fq_v4i turned[TURN ? FQS16_WAVES : 1][TURN ? 128 : 1];   // 2 KiB per wave: see fqs_turn
     const int G = K / FQ_GROUP;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int r16 = lane & 15, kq = lane >> 4;
@@ -161,8 +205,9 @@ void fq_gemm_small16_kernel(
     // than four scales; the array is 16-byte aligned and the surplus bytes never enter a sum)
     const __amdgpu_buffer_rsrc_t rsG = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t*>(gs), 0, (int)(((unsigned)N * (unsigned)G + 3u) & ~3u), 0x00020000);
-    // per sub-tile: byte offset of this lane's chunk in group 0 of its packed block, and of its scale row
-    unsigned woff[NSUB], goff[NSUB];
+    // per sub-tile: byte offset of this lane's chunk in group 0 of its packed block; per four sub-tiles: of the scale row
+    // of channel r16 of the sub-tile that this lane's quarter fetches
+    unsigned woff[NSUB], goff[ring_t::NSC];
 #pragma unroll
     for (int j = 0; j < NSUB; ++j) {
         const int c = 16 * j + r16;
@@ -171,9 +216,14 @@ void fq_gemm_small16_kernel(
         woff[j] = on ? (unsigned)(n >> 5) * (unsigned)G * 2048u + (unsigned)(kq >> 1) * 1024u +
                        (unsigned)((kq & 1) * 32 + (n & 31)) * 16u
                      : FQS16_OOB;
-        goff[j] = on ? (unsigned)n * (unsigned)G : FQS16_OOB;
     }
-    const unsigned aoff = (unsigned)(r16 < M ? r16 : M - 1) * (unsigned)K + (unsigned)kq * 32u;
+#pragma unroll
+    for (int j = 0; j < ring_t::NSC; ++j) {
+        const int c = 16 * (4 * j + kq) + r16;
+        goff[j] = c < cols && n_first + c < N ? (unsigned)(n_first + c) * (unsigned)G : FQS16_OOB;
+    }
+    const unsigned aoff = TURN ? fqs_a_offset(lane, 0, M, K, FQS16_OOB)
+                               : (unsigned)(r16 < M ? r16 : M - 1) * (unsigned)K + (unsigned)kq * 32u;
     // output factor of the (at most two) elements this thread writes at the end, fetched up front
     constexpr int NOUT = (NSUB * 256 + FQS16_THREADS - 1) / FQS16_THREADS;
     float osc[NOUT];
@@ -205,7 +255,7 @@ void fq_gemm_small16_kernel(
         }
     }
 #pragma unroll
-    for (int i = 0; i < BATCH; ++i) ring.template issue<!FUSEDQ>(i, rsA, rsW, rsG, aoff, woff, goff, g_begin + i, g_end);
+    for (int i = 0; i < BATCH; ++i) ring.template issue<!FUSEDQ, TURN>(i, rsA, rsW, rsG, aoff, woff, goff, g_begin + i, g_end);
     __builtin_amdgcn_sched_barrier(0);                    // all requests go out before any arithmetic
     if (FUSEDQ) {
         const int stride = K + 16;
@@ -260,19 +310,26 @@ void fq_gemm_small16_kernel(
         }
         __builtin_amdgcn_sched_barrier(0);
     }
+    // A slot's activations are turned AHEAD slots before their use: the way through LDS takes longer than a slot's arithmetic
+    // (16 x 4096 x 14336 10.5 us one slot ahead, 10.2 three; with a ring of four, 16 x 14336 x 4096 7.4 and 7.8)
+    constexpr int AHEAD = BATCH > 4 ? 3 : 1;
+    const fqs_turn turn(lane);
+    auto turn_slot = [&](int i) __attribute__((always_inline)) {
+        if (TURN) turn(turned[TURN ? wave : 0], ring.aq[i]);
+    };
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) turn_slot(i);
     // ROUNDS == false: no slice is longer than BATCH groups, the ring is used once and never refilled
     for (int gb = g_begin; gb < g_end; gb += BATCH) {
         unsigned sw[NSUB];
 #pragma unroll
         for (int i = 0; i < BATCH; ++i) {
-            if (i % 4 == 0) {                             // keep the word: its slot may be re-requested below
-#pragma unroll
-                for (int j = 0; j < NSUB; ++j) sw[j] = ring.scale_word(i, j, goff[j], gb + i);
-            }
-            ring.compute(i, acc, sw, gb + i < g_end);
+            if (ROUNDS || i + AHEAD < BATCH) turn_slot((i + AHEAD) % BATCH);
+            if (i % 4 == 0) ring.scale_words(i, goff, gb + i, g_end, sw);   // (their slot may be re-requested below)
+            ring.compute(i, acc, sw);
             __builtin_amdgcn_sched_barrier(0);            // slot by slot, as the data lands
             if (ROUNDS) {
-                ring.issue(i, rsA, rsW, rsG, aoff, woff, goff, gb + BATCH + i, g_end);
+                ring.template issue<!FUSEDQ, TURN>(i, rsA, rsW, rsG, aoff, woff, goff, gb + BATCH + i, g_end);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -320,26 +377,28 @@ void fq_gemm_small16_kernel(
 
 namespace {
 
-template <int NSUB, bool WORDS, bool ROUNDS, int BATCH>
+template <int NSUB, bool ROUNDS, int BATCH>
 void fq_launch_small16b(unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
                         const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols, int swiglu, const uint16_t* R) {
-    hipLaunchKernelGGL((fq_gemm_small16_kernel<NSUB, WORDS, ROUNDS, BATCH>), dim3(grid), dim3(FQS16_THREADS), 0, stream,
+    const auto kernel = M < FQS16_TURN_MIN_M ? fq_gemm_small16_kernel<NSUB, ROUNDS, BATCH, false>
+                                             : fq_gemm_small16_kernel<NSUB, ROUNDS, BATCH, true>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(FQS16_THREADS), 0, stream,
                        A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R, static_cast<float*>(nullptr));
 }
 
 // The fused form (bf16 activations in, quantised by the kernel): slices of at most four groups per wave
 // (K <= 4096), for which a slice of X fits into registers beside the ring.
-template <int NSUB, bool WORDS>
-bool fq_launch_linear16w(int per, unsigned grid, hipStream_t stream, const uint16_t* X, float* a_scale_out,
-                         const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols) {
+template <int NSUB>
+bool fq_launch_linear16(int per, unsigned grid, hipStream_t stream, const uint16_t* X, float* a_scale_out,
+                        const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols) {
     if (per > 4) return false;
     const size_t lds = (size_t)8 * (size_t)(K + 16);      // the codes of X
     static fq_device_once attr_once;                       // (one per template instance)
     fq_once_per_device(attr_once, [] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_gemm_small16_kernel<NSUB, WORDS, false, 4, true>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_gemm_small16_kernel<NSUB, false, 4, false, true>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 8 * (4096 + 16));
     });
-    hipLaunchKernelGGL((fq_gemm_small16_kernel<NSUB, WORDS, false, 4, true>), dim3(grid), dim3(FQS16_THREADS), lds, stream,
+    hipLaunchKernelGGL((fq_gemm_small16_kernel<NSUB, false, 4, false, true>), dim3(grid), dim3(FQS16_THREADS), lds, stream,
                        reinterpret_cast<const uint8_t*>(X), static_cast<const float*>(nullptr), wp, gs, tscale, Y, M, N, K, cols,
                        0, static_cast<const uint16_t*>(nullptr), a_scale_out);
     return true;
@@ -350,32 +409,25 @@ bool fq_launch_linear16w(int per, unsigned grid, hipStream_t stream, const uint1
 // go round a ring of 12 / 8 / 4 groups (ROUNDS), which exposes the latency of the refills: 16 x 4096 x 14336, 14 groups
 // per wave, 15.1 us round a ring of 12, 11.7 us with all of them requested at once.  5-7 sub-tiles are only taken
 // for slices of at most 4 groups (fqs_shape_of).
-template <int NSUB, bool WORDS>
-void fq_launch_small16w(int per, unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
-                        const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols, int swiglu, const uint16_t* R) {
+template <int NSUB>
+void fq_launch_small16(int per, unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
+                       const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols, int swiglu, const uint16_t* R) {
     constexpr int CAP = NSUB == 1 ? 16 : NSUB == 2 ? 12 : NSUB <= 4 ? 8 : 4, RING = NSUB == 1 ? 12 : NSUB == 2 ? 8 : 4;
     if constexpr (NSUB <= 4) {
         if (per > CAP)
-            return fq_launch_small16b<NSUB, WORDS, true, RING>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+            return fq_launch_small16b<NSUB, true, RING>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
         if (per > 4 && per > CAP - 4)
-            return fq_launch_small16b<NSUB, WORDS, false, CAP>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+            return fq_launch_small16b<NSUB, false, CAP>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
         if constexpr (CAP >= 12) {
             if (per > CAP - 8 && per > 4)
-                return fq_launch_small16b<NSUB, WORDS, false, CAP - 4>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+                return fq_launch_small16b<NSUB, false, CAP - 4>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
         }
         if constexpr (CAP >= 16) {
             if (per > 4)
-                return fq_launch_small16b<NSUB, WORDS, false, CAP - 8>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+                return fq_launch_small16b<NSUB, false, CAP - 8>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
         }
     }
-    fq_launch_small16b<NSUB, WORDS, false, 4>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
-}
-
-template <int NSUB>
-void fq_launch_small16(bool words, int per, unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
-                       const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols, int swiglu, const uint16_t* R) {
-    if (words) fq_launch_small16w<NSUB, true>(per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
-    else       fq_launch_small16w<NSUB, false>(per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+    fq_launch_small16b<NSUB, false, 4>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
 }
 
 }  // namespace
@@ -397,15 +449,14 @@ struct fqsm_ring {
     fq_v4i aq[BATCH][MT][2];
 
     // request group g into slot i; groups at or past g_end request nothing and read as zeros
-    // (LOAD_A = false: the activations of the slot come from elsewhere)
-    template <bool LOAD_A = true>
+    template <bool TURN>
     __device__ __forceinline__ void issue(int i, __amdgpu_buffer_rsrc_t rsA, __amdgpu_buffer_rsrc_t rsW,
                                           const unsigned (&aoff)[MT], const unsigned (&woff)[NSUB], int g, int g_end) {
         const unsigned dead = g < g_end ? 0u : FQS16_OOB;
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
             aq[i][t][0] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsA, aoff[t] | dead, g * FQ_GROUP, 0));
-            aq[i][t][1] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsA, (aoff[t] + 16u) | dead, g * FQ_GROUP, 0));
+            aq[i][t][1] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsA, aoff[t] | dead, g * FQ_GROUP + (TURN ? 64 : 16), 0));
         }
 #pragma unroll
         for (int j = 0; j < NSUB; ++j)                    // streamed once: non-temporal
@@ -449,12 +500,18 @@ void fq_gemm_smallm_kernel(
     int swiglu, const uint16_t* R) {
     typedef fqsm_ring<MT, NSUB> ring_t;
     constexpr int BATCH = ring_t::BATCH;
-    // LDS: first the scale table [G][64] bytes, later (after a barrier) the partial sums
-    // [wave][row tile][sub-tile][reg][lane] floats
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    float* red = reinterpret_cast<float*>(smem);
+    // activations in whole 64-byte pieces and turned (fqs_turn), except where two row tiles' slices are all under way at
+    // once: 64 x 4096 x 4096 10.7 -> 8.0 us, 64 x 4096 x 14336 29.7 -> 20.7, 50 x 8192 x 8192 17.6 -> 14.5, 20 x 4096 x 11008
+    // 12.7 -> 11.4, but 32 x 14336 x 4096 10.4 -> 10.7
+    constexpr bool TURN = MT >= 3 || ROUNDS;
+    // LDS: first the waves' buffers of fqs_turn and the scale table [G][64] bytes, later (after a barrier) the partial
+    // sums [wave][row tile][sub-tile][reg][lane] floats
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds_bytes[];
+    float* red = reinterpret_cast<float*>(lds_bytes);
+    uint8_t* const smem = lds_bytes + FQS16_WAVES * 2048;
     const int G = K / FQ_GROUP;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    fq_v4i* const turned = reinterpret_cast<fq_v4i*>(lds_bytes) + wave * 128;
     const int r16 = lane & 15, kq = lane >> 4;
     const int n_first = blockIdx.x * cols;                // this workgroup owns channels [n_first, n_first + cols)
     const int per = (G + FQS16_WAVES - 1) / FQS16_WAVES;
@@ -506,7 +563,7 @@ void fq_gemm_smallm_kernel(
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
         const int m = 16 * t + r16;
-        aoff[t] = (unsigned)(m < M ? m : M - 1) * (unsigned)K + (unsigned)kq * 32u;
+        aoff[t] = TURN ? fqs_a_offset(lane, 16 * t, M, K, FQS16_OOB) : (unsigned)(m < M ? m : M - 1) * (unsigned)K + (unsigned)kq * 32u;
     }
     // output factors of the elements this thread writes at the end, fetched up front
     constexpr int NOUT = (MT * NSUB * 256 + FQS16_THREADS - 1) / FQS16_THREADS;
@@ -526,7 +583,7 @@ void fq_gemm_smallm_kernel(
 
     ring_t ring;
 #pragma unroll
-    for (int i = 0; i < BATCH; ++i) ring.issue(i, rsA, rsW, aoff, woff, g_begin + i, g_end);
+    for (int i = 0; i < BATCH; ++i) ring.template issue<TURN>(i, rsA, rsW, aoff, woff, g_begin + i, g_end);
     __builtin_amdgcn_sched_barrier(0);                    // all requests go out before anything else
     // scale table: transposed to [group][channel] so that a lane's sub-tiles are 16 bytes apart
     if (scw) {
@@ -562,15 +619,22 @@ void fq_gemm_smallm_kernel(
     }
     __syncthreads();
     const uint8_t* sc = smem + r16;
+    const fqs_turn turn(lane);
+    auto turn_slot = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+            if (TURN) turn(turned, ring.aq[i][t]);
+    };
     // ROUNDS == false: no slice is longer than BATCH groups, the ring is used once and never refilled
     for (int gb = g_begin; gb < g_end; gb += BATCH) {
 #pragma unroll
         for (int i = 0; i < BATCH; ++i) {
             const int g = gb + i < G ? gb + i : G - 1;    // (a dead slot may read any scale: its sums are zero)
+            turn_slot(i);
             ring.compute(i, acc, sc, g);
             __builtin_amdgcn_sched_barrier(0);            // slot by slot, as the data lands
             if (ROUNDS) {
-                ring.issue(i, rsA, rsW, aoff, woff, gb + BATCH + i, g_end);
+                ring.template issue<TURN>(i, rsA, rsW, aoff, woff, gb + BATCH + i, g_end);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -626,7 +690,7 @@ bool fq_launch_smallm(int per, unsigned grid, hipStream_t stream, const uint8_t*
                       const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols, int swiglu, const uint16_t* R) {
     const int G = K / FQ_GROUP;
     const size_t red_bytes = (size_t)FQS16_WAVES * MT * NSUB * 256 * sizeof(float);
-    const size_t sc_bytes = (size_t)FQSM_MAXCOLS * G;
+    const size_t sc_bytes = (size_t)FQS16_WAVES * 2048 + (size_t)FQSM_MAXCOLS * G;   // (and the buffers of fqs_turn)
     const size_t lds = red_bytes > sc_bytes ? red_bytes : sc_bytes;
     if (lds > 160 * 1024) return false;
     const bool rounds = per > fqsm_ring<MT, NSUB>::BATCH;
@@ -661,15 +725,14 @@ namespace {
 // a multiple of 8, at most `max_cols`, or 64 where a wave's slice is longer than 4 groups; more channels than that go in
 // several even rounds: 16 x 28672 x 4096 15.0 us in 448 workgroups of 64 channels, 13.3 us in 256 of 112; 64 x 18432 x 4096 27.0 us in
 // 288 of 64, 25.3 in 461 of 40.  With more than 16 rows an even round of 49 to 63 channels has as many sub-tiles as one of 64 and more
-// workgroups: 64 stay, 64 x 28672 x 4096 with the residual 30.7 us, in 512 of 56 32.3), workgroups, groups per wave, sub-tiles of 16 channels, and whether the scale bytes of four consecutive groups are one aligned word.
+// workgroups: 64 stay, 64 x 28672 x 4096 with the residual 30.7 us, in 512 of 56 32.3), workgroups, groups per wave and sub-tiles of 16 channels.
 struct fqs_shape {
     int cols;
     unsigned grid;
     int per, nsub;
-    bool words;
 };
 
-fqs_shape fqs_shape_of(int M, int N, int K, const uint8_t* gs, int max_cols) {
+fqs_shape fqs_shape_of(int M, int N, int K, int max_cols) {
     const int cus = fq_device_cus();
     fqs_shape sh;
     const int G = K / FQ_GROUP;
@@ -682,7 +745,6 @@ fqs_shape fqs_shape_of(int M, int N, int K, const uint8_t* gs, int max_cols) {
     if (M > 16 && rounds > 1 && sh.cols > max_cols - 16) sh.cols = max_cols;
     sh.grid = (unsigned)((N + sh.cols - 1) / sh.cols);
     sh.nsub = (sh.cols + 15) / 16;
-    sh.words = (sh.per % 4 == 0) && (G % 4 == 0) && ((reinterpret_cast<uintptr_t>(gs) & 3) == 0);
     return sh;
 }
 
@@ -695,41 +757,33 @@ bool fq_linear_small_serves(int M, int K) {
 bool fq_launch_linear_small(const uint16_t* X, float* a_scale_out, const uint8_t* wp, const uint8_t* gs, float tscale,
                             uint16_t* Y, int M, int N, int K, hipStream_t stream) {
     if (!fq_linear_small_serves(M, K)) return false;
-    const fqs_shape sh = fqs_shape_of(M, N, K, gs, FQS16_MAXCOLS);
-    switch (2 * sh.nsub + (sh.words ? 1 : 0)) {
-        case 2: return fq_launch_linear16w<1, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 3: return fq_launch_linear16w<1, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 4: return fq_launch_linear16w<2, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 5: return fq_launch_linear16w<2, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 6: return fq_launch_linear16w<3, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 7: return fq_launch_linear16w<3, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 8: return fq_launch_linear16w<4, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 9: return fq_launch_linear16w<4, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 10: return fq_launch_linear16w<5, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 11: return fq_launch_linear16w<5, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 12: return fq_launch_linear16w<6, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 13: return fq_launch_linear16w<6, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 14: return fq_launch_linear16w<7, false>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        default: return fq_launch_linear16w<7, true>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+    const fqs_shape sh = fqs_shape_of(M, N, K, FQS16_MAXCOLS);
+    switch (sh.nsub) {
+        case 1: return fq_launch_linear16<1>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 2: return fq_launch_linear16<2>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 3: return fq_launch_linear16<3>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 4: return fq_launch_linear16<4>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 5: return fq_launch_linear16<5>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 6: return fq_launch_linear16<6>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        default: return fq_launch_linear16<7>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
     }
 }
 
 bool fq_launch_gemm_small(const uint8_t* A, const float* a_scale, const uint8_t* wp, const uint8_t* gs,
                           float tscale, uint16_t* Y, int M, int N, int K, bool swiglu_epilogue, const uint16_t* R, hipStream_t stream) {
     const int swiglu = swiglu_epilogue ? 1 : 0;
-    const fqs_shape sh = fqs_shape_of(M, N, K, gs, M <= 16 ? FQS16_MAXCOLS : FQSM_MAXCOLS);
+    const fqs_shape sh = fqs_shape_of(M, N, K, M <= 16 ? FQS16_MAXCOLS : FQSM_MAXCOLS);
     const int cols = sh.cols, per = sh.per, nsub = sh.nsub;
     const unsigned grid = sh.grid;
     if (M <= 16) {
-        const bool words = sh.words;
         switch (nsub) {
-            case 1: fq_launch_small16<1>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
-            case 2: fq_launch_small16<2>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
-            case 3: fq_launch_small16<3>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
-            case 4: fq_launch_small16<4>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
-            case 5: fq_launch_small16<5>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
-            case 6: fq_launch_small16<6>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
-            default: fq_launch_small16<7>(words, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
+            case 1: fq_launch_small16<1>(per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
+            case 2: fq_launch_small16<2>(per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
+            case 3: fq_launch_small16<3>(per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
+            case 4: fq_launch_small16<4>(per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
+            case 5: fq_launch_small16<5>(per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
+            case 6: fq_launch_small16<6>(per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
+            default: fq_launch_small16<7>(per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
         }
         return true;
     }

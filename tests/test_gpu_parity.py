@@ -721,6 +721,18 @@ def test_small_m_rings_and_sub_tiles(fq, shape):
     check_gemm(bf16_bits_from_gpu(YR)[:, pick], Yr, B, "small + residual %s" % (shape,), frobenius=M * len(pick) >= 4000)
 
 
+# Rows around every row tile's edge and around the line between the two ways the activations take (9 rows; 33 and a ring gone
+# round), with slices of 0, 1, 2 and 9 groups, scale rows at every alignment and a last workgroup with few channels.
+@pytest.mark.parametrize("N,K", [(40, 128), (77, 1408), (1030, 9088)])
+@pytest.mark.parametrize("M", [1, 7, 8, 9, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64])
+def test_small_m_row_counts(fq, kernel_choice, M, N, K):
+    A, a, q, gs, t = _rand_codes(M, N, K, seed=1000 * M + N)
+    kernel_choice("small")
+    Y = _run_gemm(fq, A, a, q, gs, t)
+    Yr, B = oracle.w4a8_gemm(A, a, q, gs, t, want_bound=True)
+    check_gemm(Y, Yr, B, "small %s" % ((M, N, K),), frobenius=M * N >= 4000)
+
+
 # waves per row (1, 4, 8, 16) and chunks per thread (2, 3, 4, 6, 8) by K and M, at both ends of each range, the last chunk and
 # the last rows of a workgroup partly there, rows in two passes
 @pytest.mark.parametrize("M,K", [(1, 8), (5, 4088), (1537, 4096), (1539, 136), (1601, 264), (65, 4104), (513, 8192), (514, 4224), (600, 8200), (64, 4104),
