@@ -183,7 +183,6 @@ __device__ __forceinline__ void fql_item(
     const __amdgpu_buffer_rsrc_t rsZ = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t*>(planes), 0, (int)((unsigned)ZU * (unsigned)M * 16u), 0x00020000);
     const unsigned abase = fql_a_lane_base(wave, lane, K, NT);
-    const uint8_t* gsrow = gs + (size_t)(n_ok ? n : N - 1) * G;
 
     // operand read offsets (in chunks) of this lane inside a 32-row tile: (half h, part) -> slot
     const int r32 = lane & 31, sw = (r32 >> 1) & 7;
@@ -200,26 +199,45 @@ __device__ __forceinline__ void fql_item(
     for (int r = 0; r < 16; ++r) zero[r] = 0.f;
 
     // ---- prologue ----
-    // The scale words of the first zero-point round are requested before anything else and wait in registers until
-    // the main loop is over: asked for at that point, with every compute unit streaming, they take about 5 us.
+    // What the first group needs is requested first; the scale words of the first zero-point round come last and wait in
+    // registers until the main loop is over: asked for at that point, with every compute unit streaming, they take about 5 us.
     const __amdgpu_buffer_rsrc_t rsS = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t*>(gs), 0, (int)(((unsigned)N * (unsigned)G + 3u) & ~3u), 0x00020000);
     const unsigned srow = n_ok ? (unsigned)n * (unsigned)G : FQL_OOB;    // channels past N read zeros
     fql_raw_scales zraw;
-    if (!LUT) fql_scales_issue(rsS, srow, n_ok, G, C2, 0, ZU < 8 ? ZU : 8, lane >> 5, zraw);
     fql_issue_a<NT>(rsA, abase, m0, K, lds, wave, 0);
     // Packed weights also travel global -> LDS directly, into two 2 KiB buffers private to the wave
     // ([half h][lane][16 bytes], the order they have in memory); buffer g & 1 holds group g.
     fq_v4i* wbuf = lds + FQL_STAGES * FQL_STAGE_CHUNKS + wave * 256;
     fql_issue_b(rsW, wbuf, lane16, wblk);
     fql_issue_b(rsW, wbuf + 128, lane16, wblk + (G > 1 ? 2048u : 0u));
-    unsigned psb[2];                                      // scale bytes in flight (group g+1, g+2)
-    psb[0] = gsrow[0];
-    psb[1] = gsrow[G > 1 ? 1 : 0];
+    // Group scales, eight groups at a time (1 .. 8, 9 .. 16, ...): lanes 0-31 fetch the aligned words around the bytes of the
+    // first four for the wave's 32 channels, lanes 32-63 those of the last four, and the halves exchange them.  (With a byte per
+    // lane and group every wave touched 32 lines a group, as many bytes on their way through L1 as its share of the A tile,
+    // and each lane a turn of the address path: 2048 x 4096 x 11008 91.2 -> 85.2 us, 8192 x 14336 x 4096 417 -> 406,
+    // 1500 x 11008 x 4096 76.6 -> 74.0, together with the prologue's order below; a lone whole tile on most compute units,
+    // 700 x 11008 x 4096, pays 1 % for the loads' place in the queue.)
+    const unsigned sgoff = n_ok ? srow + 1u + 4u * (unsigned)(lane >> 5) : FQL_OOB;
+    typedef unsigned v2u __attribute__((ext_vector_type(2)));
+    auto scale_words = [&](int g) __attribute__((always_inline)) {        // of groups g + 1 .. g + 8, g a multiple of 8
+        return __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(rsS, (sgoff & ~3u) + (unsigned)g, 0, 0));
+    };
+    const unsigned sfirst = __builtin_amdgcn_raw_buffer_load_b8(rsS, srow, 0, 0);
+    v2u sraw = scale_words(0);
+    __builtin_amdgcn_sched_barrier(0);                    // (the wait below counts the loads behind this)
+    if (!LUT) fql_scales_issue(rsS, srow, n_ok, G, C2, 0, ZU < 8 ? ZU : 8, lane >> 5, zraw);
+    __builtin_amdgcn_sched_barrier(0);
+    unsigned slo, shi;                                    // the scale bytes that follow, at most eight
+    auto scale_take = [&]() __attribute__((always_inline)) {
+        const unsigned w = __builtin_amdgcn_alignbyte(sraw[1], sraw[0], sgoff & 3u);
+        const auto h = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+        slo = h[0]; shi = h[1];
+    };
     fq_v8i b0[2], b1[2];                                  // unpacked operands: [u] current, [u^1] next
     float sc[2];
-    __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(0));
-    sc[0] = __builtin_amdgcn_cvt_f32_fp8((int)psb[0], 0);
+    __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(LUT ? 0 : 4));   // (the four loads of zraw may still be on their way)
+    scale_take();
+    sc[0] = __builtin_amdgcn_cvt_f32_fp8((int)sfirst, 0);
     if (LUT) {
         const fq_v4i t0 = fql_lut_table(sc[0]);
         b0[0] = fql_unpack_chunk_lut(wbuf[lane], t0);
@@ -261,19 +279,16 @@ __device__ __forceinline__ void fql_item(
             }
             // Group g+1 sits in buffer u^1 (requested one group ago) and is unpacked slice by slice
             // under the MFMAs below; buffer u (group g, already unpacked) is refilled with group g+2.
-            const unsigned qs = psb[u ^ 1];
             {
                 const int g2 = g + 2 < G ? g + 2 : G - 1;
                 fql_issue_b(rsW, wbuf + u * 128, lane16, wblk + (unsigned)g2 * 2048u);
-                psb[u] = gsrow[g2];
             }
-            // Transfers requested after group g+1's weights and scale byte: the NT A transfers and the
-            // 3 just above -> once at most that many are pending, g+1 has landed.
-            __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(NT + 3));
+            const int sw = (int)(slo & (g + 1 < G ? ~0u : 0u));   // (a ghost group's scale is zero)
+            const float snext = u == 0 ? __builtin_amdgcn_cvt_f32_fp8(sw, 0) : __builtin_amdgcn_cvt_f32_fp8(sw, 1);
             const fq_v4i* nxt = wbuf + (u ^ 1) * 128 + lane;
             const float s = sc[u];
             fq_v4i tabn = {0, 0, 0, 0};                   // table of group g+1 (all zero for a ghost group)
-            if (LUT) tabn = fql_lut_table((g + 1 < G) ? __builtin_amdgcn_cvt_f32_fp8((int)qs, 0) : 0.f);
+            if (LUT) tabn = fql_lut_table(snext);
             fq_v4i q = nxt[0];                            // packed words 0..3; 4..7 are fetched half-way
             fq_v16f pt;
             __builtin_amdgcn_sched_barrier(0);
@@ -319,13 +334,10 @@ __device__ __forceinline__ void fql_item(
                 if (!LUT) pprev = pt;
             }
             sprev = s;
-            {
-                const float t = __builtin_amdgcn_cvt_f32_fp8((int)qs, 0);
-                sc[u ^ 1] = (g + 1 < G) ? t : 0.f;
-            }
-            // the next group's A tile: this wave's part has landed once only the 3 transfers issued
-            // after it are pending; the barrier then vouches for the other waves' parts
-            __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(3));
+            sc[u ^ 1] = snext;
+            // the next group's A tile and the weights after it: this wave's part has landed; the barrier then vouches for the
+            // other waves' parts
+            __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(0));
             __syncthreads();
             {
                 const fq_v4i* nxs = lds + (u ^ 1) * FQL_STAGE_CHUNKS;
@@ -333,7 +345,20 @@ __device__ __forceinline__ void fql_item(
             }
         }
     };
-    for (int p = 0; p < npairs - 1; ++p) pair_of_groups(p, std::false_type());
+    int p = 0;
+    while (p < npairs - 1) {
+        const int pe = p + 4 < npairs - 1 ? p + 4 : npairs - 1;
+        auto pair_and_scales = [&]() __attribute__((always_inline)) {
+            pair_of_groups(p, std::false_type());
+            slo = __builtin_amdgcn_alignbyte(shi, slo, 2);
+            shi >>= 16;
+            ++p;
+        };
+        pair_and_scales();
+        sraw = scale_words(2 * pe);                       // (not before the octet's first transfers, which are wanted sooner)
+        while (p < pe) pair_and_scales();
+        if ((p & 3) == 0) scale_take();
+    }
     pair_of_groups(npairs - 1, std::true_type());
     // last pending row tile of the last group
     if (!LUT) {

@@ -140,23 +140,18 @@ struct fql_raw_scales { unsigned d[4][3]; };
 
 __device__ __forceinline__ void fql_scales_issue(__amdgpu_buffer_rsrc_t rsS, unsigned srow, bool n_ok, int G, int C2,
                                                  int u0, int nu, int hl, fql_raw_scales& raw) {
-    const bool unaligned_rows = (G & 3) != 0;             // (the array itself is 16-byte aligned)
 #pragma unroll
     for (int ci = 0; ci < 4; ++ci) {
         const int c = ((u0 + 2 * ci) % C2) >> 1;          // chunk index inside its plane
         const int g0 = 16 * c + 8 * hl;
         const unsigned o = srow + (unsigned)g0;
         const unsigned ob = (2 * ci < nu && n_ok && g0 < G) ? (o & ~3u) : FQL_OOB;
-        // one load instruction per chunk: the address path takes as long for a lane's 4 bytes as for its 12
-        if (unaligned_rows) {
-            typedef unsigned v3u __attribute__((ext_vector_type(3)));
-            const v3u t = __builtin_bit_cast(v3u, __builtin_amdgcn_raw_buffer_load_b96(rsS, ob, 0, 0));
-            raw.d[ci][0] = t[0]; raw.d[ci][1] = t[1]; raw.d[ci][2] = t[2];
-        } else {
-            typedef unsigned v2u __attribute__((ext_vector_type(2)));
-            const v2u t = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(rsS, ob, 0, 0));
-            raw.d[ci][0] = t[0]; raw.d[ci][1] = t[1]; raw.d[ci][2] = 0u;
-        }
+        // one load instruction per chunk, of the same width whatever the rows' alignment: the address path takes as long for a
+        // lane's 4 bytes as for its 12, and with two widths to choose from the compiler waited for all but the last load
+        // at each of the four choices
+        typedef unsigned v3u __attribute__((ext_vector_type(3)));
+        const v3u t = __builtin_bit_cast(v3u, __builtin_amdgcn_raw_buffer_load_b96(rsS, ob, 0, 0));
+        raw.d[ci][0] = t[0]; raw.d[ci][1] = t[1]; raw.d[ci][2] = t[2];
     }
 }
 

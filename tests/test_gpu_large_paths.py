@@ -192,6 +192,28 @@ def test_masked_gate_up_tiles_keep_the_row_maxima(fq, M, N):
     Hr, B = oracle.w4a8_gemm_swiglu(A.cpu().numpy(), s.cpu().numpy(), d["q"], d["gscale"], d["w_tscale"], want_bound=True)
     check_gemm(bf16_bits_from_gpu(H), Hr, B, "masked gate/up %d x %d" % (M, N))
 
+# Group counts around the eight that share a fetch of scales (groups 1 .. 8, 9 .. 16, ... and group 0 by itself), rows of scales
+# at every alignment, a ragged last channel block, whole and half tiles.
+@pytest.mark.parametrize("G", [1, 2, 3, 7, 8, 9, 10, 11, 15, 16, 17, 18, 19, 33])
+@pytest.mark.parametrize("lut", [False, True])
+def test_scales_of_every_group_count(fq, G, lut):
+    rng = np.random.default_rng(G)
+    M, N, K = 330, 203, 128 * G
+    A = (rng.integers(0, 0x58, (M, K)) | rng.integers(0, 2, (M, K)) << 7).astype(np.uint8)
+    q = rng.integers(-8, 8, (N, K), dtype=np.int8)
+    gsn = rng.integers(0x08, 0x40, (N, G)).astype(np.uint8)
+    a = rng.uniform(0.5, 2.0, M).astype(np.float32)
+    packed = fq.fq_pack_weights(_gpu(q))
+    fq.fq_test_force_kernel("large")
+    try:
+        Y = (fq.fq_w4a8_gemm_lut if lut else fq.fq_w4a8_gemm)(_gpu(A), _gpu(a), packed, _gpu(gsn), 0.5, N)
+        torch.cuda.synchronize()
+    finally:
+        fq.fq_test_force_kernel(None)
+    Yr, B = (oracle.w4a8_gemm_lut if lut else oracle.w4a8_gemm)(A, a, q, gsn, 0.5, want_bound=True)
+    check_gemm(bf16_bits_from_gpu(Y), Yr, B, "G = %d" % G)
+
+
 # ---- the K-split kernel (8-wave workgroups that split K inside the workgroup) --------------------------
 
 KSPLIT_SHAPES = [(65, 64, 1024), (128, 128, 1024), (300, 256, 1024), (129, 200, 1408), (512, 520, 2048),
