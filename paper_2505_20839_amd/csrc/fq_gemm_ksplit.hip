@@ -4,7 +4,7 @@
 // its own two LDS stages and its own packed weights (128- and 64-row tiles: both through registers, several groups
 // ahead), with two chained v_mfma_f32_32x32x64_f8f6f4 per row tile and group and the group scale applied in FP32 to each
 // group's partial sum, as in the large-M kernel; the splits' partial tiles are then added through LDS, each wave taking
-// over NMT / KS row tiles, and the zero-point update and the epilogue finish those.  The shapes:
+// over NMT / KS row tiles, and the zero-point update, whose operands travel from the start, and the epilogue finish those.  The shapes:
 //     NMT = 4, NW = 4, KS = 2   128 x 128 tiles, K halved: wherever these tiles fit one round of the compute units
 //     NMT = 4, NW = 2, KS = 4   128 x 64 tiles, K quartered: where even these do (batched decode, chunked prefill,
 //                               narrow layers)
@@ -19,8 +19,8 @@
 // 80 KiB for 8 matrix instructions per wave), so a tile finishes S times sooner.  Each slice writes its folded
 // partial tile (FP32, in the accumulators' own layout) to the workspace and counts itself in; the workgroup that
 // arrives last adds the S partial tiles in the order of the slices -- a fixed order, so the result does not
-// depend on which one that is -- and goes on to the zero-point update and the epilogue; it leaves the counter at
-// zero for the next call.  The S workgroups of a tile run on the same XCD, so the partial tiles stay in its L2.
+// depend on which one that is -- and goes on to the epilogue (each slice has made the zero-point update for its own groups);
+// it leaves the counter at zero for the next call.  The S workgroups of a tile run on the same XCD, so the partial tiles stay in its L2.
 #include <type_traits>
 #include "fq_common.h"
 #include "fq_kernels.h"
@@ -33,7 +33,7 @@ namespace {
 
 // LDS: KS * 2 stages of 32 * NMT rows x 128 bytes, then (256 x 128 shape) 8 x 4 KiB of packed weights; reused for the fold
 // (8 waves x NMT tiles of 4 KiB, all at once where they fit, else half of them at a time), the zero-point units and the output tile.
-template <int NMT, int NW, int KS>
+template <int NMT, int NW, int KS, bool ZPM>
 struct fqk_cfg {
     static constexpr int BM = 32 * NMT, BN = 32 * NW;
     static constexpr int STG = 8 * BM;                    // 16-byte chunks per A stage
@@ -42,11 +42,17 @@ struct fqk_cfg {
     static constexpr int LOOP_LDS = KS * 2 * STG * 16 + (WREG ? 0 : FQK_WAVES * 4096);
     // row tiles that go through LDS at a time when the K splits' partial tiles are added: all of them where the
     // stages have room for 8 waves x NMT tiles of 4 KiB, else half
-    static constexpr int HALF = FQK_WAVES * NMT * 4096 <= LOOP_LDS ? NMT : (NMT / 2 > 0 ? NMT / 2 : 1);
+    static constexpr int HALF = FQK_WAVES * NMT * 4096 <= (WREG ? 128 * 1024 : LOOP_LDS) ? NMT : (NMT / 2 > 0 ? NMT / 2 : 1);
     static constexpr int FOLD_LDS = FQK_WAVES * HALF * 4096;
     static constexpr int EPI_LDS = BM * OUT_STRIDE + 1024;
-    static constexpr int LDS = LOOP_LDS > FOLD_LDS ? (LOOP_LDS > EPI_LDS ? LOOP_LDS : EPI_LDS)
-                                                   : (FOLD_LDS > EPI_LDS ? FOLD_LDS : EPI_LDS);
+    static constexpr int WORK_LDS = LOOP_LDS > FOLD_LDS ? (LOOP_LDS > EPI_LDS ? LOOP_LDS : EPI_LDS)
+                                                        : (FOLD_LDS > EPI_LDS ? FOLD_LDS : EPI_LDS);
+    // zero-point units: rounds of 8 units of BM rows; the first two have a place of their own and travel from the start
+    // (256 x 128 shape: no room)
+    static constexpr int ZROUND = 8 * BM;                 // chunks
+    static constexpr bool ZPRE = WREG && !ZPM;
+    static constexpr int LDS = WORK_LDS + (ZPRE ? 2 * ZROUND * 16 : 0);
+    static constexpr int ZBATCH = WORK_LDS / (ZROUND * 16) < 4 ? WORK_LDS / (ZROUND * 16) : 4;   // later rounds that travel together
     static_assert(NW * KS == FQK_WAVES && (NMT % KS == 0 || KS % NMT == 0) && (4 * NMT) % NW == 0 && 8 % NMT == 0, "shape");
     static_assert(LDS <= 160 * 1024, "LDS");
 };
@@ -60,7 +66,7 @@ void fq_gemm_ksplit_kernel(
     const uint8_t* __restrict__ gs, float tscale, uint16_t* Y, int M, int N, int K,
     int tiles_m, int tiles_n, int pm, const uint16_t* __restrict__ planes, const uint16_t* R,
     int S, unsigned* counters, float* partials) {
-    typedef fqk_cfg<NMT, NW, KS> cfg;
+    typedef fqk_cfg<NMT, NW, KS, ZPM> cfg;
     constexpr int NT = 4 * NMT / NW;                      // A transfers (8 rows each) per wave and stage
     constexpr int OWN = NMT >= KS ? NMT / KS : 1;         // row tiles a wave finishes (fewer row tiles than splits:
                                                           // the first NMT splits finish one each, the others none)
@@ -87,14 +93,10 @@ void fq_gemm_ksplit_kernel(
         m0 = tm * cfg::BM;
         n0 = tn * cfg::BN;
     }
-    // the output factor of row m0 + threadIdx.x, fetched now so that the epilogue does not wait for it
-    // (x 2^9: the weights are fed in units of 2^-9)
-    static_assert(cfg::BM <= FQK_THREADS, "one row factor per thread");
-    float row_factor = 0.f;
-    if ((int)threadIdx.x < cfg::BM) {
-        const int m = m0 + (int)threadIdx.x;
-        row_factor = a_scale[m < M ? m : M - 1] * (tscale * 512.0f);
-    }
+    // the scale of row m0 + threadIdx.x, fetched now so that the epilogue does not wait for it (and not touched until then:
+    // its product formed here held every other request back for the time of one load)
+    static_assert(cfg::BM <= FQK_THREADS, "one row scale per thread");
+    const float row_scale = a_scale[m0 + (int)threadIdx.x < M ? m0 + (int)threadIdx.x : M - 1];
     const int nw0 = n0 + nw * 32;                         // first output channel of this wave
     const bool wave_on = nw0 < N;                         // waves past N compute a duplicate tile and store nothing
     const int n = nw0 + (lane & 31);
@@ -123,6 +125,43 @@ void fq_gemm_ksplit_kernel(
     auto gclamp = [&](int j) { const int g = gb + j; return g < ge ? g : (ge > gb ? ge - 1 : glast); };
     // ghost steps request their operands out of range: zeros arrive at once and nothing is fetched
     auto ghost = [&](int j) { return gb + j < ge ? 0u : FQL_OOB; };
+
+    // ---- zero-point units of this slice's groups ----
+    // Plane 0's units, then plane 1's (fql_c2), `znp` places each (an even number: places 2 i, 2 i + 1 are the two lane halves of one
+    // matrix instruction), those past the slice's last unit empty.  Round r is places 8 r .. 8 r + 7.
+    const int zu0 = sb >> 3, zun = ((se + 7) >> 3) - zu0, znp = (zun + 1) & ~1;
+    const int rounds = ZPM ? 0 : (2 * znp + 7) >> 3;
+    auto issue_z = [&](fq_v4i* dst, int r) __attribute__((always_inline)) {
+        constexpr int SUBS = cfg::BM / 64;
+#pragma unroll
+        for (int t = 0; t < 8 * SUBS / FQK_WAVES; ++t) {
+            const int q = wave + FQK_WAVES * t, slot = q / SUBS, sub = q - slot * SUBS;
+            const int i = 8 * r + slot, plane = i >= znp ? 1 : 0, k = i - plane * znp;
+            // (rows past M are masked too: the range check sees the per-lane offset only)
+            const int row = m0 + 64 * sub + lane;
+            const unsigned v = k < zun && row < M ? (unsigned)row * 16u : FQL_OOB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsZ, (fql_lds_ptr)(dst + slot * cfg::BM + 64 * sub), 16, v,
+                                                     (int)((unsigned)(plane * C2 + zu0 + k) * (unsigned)M * 16u), 0, 0);
+        }
+    };
+    // their factors: 8 groups of this lane's channel per place, the aligned words around them (see fql_scales_issue)
+    const int hl = lane >> 5;
+    const __amdgpu_buffer_rsrc_t rsS = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t*>(gs), 0, (int)(((unsigned)N * (unsigned)G + 3u) & ~3u), 0x00020000);
+    auto zgroup = [&](int r, int ci) __attribute__((always_inline)) {    // first group of this lane's place of chunk ci
+        const int i = 8 * r + 2 * ci;
+        return 8 * (zu0 + (i >= znp ? i - znp : i) + hl);
+    };
+    auto issue_sig = [&](int r, fql_raw_scales& raw) __attribute__((always_inline)) {
+        typedef unsigned v3u __attribute__((ext_vector_type(3)));
+#pragma unroll
+        for (int ci = 0; ci < 4; ++ci) {
+            const int g0 = zgroup(r, ci);
+            const unsigned o = 8 * r + 2 * ci < 2 * znp && n_ok && g0 < se ? ((unsigned)n * (unsigned)G + (unsigned)g0) & ~3u : FQL_OOB;
+            const v3u t = __builtin_bit_cast(v3u, __builtin_amdgcn_raw_buffer_load_b96(rsS, o, 0, 0));
+            raw.d[ci][0] = t[0]; raw.d[ci][1] = t[1]; raw.d[ci][2] = t[2];
+        }
+    };
 
     const int r32 = lane & 31, sw = (r32 >> 1) & 7;
     const int o00 = r32 * 8 + ((2 * (lane >> 5)) ^ sw);
@@ -176,7 +215,7 @@ void fq_gemm_ksplit_kernel(
         auto load_s = [&](int p) __attribute__((always_inline)) {
             return __builtin_amdgcn_raw_buffer_load_b32(rsG, (goff & ~3u) + 4u * (unsigned)p, 0, 0);
         };
-        unsigned sw0 = load_s(0), sw1 = load_s(1), sw2 = load_s(2);
+        unsigned sw0 = load_s(0), sw1 = load_s(1), sw2 = 0u;
         // requested in the order of the steady state (the waits are timed for the shortest path into the loop)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -187,6 +226,11 @@ void fq_gemm_ksplit_kernel(
             load_w(i, i, 1);
         }
         __builtin_amdgcn_sched_barrier(0);
+        if (cfg::ZPRE) {
+            issue_z(lds + cfg::WORK_LDS / 16, 0);
+            issue_z(lds + cfg::WORK_LDS / 16 + cfg::ZROUND, 1);   // (past the last round: nothing is fetched)
+        }
+        __builtin_amdgcn_sched_barrier(0);
         fq_v8i b0[2], b1[2];
         b0[0] = fq_unpack_chunk(wr[0][0]);
         b1[0] = fq_unpack_chunk(wr[0][1]);
@@ -195,13 +239,10 @@ void fq_gemm_ksplit_kernel(
         for (int x = 0; x < NT; ++x) put_a(0, 0, x);
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         fq_v8i an = fql_join(stages[o00], stages[o01]);
-        for (int p = 0; 4 * p < gper; ++p) {
-            const unsigned sw = __builtin_amdgcn_alignbyte(sw1, sw0, goff & 3u);
-            sw0 = sw1; sw1 = sw2;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int j = 4 * p + u;                  // step of this split; group gb + j
-                if (u > 0 && j >= gper) break;            // (the same for all splits)
+        // Step 4 p + u of this split (group gb + 4 p + u); `sw`: the scale bytes of steps 4 p .. 4 p + 3.
+        auto step = [&](const int p, const unsigned sw, auto uc) __attribute__((always_inline)) {
+                constexpr int u = decltype(uc)::value;
+                const int j = 4 * p + u;
                 const fq_v4i* cur = stages + (u & 1) * cfg::STG;
                 const float t = u == 0 ? __builtin_amdgcn_cvt_f32_fp8((int)sw, 0) : u == 1 ? __builtin_amdgcn_cvt_f32_fp8((int)sw, 1)
                               : u == 2 ? __builtin_amdgcn_cvt_f32_fp8((int)sw, 2) : __builtin_amdgcn_cvt_f32_fp8((int)sw, 3);
@@ -225,10 +266,10 @@ void fq_gemm_ksplit_kernel(
                             if (x * SLOTS / NT == sl) load_a(u % RA, j + RA, x);
                         if (sl == SLOTS / 2) load_w(u, j + 4, 0);
                         if (sl == SLOTS - 2) load_w(u, j + 4, 1);
-                        if (u == 0 && sl == SLOTS - 1) sw2 = load_s(p + 3);
+                        if (u == 0 && sl == SLOTS - 1) sw2 = load_s(p + 2);
 #pragma unroll
                         for (int x = 0; x < NT; ++x)
-                            if (SLOTS - 2 - x * (SLOTS / 2) / NT == sl) put_a((u + 1) % RA, (u & 1) ^ 1, x);
+                            if (SLOTS / 2 - 1 + x * (SLOTS / 2) / NT == sl) put_a((u + 1) % RA, (u & 1) ^ 1, x);
                         const fq_v8i ac = an;
                         if (h == 0) {
                             an = fql_join(cur[mt * 256 + o10], cur[mt * 256 + o11]);
@@ -264,6 +305,27 @@ void fq_gemm_ksplit_kernel(
                     pprev = pt;
                 }
                 sprev = s;
+        };
+        // Whole rounds of four steps, then the rest (the same number for all splits), the loop left at its end only: where a step
+        // in its middle could leave it, the compiler timed the waits of its start for that way round and let hardly a request be
+        // under way at the end of each round; and where the loop alone used the requests above, it put them behind its first
+        // test, where the prologue paid their latency on top of the first operands' (200 x 4096 x 11008 25.5 -> 24.3 us,
+        // 128 x 14336 x 4096 17.1 -> 16.2, 1500 x 2048 x 8192 34.2 -> 32.8, 64 x 14336 x 4096 12.1 -> 11.5).
+        int p = 0;
+        for (; 4 * p + 4 <= gper; ++p) {
+            const unsigned sw = __builtin_amdgcn_alignbyte(sw1, sw0, goff & 3u);
+            step(p, sw, std::integral_constant<int, 0>());
+            step(p, sw, std::integral_constant<int, 1>());
+            step(p, sw, std::integral_constant<int, 2>());
+            step(p, sw, std::integral_constant<int, 3>());
+            sw0 = sw1; sw1 = sw2;
+        }
+        if (4 * p < gper) {
+            const unsigned sw = __builtin_amdgcn_alignbyte(sw1, sw0, goff & 3u);
+            step(p, sw, std::integral_constant<int, 0>());
+            if (4 * p + 1 < gper) {
+                step(p, sw, std::integral_constant<int, 1>());
+                if (4 * p + 2 < gper) step(p, sw, std::integral_constant<int, 2>());
             }
         }
     } else {
@@ -353,6 +415,10 @@ void fq_gemm_ksplit_kernel(
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[NMT - 1][r] = fmaf(sprev, pprev[r], acc[NMT - 1][r]);
 
+    // The first zero-point units, older than any request of the loop, and ghost requests, which fetch nothing, have landed
+    // (waited for here, or the compiler makes the barrier below wait for the residual and the scale words too).
+    if (cfg::ZPRE) __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(0));
+
     // ---- residual tile: requested now, used in the epilogue ----
     // (step `it` of the epilogue: rows 8 * it + 4 * (lane / 32) + 0..3 of the wave's own rows; the even lane of a pair
     // fetches both channels' bf16 of rows 0, 1 as dwords, the odd lane those of rows 2, 3.  Rows past M lie behind the
@@ -374,13 +440,19 @@ void fq_gemm_ksplit_kernel(
                 rres[it][x] = __builtin_amdgcn_raw_buffer_load_b32(rsR, rlane + (unsigned)(8 * it + x) * (unsigned)N * 2u, 0, 0);
     }
 
+    fql_raw_scales zraw[2];
+    if (cfg::ZPRE) {
+        issue_sig(0, zraw[0]);
+        issue_sig(1, zraw[1]);
+    }
+
     // ---- fold: add the K splits' partial tiles through LDS ----
     // Row tiles are handed out in blocks: split kw finishes row tiles kw * OWN .. kw * OWN + OWN - 1 (for its
     // NW waves' channels).  All row tiles go through LDS at once where they fit, else half of them at a time: every
     // wave writes its partial tiles of the pass ([wave][tile of the pass][4 x 4 registers][64 lanes], 16 bytes per lane and access), and
     // the waves that own one of them add up the KS partials in the order of the splits (a fixed order: the result
     // is deterministic).
-    __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(0));           // ghost transfers have landed: the stages can be reused
+    if (!cfg::WREG) __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(0));   // ghost transfers have landed: the stages can be reused
     __syncthreads();
     fq_v16f fin[OWN];
     const bool owner = kw * OWN < NMT;                    // this wave finishes row tiles kw * OWN ..
@@ -419,14 +491,65 @@ void fq_gemm_ksplit_kernel(
         }
     }
 
-    // the first round of zero-point units is requested now: it travels while the slices hand over
-    const int rounds = ZPM ? 0 : (ZU + 7) >> 3;
-    if (!ZPM) fql_issue_z<NMT, FQK_WAVES>(rsZ, lds, wave, lane, m0, M, 0, ZU < 8 ? ZU : 8);
-    const __amdgpu_buffer_rsrc_t rsS = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t*>(gs), 0, (int)(((unsigned)N * (unsigned)G + 3u) & ~3u), 0x00020000);
-    const unsigned srow = n_ok ? (unsigned)n * (unsigned)G : FQL_OOB;    // channels past N read zeros
-    fql_raw_scales zraw;                                  // the round's scale words, requested a round ahead
-    if (!ZPM) fql_scales_issue(rsS, srow, n_ok, G, C2, 0, ZU < 8 ? ZU : 8, lane >> 5, zraw);
+    // ---- zero point: fin += Z * gscale^T over the slice's groups, on the fp16 matrix cores ----
+    // (per slice, its units under way since the start: with all groups' units fetched and applied by the workgroup that
+    // finishes the tile, behind the hand-over, 200 x 4096 x 11008 took 24.4 us, 22.4 now; 128 x 4096 x 11008 20.6, 18.5; without
+    // slices 1000 x 1024 x 8192 23.3, 22.5)
+    if (!ZPM) {
+        auto apply = [&](const fq_v4i* stage, int r, const fql_raw_scales& raw) __attribute__((always_inline)) {
+#pragma unroll
+            for (int ci = 0; ci < 4; ++ci) {
+                if (8 * r + 2 * ci < 2 * znp) {
+                    const int g0 = zgroup(r, ci);
+                    const unsigned sh = ((unsigned)n * (unsigned)G + (unsigned)g0) & 3u;
+                    unsigned long long w = (unsigned long long)__builtin_amdgcn_alignbyte(raw.d[ci][1], raw.d[ci][0], sh) |
+                                           (unsigned long long)__builtin_amdgcn_alignbyte(raw.d[ci][2], raw.d[ci][1], sh) << 32;
+                    // bytes of groups outside [sb, se) are another slice's, or another channel's
+                    const int lo = sb - g0 < 0 ? 0 : sb - g0, hi = se - g0;      // lo is at most 7
+                    if (hi < 8) w &= hi <= 0 ? 0ull : (1ull << (8 * hi)) - 1ull;
+                    w &= ~0ull << (8 * lo);
+                    fq_v4i pk;
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) {
+                        const int v = (int)(x == 0 ? (unsigned)w : (unsigned)(w >> 32));
+                        pk[2 * x]     = __builtin_bit_cast(int, __builtin_amdgcn_cvt_pkrtz(
+                            __builtin_amdgcn_cvt_f32_fp8(v, 0), __builtin_amdgcn_cvt_f32_fp8(v, 1)));
+                        pk[2 * x + 1] = __builtin_bit_cast(int, __builtin_amdgcn_cvt_pkrtz(
+                            __builtin_amdgcn_cvt_f32_fp8(v, 2), __builtin_amdgcn_cvt_f32_fp8(v, 3)));
+                    }
+                    const fq_v4i* unit = stage + (2 * ci + hl) * cfg::BM + kw * (32 * OWN) + (lane & 31);
+#pragma unroll
+                    for (int i = 0; i < OWN; ++i)
+                        fin[i] = FQ_MFMA_F16(__builtin_bit_cast(fql_v8h, unit[32 * i]), __builtin_bit_cast(fql_v8h, pk), fin[i]);
+                }
+            }
+        };
+        // rounds past the first two (K beyond 8192 in one slice) travel through the stages, which the fold is done with
+        constexpr int PRE = cfg::ZPRE ? 2 : 0;
+        auto issue_batch = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < cfg::ZBATCH; ++t)
+                if (r0 + t < rounds) issue_z(lds + t * cfg::ZROUND, r0 + t);
+        };
+        if (PRE < rounds) issue_batch(PRE);
+        if (cfg::ZPRE) {
+            apply(lds + cfg::WORK_LDS / 16, 0, zraw[0]);
+            if (rounds > 1) apply(lds + cfg::WORK_LDS / 16 + cfg::ZROUND, 1, zraw[1]);
+        }
+        for (int r0 = PRE; r0 < rounds; r0 += cfg::ZBATCH) {
+            fql_raw_scales raw;
+            if (r0 > PRE) issue_batch(r0);
+            issue_sig(r0, raw);
+            __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(0));
+            __syncthreads();
+            for (int t = 0; t < cfg::ZBATCH && r0 + t < rounds; ++t) {
+                const fql_raw_scales cur = raw;
+                if (r0 + t + 1 < rounds) issue_sig(r0 + t + 1, raw);
+                apply(lds + t * cfg::ZROUND, r0 + t, cur);
+            }
+            __syncthreads();                              // read: LDS is free again
+        }
+    }
 
     // ---- K slices: hand the partial tile over; the workgroup that arrives last adds them up and goes on ----
     // The partial tiles and the counter are written and read with device-scope accesses (the sc1 bit: they go to
@@ -449,11 +572,12 @@ void fq_gemm_ksplit_kernel(
             }
         __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(0));       // this wave's partial sums have arrived ...
         __syncthreads();
-        unsigned* flag = reinterpret_cast<unsigned*>(lds + cfg::LDS / 16 - 1);   // (past the zero-point units on their way)
+        unsigned* flag = reinterpret_cast<unsigned*>(lds + cfg::LDS / 16 - 1);
         if (threadIdx.x == 0)                             // ... before the workgroup counts itself in
             flag[0] = __hip_atomic_fetch_add(&counters[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
-        const unsigned arrived = *reinterpret_cast<volatile unsigned*>(flag);
+        // (one value for the whole wave, said so: else the addresses below count as each lane's own and every load becomes a loop)
+        const unsigned arrived = (unsigned)__builtin_amdgcn_readfirstlane((int)*reinterpret_cast<volatile unsigned*>(flag));
         if (arrived != (unsigned)(S - 1)) return;
         if (threadIdx.x == 0)                             // every slice has counted: ready for the next call
             __hip_atomic_store(&counters[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -482,39 +606,9 @@ void fq_gemm_ksplit_kernel(
         }
     }
 
-    // ---- zero point: fin += Z * gscale^T over all groups (fp16 matrix cores), 8 units of Z per round ----
-    if (!ZPM) {
-        constexpr int RT = 32 * NMT;
-        const int hl = lane >> 5;
-        for (int r = 0; r < rounds; ++r) {
-            const int u0 = 8 * r;
-            const int nu = ZU - u0 < 8 ? ZU - u0 : 8;
-            __builtin_amdgcn_s_waitcnt(FQL_WAIT_VM(0));
-            __syncthreads();                              // round r has landed (stage r & 1)
-            fql_v8h sig[4];
-            fql_scales_finish(zraw, srow, G, C2, u0, hl, sig);
-            if (r + 1 < rounds) {
-                const int nn = ZU - u0 - 8 < 8 ? ZU - u0 - 8 : 8;
-                fql_issue_z<NMT, FQK_WAVES>(rsZ, lds + ((r + 1) & 1) * cfg::STG, wave, lane, m0, M, u0 + 8, nn);
-                fql_scales_issue(rsS, srow, n_ok, G, C2, u0 + 8, nn, hl, zraw);
-            }
-            const fq_v4i* stage = lds + (r & 1) * cfg::STG;
-#pragma unroll
-            for (int ci = 0; ci < 4; ++ci) {
-                if (2 * ci < nu) {
-                    const fq_v4i* unit = stage + (2 * ci + hl) * RT + kw * (32 * OWN) + (lane & 31);
-#pragma unroll
-                    for (int i = 0; i < OWN; ++i)
-                        fin[i] = FQ_MFMA_F16(__builtin_bit_cast(fql_v8h, unit[32 * i]), sig[ci], fin[i]);
-                }
-            }
-        }
-        __syncthreads();                                  // the last round has been read: LDS is free again
-    }
-
     // ---- epilogue: per-token and per-tensor factors, the residual if any, one rounding to bf16, store ----
     float* osc = reinterpret_cast<float*>(reinterpret_cast<char*>(lds) + cfg::BM * cfg::OUT_STRIDE);
-    if ((int)threadIdx.x < cfg::BM) osc[threadIdx.x] = row_factor;
+    if ((int)threadIdx.x < cfg::BM) osc[threadIdx.x] = row_scale * (tscale * 512.0f);   // x 2^9: the weights were fed in units of 2^-9
     __syncthreads();
     if (wide_rows) {
         // transpose through LDS so that every store instruction writes whole rows of the tile
@@ -585,7 +679,7 @@ template <int NMT, int NW, int KS, bool ZPM = false>
 void fqk_launch(const uint8_t* A, const float* a_scale, const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y,
                 int M, int N, int K, const uint16_t* planes, const uint16_t* R, int S, unsigned* counters, float* partials,
                 hipStream_t stream) {
-    typedef fqk_cfg<NMT, NW, KS> cfg;
+    typedef fqk_cfg<NMT, NW, KS, ZPM> cfg;
     static fq_device_once attr_once;                      // (one per template instance)
     fq_once_per_device(attr_once, [] {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_gemm_ksplit_kernel<NMT, NW, KS, ZPM>),

@@ -418,6 +418,21 @@ def test_large_m_range_on_k_split_tiles(fq, shape, tiles):
     check_gemm(bf16_bits_from_gpu(YR)[:, pick], Yr, B, "split tiles + residual %s" % (shape,))
 
 
+# Zero-point units past the two rounds that travel from the start: a third round (71 groups), a second batch of later rounds (260
+# groups), on both shapes; the odd number of units of 65 groups; splits that run 4 n + 1, 2 and 3 steps.
+@pytest.mark.parametrize("shape,tiles", [((600, 1024, 9088), 1), ((520, 72, 33280), 1), ((1000, 2560, 9088), 2), ((513, 130, 8320), 1),
+                                         ((513, 130, 2560), 1), ((513, 130, 3072), 1), ((513, 130, 3584), 1)])
+def test_k_split_zero_point_rounds(fq, shape, tiles):
+    test_large_m_range_on_k_split_tiles(fq, shape, tiles)
+
+
+# K slices whose borders fall inside a zero-point unit (11, 14 and 22 groups a slice), with an empty place beside the last unit
+@pytest.mark.parametrize("shape", [(100, 96, 11008), (200, 4096, 3584), (129, 1000, 11008)])
+def test_k_split_slices_share_zero_point_units(fq, shape):
+    assert _plan(fq, shape)["ksplit_slices"] > 1
+    test_k_split_kernel_every_element(fq, shape)
+
+
 # the last round in halves (11 tiles on an XCD's 64 slots) and in quarters: 1 or 2 tiles behind a full round, with a ragged last row
 # tile (52 rows: the second to fourth quarter are empty) and a ragged channel edge; quarters alone, odd group counts, two
 # rounds of zero-point units
