@@ -98,6 +98,14 @@ def lib() -> ctypes.CDLL:
     L.fq_cas_scales.argtypes = [vp, cf, vp, ci, ci, vp]
     L.fq_pts_exponent.restype = ci
     L.fq_pts_exponent.argtypes = [vp, vp, vp, ci, ci, vp]
+    L.fq_cas_scales_workspace_bytes.restype = ctypes.c_size_t
+    L.fq_cas_scales_workspace_bytes.argtypes = [ci, ci]
+    L.fq_cas_scales_ws.restype = ci
+    L.fq_cas_scales_ws.argtypes = [vp, cf, vp, ci, ci, vp, ctypes.c_size_t, vp]
+    L.fq_pts_exponent_workspace_bytes.restype = ctypes.c_size_t
+    L.fq_pts_exponent_workspace_bytes.argtypes = [ci, ci]
+    L.fq_pts_exponent_ws.restype = ci
+    L.fq_pts_exponent_ws.argtypes = [vp, vp, vp, ci, ci, vp, ctypes.c_size_t, vp]
     L.fq_quantize_weights.restype = ci
     L.fq_quantize_weights.argtypes = [vp, vp, ci, ci, vp, vp, ci, ci, vp]
     L.fq_w4a8_gemm_plan.restype = ci
@@ -180,7 +188,10 @@ def fq_cas_scales(W: torch.Tensor, target: float) -> torch.Tensor:
     W = _dev(W, torch.bfloat16, "W")
     N, K = W.shape
     lam = torch.empty((K,), dtype=torch.float32, device=W.device)
-    rc = lib().fq_cas_scales(W.data_ptr(), ctypes.c_float(float(target)), lam.data_ptr(), N, K, _stream())
+    need = lib().fq_cas_scales_workspace_bytes(N, K)
+    ws = torch.empty((need,), dtype=torch.uint8, device=W.device) if need else None
+    rc = lib().fq_cas_scales_ws(W.data_ptr(), ctypes.c_float(float(target)), lam.data_ptr(), N, K, ws.data_ptr() if need else 0, need,
+                                _stream())
     if rc != 0:
         raise FireqError(rc, "fq_cas_scales")
     return lam
@@ -201,7 +212,9 @@ def fq_pts_exponent(W: torch.Tensor, lam: Optional[torch.Tensor] = None) -> torc
     W = _dev(W, torch.bfloat16, "W")
     N, K = W.shape
     out = torch.empty((16,), dtype=torch.int32, device=W.device)
-    rc = lib().fq_pts_exponent(W.data_ptr(), _lambda_ptr(lam, K), out.data_ptr(), N, K, _stream())
+    need = lib().fq_pts_exponent_workspace_bytes(N, K)
+    ws = torch.empty((need,), dtype=torch.uint8, device=W.device) if need else None
+    rc = lib().fq_pts_exponent_ws(W.data_ptr(), _lambda_ptr(lam, K), out.data_ptr(), N, K, ws.data_ptr() if need else 0, need, _stream())
     if rc != 0:
         raise FireqError(rc, "fq_pts_exponent")
     return out

@@ -2,6 +2,7 @@
 // Declarations and the contract of every call are in include/fireq.h.
 #include "../../include/fireq.h"
 #include "../../include/fireq_kv4_ws.h"
+#include "../../include/fireq_wquant_ws.h"
 #include "fq_common.h"
 #include "fq_kernels.h"
 
@@ -134,17 +135,42 @@ int fq_quantize_act(const uint16_t* X_bf16, uint8_t* A_fp8, float* a_scale, int 
 }
 
 int fq_cas_scales(const uint16_t* W_bf16, float target, float* lambda, int N, int K, void* stream) {
+    return fq_cas_scales_ws(W_bf16, target, lambda, N, K, nullptr, 0, stream);
+}
+
+size_t fq_cas_scales_workspace_bytes(int N, int K) { return N > 0 && K > 0 ? fq_cas_scales_scratch(N, K) : 0; }
+
+int fq_cas_scales_ws(const uint16_t* W_bf16, float target, float* lambda, int N, int K, void* workspace, size_t workspace_bytes,
+                     void* stream) {
     if (N <= 0 || K <= 0 || !(target > 0.f)) return FQ_ERR_SHAPE;
     if (!W_bf16 || !lambda) return FQ_ERR_NULL;
-    fq_launch_cas_scales(W_bf16, target, lambda, N, K, static_cast<hipStream_t>(stream));
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const size_t need = workspace ? fq_cas_scales_scratch(N, K) : 0;
+    if (need != 0) {
+        if (!aligned16(workspace)) return FQ_ERR_ALIGN;
+        if (workspace_bytes < need) return FQ_ERR_MEMORY;
+    }
+    if (need != 0 && aligned16(W_bf16)) fq_launch_cas_scales_split(W_bf16, target, lambda, N, K, workspace, s);
+    else fq_launch_cas_scales(W_bf16, target, lambda, N, K, s);
     return after_launch();
 }
 
 int fq_pts_exponent(const uint16_t* W_bf16, const float* lambda, int* n_out, int N, int K, void* stream) {
+    return fq_pts_exponent_ws(W_bf16, lambda, n_out, N, K, nullptr, 0, stream);
+}
+
+size_t fq_pts_exponent_workspace_bytes(int N, int K) {
+    return N > 0 && K > 0 && (K % FQ_GROUP) == 0 ? fq_pts_exponent_scratch(K) : 0;
+}
+
+int fq_pts_exponent_ws(const uint16_t* W_bf16, const float* lambda, int* n_out, int N, int K, void* workspace,
+                       size_t workspace_bytes, void* stream) {
     if (N <= 0 || K <= 0 || (K % FQ_GROUP) != 0) return FQ_ERR_SHAPE;
     if (!W_bf16 || !n_out) return FQ_ERR_NULL;
-    if (!aligned16(W_bf16) || !aligned16(n_out)) return FQ_ERR_ALIGN;
-    fq_launch_pts_exponent(W_bf16, lambda, n_out, N, K, static_cast<hipStream_t>(stream));
+    const size_t need = workspace ? fq_pts_exponent_scratch(K) : 0;
+    if (!aligned16(W_bf16) || !aligned16(n_out) || (need != 0 && !aligned16(workspace))) return FQ_ERR_ALIGN;
+    if (workspace_bytes < need) return FQ_ERR_MEMORY;
+    fq_launch_pts_exponent(W_bf16, lambda, n_out, N, K, need != 0 ? workspace : nullptr, static_cast<hipStream_t>(stream));
     return after_launch();
 }
 

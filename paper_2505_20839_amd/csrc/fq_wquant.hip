@@ -121,6 +121,35 @@ __device__ __forceinline__ double fqw_dpp_f64(double v) {
                             __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false));
 }
 
+__device__ __forceinline__ void fqw_cas_add(double (&s)[8], const fq_v4i& v) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const unsigned word = (unsigned)v[i];
+        s[2 * i] += __hiloint2double((int)((word << 13) & 0x0FFFE000u), 0);
+        s[2 * i + 1] += __hiloint2double((int)((word >> 3) & 0x0FFFE000u), 0);
+    }
+}
+
+// A channel's sum (times 2^-896) -> its scale, by one wave that holds channel k0 + lane in lane `lane`.
+__device__ __forceinline__ void fqw_cas_close(double t, bool mine, const uint16_t* __restrict__ W, float target,
+                                              float* __restrict__ lambda, int k0, int lane, int N, int K) {
+    t *= 0x1p+896;
+    for (unsigned long long big = __ballot(mine && t >= 0x1p+128); big != 0; big &= big - 1) {
+        const int c = __ffsll(big) - 1;
+        bool inf = false, nan = false;
+        for (int n = lane; n < N; n += 64) {
+            const unsigned b = W[(size_t)n * K + k0 + c] & 0x7FFFu;
+            inf |= b == 0x7F80u;
+            nan |= b > 0x7F80u;
+        }
+        const bool any_inf = __ballot(inf) != 0, any_nan = __ballot(nan) != 0;
+        if (lane == c) t = any_nan ? __builtin_nan("") : any_inf ? __builtin_inf() : t;
+    }
+    if (mine)
+        lambda[k0 + lane] =
+            t == 0.0 ? 1.0f : (float)((double)target / (t / (double)N));            // an all-zero channel keeps 1
+}
+
 template <int LPR, bool STREAM>
 __global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_scales_wide_kernel(const uint16_t* __restrict__ W, float target,
                                                                               float* __restrict__ lambda, int N, int K) {
@@ -137,14 +166,6 @@ __global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_scales_wide_kernel(co
 #pragma unroll
     for (int i = 0; i < 8; ++i) s[i] = 0.0;
     fq_v4i w[FQW_CASW_UNROLL];
-    const auto add = [&](const fq_v4i& v) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const unsigned word = (unsigned)v[i];
-            s[2 * i] += __hiloint2double((int)((word << 13) & 0x0FFFE000u), 0);
-            s[2 * i + 1] += __hiloint2double((int)((word >> 3) & 0x0FFFE000u), 0);
-        }
-    };
     if constexpr (LPR == 8) {
         // Whole lines per workgroup and a long row stride: all workgroups fetch a batch of bands at a time, which keeps them on
         // the same rows of W.  The ring below lets them drift apart, and memory then serves rows 22 to 57 KB apart at random:
@@ -161,7 +182,7 @@ __global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_scales_wide_kernel(co
                 }
             }
 #pragma unroll
-            for (int u = 0; u < FQW_CASW_UNROLL; ++u) add(w[u]);
+            for (int u = 0; u < FQW_CASW_UNROLL; ++u) fqw_cas_add(s, w[u]);
         }
     } else {
         fqw_bands bands(W, N, K, k0, ROWS);
@@ -175,14 +196,14 @@ __global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_scales_wide_kernel(co
         for (; n0 + ROWS * FQW_CASW_UNROLL / 2 < N; n0 += ROWS * FQW_CASW_UNROLL) {
 #pragma unroll
             for (int u = 0; u < FQW_CASW_UNROLL; ++u) {
-                add(w[u]);
+                fqw_cas_add(s, w[u]);
                 w[u] = bands.next(lane_off);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
 #pragma unroll
         for (int u = 0; u < FQW_CASW_UNROLL / 2; ++u)
-            if (n0 + ROWS * u < N) add(w[u]);
+            if (n0 + ROWS * u < N) fqw_cas_add(s, w[u]);
     }
     // the rows of a wave are added inside its four 16-lane rows by rotations (lanes LPR apart hold the same channels; DPP:
     // shuffles through LDS took 3 us), the rest through LDS, all in a fixed order
@@ -203,22 +224,73 @@ __global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_scales_wide_kernel(co
     if (mine) {
 #pragma unroll 16
         for (int r = 0; r < 64; ++r) t += part[r][lane];
-        t *= 0x1p+896;
     }
-    for (unsigned long long big = __ballot(mine && t >= 0x1p+128); big != 0; big &= big - 1) {
-        const int c = __ffsll(big) - 1;
-        bool inf = false, nan = false;
-        for (int n = lane; n < N; n += 64) {
-            const unsigned b = W[(size_t)n * K + k0 + c] & 0x7FFFu;
-            inf |= b == 0x7F80u;
-            nan |= b > 0x7F80u;
+    fqw_cas_close(t, mine, W, target, lambda, k0, lane, N, K);
+}
+
+// The same with scratch, for large matrices: a workgroup sums a share of the rows of a slab of up to 512 channels (`cw` 16-byte
+// columns, the slabs as even as they can be) and leaves its FP64 sums in part[share][K]; a second kernel adds the shares in their
+// order.  A wave reads up to 1 KiB of a row at once, where the kernels above, whose workgroups each need all rows of their
+// channels, read 32 to 128 bytes of a row, at a third of the memory's rate.  Read nontemporally: W comes from memory once, and what
+// it would push out of the last-level cache has to be written back if it was written lately (11008 x 4096 after a kernel
+// that wrote 320 MB: 38.5 us through the cache, 22.0 past it, 47.2 for the kernel above; all four calls of the quantiser
+// in a row 82 us either way).  Back to back from memory, both launches (above, here): 11008 x 4096 35.2 -> 19.7 us, 22016 x 4096
+// 72.0 -> 33.2.
+#define FQW_CASP_UNROLL 8
+__global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_partial_kernel(const uint16_t* __restrict__ W, double* __restrict__ part,
+                                                                          int N, int K, int slabs, int cw, int rows) {
+    __shared__ double red[8][FQW_CASW_THREADS];
+    const int slab = blockIdx.x % slabs, share = blockIdx.x / slabs;
+    const int r0 = share * rows, left = N - r0 < rows ? N - r0 : rows;
+    const int c0 = slab * cw, cols = K / 8 - c0 < cw ? K / 8 - c0 : cw;      // this slab's columns
+    const int par = FQW_CASW_THREADS / cw;                // rows side by side
+    const int r = threadIdx.x / cw, c = threadIdx.x % cw;
+    double s[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] = 0.0;
+    fqw_bands bands(W + (size_t)r0 * K, left, K, 8 * c0, par);
+    const unsigned lane_off = r < par && c < cols ? (unsigned)r * (unsigned)K * 2u + 16u * (unsigned)c : FQW_OOB;
+    fq_v4i w[FQW_CASP_UNROLL];
+#pragma unroll
+    for (int u = 0; u < FQW_CASP_UNROLL; ++u) w[u] = bands.next<2>(lane_off);
+    int n0 = 0;
+    for (; n0 + par * FQW_CASP_UNROLL <= left; n0 += par * FQW_CASP_UNROLL) {
+#pragma unroll
+        for (int u = 0; u < FQW_CASP_UNROLL; ++u) {
+            fqw_cas_add(s, w[u]);
+            w[u] = bands.next<2>(lane_off);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        const bool any_inf = __ballot(inf) != 0, any_nan = __ballot(nan) != 0;
-        if (lane == c) t = any_nan ? __builtin_nan("") : any_inf ? __builtin_inf() : t;
     }
-    if (mine)
-        lambda[k0 + lane] =
-            t == 0.0 ? 1.0f : (float)((double)target / (t / (double)N));            // an all-zero channel keeps 1
+#pragma unroll
+    for (int u = 0; u < FQW_CASP_UNROLL; ++u)             // the bands left that hold rows
+        if (n0 + par * u < left) fqw_cas_add(s, w[u]);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) red[i][threadIdx.x] = s[i];
+    __syncthreads();
+    for (int j = threadIdx.x; j < 8 * cols; j += FQW_CASW_THREADS) {
+        const int i = j & 7, col = j >> 3;
+        double t = 0.0;
+        for (int q = 0; q < par; ++q) t += red[i][q * cw + col];
+        part[(size_t)share * K + 8 * c0 + j] = t;
+    }
+}
+
+__global__ __launch_bounds__(256) void fq_cas_fold_kernel(const double* __restrict__ part, const uint16_t* __restrict__ W,
+                                                          float target, float* __restrict__ lambda, int N, int K, int shares) {
+    __shared__ double red[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, k0 = blockIdx.x * 64;
+    const bool mine = k0 + lane < K;
+    double t = 0.0;
+    if (mine) {
+#pragma unroll 8
+        for (int s = wave; s < shares; s += 4) t += part[(size_t)s * K + k0 + lane];
+    }
+    red[wave][lane] = t;
+    __syncthreads();
+    if (wave != 0) return;
+    t = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    fqw_cas_close(t, mine, W, target, lambda, k0, lane, N, K);
 }
 
 // ---- per-tensor scaling: statistics, then the choice of n --------------------------------------------
@@ -254,12 +326,15 @@ __device__ __forceinline__ int fqw_pts_resolve(unsigned vmin, unsigned vmax) {
 // and close with two atomics each, which queue up (11008 x 4096, all three launches: 24.8 us with 256 workgroups of
 // 1024 threads, 29.0 with 512 of 512, 43.9 with 1024 of 256; counting the workgroups in, so that the last one resolves n
 // and the third launch goes, cost 12 us more than that launch; 37 us with 512 workgroups that fetch four rows at a time).
+// PARTS, with scratch: a pair of statistics per workgroup and a kernel that folds them, without the launch that presets the
+// statistics and without atomics (without | with scratch: 1024 x 1024 13.0 | 8.6 us, 4096 x 4096 18.4 | 11.7, 11008 x 4096 24.2 | 20.6,
+// 22016 x 11008 77.6 | 76.3).
 // A small matrix (at most 32 such workgroups) takes workgroups of 256, which start and fold sooner; STREAM: a matrix
 // larger than the last-level cache is read nontemporally (fq_launch_pts_exponent has the figures).
 #define FQW_PTS_UNROLL 6
 #define FQW_PTS_THREADS 1024
 #define FQW_PTS_WGS 256
-template <int THREADS, bool STREAM>
+template <int THREADS, bool STREAM, bool PARTS>
 __global__ __launch_bounds__(THREADS) void fq_pts_stats_kernel(const uint16_t* __restrict__ W,
                                                            const float* __restrict__ lambda,
                                                            unsigned* __restrict__ stats,
@@ -322,6 +397,10 @@ __global__ __launch_bounds__(THREADS) void fq_pts_stats_kernel(const uint16_t* _
             m1 = red[w][1] > m1 ? red[w][1] : m1;
         }
         if (m0 != 0xFFFFFFFFu) m0 += 1u;
+        if (PARTS) {                                      // stats: a pair per workgroup, folded by the next kernel
+            *reinterpret_cast<uint2*>(stats + 2 * blockIdx.x) = make_uint2(m0, m1);
+            return;
+        }
         // only the atomics that would change a statistic (the plain reads may be stale: that costs at most an
         // atomic that changes nothing)
         const volatile unsigned* seen = stats;
@@ -332,6 +411,33 @@ __global__ __launch_bounds__(THREADS) void fq_pts_stats_kernel(const uint16_t* _
 
 __global__ void fq_pts_resolve_kernel(const unsigned* __restrict__ stats, int* __restrict__ n_out) {
     if (threadIdx.x == 0) n_out[0] = fqw_pts_resolve(stats[0], stats[1]);
+}
+
+// The workgroups' pairs, at most FQW_PTS_WGS of them, one per thread.
+__global__ __launch_bounds__(FQW_PTS_WGS) void fq_pts_fold_kernel(const unsigned* __restrict__ parts, int count, int* __restrict__ n_out) {
+    __shared__ unsigned red[FQW_PTS_WGS / 64][2];
+    uint2 v = make_uint2(0xFFFFFFFFu, 0u);
+    if ((int)threadIdx.x < count) v = *reinterpret_cast<const uint2*>(parts + 2 * threadIdx.x);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const unsigned lo = (unsigned)__shfl_xor((int)v.x, o, 64), hi = (unsigned)__shfl_xor((int)v.y, o, 64);
+        v.x = lo < v.x ? lo : v.x;
+        v.y = hi > v.y ? hi : v.y;
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6][0] = v.x;
+        red[threadIdx.x >> 6][1] = v.y;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned m0 = red[0][0], m1 = red[0][1];
+#pragma unroll
+        for (int w = 1; w < FQW_PTS_WGS / 64; ++w) {
+            m0 = red[w][0] < m0 ? red[w][0] : m0;
+            m1 = red[w][1] > m1 ? red[w][1] : m1;
+        }
+        n_out[0] = fqw_pts_resolve(m0, m1);
+    }
 }
 
 // ---- group-wise INT4 quantisation ------------------------------------------------------------------
@@ -417,7 +523,37 @@ namespace {
 // W is larger than the last-level cache (256 MiB): read once from end to end, nothing of it is left for the next pass.
 bool fqw_past_cache(int N, int K) { return (long long)N * K * 2 > (256ll << 20); }
 
+// How the rows and channels of W are shared out over one workgroup per compute unit.
+struct fqw_cas_split { int slabs, cw, rows, shares; };
+fqw_cas_split fqw_split_rows(int N, int K) {
+    fqw_cas_split p;
+    const int cols = K / 8;
+    p.slabs = (cols + 63) / 64;
+    p.cw = (cols + p.slabs - 1) / p.slabs;
+    const int most = fq_device_cus() > p.slabs ? fq_device_cus() / p.slabs : 1;
+    p.rows = (N + most - 1) / most;
+    p.shares = (N + p.rows - 1) / p.rows;
+    return p;
+}
+
 }  // namespace
+
+// Where the kernels without scratch read less than whole lines per workgroup (16 or 32 channels) of many rows; few rows or 64
+// channels are served as fast without a second launch.  From memory, without | with scratch, us: 5120 x 2048 15.1 | 9.5, 11008 x
+// 1024 29.1 | 10.8, 6144 x 4096 19.7 | 13.4, 7000 x 5120 30.1 | 18.2, 11008 x 4096 35.0 | 19.4, 22016 x 4096 68.1 | 32.6; on the
+// other side of the line 4000 x 4224 13.3 | 13.5, 2000 x 8192 10.3 | 11.5, 1024 x 4096 4.7 | 7.4, 4096 x 11008 20.5 | 21.4,
+// 22016 x 11008 90.8 | 89.6; 4096 x 4096 13.8 | 11.6, but 7.7 | 10.4 from the cache.
+size_t fq_cas_scales_scratch(int N, int K) {
+    if (K % 8 != 0 || 2 * ((K + 63) / 64) > fq_device_cus() || N < 5120 || (long long)N * K < (8ll << 20)) return 0;
+    return (size_t)fqw_split_rows(N, K).shares * (size_t)K * sizeof(double);
+}
+
+void fq_launch_cas_scales_split(const uint16_t* W, float target, float* lambda, int N, int K, void* scratch, hipStream_t stream) {
+    const fqw_cas_split p = fqw_split_rows(N, K);
+    double* part = static_cast<double*>(scratch);
+    hipLaunchKernelGGL(fq_cas_partial_kernel, dim3((unsigned)(p.slabs * p.shares)), dim3(FQW_CASW_THREADS), 0, stream, W, part, N, K, p.slabs, p.cw, p.rows);
+    hipLaunchKernelGGL(fq_cas_fold_kernel, dim3((unsigned)((K + 63) / 64)), dim3(256), 0, stream, part, W, target, lambda, N, K, p.shares);
+}
 
 void fq_launch_cas_scales(const uint16_t* W, float target, float* lambda, int N, int K, hipStream_t stream) {
     if ((K % 8) == 0 && (reinterpret_cast<uintptr_t>(W) % 16) == 0) {
@@ -440,8 +576,12 @@ void fq_launch_cas_scales(const uint16_t* W, float target, float* lambda, int N,
     hipLaunchKernelGGL(fq_cas_scales_kernel, dim3((unsigned)((K + CH - 1) / CH)), dim3(FQW_CAS_THREADS), 0, stream, W, target, lambda, N, K);
 }
 
-void fq_launch_pts_exponent(const uint16_t* W, const float* lambda, int* n_out, int N, int K, hipStream_t stream) {
-    unsigned* stats = reinterpret_cast<unsigned*>(n_out) + 8;     // the caller's 64 bytes: [0] = n, [8..9] statistics
+// (rows of more chunks than that many workgroups have threads take more workgroups: none for those)
+size_t fq_pts_exponent_scratch(int K) { return K / 8 <= FQW_PTS_WGS * FQW_PTS_THREADS ? 2 * sizeof(unsigned) * FQW_PTS_WGS : 0; }
+
+void fq_launch_pts_exponent(const uint16_t* W, const float* lambda, int* n_out, int N, int K, void* scratch, hipStream_t stream) {
+    unsigned* stats = scratch ? static_cast<unsigned*>(scratch)
+                              : reinterpret_cast<unsigned*>(n_out) + 8;     // the caller's 64 bytes: [0] = n, [8..9] statistics
     // at most FQW_PTS_WGS workgroups' worth of threads, as whole rows of K / 8 chunk columns, with the same number of rows each.
     // One workgroup more than that (the number of rows rounded up, as it used to be) has to share a compute unit: 11008 x
     // 11008, 257 workgroups, 62 us, with 256 41; 256 x 11008 19.0, 13.7.
@@ -451,16 +591,22 @@ void fq_launch_pts_exponent(const uint16_t* W, const float* lambda, int* n_out, 
     const int passes = (N + rows_par - 1) / rows_par;
     rows_par = (N + passes - 1) / passes;
     const size_t threads = (size_t)KC * (size_t)rows_par;
-    hipLaunchKernelGGL(fq_pts_init_kernel, dim3(1), dim3(64), 0, stream, stats);
+    if (!scratch) hipLaunchKernelGGL(fq_pts_init_kernel, dim3(1), dim3(64), 0, stream, stats);
+#define FQW_PTS_AS(THREADS_, STREAM_, PARTS_) \
+    hipLaunchKernelGGL((fq_pts_stats_kernel<THREADS_, STREAM_, PARTS_>), dim3((unsigned)((threads + THREADS_ - 1u) / THREADS_)), dim3(THREADS_), 0, \
+                       stream, W, lambda, stats, N, K, rows_par)
 #define FQW_PTS(THREADS_, STREAM_) \
-    hipLaunchKernelGGL((fq_pts_stats_kernel<THREADS_, STREAM_>), dim3((unsigned)((threads + THREADS_ - 1u) / THREADS_)), dim3(THREADS_), 0, stream, \
-                       W, lambda, stats, N, K, rows_par)
+    do { if (scratch) FQW_PTS_AS(THREADS_, STREAM_, true); else FQW_PTS_AS(THREADS_, STREAM_, false); } while (0)
     // (64 x 128 10.0 us with workgroups of 1024, 7.3 with 256; 64 x 4096, 32 of 1024: 10.8, 9.6; 64 x 8192: 11.4, 13)
-    if (threads <= 32u * FQW_PTS_THREADS) FQW_PTS(256, false);
+    const bool narrow = threads <= 32u * FQW_PTS_THREADS;
+    if (narrow) FQW_PTS(256, false);
     else if (fqw_past_cache(N, K)) FQW_PTS(FQW_PTS_THREADS, true);
     else FQW_PTS(FQW_PTS_THREADS, false);
 #undef FQW_PTS
-    hipLaunchKernelGGL(fq_pts_resolve_kernel, dim3(1), dim3(64), 0, stream, stats, n_out);
+#undef FQW_PTS_AS
+    const size_t wg = narrow ? 256u : FQW_PTS_THREADS;
+    if (scratch) hipLaunchKernelGGL(fq_pts_fold_kernel, dim3(1), dim3(FQW_PTS_WGS), 0, stream, stats, (int)((threads + wg - 1u) / wg), n_out);
+    else hipLaunchKernelGGL(fq_pts_resolve_kernel, dim3(1), dim3(64), 0, stream, stats, n_out);
 }
 
 void fq_launch_quantize_weights(const uint16_t* W, const float* lambda, int n_pts, bool sigma_rne, int8_t* q,

@@ -122,6 +122,16 @@ def test_bad_arguments_are_rejected_without_a_launch():
     assert L.fq_cas_scales(p, f1, p, 0, 128, null) == -2
     assert L.fq_cas_scales(p, ctypes.c_float(0.0), p, 4, 128, null) == -2
     assert L.fq_cas_scales(null, f1, p, 4, 128, null) == -1
+    # the forms with scratch: the same refusals, scratch too small or misaligned; no scratch where a call has no use for it
+    need = L.fq_cas_scales_workspace_bytes(11008, 4096)
+    assert need == 32 * 4096 * 8 and L.fq_cas_scales_workspace_bytes(1024, 1024) == L.fq_cas_scales_workspace_bytes(11008, 11008) == 0
+    assert L.fq_cas_scales_ws(null, f1, p, 11008, 4096, p, need, null) == -1
+    assert L.fq_cas_scales_ws(p, f1, p, 11008, 4096, p, need - 1, null) == -5
+    assert L.fq_cas_scales_ws(p, f1, p, 11008, 4096, odd, need, null) == -3
+    assert L.fq_pts_exponent_workspace_bytes(4, 128) == 2048 and L.fq_pts_exponent_workspace_bytes(1, (1 << 21) + 128) == 0
+    assert L.fq_pts_exponent_ws(p, null, p, 4, 100, p, 2048, null) == -2
+    assert L.fq_pts_exponent_ws(p, null, p, 4, 128, p, 2047, null) == -5
+    assert L.fq_pts_exponent_ws(p, null, p, 4, 128, odd, 2048, null) == -3
     assert L.fq_pts_exponent(p, null, p, 4, 100, null) == -2
     assert L.fq_pts_exponent(p, null, null, 4, 128, null) == -1
     assert L.fq_pts_exponent(p, null, odd, 4, 128, null) == -3

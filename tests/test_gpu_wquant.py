@@ -229,3 +229,39 @@ def test_cas_scales_of_rows_beyond_32_bit_band_offsets(fq, N, K):
     lam = fq.fq_cas_scales(W, 0.25)
     torch.cuda.synchronize()
     assert bool((lam[:-1] == 0.5).all()) and float(lam[-1]) == 0.125
+
+
+# (rows shared out over the chip: an even slab of channels, uneven ones, a last share with fewer rows, more rows than one share's
+# ring of bands; K = 1640: 205 columns in slabs of 52)
+@pytest.mark.parametrize("N,K", [(5120, 1640), (5121, 4096), (9001, 1032), (16400, 512), (5200, 8192), (40000, 216)])
+def test_cas_scales_with_scratch(fq, N, K):
+    """The means of every channel, non-finite channels among them, against FP64 and against the call without scratch, which sums
+    the same FP64 values in another order: one FP32 step apart at most."""
+    assert fq.lib().fq_cas_scales_workspace_bytes(N, K) > 0
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).to(torch.bfloat16)
+    W[:, 2] = 0
+    W[:, 3] = 3.3895313892515355e38                            # the largest bf16: sums beyond 2^128
+    W[N - 1, K - 1] = float("nan")
+    W[0, 8] = float("inf")
+    lam = fq.fq_cas_scales(W, 0.02)
+    plain = torch.empty_like(lam)
+    assert fq.lib().fq_cas_scales(W.data_ptr(), 0.02, plain.data_ptr(), N, K, torch.cuda.current_stream().cuda_stream) == 0
+    assert bool(torch.isnan(lam[K - 1])) and float(lam[8]) == 0.0 and float(lam[2]) == 1.0
+    mean = W.double().abs().mean(dim=0)
+    want = torch.where(mean == 0, torch.ones_like(mean), 0.02 / mean).float()
+    ok = torch.ones(K, dtype=torch.bool, device="cuda")
+    ok[[8, K - 1]] = False
+    for got in (plain, want):
+        assert int((lam.view(torch.int32) - got.view(torch.int32))[ok].abs().max()) <= 1
+
+
+@pytest.mark.parametrize("N,K", [(3, 128), (64, 4096), (65, 4096), (2060, 4096), (400, 11008)])
+def test_pts_exponent_without_scratch(fq, N, K):
+    """The statistics met in the caller's 64 bytes: the same exponent, wherever the element that decides is."""
+    for pos in [(0, 0), (N - 1, K - 1), (N // 2, K // 2)]:
+        for rest, one, n in ((0x3F80, 0x3980, 6), (0x3580, 0x43DF, 0)):
+            Wb = np.full((N, K), rest, np.uint16); Wb[pos] = one
+            W, out = to_gpu_bf16(Wb), torch.empty((16,), dtype=torch.int32, device="cuda")
+            assert fq.lib().fq_pts_exponent(W.data_ptr(), 0, out.data_ptr(), N, K, torch.cuda.current_stream().cuda_stream) == 0
+            assert int(out[0]) == n == int(fq.fq_pts_exponent(W)[0])
