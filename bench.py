@@ -226,9 +226,8 @@ def main() -> int:
 
     def ffn_chain(wl="ffn_l2_7b_gateup_swiglu"):
         """The gate/up layer with its fused epilogue followed by the quantisation of its output for the down
-        projection: the separate quantiser (fq_w4a8_gemm_swiglu_ws + fq_quantize_act_ws, which searches each row for
-        its largest magnitude) against fq_w4a8_gemm_swiglu_quant_ws (row maxima raised by the GEMM's epilogue, then an
-        element-wise kernel); both leave the same codes, scales and prepared workspace."""
+        projection: in two calls (fq_w4a8_gemm_swiglu_ws + fq_quantize_act_ws) and in one
+        (fq_w4a8_gemm_swiglu_quant_ws); both leave the same codes, scales and prepared workspace."""
         w, d, X, packed, gs = upload(wl)
         NH = w.N // 2
         need = fq.fq_w4a8_gemm_workspace_bytes(w.M, w.N, w.K)

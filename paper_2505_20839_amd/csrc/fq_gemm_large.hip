@@ -161,7 +161,7 @@ __device__ __forceinline__ void fql_item(
     const uint8_t* __restrict__ A, const float* __restrict__ a_scale, const uint8_t* __restrict__ wp,
     const uint8_t* __restrict__ gs, float tscale, uint16_t* Y, int M, int N, int K,
     int tiles_m, int tiles_n, int slots, int pm, const uint16_t* __restrict__ planes, const int swiglu,
-    const uint16_t* R, unsigned* rowmax = nullptr) {
+    const uint16_t* R) {
     constexpr int NT = NMT;                               // A transfers per wave and stage
     const int G = K / FQ_GROUP;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -476,8 +476,7 @@ __device__ __forceinline__ void fql_item(
             __syncthreads();
             // wave w stores rows 8*NMT*w ..., eight rows of 128 bytes per instruction
             // (rows past M lie behind the descriptor's range, channels past N get an offset out of range: such
-            // lanes store nothing.  Element-wise stores here, with an atomic per element for the row maxima, took
-            // 4.2 ms of a 1000 x 22016 x 4096 layer's 4.3; masked it is 96 us.)
+            // lanes store nothing.)
             const __amdgpu_buffer_rsrc_t rsH = __builtin_amdgcn_make_buffer_rsrc(
                 Y + (size_t)m0 * NH + (n0 >> 1), 0, (int)(((unsigned)mrows * (unsigned)NH - (unsigned)(n0 >> 1)) * 2u), 0x00020000);
             const bool col_ok = (n0 >> 1) + (lane & 7) * 8 < NH;
@@ -487,30 +486,10 @@ __device__ __forceinline__ void fql_item(
             for (int j = 0; j < NMT; ++j) {
                 const fq_v4i v = *reinterpret_cast<const fq_v4i*>(rd + 8 * j * HS);
                 __builtin_amdgcn_raw_buffer_store_b128(v, rsH, col_ok ? hlane + (unsigned)(8 * j) * (unsigned)NH * 2u : FQL_OOB, 0, 0);
-                if (rowmax) {
-                    // largest |H| of this row's 64 columns of the tile: bf16 magnitudes order like 16-bit integers;
-                    // the 8 lanes of a row fold theirs and one of them raises the row's maximum (the bits of the
-                    // number as FP32), which the quantiser of the next layer takes its scale from
-                    typedef unsigned short v2us __attribute__((ext_vector_type(2)));
-                    v2us mx = __builtin_bit_cast(v2us, (unsigned)v[0] & 0x7FFF7FFFu);
-#pragma unroll
-                    for (int e = 1; e < 4; ++e)
-                        mx = __builtin_elementwise_max(mx, __builtin_bit_cast(v2us, (unsigned)v[e] & 0x7FFF7FFFu));
-                    unsigned m16 = mx[0] > mx[1] ? mx[0] : mx[1];
-                    m16 = col_ok ? m16 : 0u;
-#pragma unroll
-                    for (int o = 1; o < 8; o <<= 1) {
-                        const unsigned other = (unsigned)__shfl_xor((int)m16, o, 64);
-                        m16 = other > m16 ? other : m16;
-                    }
-                    const int row = wave * (8 * NMT) + (lane >> 3) + 8 * j;
-                    if ((lane & 7) == 0 && row < mrows) atomicMax(&rowmax[m0 + row], m16 << 16);
-                }
             }
             return;
         }
-        // rows of H not in 16-byte steps: element-wise (both lanes of a pair are inside or both outside, N being
-        // even; never with rowmax, whose callers need N / 2 a multiple of 8)
+        // rows of H not in 16-byte steps: element-wise (both lanes of a pair are inside or both outside, N being even)
         if (!wave_on || !n_ok) return;
 #pragma unroll
         for (int mt = 0; mt < NMT; ++mt) {
@@ -634,14 +613,13 @@ void fq_gemm_large_kernel(
     const uint8_t* __restrict__ A, const float* __restrict__ a_scale, const uint8_t* __restrict__ wp,
     const uint8_t* __restrict__ gs, float tscale, uint16_t* Y, int M, int N, int K,
     int tiles_m, int tiles_n, int slots, int pm, const uint16_t* __restrict__ planes, unsigned full_wgs,
-    int swiglu, const uint16_t* R, unsigned* rowmax) {
+    int swiglu, const uint16_t* R) {
     extern __shared__ fq_v4i lds[];                       // 2 A stages (64 KiB) + 4 x 4 KiB of packed weights
     if (blockIdx.x < full_wgs)
-        fql_item<8>(lds, blockIdx.x, A, a_scale, wp, gs, tscale, Y, M, N, K, tiles_m, tiles_n, slots, pm, planes, swiglu, R,
-                    rowmax);
+        fql_item<8>(lds, blockIdx.x, A, a_scale, wp, gs, tscale, Y, M, N, K, tiles_m, tiles_n, slots, pm, planes, swiglu, R);
     else
         fql_item<TAIL_NMT>(lds, blockIdx.x - full_wgs, A, a_scale, wp, gs, tscale, Y, M, N, K, tiles_m, tiles_n, slots, pm,
-                           planes, swiglu, R, rowmax);
+                           planes, swiglu, R);
 }
 
 // The table mode of the same items (no zero-point planes; halves only).
@@ -691,7 +669,7 @@ void fq_launch_zero_point(const uint8_t* A, void* workspace, int M, int K, hipSt
 
 void fq_launch_gemm_large(const uint8_t* A, const float* a_scale, const uint8_t* wp, const uint8_t* gs,
                           float tscale, uint16_t* Y, int M, int N, int K, void* workspace, bool prepared,
-                          bool swiglu, const uint16_t* R, hipStream_t stream, bool lut, unsigned* rowmax) {
+                          bool swiglu, const uint16_t* R, hipStream_t stream, bool lut) {
     static fq_device_once attr_once;
     fq_once_per_device(attr_once, [] {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_gemm_large_kernel<4>),
@@ -724,5 +702,5 @@ void fq_launch_gemm_large(const uint8_t* A, const float* a_scale, const uint8_t*
     }
     hipLaunchKernelGGL(parts == 4 ? fq_gemm_large_kernel<2> : fq_gemm_large_kernel<4>, dim3(full_wgs + tail_wgs), dim3(FQL_THREADS), FQL_LDS_BYTES, stream,
                        A, a_scale, wp, gs, tscale, Y, M, N, K, tiles_m, tiles_n, slots, pm, planes, full_wgs,
-                       swiglu ? 1 : 0, R, swiglu ? rowmax : nullptr);
+                       swiglu ? 1 : 0, R);
 }

@@ -30,9 +30,7 @@ __device__ __forceinline__ float fq_sum8(fq_v2i o) {
 // kernels take from their workspace: -2^-6 * (sum of the group's E4M3 values) as two fp16 terms,
 // laid out as that kernel reads it ([plane][group / 8][M rows][group % 8]; groups up to the next
 // multiple of 16 are zero).  Needs K % 128 == 0 and the row in registers.
-// KNOWN: the row's largest magnitude is not searched for but taken from a_scale[m], where the kernel that
-// produced X left it (the fused gate/up epilogue); the scale replaces it there.
-template <int WPR, int CH, bool ZP, bool KNOWN, bool REREAD>
+template <int WPR, int CH, bool ZP, bool REREAD>
 __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(const uint16_t* __restrict__ X,
                                                                    uint8_t* __restrict__ A,
                                                                    float* __restrict__ a_scale, int K,
@@ -72,27 +70,19 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(c
             keep[i] = (fq_v4i){0, 0, 0, 0};
             if (CH <= 2 || i * T < nchunk) keep[i] = x[c];
         }
-        if (!KNOWN) {
 #pragma unroll
-            for (int i = 0; i < CH; ++i) search(keep[i]);
-        }
-    } else if (!KNOWN) {
+        for (int i = 0; i < CH; ++i) search(keep[i]);
+    } else {
         for (int c = t; c < nchunk; c += T) search(x[c]);
     }
-    if (KNOWN) {                                          // (read by one thread before anyone overwrites it below)
-        if (t == 0) red[row * WPR] = a_scale[on ? m : M - 1];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+    if (WPR > 1) {
+        if ((t & 63) == 0) red[row * WPR + (t >> 6)] = amax;
         __syncthreads();
         amax = red[row * WPR];
-    } else {
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
-        if (WPR > 1) {
-            if ((t & 63) == 0) red[row * WPR + (t >> 6)] = amax;
-            __syncthreads();
-            amax = red[row * WPR];
-#pragma unroll
-            for (int i = 1; i < WPR; ++i) amax = fmaxf(amax, red[row * WPR + i]);
-        }
+        for (int i = 1; i < WPR; ++i) amax = fmaxf(amax, red[row * WPR + i]);
     }
     const float s = (amax == 0.f) ? 1.0f : amax / 448.0f;
     if (t == 0 && on) a_scale[m] = s;
@@ -163,10 +153,10 @@ namespace {
 //     512 x 16384   6.2 / 8.1 | <16, 2> 5.7 / 6.9; <8, 4> 5.5 / 6.9.   4096 x 16384  34.7 / 40.5 | <8, 4> 32.0 / 34.7; <16, 2> 31.0 / 35.5
 //     1024 x 16512  12.6 | <16, 4> 11.7; <16, 8> 17.5.                 2048 x 32768 49.2 | <16, 4> 32.6; <16, 8> 40.6
 //     512 x 40960   19.9 | <16, 8> 15.9 (rows read twice by 16 waves: 14.6).  Longer rows do not fit and are read twice.
-template <bool ZP, bool KNOWN>
+template <bool ZP>
 void fq_launch_quantize_as(const uint16_t* X, uint8_t* A, float* a_scale, int M, int K, uint16_t* planes, hipStream_t stream) {
 #define FQ_QUANTIZE(WPR_, CH_, REREAD_) \
-    hipLaunchKernelGGL((fq_quantize_kernel<WPR_, CH_, ZP, KNOWN, REREAD_>), dim3((unsigned)((M + (WPR_ > 4 ? 1 : 4 / WPR_) - 1) / (WPR_ > 4 ? 1 : 4 / WPR_))), \
+    hipLaunchKernelGGL((fq_quantize_kernel<WPR_, CH_, ZP, REREAD_>), dim3((unsigned)((M + (WPR_ > 4 ? 1 : 4 / WPR_) - 1) / (WPR_ > 4 ? 1 : 4 / WPR_))), \
                        dim3(WPR_ > 4 ? 64 * WPR_ : 256), 0, stream, X, A, a_scale, K, planes, M)
     if (K > 4 * 4096) {
         if constexpr (!ZP) {                              // (no zero-point terms for rows this long)
@@ -186,27 +176,12 @@ void fq_launch_quantize_as(const uint16_t* X, uint8_t* A, float* a_scale, int M,
 }  // namespace
 
 void fq_launch_quantize(const uint16_t* X, uint8_t* A, float* a_scale, int M, int K, hipStream_t stream) {
-    fq_launch_quantize_as<false, false>(X, A, a_scale, M, K, nullptr, stream);
+    fq_launch_quantize_as<false>(X, A, a_scale, M, K, nullptr, stream);
 }
 
 bool fq_quantize_can_write_zero_point(int K) { return (K % FQ_GROUP) == 0 && K <= 16384; }
 
-void fq_launch_quantize_known(const uint16_t* X, uint8_t* A, float* a_scale, int M, int K, void* workspace,
-                              hipStream_t stream) {
-    if (workspace) fq_launch_quantize_as<true, true>(X, A, a_scale, M, K, static_cast<uint16_t*>(workspace), stream);
-    else           fq_launch_quantize_as<false, true>(X, A, a_scale, M, K, nullptr, stream);
-}
-
-__global__ void fq_fill_zero_kernel(unsigned* __restrict__ p, int n) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = 0u;
-}
-
-void fq_launch_fill_zero(unsigned* p, int n, hipStream_t stream) {
-    hipLaunchKernelGGL(fq_fill_zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, p, n);
-}
-
 void fq_launch_quantize_zp(const uint16_t* X, uint8_t* A, float* a_scale, int M, int K, void* workspace,
                            hipStream_t stream) {
-    fq_launch_quantize_as<true, false>(X, A, a_scale, M, K, static_cast<uint16_t*>(workspace), stream);
+    fq_launch_quantize_as<true>(X, A, a_scale, M, K, static_cast<uint16_t*>(workspace), stream);
 }

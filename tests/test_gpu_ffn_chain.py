@@ -60,7 +60,7 @@ def test_codes_and_scales_are_those_of_the_quantiser_on_the_same_h(fq, shape):
     check_gemm(Hb, Ho, B, "gate/up + quantised output %s" % (shape,))
 
 
-# one shape per form of the quantiser that takes the row maxima from the GEMM (the output's rows are N/2 long), and one more
+# one shape per form of the quantiser (the output's rows are N/2 long), and one more
 # at the form's edge; the last three are too long for zero-point terms
 KNOWN_ROWS = [(1601, 528), (2050, 4096), (300, 4096), (1536, 512), (600, 8448), (2050, 12288), (300, 8448), (130, 16384),
               (200, 16640), (260, 16640), (258, 20480), (130, 20736), (514, 20736), (513, 32768), (300, 33024), (65, 65792), (66, 131584)]
@@ -90,8 +90,7 @@ def test_every_form_of_the_quantiser_of_known_rows(fq, M, N):
 
 
 def test_two_calls_in_a_row_leave_nothing_behind(fq):
-    """The row maxima live in the scale array between the two kernels of a call: a second call with other operands
-    (smaller magnitudes) into the same arrays must not see the first call's maxima."""
+    """A second call with other operands (smaller magnitudes) into the same arrays must not see anything of the first."""
     M, N, K = 512, 1024, 512
     L = fq.lib()
     import ctypes
