@@ -476,7 +476,7 @@ __device__ __forceinline__ void fql_item(
             __syncthreads();
             // wave w stores rows 8*NMT*w ..., eight rows of 128 bytes per instruction
             // (rows past M lie behind the descriptor's range, channels past N get an offset out of range: such
-            // lanes store nothing.)
+            // lanes store nothing; nontemporal as below)
             const __amdgpu_buffer_rsrc_t rsH = __builtin_amdgcn_make_buffer_rsrc(
                 Y + (size_t)m0 * NH + (n0 >> 1), 0, (int)(((unsigned)mrows * (unsigned)NH - (unsigned)(n0 >> 1)) * 2u), 0x00020000);
             const bool col_ok = (n0 >> 1) + (lane & 7) * 8 < NH;
@@ -485,7 +485,7 @@ __device__ __forceinline__ void fql_item(
 #pragma unroll
             for (int j = 0; j < NMT; ++j) {
                 const fq_v4i v = *reinterpret_cast<const fq_v4i*>(rd + 8 * j * HS);
-                __builtin_amdgcn_raw_buffer_store_b128(v, rsH, col_ok ? hlane + (unsigned)(8 * j) * (unsigned)NH * 2u : FQL_OOB, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(v, rsH, col_ok ? hlane + (unsigned)(8 * j) * (unsigned)NH * 2u : FQL_OOB, 0, 2);
             }
             return;
         }
@@ -573,6 +573,10 @@ __device__ __forceinline__ void fql_item(
         // N get an offset out of range, such lanes store nothing (M = 500, N = 14336, quantiser and GEMM: 40.8 us with
         // element-wise stores in the edge tiles, 37.4 us; a second, unmasked copy of these stores for inner tiles,
         // row steps in the scalar offset, was no faster at 2048 or 8192 rows and 39.3 us here).
+        // Nontemporal: the output leaves the operands of the tiles behind it in the cache (through the cache -> past it, both with
+        // the quantiser, us: 500 x 14336 x 4096 39.4 -> 37.5, 1000 x 6144 x 4096 38.2 -> 37.0, 8192 x 14336 x 4096 425 -> 419, 2000 x 4096 x
+        // 11008 101.8 -> 100.0; followed by a quantiser and an addition that read the output, 2000 x 4096 x 11008 118.5 ->
+        // 117.6, 4000 x 8192 x 4096 187.2 -> 185.8).
         const __amdgpu_buffer_rsrc_t rsY = __builtin_amdgcn_make_buffer_rsrc(
             Y + (size_t)m0 * N + n0, 0, (int)(((unsigned)mrows * (unsigned)N - (unsigned)n0) * 2u), 0x00020000);
         const unsigned ylane = (unsigned)(wave * (8 * NMT) + (lane >> 4)) * (unsigned)N * 2u + (unsigned)(lane & 15) * 16u;
@@ -583,7 +587,7 @@ __device__ __forceinline__ void fql_item(
 #pragma unroll
         for (int j = 0; j < 2 * NMT; ++j) {
             const fq_v4i v = *reinterpret_cast<const fq_v4i*>(rd + 4 * j * 256);
-            __builtin_amdgcn_raw_buffer_store_b128(v, rsY, col_ok ? ylane + (unsigned)(4 * j) * (unsigned)N * 2u : FQL_OOB, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(v, rsY, col_ok ? ylane + (unsigned)(4 * j) * (unsigned)N * 2u : FQL_OOB, 0, 2);
         }
         return;
     }
