@@ -30,18 +30,21 @@ __device__ __forceinline__ float fq_sum8(fq_v2i o) {
 // kernels take from their workspace: -2^-6 * (sum of the group's E4M3 values) as two fp16 terms,
 // laid out as that kernel reads it ([plane][group / 8][M rows][group % 8]; groups up to the next
 // multiple of 16 are zero).  Needs K % 128 == 0 and the row in registers.
-template <int WPR, int CH, bool ZP, bool REREAD>
+// PARTS: that many workgroups per row; each searches the whole row and converts and stores every PARTS-th of the chunks
+// its threads hold.  For a few rows, which leave the chip idle: the search is a small part of a row's work.
+template <int WPR, int CH, bool ZP, bool REREAD, int PARTS>
 __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(const uint16_t* __restrict__ X,
                                                                    uint8_t* __restrict__ A,
                                                                    float* __restrict__ a_scale, int K,
                                                                    uint16_t* __restrict__ planes, int M) {
     static_assert(!(ZP && REREAD), "the zero-point terms are summed from registers");
+    static_assert(PARTS == 1 || (WPR >= 4 && !ZP && !REREAD), "one row per workgroup, codes only");
     constexpr int WAVES = WPR > 4 ? WPR : 4, ROWS = WAVES / WPR, T = 64 * WPR;
     constexpr int MAXG = T * CH / 16 + 16;           // groups of a row, padded
     __shared__ float red[WAVES];
     __shared__ __attribute__((aligned(16))) uint16_t zrow[ZP ? ROWS : 1][2][ZP ? MAXG : 8];   // [row][plane][group]
     const int row = (int)threadIdx.x / T, t = (int)threadIdx.x % T;
-    const int m = blockIdx.x * ROWS + row;
+    const int m = PARTS > 1 ? (int)blockIdx.x / PARTS : (int)blockIdx.x * ROWS + row, mine = (int)blockIdx.x % PARTS;
     if (ZP && M <= FQ_KSPLIT_MAX_M) {                     // the arrival counters behind the planes start at zero
         const int G = K >> 7, C2 = 2 * ((G + 15) >> 4);
         unsigned* counters = reinterpret_cast<unsigned*>(planes + (size_t)2 * C2 * M * 8);
@@ -85,7 +88,7 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(c
         for (int i = 1; i < WPR; ++i) amax = fmaxf(amax, red[row * WPR + i]);
     }
     const float s = (amax == 0.f) ? 1.0f : amax / 448.0f;
-    if (t == 0 && on) a_scale[m] = s;
+    if (t == 0 && on && mine == 0) a_scale[m] = s;
     const float rcp = 1.0f / s;
     // One choice of quotient per row (s is the same in every thread of a wave): the range the
     // short quotient was checked on, else the full division; straight-line code either way.
@@ -98,6 +101,7 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(c
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const int c = t + i * T;
+            if (PARTS > 1 && i % PARTS != mine) continue;
             if (CH > 2 && i * T >= nchunk) break;         // (the same for the whole wave)
             if (c < nchunk) {
                 const fq_v2i o = fq_quant8<FAST>(keep[i], s, rcp);
@@ -155,9 +159,26 @@ namespace {
 //     512 x 40960   19.9 | <16, 8> 15.9 (rows read twice by 16 waves: 14.6).  Longer rows do not fit and are read twice.
 template <bool ZP>
 void fq_launch_quantize_as(const uint16_t* X, uint8_t* A, float* a_scale, int M, int K, uint16_t* planes, hipStream_t stream) {
-#define FQ_QUANTIZE(WPR_, CH_, REREAD_) \
-    hipLaunchKernelGGL((fq_quantize_kernel<WPR_, CH_, ZP, REREAD_>), dim3((unsigned)((M + (WPR_ > 4 ? 1 : 4 / WPR_) - 1) / (WPR_ > 4 ? 1 : 4 / WPR_))), \
+#define FQ_QUANTIZE_IN(WPR_, CH_, REREAD_, PARTS_) \
+    hipLaunchKernelGGL((fq_quantize_kernel<WPR_, CH_, ZP, REREAD_, PARTS_>), \
+                       dim3((unsigned)((M + (WPR_ > 4 ? 1 : 4 / WPR_) - 1) / (WPR_ > 4 ? 1 : 4 / WPR_) * PARTS_)), \
                        dim3(WPR_ > 4 ? 64 * WPR_ : 256), 0, stream, X, A, a_scale, K, planes, M)
+#define FQ_QUANTIZE(WPR_, CH_, REREAD_) FQ_QUANTIZE_IN(WPR_, CH_, REREAD_, 1)
+    if constexpr (!ZP) {
+        // few rows: two workgroups each (one / two per row, us: 16 x 4096 2.51 / 2.35, 64 x 4096 2.58 / 2.41, 64 x 8192 2.82 / 2.72, 16 x
+        // 14336 3.23 / 2.95, 64 x 14336 3.35 / 3.20, 128 x 16384 3.58 / 4.33; 32 x 32016 4.78 / 4.35, 64 x 32016 5.01 / 5.21; a
+        // row whose second half of chunks is empty gains nothing: 1 x 2048 the same)
+        if (M <= 64 && K > 2048 && K <= 4 * 4096) {
+            if (K <= 4096) FQ_QUANTIZE_IN(4, 2, false, 2);
+            else if (K <= 2 * 4096) FQ_QUANTIZE_IN(8, 2, false, 2);
+            else FQ_QUANTIZE_IN(16, 2, false, 2);
+            return;
+        }
+        if (M <= 32 && K > 4 * 4096 && K <= 8 * 4096) {
+            FQ_QUANTIZE_IN(16, 4, false, 2);
+            return;
+        }
+    }
     if (K > 4 * 4096) {
         if constexpr (!ZP) {                              // (no zero-point terms for rows this long)
             if (K > 16 * 4096) FQ_QUANTIZE(16, 8, true);
@@ -171,6 +192,7 @@ void fq_launch_quantize_as(const uint16_t* X, uint8_t* A, float* a_scale, int M,
     else if (K > 2048 || M <= 1536) FQ_QUANTIZE(4, 2, false);
     else FQ_QUANTIZE(1, 4, false);
 #undef FQ_QUANTIZE
+#undef FQ_QUANTIZE_IN
 }
 
 }  // namespace

@@ -124,6 +124,19 @@ def test_quantize_matches_oracle(fq, M, K, act, frac, seed):
     _check_quantize(fq, X)
 
 
+# (two workgroups per row of 2049 to 16384 elements up to 64 rows, of up to 32768 up to 32: both sides of each line, and rows that
+# end in the first or the last chunk of a thread)
+@pytest.mark.parametrize("M", [1, 32, 33, 64, 65])
+@pytest.mark.parametrize("K", [2048, 2056, 3000, 4096, 4104, 8192, 8200, 16384, 16392, 24584, 32768, 32776])
+def test_quantize_few_rows(fq, M, K):
+    g = np.random.default_rng(M * K)
+    X = g.standard_normal((M, K)).astype(np.float32)
+    X[M - 1, K - 1] = 50.0                                     # the largest magnitude in the last place of a row,
+    X[0, 0] = -70.0                                            # in the first,
+    X[M // 2] = 0.0                                            # and a row of zeros
+    _check_quantize(fq, workloads.f32_to_bf16_bits(X))
+
+
 def test_quantize_all_finite_bf16_values_and_zero_row(fq):
     allbits = np.arange(65536, dtype=np.uint32).astype(np.uint16)
     vals = oracle.bf16_bits_to_f64(allbits)
