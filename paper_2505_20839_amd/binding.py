@@ -4,7 +4,7 @@ Every step of the path runs in the HIP kernels of ``libfireq.so``; torch is used
 memory and the current stream.  There is no CPU fallback: if the library cannot be loaded or a
 tensor is not on the GPU, the call raises.
 
-The calls of a running model marshal their arguments in native code (``_fq_marshal-*.so``, see its source); whatever that
+The calls of a running model, and those that prepare its weights and caches, marshal their arguments in native code (``_fq_marshal-*.so``, see its source); whatever that
 does not take -- another kind of tensor, a wrong shape, an argument to be refused -- comes back as None and goes through
 the Python form below it, which decides and raises.  Without that extension every call takes its Python form.
 """
@@ -29,7 +29,9 @@ _marshal = None
 # the C functions the marshalling calls, in the order it expects them
 _MARSHALLED = ("fq_quantize_act", "fq_quantize_act_ws", "fq_packed_weight_bytes", "fq_w4a8_gemm_workspace_bytes", "fq_w4a8_gemm_ws",
                "fq_w4a8_gemm_swiglu_ws", "fq_w4a8_gemm_add_ws", "fq_w4a8_gemm_swiglu_quant_ws", "fq_w4a8_linear_workspace_bytes",
-               "fq_w4a8_linear_ws", "fq_kv4_packed_bytes", "fq_kv4_scores", "fq_kv4_output_workspace_bytes", "fq_kv4_output_ws")
+               "fq_w4a8_linear_ws", "fq_kv4_packed_bytes", "fq_kv4_scores", "fq_kv4_output_workspace_bytes", "fq_kv4_output_ws",
+               "fq_kv4_pack", "fq_pack_weights", "fq_cas_scales_workspace_bytes", "fq_cas_scales_ws", "fq_pts_exponent_workspace_bytes",
+               "fq_pts_exponent_ws", "fq_quantize_weights")
 
 
 class FireqError(RuntimeError):
@@ -185,6 +187,11 @@ def _stream() -> ctypes.c_void_p:
 
 def fq_cas_scales(W: torch.Tensor, target: float) -> torch.Tensor:
     """float32 [K]: lambda[k] = target / absmean_n(W[n,k]) of a bf16 weight matrix [N,K]."""
+    r = (_marshal or marshal()).cas_scales(W, target)
+    if r is not None:
+        if type(r) is int:
+            raise FireqError(r, "fq_cas_scales")
+        return r
     W = _dev(W, torch.bfloat16, "W")
     N, K = W.shape
     lam = torch.empty((K,), dtype=torch.float32, device=W.device)
@@ -209,6 +216,11 @@ def _lambda_ptr(lam, K):
 def fq_pts_exponent(W: torch.Tensor, lam: Optional[torch.Tensor] = None) -> torch.Tensor:
     """int32 device tensor of 16 ints whose first element is the per-tensor exponent n (delta = 2^n) of the
     bf16 matrix W [N,K] scaled by lam [K]; reading it (``int(t[0])``) synchronises, the call does not."""
+    r = (_marshal or marshal()).pts_exponent(W, lam)
+    if r is not None:
+        if type(r) is int:
+            raise FireqError(r, "fq_pts_exponent")
+        return r
     W = _dev(W, torch.bfloat16, "W")
     N, K = W.shape
     out = torch.empty((16,), dtype=torch.int32, device=W.device)
@@ -223,6 +235,11 @@ def fq_pts_exponent(W: torch.Tensor, lam: Optional[torch.Tensor] = None) -> torc
 def fq_quantize_weights(W: torch.Tensor, lam: Optional[torch.Tensor] = None, n_pts: int = 0,
                         sigma_nearest: bool = False):
     """(int8 [N,K] INT4 codes, uint8 [N,K/128] E4M3 group scales) of W * lam * 2^n_pts."""
+    r = (_marshal or marshal()).quantize_weights(W, lam, n_pts, sigma_nearest)
+    if r is not None:
+        if type(r) is int:
+            raise FireqError(r, "fq_quantize_weights")
+        return r
     W = _dev(W, torch.bfloat16, "W")
     N, K = W.shape
     if K % GROUP:
@@ -238,6 +255,11 @@ def fq_quantize_weights(W: torch.Tensor, lam: Optional[torch.Tensor] = None, n_p
 
 def fq_pack_weights(q: torch.Tensor) -> torch.Tensor:
     """int8 [N,K] codes in -8..7 -> packed uint8 buffer of fq_packed_weight_bytes(N,K) bytes."""
+    r = (_marshal or marshal()).pack_weights(q)
+    if r is not None:
+        if type(r) is int:
+            raise FireqError(r, "fq_pack_weights")
+        return r
     q = _dev(q, torch.int8, "q")
     N, K = q.shape
     nbytes = fq_packed_weight_bytes(N, K)
@@ -544,6 +566,11 @@ def fq_w4a8_gemm_lut(A: torch.Tensor, a_scale: torch.Tensor, Wq_packed: torch.Te
 
 def fq_kv4_pack(codes: torch.Tensor, values: bool) -> torch.Tensor:
     """int8 [H,T,128] INT4 codes of a key (values=False) or value (values=True) cache -> the packed cache."""
+    r = (_marshal or marshal()).kv4_pack(codes, values)
+    if r is not None:
+        if type(r) is int:
+            raise FireqError(r, "fq_kv4_pack")
+        return r
     codes = _dev(codes, torch.int8, "codes")
     H, T, D = codes.shape
     if D != GROUP:

@@ -53,7 +53,8 @@ def marshal_path() -> str:
     import torch
     include = os.path.join(os.path.dirname(os.path.dirname(CSRC)), "include")
     digest = hashlib.sha256()
-    for path in (os.path.join(CSRC, "fq_marshal.cpp"), os.path.join(include, "fireq.h"), os.path.join(include, "fireq_kv4_ws.h")):
+    for path in (os.path.join(CSRC, "fq_marshal.cpp"), os.path.join(include, "fireq.h"), os.path.join(include, "fireq_kv4_ws.h"),
+                 os.path.join(include, "fireq_wquant_ws.h")):
         with open(path, "rb") as f:
             digest.update(f.read())
     digest.update(repr((torch.__version__, sysconfig.get_config_var("EXT_SUFFIX"))).encode())

@@ -165,6 +165,49 @@ def test_attention_operand_calls(fq, H, R, T, ldp):
     _same(fq, "fq_kv4_output", lambda: ((u8(H, many, ldp), torch.rand((H, many), device="cuda"), vp, sc), {}), fq.FireqError)
 
 
+@pytest.mark.parametrize("H,T", [(2, 1), (3, 130), (8, 400)])
+def test_cache_packing_calls(fq, H, T):
+    codes = torch.randint(-8, 8, (H, T, 128), generator=torch.Generator(device="cuda").manual_seed(T), device="cuda", dtype=torch.int8)
+    for values in (False, True):
+        if T % 128 == 0 or not values:                         # (tokens past T are padding the call need not define)
+            _same(fq, "fq_kv4_pack", lambda: ((codes, values), {}), native=True)
+        packed = fq.fq_kv4_pack(codes, values)
+        assert torch.equal(fq.fq_kv4_unpack(packed, H, T, values), codes)
+    _same(fq, "fq_kv4_pack", lambda: ((codes, 0), {}), native=False)
+    _same(fq, "fq_kv4_pack", lambda: ((codes[:0], False), {}), native=False)
+    for bad, exc in [((codes.cpu(), False), TypeError), ((codes.view(torch.uint8), False), TypeError), ((codes.transpose(0, 1)[:, :, :64], True), ValueError),
+                     ((codes[:, :, :64].contiguous(), False), fq.FireqError), ((codes.view(-1, 128), False), ValueError)]:
+        _same(fq, "fq_kv4_pack", lambda: (bad, {}), exc, native=False)
+
+
+@pytest.mark.parametrize("N,K", [(3, 128), (130, 1024), (5200, 1664)])
+def test_offline_calls(fq, N, K):
+    W = (torch.randn((N, K), generator=torch.Generator(device="cuda").manual_seed(N), device="cuda") * 0.02).bfloat16()
+    lam = fq.fq_cas_scales(W, 0.02)
+    for target in (0.02, 1):
+        _same(fq, "fq_cas_scales", lambda: ((W, target), {}), native=True)
+    _same(fq, "fq_cas_scales", lambda: ((W, np.float32(0.5)), {}), native=False)
+    _same(fq, "fq_cas_scales", lambda: ((W, -1.0), {}), fq.FireqError, native=True)
+    for a in ((W,), (W, lam), (W, None)):                      # (the first of the 16 ints is the result)
+        native, form, taken = _both(fq, "fq_pts_exponent", lambda: (a, {}))
+        assert taken == [True] and native[0].shape == form[0].shape and native[0].dtype == form[0].dtype and int(native[0][0]) == int(form[0][0])
+    for a, kw in (((W,), {}), ((W, lam, 3), {}), ((W, None, 1, True), {}), ((W, lam), {"sigma_nearest": True})):
+        _same(fq, "fq_quantize_weights", lambda: (a, kw), native=True)
+    _same(fq, "fq_quantize_weights", lambda: ((W, lam, np.int64(2)), {}), native=False)
+    q = fq.fq_quantize_weights(W, lam)[0]
+    _same(fq, "fq_pack_weights", lambda: ((q,), {}), native=True)
+    _same(fq, "fq_pack_weights", lambda: ((q.as_subclass(_Sub),), {}), native=False)
+    odd = W[:, :K - 64].contiguous()
+    for name, bad, exc in [("fq_cas_scales", (W.float(), 0.02), TypeError), ("fq_cas_scales", (W.cpu(), 0.02), TypeError),
+                           ("fq_cas_scales", (W.t(), 0.02), ValueError), ("fq_cas_scales", (W, None), TypeError),
+                           ("fq_pts_exponent", (W, lam[:-1]), fq.FireqError), ("fq_pts_exponent", (W, lam.double()), TypeError),
+                           ("fq_pts_exponent", (odd,), fq.FireqError), ("fq_quantize_weights", (odd,), fq.FireqError),
+                           ("fq_quantize_weights", (W, lam[:-1]), fq.FireqError), ("fq_quantize_weights", (W, lam, 127), fq.FireqError),
+                           ("fq_quantize_weights", (W, lam, -1), fq.FireqError), ("fq_pack_weights", (q.view(torch.uint8),), TypeError),
+                           ("fq_pack_weights", (q[:, :K - 64].contiguous(),), fq.FireqError), ("fq_pack_weights", (q.view(-1),), ValueError)]:
+        _same(fq, name, lambda: (bad, {}), exc)
+
+
 def test_another_stream_and_a_torch_function_mode(fq):
     """The native form runs on the current stream; under an active torch-function mode the Python form runs (the mode sees
     its calls)."""
