@@ -4,9 +4,10 @@ Every step of the path runs in the HIP kernels of ``libfireq.so``; torch is used
 memory and the current stream.  There is no CPU fallback: if the library cannot be loaded or a
 tensor is not on the GPU, the call raises.
 
-The calls of a running model, and those that prepare its weights and caches, marshal their arguments in native code (``_fq_marshal-*.so``, see its source); whatever that
-does not take -- another kind of tensor, a wrong shape, an argument to be refused -- comes back as None and goes through
-the Python form below it, which decides and raises.  Without that extension every call takes its Python form.
+The calls of a running model, and those that prepare its weights and caches, marshal their arguments in native code
+(``_fq_marshal-*.so``, see its source); whatever that does not take -- another kind of tensor, a wrong shape, an argument to
+be refused -- comes back as None and goes through the Python form below it, which decides and raises.  Without that
+extension every call takes its Python form.
 """
 from __future__ import annotations
 
