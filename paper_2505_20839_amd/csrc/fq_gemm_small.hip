@@ -13,6 +13,7 @@
 #include <type_traits>
 #include "fq_common.h"
 #include "fq_kernels.h"
+#include "fq_turn.h"
 
 namespace {
 
@@ -22,29 +23,6 @@ __device__ __forceinline__ fq_v8i fqs_join(fq_v4i lo, fq_v4i hi) {
     r[4] = hi[0]; r[5] = hi[1]; r[6] = hi[2]; r[7] = hi[3];
     return r;
 }
-
-// Activations of one group of 16 rows, on their way to an operand of the 16x16x128 MFMA.  The operand of lane 16*kq + r
-// is 32 bytes of row r: neighbouring lanes hold different rows, so a wave that loads it as such touches 64 places of 16
-// bytes, each of which takes the address path as long as four lanes that share 64 bytes.  So lane 4*r + c loads bytes
-// 16*c .. of each 64-byte half of row r (two loads), and the halves change lanes through LDS: 2 KiB per wave, row-major,
-// 16-byte slot x of row r at x ^ fqs_swizzle(r / 2), which spreads writes and reads over the banks.  The buffer is the wave's
-// own and a wave's LDS accesses keep their order: no barrier, and one buffer is enough for any number of groups in a row.
-__device__ __forceinline__ int fqs_swizzle(int h) { return h ^ ((h & 2) << 1); }
-
-struct fqs_turn {
-    int wr, rd;                                           // this lane's chunk in a row tile: to write (first half) and to read
-    __device__ __forceinline__ fqs_turn(int lane) {
-        const int rw = lane >> 2, rr = lane & 15;
-        wr = 8 * rw + ((lane & 3) ^ fqs_swizzle(rw >> 1));
-        rd = 8 * rr + ((2 * (lane >> 4)) ^ fqs_swizzle(rr >> 1));
-    }
-    __device__ __forceinline__ void operator()(fq_v4i* buf, fq_v4i (&half)[2]) const {   // the two halves as loaded -> the operand
-        buf[wr] = half[0];
-        buf[wr ^ 4] = half[1];
-        half[0] = buf[rd];
-        half[1] = buf[rd ^ 1];
-    }
-};
 
 // Byte offset of lane 4*r + c's chunk in the first half of group 0, row m0 + r; rows past M are requested out of range.
 __device__ __forceinline__ unsigned fqs_a_offset(int lane, int m0, int M, int K, unsigned oob) {
