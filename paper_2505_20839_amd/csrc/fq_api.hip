@@ -205,7 +205,7 @@ int fq_w4a8_gemm_plan(int M, int N, int K, int cus, int* plan) {
     if (!plan) return FQ_ERR_NULL;
     for (int i = 0; i < 8; ++i) plan[i] = 0;
     const GemmKernel k = choose_kernel(M);
-    plan[0] = k == GemmKernel::Simple ? 0 : k == GemmKernel::Small ? (M <= 16 ? 1 : 2) : 3;
+    plan[0] = k == GemmKernel::Simple ? 0 : k == GemmKernel::Small ? (!fq_gemm_small_serves(M, K) ? 0 : M <= 16 ? 1 : 2) : 3;
     if (k == GemmKernel::Small && forced_kernel() == GemmKernel::Auto &&
         fq_gemm_ksplit64_serves(M, N, K, cus > 0 ? cus : fq_device_cus())) {
         plan[0] = 6;

@@ -417,6 +417,8 @@ void fq_launch_small16(int per, unsigned grid, hipStream_t stream, const uint8_t
 // instead of being fetched per group.
 // ---------------------------------------------------------------------------------------------
 #define FQSM_MAXCOLS 64
+#define FQSM_TURN_BYTES (FQS16_WAVES * 2048)             // the waves' buffers of fqs_turn
+#define FQSM_LDS_BYTES (160 * 1024)
 
 template <int MT, int NSUB>
 struct fqsm_ring {
@@ -470,7 +472,8 @@ struct fqsm_ring {
     }
 };
 
-template <int MT, int NSUB, bool ROUNDS>
+// TURN: the activations come in whole 64-byte pieces and are turned (fqs_turn); fq_launch_smallm has the rule.
+template <int MT, int NSUB, bool ROUNDS, bool TURN>
 __global__ __launch_bounds__(FQS16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void fq_gemm_smallm_kernel(
     const uint8_t* __restrict__ A, const float* __restrict__ a_scale, const uint8_t* __restrict__ wp,
@@ -478,15 +481,11 @@ void fq_gemm_smallm_kernel(
     int swiglu, const uint16_t* R) {
     typedef fqsm_ring<MT, NSUB> ring_t;
     constexpr int BATCH = ring_t::BATCH;
-    // activations in whole 64-byte pieces and turned (fqs_turn), except where two row tiles' slices are all under way at
-    // once: 64 x 4096 x 4096 10.7 -> 8.0 us, 64 x 4096 x 14336 29.7 -> 20.7, 50 x 8192 x 8192 17.6 -> 14.5, 20 x 4096 x 11008
-    // 12.7 -> 11.4, but 32 x 14336 x 4096 10.4 -> 10.7
-    constexpr bool TURN = MT >= 3 || ROUNDS;
-    // LDS: first the waves' buffers of fqs_turn and the scale table [G][64] bytes, later (after a barrier) the partial
+    // LDS: first the waves' buffers of fqs_turn, if any, and the scale table [G][64] bytes, later (after a barrier) the partial
     // sums [wave][row tile][sub-tile][reg][lane] floats
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_bytes[];
     float* red = reinterpret_cast<float*>(lds_bytes);
-    uint8_t* const smem = lds_bytes + FQS16_WAVES * 2048;
+    uint8_t* const smem = lds_bytes + (TURN ? FQSM_TURN_BYTES : 0);
     const int G = K / FQ_GROUP;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     fq_v4i* const turned = reinterpret_cast<fq_v4i*>(lds_bytes) + wave * 128;
@@ -663,29 +662,35 @@ void fq_gemm_smallm_kernel(
 
 namespace {
 
-template <int MT, int NSUB>
-bool fq_launch_smallm(int per, unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
-                      const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols, int swiglu, const uint16_t* R) {
-    const int G = K / FQ_GROUP;
+template <int MT, int NSUB, bool ROUNDS, bool TURN>
+void fq_launch_smallm_as(unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
+                         const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols, int swiglu, const uint16_t* R) {
     const size_t red_bytes = (size_t)FQS16_WAVES * MT * NSUB * 256 * sizeof(float);
-    const size_t sc_bytes = (size_t)FQS16_WAVES * 2048 + (size_t)FQSM_MAXCOLS * G;   // (and the buffers of fqs_turn)
+    const size_t sc_bytes = (size_t)FQSM_MAXCOLS * (K / FQ_GROUP) + (TURN ? FQSM_TURN_BYTES : 0);
     const size_t lds = red_bytes > sc_bytes ? red_bytes : sc_bytes;
-    if (lds > 160 * 1024) return false;
-    const bool rounds = per > fqsm_ring<MT, NSUB>::BATCH;
-    const void* fn = rounds ? reinterpret_cast<const void*>(fq_gemm_smallm_kernel<MT, NSUB, true>)
-                            : reinterpret_cast<const void*>(fq_gemm_smallm_kernel<MT, NSUB, false>);
-    if (lds > 64 * 1024) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (rounds)
-        hipLaunchKernelGGL((fq_gemm_smallm_kernel<MT, NSUB, true>), dim3(grid), dim3(FQS16_THREADS), lds, stream,
-                           A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+    if (lds > 64 * 1024)
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_gemm_smallm_kernel<MT, NSUB, ROUNDS, TURN>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL((fq_gemm_smallm_kernel<MT, NSUB, ROUNDS, TURN>), dim3(grid), dim3(FQS16_THREADS), lds, stream,
+                       A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+}
+
+// The activations are turned except where two row tiles' slices are all under way at once (64 x 4096 x 4096 10.7 -> 8.0 us, 64 x 4096
+// x 14336 29.7 -> 20.7, 50 x 8192 x 8192 17.6 -> 14.5, 20 x 4096 x 11008 12.7 -> 11.4, but 32 x 14336 x 4096 10.4 -> 10.7), and
+// where the scale table leaves no room for the buffers (K > 294912).
+template <int MT, int NSUB>
+void fq_launch_smallm(int per, unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
+                      const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols, int swiglu, const uint16_t* R) {
+    if (per <= fqsm_ring<MT, NSUB>::BATCH)
+        fq_launch_smallm_as<MT, NSUB, false, (MT >= 3)>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+    else if (FQSM_MAXCOLS * (K / FQ_GROUP) + FQSM_TURN_BYTES <= FQSM_LDS_BYTES)
+        fq_launch_smallm_as<MT, NSUB, true, true>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
     else
-        hipLaunchKernelGGL((fq_gemm_smallm_kernel<MT, NSUB, false>), dim3(grid), dim3(FQS16_THREADS), lds, stream,
-                           A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
-    return true;
+        fq_launch_smallm_as<MT, NSUB, true, false>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
 }
 
 template <int MT>
-bool fq_launch_smallm_mt(int nsub, int per, unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
+void fq_launch_smallm_mt(int nsub, int per, unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
                          const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols, int swiglu, const uint16_t* R) {
     switch (nsub) {
         case 1: return fq_launch_smallm<MT, 1>(per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
@@ -747,8 +752,14 @@ bool fq_launch_linear_small(const uint16_t* X, float* a_scale_out, const uint8_t
     }
 }
 
+// M <= 64: the scale table of the kernel for more than 16 rows has to fit LDS (K <= 327680)
+bool fq_gemm_small_serves(int M, int K) {
+    return M <= 16 || (M <= 64 && (long long)FQSM_MAXCOLS * (K / FQ_GROUP) <= FQSM_LDS_BYTES);
+}
+
 bool fq_launch_gemm_small(const uint8_t* A, const float* a_scale, const uint8_t* wp, const uint8_t* gs,
                           float tscale, uint16_t* Y, int M, int N, int K, bool swiglu_epilogue, const uint16_t* R, hipStream_t stream) {
+    if (!fq_gemm_small_serves(M, K)) return false;
     const int swiglu = swiglu_epilogue ? 1 : 0;
     const fqs_shape sh = fqs_shape_of(M, N, K, M <= 16 ? FQS16_MAXCOLS : FQSM_MAXCOLS);
     const int cols = sh.cols, per = sh.per, nsub = sh.nsub;
@@ -765,10 +776,10 @@ bool fq_launch_gemm_small(const uint8_t* A, const float* a_scale, const uint8_t*
         }
         return true;
     }
-    if (M > 64) return false;
-    switch ((M + 15) / 16) {                              // false: the scale table does not fit LDS (K > 300000)
-        case 2: return fq_launch_smallm_mt<2>(nsub, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
-        case 3: return fq_launch_smallm_mt<3>(nsub, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
-        default: return fq_launch_smallm_mt<4>(nsub, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+    switch ((M + 15) / 16) {
+        case 2: fq_launch_smallm_mt<2>(nsub, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
+        case 3: fq_launch_smallm_mt<3>(nsub, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
+        default: fq_launch_smallm_mt<4>(nsub, per, grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R); break;
     }
+    return true;
 }

@@ -64,7 +64,8 @@ void fq_launch_zero_point(const uint8_t* A, void* workspace, int M, int K, hipSt
 void fq_launch_gemm_large(const uint8_t* A, const float* a_scale, const uint8_t* wp, const uint8_t* gs,
                           float tscale, uint16_t* Y, int M, int N, int K, void* workspace, bool prepared,
                           bool swiglu, const uint16_t* R, hipStream_t stream, bool lut = false);
-// M <= 64 only; returns false (nothing enqueued) for a shape it does not serve.
+// M <= 64, K up to 327680 above 16 rows (fq_gemm_small_serves); returns false (nothing enqueued) for a shape it does not serve.
+bool fq_gemm_small_serves(int M, int K);
 bool fq_launch_gemm_small(const uint8_t* A, const float* a_scale, const uint8_t* wp, const uint8_t* gs,
                           float tscale, uint16_t* Y, int M, int N, int K, bool swiglu, const uint16_t* R,
                            hipStream_t stream);

@@ -746,6 +746,16 @@ def test_small_m_row_counts(fq, kernel_choice, M, N, K):
     check_gemm(Y, Yr, B, "small %s" % ((M, N, K),), frobenius=M * N >= 4000)
 
 
+# The longest K: both sides of the line beyond which the activations are not turned, and the last one that this kernel serves
+@pytest.mark.parametrize("M,N,K", [(17, 24, 294912), (17, 24, 295040), (33, 8, 295040), (64, 24, 327680)])
+def test_small_m_longest_k(fq, M, N, K):
+    assert fq.fq_w4a8_gemm_plan(M, N, K)["kernel"] == "smallm"
+    A, a, q, gs, t = _rand_codes(M, N, K, seed=M + K)
+    Y = _run_gemm(fq, A, a, q, gs, t)
+    Yr, B = oracle.w4a8_gemm(A, a, q, gs, t, want_bound=True)
+    check_gemm(Y, Yr, B, "small %s" % ((M, N, K),), frobenius=False)
+
+
 # waves per row (1, 4, 8, 16) and chunks per thread (2, 3, 4, 6, 8) by K and M, at both ends of each range, the last chunk and
 # the last rows of a workgroup partly there, rows in two passes
 @pytest.mark.parametrize("M,K", [(1, 8), (5, 4088), (1537, 4096), (1539, 136), (1601, 264), (65, 4104), (513, 8192), (514, 4224), (600, 8200), (64, 4104),

@@ -45,6 +45,17 @@ def test_kernel_choice_follows_m_and_the_tile_count():
                 assert p["ksplit_slices"] == 1
 
 
+def test_rows_above_16_keep_their_kernel_up_to_the_longest_scale_table():
+    """17 to 64 rows: the kernel's scale table, 64 bytes per group of 128, fills LDS at K = 327680; the buffers that its faster form
+    keeps beside the table must not take anything off that."""
+    binding.fq_test_force_kernel(None)
+    for M, N in itertools.product([17, 32, 33, 64], [8, 40, 4096]):
+        for K in (8320, 294912, 294912 + 128, 300032, 327680):
+            assert _plan(M, N, K)["kernel"] == "smallm", (M, N, K)
+        assert _plan(M, N, 327680 + 128)["kernel"] == "simple"
+        assert _plan(16, N, 327680 + 128)["kernel"] == "small16"
+
+
 def test_large_kernel_tiles_cover_the_problem_once():
     """Whole tiles count 256 rows, half tiles 128: together they cover every 128-row x 128-channel block of the
     padded problem exactly once."""
