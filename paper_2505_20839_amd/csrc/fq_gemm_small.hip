@@ -52,10 +52,6 @@ __device__ __forceinline__ unsigned fqs_a_offset(int lane, int m0, int M, int K,
 #define FQS16_WAVES 8
 #define FQS16_MAXCOLS 112                                 // channels of a workgroup (7 sub-tiles: 56 KiB of partial sums in LDS)
 #define FQS16_FUSED_MAX_M 6                               // rows up to which quantising inside the GEMM kernel pays (<= waves)
-// Rows from which the activations are loaded in whole 64-byte pieces and turned (fqs_turn); with fewer, most lanes of the
-// direct form repeat a row at no cost and the way through LDS is not worth it (us, turned / direct, N = 4096, K = 14336:
-// M = 2 8.8 / 8.3, 8 9.0 / 9.3, 10 8.9 / 9.3, 16 10.0 / 10.9; N = 6144, K = 4096: 16 4.6 / 5.2).
-#define FQS16_TURN_MIN_M 9
 #define FQS16_OOB 0xFFFFFF00u                             // beyond any 32-bit buffer size
 // byte `i` (0..3, compile-time) of a word of E4M3 codes -> float
 __device__ __forceinline__ float fq_e4m3_byte_to_float(unsigned w, int i) {
@@ -355,11 +351,27 @@ void fq_gemm_small16_kernel(
 
 namespace {
 
+// Whether the activations are loaded in whole 64-byte pieces and turned (fqs_turn).  With few rows most lanes of the direct form
+// repeat a row at no cost, and the way through LDS stands before a wave's first matrix instruction, which few groups do not
+// win back (`per`: groups per wave; us, turned / direct; N = 4096 is one sub-tile, 8192 two, 12288 three, 14336 four):
+//     per 1   16 x 4096 x 1024 3.80 / 3.79, 16 x 14336 x 256 4.20 / 3.93
+//     per 2   9 x 4096 x 1408 3.72 / 3.65, 12 x 4096 x 2048 3.95 / 4.00, 16 x 4096 x 2048 3.94 / 4.10; 12 x 8192 x 2048 4.64 / 4.56
+//     per 4   9 x 4096 x 4096 4.22 / 4.30, 16 rows 4.47 / 4.84; 9 x 8192 x 4096 5.45 / 5.36, 16 rows 5.62 / 5.73; 16 x 14336 x 4096
+//             7.85 / 7.61
+//     more    9 x 12288 x 5120 9.31 / 9.28, 16 rows 9.45 / 9.94; 9 x 8192 x 8192 8.20 / 7.91, 16 rows 8.47 / 8.71
+inline bool fqs16_turns(int M, int per, int nsub) {
+    if (nsub == 1) return M >= 9 && M * per >= 24;
+    return M >= 12 && per >= (nsub == 2 ? 3 : 5);
+}
+
 template <int NSUB, bool ROUNDS, int BATCH>
 void fq_launch_small16b(unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
                         const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols, int swiglu, const uint16_t* R) {
-    const auto kernel = M < FQS16_TURN_MIN_M ? fq_gemm_small16_kernel<NSUB, ROUNDS, BATCH, false>
-                                             : fq_gemm_small16_kernel<NSUB, ROUNDS, BATCH, true>;
+    const int per = (K / FQ_GROUP + FQS16_WAVES - 1) / FQS16_WAVES;
+    auto kernel = fq_gemm_small16_kernel<NSUB, ROUNDS, BATCH, false>;
+    if constexpr (NSUB <= 2 || ROUNDS || BATCH > 4) {     // (three sub-tiles and more with at most four groups never turn)
+        if (fqs16_turns(M, per, NSUB)) kernel = fq_gemm_small16_kernel<NSUB, ROUNDS, BATCH, true>;
+    }
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(FQS16_THREADS), 0, stream,
                        A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R, static_cast<float*>(nullptr));
 }
@@ -675,15 +687,21 @@ void fq_launch_smallm_as(unsigned grid, hipStream_t stream, const uint8_t* A, co
                        A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
 }
 
-// The activations are turned except where two row tiles' slices are all under way at once (64 x 4096 x 4096 10.7 -> 8.0 us, 64 x 4096
-// x 14336 29.7 -> 20.7, 50 x 8192 x 8192 17.6 -> 14.5, 20 x 4096 x 11008 12.7 -> 11.4, but 32 x 14336 x 4096 10.4 -> 10.7), and
-// where the scale table leaves no room for the buffers (K > 294912).
+// The activations are turned where slices go round the ring and LDS has room for the buffers beside the scale table (K up to
+// 294912): 64 x 4096 x 4096 10.8 -> 8.6 us, 64 x 4096 x 14336 30 -> 21, 48 x 8192 x 8192 16 -> 13.2, 24 x 4096 x 11008 13.6 -> 12.2.
+// A slice that is all under way at once wins back the way through LDS only with three or four row tiles and two groups, from the
+// rows below on (turned / direct: 33 x 4096 x 1408 1.07, 40 x 4096 x 2048 0.965, 48 1.00 and 0.92; 56 x 8192 x 2048 1.04, 64 x 6144 x
+// 1408 0.97; 40 x 28672 x 2048 1.03, 49 1.02, 64 0.97; one group: 33 x 8192 x 1024 1.10, 48 1.08; two row tiles: 32 x 14336 x 4096 1.03).
 template <int MT, int NSUB>
 void fq_launch_smallm(int per, unsigned grid, hipStream_t stream, const uint8_t* A, const float* a_scale,
                       const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols, int swiglu, const uint16_t* R) {
-    if (per <= fqsm_ring<MT, NSUB>::BATCH)
-        fq_launch_smallm_as<MT, NSUB, false, (MT >= 3)>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
-    else if (FQSM_MAXCOLS * (K / FQ_GROUP) + FQSM_TURN_BYTES <= FQSM_LDS_BYTES)
+    if (per <= fqsm_ring<MT, NSUB>::BATCH) {
+        if constexpr (MT >= 3) {
+            if (per == 2 && M >= (NSUB == 1 ? 40 : 57))
+                return fq_launch_smallm_as<MT, NSUB, false, true>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+        }
+        fq_launch_smallm_as<MT, NSUB, false, false>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
+    } else if (FQSM_MAXCOLS * (K / FQ_GROUP) + FQSM_TURN_BYTES <= FQSM_LDS_BYTES)
         fq_launch_smallm_as<MT, NSUB, true, true>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
     else
         fq_launch_smallm_as<MT, NSUB, true, false>(grid, stream, A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);

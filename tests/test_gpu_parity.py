@@ -734,8 +734,7 @@ def test_small_m_rings_and_sub_tiles(fq, shape):
     check_gemm(bf16_bits_from_gpu(YR)[:, pick], Yr, B, "small + residual %s" % (shape,), frobenius=M * len(pick) >= 4000)
 
 
-# Rows around every row tile's edge and around the line between the two ways the activations take (9 rows; 33 and a ring gone
-# round), with slices of 0, 1, 2 and 9 groups, scale rows at every alignment and a last workgroup with few channels.
+# Rows around every row tile's edge, with slices of 0, 1, 2 and 9 groups, scale rows at every alignment and a last workgroup with few channels.
 @pytest.mark.parametrize("N,K", [(40, 128), (77, 1408), (1030, 9088)])
 @pytest.mark.parametrize("M", [1, 7, 8, 9, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64])
 def test_small_m_row_counts(fq, kernel_choice, M, N, K):
@@ -744,6 +743,14 @@ def test_small_m_row_counts(fq, kernel_choice, M, N, K):
     Y = _run_gemm(fq, A, a, q, gs, t)
     Yr, B = oracle.w4a8_gemm(A, a, q, gs, t, want_bound=True)
     check_gemm(Y, Yr, B, "small %s" % ((M, N, K),), frobenius=M * N >= 4000)
+
+
+# Both sides of every line between the two ways the activations take: sub-tiles per workgroup, groups per wave, rows
+@pytest.mark.parametrize("M,N,K", [(11, 40, 2048), (12, 40, 2048), (16, 40, 1024), (8, 1030, 3200), (9, 1030, 3200), (11, 6152, 2176), (12, 6152, 2176),
+                                   (16, 6152, 2048), (11, 12296, 4224), (12, 12296, 4224), (16, 12296, 4096), (39, 77, 1408), (40, 77, 2048), (56, 6152, 1408),
+                                   (57, 6152, 2048), (56, 12296, 1408), (57, 12296, 2048), (64, 24576, 1152), (64, 77, 1024)])
+def test_small_m_both_ways_of_the_activations(fq, kernel_choice, M, N, K):
+    test_small_m_row_counts(fq, kernel_choice, M, N, K)
 
 
 # The longest K: both sides of the line beyond which the activations are not turned, and the last one that this kernel serves
