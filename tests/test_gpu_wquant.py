@@ -256,6 +256,23 @@ def test_cas_scales_with_scratch(fq, N, K):
         assert int((lam.view(torch.int32) - got.view(torch.int32))[ok].abs().max()) <= 1
 
 
+@pytest.mark.parametrize("N,K", [(5120, 1640), (9001, 1032), (40000, 216)])
+def test_cas_scales_same_bits_where_the_sums_are_exact(fq, N, K):
+    """Magnitudes 2^-31 .. 1 in steps of 2^-38 and more, sums below 2^15: FP64 holds every partial sum, so that the calls with and
+    without scratch and the one on a misaligned W agree in every bit, and with the FP64 mean."""
+    g = torch.Generator(device="cuda").manual_seed(N)
+    e = torch.randint(-30, 1, (N, K), generator=g, device="cuda", dtype=torch.int32)
+    store = torch.empty((N * K + 1,), dtype=torch.bfloat16, device="cuda")
+    W, off = torch.ldexp(torch.rand((N, K), generator=g, device="cuda") * 0.5 + 0.5, e).to(torch.bfloat16), store[1:].view(N, K)
+    off.copy_(W)
+    lam = fq.fq_cas_scales(W, 0.02)
+    others = [torch.empty_like(lam) for _ in range(2)]
+    for M, out in zip((W, off), others):
+        assert fq.lib().fq_cas_scales(M.data_ptr(), 0.02, out.data_ptr(), N, K, torch.cuda.current_stream().cuda_stream) == 0
+    assert all(torch.equal(lam, out) for out in others + [fq.fq_cas_scales(off, 0.02)])
+    assert torch.equal(lam, (float(np.float32(0.02)) / (W.double().abs().sum(dim=0) / N)).float())
+
+
 @pytest.mark.parametrize("N,K", [(3, 128), (64, 4096), (65, 4096), (2060, 4096), (400, 11008)])
 def test_pts_exponent_without_scratch(fq, N, K):
     """The statistics met in the caller's 64 bytes: the same exponent, wherever the element that decides is."""
