@@ -178,19 +178,22 @@ def test_masked_stores_at_ragged_edges(fq, shape):
 
 
 @pytest.mark.parametrize("M,N", [(1000, 1296), (300, 528), (129, 2064)])
-def test_masked_gate_up_tiles_keep_the_row_maxima(fq, M, N):
+def test_masked_gate_up_tiles(fq, M, N):
     """The fused gate/up layer with quantised output at ragged edges: the masked rows and channels of an edge tile
-    neither reach the output nor the row maxima (the scales and codes are the separate quantiser's, bit for bit)."""
+    reach neither the output nor its scales and codes (the oracle's on the GPU's H)."""
     K = 512
     d = _problem((M, N, K), seed=M + N)
     A, s = fq.fq_quantize_act(to_gpu_bf16(d["X_bf16"]))
     packed, gs = fq.fq_pack_weights(_gpu(d["q"])), _gpu(d["gscale"])
     H, codes, scales = fq.fq_w4a8_gemm_swiglu_quant(A, s, packed, gs, d["w_tscale"], N)
-    codes2, scales2 = fq.fq_quantize_act(H)
     torch.cuda.synchronize()
-    assert torch.equal(codes, codes2) and torch.equal(scales, scales2)
+    C_or, s_or = oracle.quantize_act(bf16_bits_from_gpu(H))
+    codes = codes.cpu().numpy()
+    assert np.array_equal(scales.cpu().numpy(), s_or)
+    assert np.array_equal(codes & 0x7F, C_or & 0x7F) and np.array_equal((codes & 0x80)[(C_or & 0x7F) != 0], (C_or & 0x80)[(C_or & 0x7F) != 0])
     Hr, B = oracle.w4a8_gemm_swiglu(A.cpu().numpy(), s.cpu().numpy(), d["q"], d["gscale"], d["w_tscale"], want_bound=True)
     check_gemm(bf16_bits_from_gpu(H), Hr, B, "masked gate/up %d x %d" % (M, N))
+
 
 # Group counts around the eight that share a fetch of scales (groups 1 .. 8, 9 .. 16, ... and group 0 by itself), rows of scales
 # at every alignment, a ragged last channel block, whole and half tiles.

@@ -165,7 +165,7 @@ def test_attention_operand_calls(fq, H, R, T, ldp):
     _same(fq, "fq_kv4_output", lambda: ((u8(H, many, ldp), torch.rand((H, many), device="cuda"), vp, sc), {}), fq.FireqError)
 
 
-@pytest.mark.parametrize("H,T", [(2, 1), (3, 130), (8, 400)])
+@pytest.mark.parametrize("H,T", [(2, 1), (3, 130), (4, 256), (8, 400)])
 def test_cache_packing_calls(fq, H, T):
     codes = torch.randint(-8, 8, (H, T, 128), generator=torch.Generator(device="cuda").manual_seed(T), device="cuda", dtype=torch.int8)
     for values in (False, True):
