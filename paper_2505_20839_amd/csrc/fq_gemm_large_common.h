@@ -63,14 +63,14 @@ __device__ __forceinline__ void fql_issue_b(__amdgpu_buffer_rsrc_t rsrc, fq_v4i*
 // One round of zero-point units (up to 8, numbers u0 ..) -> an A stage: NMT transfers of 64 rows per
 // wave (4 waves), the same number as an A tile takes, so that the pipeline's wait counts do not change; slots
 // past the last unit are requested out of range (zeros).  Unit slot s occupies chunks [s * RT, (s+1) * RT).
-template <int NMT, int WAVES = 4>
+template <int NMT>
 __device__ __forceinline__ void fql_issue_z(__amdgpu_buffer_rsrc_t rsZ, fq_v4i* lds_stage, int wave, int lane,
                                             int m0, int M, int u0, int nu) {
     constexpr int RT = 32 * NMT, SUBS = RT / 64;
-    static_assert(RT % 64 == 0 && (4 * NMT) % WAVES == 0, "whole transfers of 64 rows, an equal number per wave");
+    static_assert(RT % 64 == 0, "whole transfers of 64 rows");
 #pragma unroll
-    for (int t = 0; t < 4 * NMT / WAVES; ++t) {
-        const int q = wave + WAVES * t;
+    for (int t = 0; t < NMT; ++t) {
+        const int q = wave + 4 * t;
         const int slot = q / SUBS, sub = q - slot * SUBS;
         // rows past M are masked like slots past the last unit: the range check sees the per-lane
         // offset only, and the last unit's scalar offset would carry such a row past the workspace
