@@ -359,7 +359,8 @@ int fq_w4a8_gemm_swiglu_quant_ws(const uint8_t* A_fp8, const float* a_scale, con
     }
     // The gate/up GEMM, then the quantiser, which reads a row once, search included.  Row maxima raised by the GEMM's epilogue
     // (an atomic per row and tile, into scales that another launch has cleared) save the search and cost more than it: 1000 x 22016
-    // x 4096 and the layer behind it 155 us with them, 151 without; 2048 x 22016 x 4096 alone 190.8, 186.2.
+    // x 4096 and the layer behind it 155 us with them, 151 without; 2048 x 22016 x 4096 alone 201, 192; 65 x 22016 x 4096 39.5, 35.5.
+    // (Only rows of more than 32768 outputs over a short K show the search: 2048 x 65792 x 512 179, 192.)
     const int g = fq_w4a8_gemm_swiglu_ws(A_fp8, a_scale, Wq_packed, w_gscale, w_tscale, H_bf16, M, N, K, workspace,
                                          workspace_bytes, workspace_prepared, stream);
     if (g != FQ_OK) return g;

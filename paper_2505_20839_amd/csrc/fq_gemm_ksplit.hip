@@ -698,15 +698,16 @@ void fqk_launch(const uint8_t* A, const float* a_scale, const uint8_t* wp, const
 // Which shape of this kernel, if any, serves the problem better than the large-M kernel's own tiles: 0 = none,
 // 2 = 128 x 64 tiles with K quartered, 3 = 128 x 128 tiles with K halved (1 = 256 x 128 tiles is never chosen).
 // A shape wins where its tiles fit one round of the compute units, the smaller one first; GEMM alone with a prepared
-// workspace, large-M kernel -> 128 x 128 -> 128 x 64, us: 256 x 14336 x 4096 25.1 -> 21.9 -> 30.2 (two rounds); 700 x 4096 x 4096
-// 23.1 -> 20.0 -> 28.4; 1000 x 4096 x 11008 58.7 -> 49.2 -> 67.4; 1024 x 4096 x 14336 74.1 -> 62.5 -> 83.3; 1500 x 2048 x
-// 8192 43.4 -> 33.7 -> 48.2; 1000 x 2048 x 4096 20.4 -> 19.0 -> 15.8; 1000 x 1024 x 8192 35.8 -> 31.6 -> 24.8; beyond one round
-// both lose (2048 x 4096 x 11008, 512 tiles: 89.6 -> 98.9; 512 x 14336 x 4096: 33.9 -> 42.2).  A single row tile with K >= 5120 is
-// given two rounds of 128 x 64 tiles all the same: that line was drawn when the large-M kernel took 46.7 us for 128 x 20480 x 5120
-// and 74.5 for 128 x 28672 x 8192; it now takes 24.2 and 37.6, two rounds 36.4 and 51.7, so the line is no longer where they meet.
+// workspace, large-M kernel -> 128 x 128 -> 128 x 64, us: 256 x 14336 x 4096 27.2 -> 22.9 -> 33.9 (two rounds); 700 x 4096 x 4096
+// 21.9 -> 19.1 -> 28.1; 1000 x 4096 x 11008 68.4 -> 49.4 -> 67.6; 1024 x 4096 x 14336 87.6 -> 62.0 -> 84.5; 1500 x 2048 x
+// 8192 39.6 -> 31.6 -> 45.3; 1000 x 2048 x 4096 19.6 -> 18.3 -> 16.2; 1000 x 1024 x 8192 34.4 -> 29.1 -> 23.3; beyond one round
+// both lose (2048 x 4096 x 11008, 512 tiles: 85.5 -> 99.4; 512 x 14336 x 4096: 33.6 -> 42.9).  A single row tile with K >= 5120 is
+// given two rounds of 128 x 64 tiles all the same: that line was drawn before there were 128 x 128 tiles, which would take
+// these problems otherwise and in two thirds of the time: 128 x 20480 x 5120 42.3 -> 26.6 -> 40.2, 128 x 28672 x 8192
+// 62.6 -> 41.9 -> 58.7, 80 x 22016 x 8192 50.9 -> 33.7 -> 46.0.
 // With a short K the large-M kernel is the better one where its 128-row halves are one round too (large-M -> 128 x 128: 256
-// x 11008 x 1024 9.75 -> 10.7 us, 512 x 6144 x 1024 9.75 -> 10.7, 200 x 8200 x 1536 10.9 -> 11.5, 1280 x 3000 x 1024 10.3 -> 11.2; 256
-// x 14336 x 2048 13.7 -> 14.1, x 3072 18.5 -> 17.9); two rounds of halves lose at any K (300 x 8200 x 1024 11.4 -> 10.6).
+// x 11008 x 1024 9.8 -> 10.5 us, 512 x 6144 x 1024 9.7 -> 10.5, 1280 x 3000 x 1024 10.9 -> 11.1, but 200 x 8200 x 1536 11.8 -> 11.4; 256
+// x 14336 x 2048 13.4 -> 14.3, x 3072 22.7 -> 18.8); two rounds of halves lose at any K (300 x 8200 x 1024 11.7 -> 10.4).
 int fq_gemm_ksplit_choice(int M, int N, int K, int cus) {
     const int G = K / FQ_GROUP;
     if (M <= 64 || G < 8) return 0;
@@ -754,12 +755,12 @@ void fq_launch_gemm_ksplit(int choice, const uint8_t* A, const float* a_scale, c
 }
 
 // 16 < M <= 64 without a workspace: 64 x 64 tiles, K quartered, the zero point through the matrix cores; its time hardly
-// depends on M.  Against the M <= 64 kernel, M <= 64 -> this, us: N = 14336, K = 4096: M = 64 14.7 -> 10.5, M = 48 12.3 -> 10.2,
-// M = 33 11.1 -> 10.2; 11008 x 4096: 13.4 -> 10.0, 11.3 -> 9.8, 9.9 -> 9.6; 8192 x 8192: 19.3 -> 16.0, 15.9 -> 15.8, 13.3 -> 15.6;
-// 12288 x 2048: 8.7 -> 7.3, 7.0 -> 7.2, 6.4 -> 7.2; 8192 x 1024: 5.9 -> 5.9, 4.9 -> 5.9, 4.6 -> 5.8; fewer tiles: 6144 x 4096
-// 11.6 -> 9.6, 9.4 -> 9.6; 4096 x 4096 10.6 -> 9.5, 8.7 -> 9.5; 14336 x 11008 32.6 -> 22.7, 27.3 -> 22.2.  So: the top of the
-// range, at least half a round of tiles, K up to 8192, on the safe side on all three but
-// for a short K (57 x 8192 x 1024 5.7 -> 6.0).
+// depends on M.  Against the M <= 64 kernel, M <= 64 -> this, us, at M = 64, 57, 48 and 33: 14336 x 4096 14.3 -> 13.3, 13.9 -> 13.1,
+// 12.2 -> 12.7, 11.6 -> 12.3; 11008 x 4096 12.6 -> 12.2, 12.3 -> 12.0, 10.7 -> 11.7, 10.2 -> 11.4; 12288 x 2048 8.7 -> 8.3, 8.7 -> 8.2, 7.6 ->
+// 8.2, 7.1 -> 8.1; 8192 x 8192 15.7 -> 18.7, 15.6 -> 18.4, 13.5 -> 17.8, 12.3 -> 17.1; 8192 x 1024 6.1 -> 6.4, 6.0 -> 6.4, 5.2 -> 6.3, 5.0 ->
+// 6.2; outside the line 6144 x 4096 10.6 -> 10.4 at 64, 8.8 -> 10.2 at 48; 4096 x 4096 8.7 -> 10.2; 14336 x 11008 28.8 -> 27.0 at 64, even
+// at 48.  So: the top of the range, at least half a round of tiles, K up to 8192; drawn when the M <= 64 kernel took
+// 19.3 us for 64 x 8192 x 8192, the line now holds from 11008 channels on and is too low for 8192.
 bool fq_gemm_ksplit64_serves(int M, int N, int K, int cus) {
     const int tiles = (N + 63) / 64;
     return M > FQ_KSPLIT64_MIN_M && M <= 64 && K / FQ_GROUP >= 8 && K <= 8192 && tiles <= cus && 2 * tiles >= cus;

@@ -285,7 +285,7 @@ void fq_gemm_small16_kernel(
         __builtin_amdgcn_sched_barrier(0);
     }
     // A slot's activations are turned AHEAD slots before their use: the way through LDS takes longer than a slot's arithmetic
-    // (16 x 4096 x 14336 10.5 us one slot ahead, 10.2 three; with a ring of four, 16 x 14336 x 4096 7.4 and 7.8)
+    // (16 x 4096 x 14336 10.5 us one slot ahead, 10.2 three; with a ring of four it is the other way round)
     constexpr int AHEAD = BATCH > 4 ? 3 : 1;
     const fqs_turn turn(lane);
     auto turn_slot = [&](int i) __attribute__((always_inline)) {

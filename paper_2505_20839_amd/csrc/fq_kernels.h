@@ -77,11 +77,11 @@ bool fq_launch_linear_small(const uint16_t* X, float* a_scale_out, const uint8_t
 
 // Offline weight quantisation (fq_wquant.hip).  W is [N,K] bf16; lambda (may be NULL) is [K] FP32.
 void fq_launch_cas_scales(const uint16_t* W, float target, float* lambda, int N, int K, hipStream_t stream);
-// n_out: 64 bytes of device memory; int 0 receives n, ints 8..12 are scratch for the statistics.
 // Scratch bytes of the form whose workgroups share out the rows (0: W is not for it); W is 16-byte aligned there.
 size_t fq_cas_scales_scratch(int N, int K);
 void fq_launch_cas_scales_split(const uint16_t* W, float target, float* lambda, int N, int K, void* scratch, hipStream_t stream);
-// scratch: fq_pts_exponent_scratch(K) bytes, or nullptr (the statistics then meet in the caller's 64 bytes; always where that is 0).
+// n_out: 64 bytes of device memory, int 0 receives n.  scratch: fq_pts_exponent_scratch(K) bytes, or nullptr (always where that is 0):
+// the statistics then meet in ints 8 and 9 of n_out.
 size_t fq_pts_exponent_scratch(int K);
 void fq_launch_pts_exponent(const uint16_t* W, const float* lambda, int* n_out, int N, int K, void* scratch, hipStream_t stream);
 void fq_launch_quantize_weights(const uint16_t* W, const float* lambda, int n_pts, bool sigma_rne, int8_t* q,

@@ -57,7 +57,7 @@ struct fqw_bands {
 
 // ---- channel-wise absmean scaling ------------------------------------------------------------------
 // FP64 sums over the rows of a channel, combined in a fixed order: the result does not depend on timing.  A column sum
-// stays inside one workgroup (there is no scratch buffer for partial sums).
+// stays inside one workgroup here; fq_cas_partial_kernel below shares it out, where the caller has given scratch for the parts.
 //
 // Any W: 16 waves per 32 input channels; 16 lanes cover the 32 channels of a row (a dword = two channels each), so a
 // wave reads 4 rows per instruction and the 16 waves 64; FQW_CAS_UNROLL such loads are in flight per lane.
@@ -234,8 +234,8 @@ __global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_scales_wide_kernel(co
 // channels, read 32 to 128 bytes of a row, at a third of the memory's rate.  Read nontemporally: W comes from memory once, and what
 // it would push out of the last-level cache has to be written back if it was written lately (11008 x 4096 after a kernel
 // that wrote 320 MB: 38.5 us through the cache, 22.0 past it, 47.2 for the kernel above; all four calls of the quantiser
-// in a row 82 us either way).  Back to back from memory, both launches (above, here): 11008 x 4096 35.2 -> 19.7 us, 22016 x 4096
-// 72.0 -> 33.2.
+// in a row 82 us either way).  Back to back from memory, the kernel above and both launches here: 11008 x 4096 38.0 -> 19.9 us, 22016 x
+// 4096 74.8 -> 33.3.
 #define FQW_CASP_UNROLL 8
 __global__ __launch_bounds__(FQW_CASW_THREADS) void fq_cas_partial_kernel(const uint16_t* __restrict__ W, double* __restrict__ part,
                                                                           int N, int K, int slabs, int cw, int rows) {
@@ -539,9 +539,11 @@ fqw_cas_split fqw_split_rows(int N, int K) {
 }  // namespace
 
 // Where the kernels without scratch read less than whole lines per workgroup (16 or 32 channels) of many rows; few rows or 64
-// channels are served as fast without a second launch.  From memory, without | with scratch, us: 5120 x 2048 15.1 | 9.5, 11008 x
-// 1024 29.1 | 10.8, 6144 x 4096 19.7 | 13.4, 7000 x 5120 30.1 | 18.2, 11008 x 4096 35.0 | 19.4, 22016 x 4096 68.1 | 32.6; on the
-// other side of the line 4000 x 4224 13.3 | 13.5, 2000 x 8192 10.3 | 11.5, 1024 x 4096 4.7 | 7.4, 4096 x 11008 20.5 | 21.4,
+// channels are served as fast without a second launch.  Without | with scratch, us, from memory: 5120 x 2048 11.8 | 9.6, 11008 x
+// 1024 24.9 | 11.2, 5120 x 5120 24.6 | 15.6, 6144 x 4096 22.3 | 13.6, 11008 x 4096 38.0 | 19.9, 22016 x 4096 74.8 | 33.3, 28672 x 8192
+// 120 | 76; a matrix that the last-level cache holds: 5120 x 2048 8.2 | 9.1, 11008 x 1024 11.1 | 10.3, 5120 x 5120 16.3 | 14.5, 11008 x
+// 4096 24.0 | 18.8 (at the line, what it costs the smallest of them from the cache it gives from memory).  On the other side
+// of the line, from memory: 4000 x 4224 13.3 | 13.5, 2000 x 8192 10.3 | 11.5, 1024 x 4096 4.7 | 7.4, 4096 x 11008 20.5 | 21.4,
 // 22016 x 11008 90.8 | 89.6; 4096 x 4096 13.8 | 11.6, but 7.7 | 10.4 from the cache.
 size_t fq_cas_scales_scratch(int N, int K) {
     if (K % 8 != 0 || 2 * ((K + 63) / 64) > fq_device_cus() || N < 5120 || (long long)N * K < (8ll << 20)) return 0;
