@@ -441,79 +441,103 @@ __global__ __launch_bounds__(FQW_PTS_WGS) void fq_pts_fold_kernel(const unsigned
 }
 
 // ---- group-wise INT4 quantisation ------------------------------------------------------------------
-// 16 lanes per group of 128 weights (8 neighbouring weights = 16 bytes per lane): a wave quantises four groups at a time,
-// UNROLL times, all of them requested before the first is worked on (11008 x 4096: 37.6 us with a division per
-// weight, 32.9 / 30.9 / 32.8 with 1 / 2 / 4 at a time).  Bound by HBM (3 bytes per weight) once
-// the quotient is short: a full IEEE division per weight (about eleven instructions) made it VALU bound.  With r = the
-// correctly rounded 1 / sigma8 (one division per group), q0 = v * r, the exact residual e = fma(-q0, sigma8, v) and
+// 16 lanes per group of 128 weights (8 neighbouring weights = 16 bytes per lane); a thread quantises the same 8 columns of ROWS
+// neighbouring rows, all of them requested before the first is worked on, so that it finds its place and fetches its lambda
+// once.  3 bytes per weight, but a vector instruction per weight takes 1.1 us at 11008 x 4096, and some 22 of them (the place by
+// a 64-bit modulo and lambda per row, two IEEE divisions per lane, the maximum through LDS, separate rounding, conversion and
+// packing) held the reading back; with 13 it runs at 5.0 to 5.8 TB/s (from memory, us, before -> now: 11008 x 4096 33.4 -> 26.8, 4096 x 4096
+// 15.5 -> 12.3, 22016 x 8192 115 -> 94, 4096 x 11008 34.0 -> 27.2, 2048 x 1024 3.6 -> 3.2; four rows per thread are even, nontemporal loads too).
+// The quotient: with r = the correctly rounded 1 / sigma8, q0 = v * r, the exact residual e = fma(-q0, sigma8, v) and
 // q1 = fma(e, r, q0), rint(q1) equals rint of the IEEE quotient for every FP32 v and every E4M3 sigma8 (a program on
 // the host has gone through all of them, the tests go through every third v; sigma8 has four significant bits, and a power
-// of two moves nothing).  v is cut to +-16 sigma8 first, which changes no code (they end at -8 and 7) and keeps the residual finite.
-template <int UNROLL>
+// of two moves nothing).  The same steps by 1/7 give sigma (all significands checked there too), and r itself is the
+// hardware's reciprocal after one step of Newton's: 1 / sigma8 is periodic in at most 12 bits, so never near a midpoint.
+// A group whose largest weight times 2^n is infinite, or with sigma8 = 0, is cut to +-16 sigma8 first, which changes no code of a finite weight (they end
+// at -8 and 7) and keeps the residual finite (with sigma8 = 0 every code is 0).  rint and the conversion are one addition:
+// q1 cut to [-8, 7], plus 1.5 * 2^23, has the code in its low byte.
+// 2^n multiplies sigma and divides sigma8 instead of every weight, up to 2^64, where every step stays exact (the smallest
+// weights that matter are 2^-75 then, their residuals' last bits above 2^-130); beyond, the weights are multiplied.
+#define FQW_MANY_PTS 64
+template <int CTRL>
+__device__ __forceinline__ float fqw_dpp_max(float v) {
+    return fmaxf(v, __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, false)));
+}
+
+template <int ROWS>
 __global__ __launch_bounds__(256) void fq_quantize_weights_kernel(const uint16_t* __restrict__ W,
                                                                   const float* __restrict__ lambda, int n_pts,
                                                                   int sigma_rne, int8_t* __restrict__ q,
-                                                                  uint8_t* __restrict__ gs, size_t groups, int K) {
-    const size_t grp0 = (size_t)blockIdx.x * (16u * UNROLL) + (threadIdx.x >> 4);
+                                                                  uint8_t* __restrict__ gs, int N, int K) {
+    const unsigned KC = (unsigned)K / 8u, t = blockIdx.x * 256u + threadIdx.x, set = t / KC, cc = t - set * KC;
+    const size_t row0 = (size_t)set * ROWS;
+    if (row0 >= (size_t)N) return;                        // (K is a multiple of 128: the 16 lanes of a group stay together)
     const float p2n = __uint_as_float((unsigned)(n_pts + 127) << 23);    // 2^n, 0 <= n <= 126
-    const int sub = threadIdx.x & 15;
-    fq_v4i w[UNROLL];
-    fq_v4f l0[UNROLL], l1[UNROLL];
+    const bool many = n_pts > FQW_MANY_PTS;
+    const float back = many ? 1.0f : __uint_as_float((unsigned)(127 - n_pts) << 23), up = many ? 1.0f : p2n;
+    fq_v4i w[ROWS];
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-        const size_t grp = grp0 + 16u * u < groups ? grp0 + 16u * u : groups - 1;   // (past the end: repeated, not stored)
-        const size_t e0 = grp * FQ_GROUP + 8 * sub;       // K is a multiple of 128: a group never straddles rows
-        w[u] = *reinterpret_cast<const fq_v4i*>(W + e0);
-        if (lambda) {
-            const int k = (int)(grp % (size_t)(K / FQ_GROUP)) * FQ_GROUP + 8 * sub;
-            l0[u] = *reinterpret_cast<const fq_v4f*>(lambda + k);
-            l1[u] = *reinterpret_cast<const fq_v4f*>(lambda + k + 4);
-        }
+    for (int u = 0; u < ROWS; ++u) {
+        const size_t row = row0 + u < (size_t)N ? row0 + u : (size_t)N - 1;   // (past the end: repeated, not stored)
+        w[u] = *reinterpret_cast<const fq_v4i*>(W + row * (size_t)K + 8u * cc);
+    }
+    fq_v4f l0 = {1.f, 1.f, 1.f, 1.f}, l1 = l0;
+    if (lambda) {
+        l0 = *reinterpret_cast<const fq_v4f*>(lambda + 8u * cc);
+        l1 = *reinterpret_cast<const fq_v4f*>(lambda + 8u * cc + 4);
     }
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-        const size_t grp = grp0 + 16u * u;
+    for (int u = 0; u < ROWS; ++u) {
         float v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const unsigned word = (unsigned)w[u][i >> 1];
-            v[i] = __uint_as_float((i & 1) ? (word & 0xFFFF0000u) : (word << 16));
+            v[i] = __uint_as_float((i & 1) ? (word & 0xFFFF0000u) : (word << 16)) * (i < 4 ? l0[i & 3] : l1[i & 3]);
         }
-        if (lambda) {
+        if (many) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                v[i] *= l0[u][i];
-                v[4 + i] *= l1[u][i];
-            }
+            for (int i = 0; i < 8; ++i) v[i] *= p2n;
         }
         float vmax = 0.f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            v[i] *= p2n;
-            vmax = fmaxf(vmax, fabsf(v[i]));
-        }
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, o, 64));
-        const float sigma = fminf(vmax / 7.0f, 448.0f);
+        for (int i = 0; i < 8; ++i) vmax = fmaxf(vmax, fabsf(v[i]));
+        // over the group's 16 lanes: pairs, quads, eights, sixteens
+        vmax = fqw_dpp_max<0xB1>(vmax);
+        vmax = fqw_dpp_max<0x4E>(vmax);
+        vmax = fqw_dpp_max<0x141>(vmax);                  // row_half_mirror
+        vmax = fqw_dpp_max<0x140>(vmax);                  // row_mirror
+        const float vm = vmax * up, s0 = vm * (1.0f / 7.0f);
+        const float sigma = fminf(fmaf(fmaf(-7.0f, s0, vm), 1.0f / 7.0f, s0), 448.0f);   // (an infinity: NaN, and so 448)
         unsigned code = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(sigma, sigma, 0, false) & 0xFFu;   // nearest even
         float s8 = __builtin_amdgcn_cvt_f32_fp8((int)code, 0);
         if (!sigma_rne && s8 > sigma) {                   // toward zero: one code down (positive codes are ordered)
             code -= 1u;
             s8 = __builtin_amdgcn_cvt_f32_fp8((int)code, 0);
         }
-        unsigned out[2] = {0u, 0u};
-        const float r = s8 > 0.f ? 1.0f / s8 : 0.f, cut = 16.0f * s8;    // (sigma8 = 0: every code comes out 0)
+        const float r0 = __builtin_amdgcn_rcpf(s8);
+        const float r = s8 > 0.f ? fmaf(fmaf(-s8, r0, 1.0f), r0, r0) * up : 0.f, sb = s8 * back;
+        if (!(s8 > 0.f) || !(vm < __builtin_inff())) {
+            const float cut = 16.0f * sb;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = fminf(fmaxf(v[i], -cut), cut);
+        }
+        unsigned y[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const float x = fminf(fmaxf(v[i], -cut), cut);
-            const float q0 = x * r;
-            const float q1 = fmaf(fmaf(-q0, s8, x), r, q0);
-            const int c = (int)fminf(fmaxf(rintf(q1), -8.f), 7.f);
-            out[i >> 2] |= (unsigned)(c & 0xFF) << (8 * (i & 3));
+            const float q0 = v[i] * r;
+            const float q1 = fmaf(fmaf(-q0, sb, v[i]), r, q0);
+            y[i] = __float_as_uint(__builtin_amdgcn_fmed3f(q1, -8.f, 7.f) + 12582912.0f);
         }
-        if (grp < groups) {
-            *reinterpret_cast<fq_v2i*>(q + grp * FQ_GROUP + 8 * sub) = (fq_v2i){(int)out[0], (int)out[1]};
-            if (sub == 0) gs[grp] = (uint8_t)code;
+        fq_v2i out;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const unsigned lo = __builtin_amdgcn_perm(y[4 * x + 1], y[4 * x], 0x0C0C0400u);
+            const unsigned hi = __builtin_amdgcn_perm(y[4 * x + 3], y[4 * x + 2], 0x04000C0Cu);
+            out[x] = (int)(lo | hi);
+        }
+        const size_t row = row0 + u;
+        if (row < (size_t)N) {
+            *reinterpret_cast<fq_v2i*>(q + row * (size_t)K + 8u * cc) = out;
+            if ((cc & 15u) == 0) gs[row * (size_t)(K / FQ_GROUP) + (cc >> 4)] = (uint8_t)code;
         }
     }
 }
@@ -614,11 +638,11 @@ void fq_launch_pts_exponent(const uint16_t* W, const float* lambda, int* n_out, 
 void fq_launch_quantize_weights(const uint16_t* W, const float* lambda, int n_pts, bool sigma_rne, int8_t* q,
                                 uint8_t* gs, int N, int K, hipStream_t stream) {
     const size_t groups = (size_t)N * (size_t)(K / FQ_GROUP);
-#define FQW_QUANTIZE(U_) \
-    hipLaunchKernelGGL((fq_quantize_weights_kernel<U_>), dim3((unsigned)((groups + 16u * U_ - 1u) / (16u * U_))), dim3(256), 0, stream, W, lambda, \
-                       n_pts, sigma_rne ? 1 : 0, q, gs, groups, K)
-    // one group at a time where that takes at most four workgroups per compute unit: a second one only adds its latency (512 x 1024,
-    // 4096 groups: 3.2 us with two, 2.6 with one; 512 x 4096, 16384 groups: 3.8, 3.3; 1024 x 4096: 5.0, 5.1)
+#define FQW_QUANTIZE(R_) \
+    hipLaunchKernelGGL((fq_quantize_weights_kernel<R_>), dim3((unsigned)(((size_t)((N + R_ - 1) / R_) * (size_t)(K / 8) + 255u) / 256u)), dim3(256), \
+                       0, stream, W, lambda, n_pts, sigma_rne ? 1 : 0, q, gs, N, K)
+    // one row at a time where that takes at most four workgroups per compute unit: a second one only adds its latency (512 x 4096, 16384
+    // groups: 3.3 us with one, 3.8 with two; 1024 x 4096: 5.1, 5.0)
     if (groups <= 16384u) FQW_QUANTIZE(1);
     else FQW_QUANTIZE(2);
 #undef FQW_QUANTIZE

@@ -202,6 +202,23 @@ def test_quantize_weights_at_the_edges_of_a_workgroup(fq, N, K, n_pts):
         assert np.array_equal(gs.cpu().numpy(), gr) and np.array_equal(q.cpu().numpy(), qr)
 
 
+@pytest.mark.parametrize("n_pts", [0, 63, 64, 65, 100, 126])
+@pytest.mark.parametrize("N,K", [(3, 128), (257, 8320)])
+def test_quantize_weights_from_the_smallest_to_the_largest_weights(fq, N, K, n_pts):
+    """Magnitudes from bf16's smallest to its largest, so that v * 2^n lies below, in and above the scale's range on both sides of
+    the exponent from which 2^n multiplies the weights instead of the scale; an odd number of rows, so that the last pair is half a
+    pair: codes and scales bit for bit."""
+    rng = np.random.default_rng(N + n_pts)
+    e = np.repeat(rng.integers(0, 255, (N, K // 128)), 128, axis=1)        # one exponent per group, three binades wide
+    e = np.clip(e - rng.integers(0, 3, (N, K)), 0, 254)
+    e[0, :128] = 135 - n_pts                                               # a group in the middle of the scale's range
+    Wb = ((rng.integers(0, 2, (N, K)) << 15) | (e << 7) | rng.integers(0, 128, (N, K))).astype(np.uint16)
+    for rne in (False, True):
+        q, gs = fq.fq_quantize_weights(to_gpu_bf16(Wb), None, n_pts, rne)
+        qr, gr = oracle.quantize_weights(Wb, None, n_pts, sigma_rne=rne)
+        assert np.array_equal(gs.cpu().numpy(), gr) and np.array_equal(q.cpu().numpy(), qr)
+
+
 @pytest.mark.parametrize("N,K", [(5, 72), (700, 72), (129, 8208), (70, 16392), (3, 75)])
 def test_cas_scales_of_channels_that_are_not_finite(fq, N, K):
     """A NaN anywhere in a channel gives a NaN scale, an infinity a scale of 0, in every form of the kernel (K odd: the one
