@@ -93,27 +93,82 @@ __device__ __forceinline__ float fq_silu_mul(float g, float u) {
 __device__ __forceinline__ float fq_bf16_hi(unsigned w) { return __uint_as_float(w & 0xFFFF0000u); }
 __device__ __forceinline__ float fq_bf16_lo(unsigned w) { return __uint_as_float(w << 16); }
 
-// x / s.  FAST: from rcp = 1 / s with one exact residual step; the E4M3 code of the result equals that
-// of the IEEE quotient for every finite bf16 x with |x| <= 448 * s and s in [2^-60, 2^60] (checked
-// exhaustively by a host program); otherwise the full division.  FAST is a template argument so that
-// the choice is made once per row (fq_scale_is_fast), not per element.
-template <bool FAST>
-__device__ __forceinline__ float fq_quotient(float x, float s, float rcp) {
-    if (!FAST) return x / s;
-    const float q = x * rcp;
-    const float e = fmaf(-q, s, x);
-    return copysignf(fmaf(e, rcp, q), x);
+// The largest magnitude of a row is searched among the bf16 patterns (they order as the numbers do, NaN patterns above all),
+// two to an instruction.
+typedef unsigned short fq_v2us __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ fq_v2us fq_pattern_max(fq_v2us m, fq_v4i v) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) m = __builtin_elementwise_max(m, __builtin_bit_cast(fq_v2us, (unsigned)v[j] & 0x7FFF7FFFu));
+    return m;
 }
 
-__device__ __forceinline__ bool fq_scale_is_fast(float s) { return s >= 0x1p-60f && s <= 0x1p60f; }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned fq_dpp_umax(unsigned v) {
+    const unsigned o = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+    return o > v ? o : v;
+}
 
-// Four quotients -> four E4M3 codes (nearest even, saturating at +-448 instead of becoming NaN).
+// The largest value of 16 neighbouring lanes, in each of them: pairs, quads, eights, sixteens.
+__device__ __forceinline__ unsigned fq_row16_max(unsigned v) {
+    v = fq_dpp_umax<0xB1, 0xF>(v);
+    v = fq_dpp_umax<0x4E, 0xF>(v);
+    v = fq_dpp_umax<0x141, 0xF>(v);
+    return fq_dpp_umax<0x140, 0xF>(v);
+}
+
+// The largest value of a wave, in every lane (all 64 lanes take part).
+__device__ __forceinline__ unsigned fq_wave_max(unsigned v) {
+    v = fq_row16_max(v);
+    v = fq_dpp_umax<0x142, 0xA>(v);                       // row 0 -> 1, row 2 -> 3
+    v = fq_dpp_umax<0x143, 0xC>(v);                       // rows 0, 1 -> 2, 3
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+#define FQ_BF16_INF 0x7F80u                               // patterns above it are NaN
+
+// The largest magnitude of eight bf16, NaN passed over (rows that hold a NaN only).
+__device__ __forceinline__ float fq_absmax_numbers(float amax, fq_v4i v) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const unsigned w = (unsigned)v[j];
+        amax = fmaxf(amax, fmaxf(fabsf(fq_bf16_lo(w)), fabsf(fq_bf16_hi(w))));
+    }
+    return amax;
+}
+
+// A row's scale s = absmax / 448 (1 for an all-zero row) from the largest pattern, and the reciprocal that the short quotient takes.
+// Both are the IEEE quotients: s by one exact residual step from absmax * fp32(1 / 448), r by one step of Newton's from the
+// hardware's reciprocal (tests/host: every significand of absmax, every estimate within one unit).  `fast`: s lies in
+// [2^-60, 2^60], where those steps and the short quotient were checked; else the full divisions.
+struct fq_row_scale { float s, rcp; bool fast; };
+__device__ __forceinline__ fq_row_scale fq_scale_of(unsigned top) {
+    const float amax = __uint_as_float(top << 16), c = 1.0f / 448.0f, q = amax * c;
+    fq_row_scale o;
+    o.s = top == 0u ? 1.0f : fmaf(fmaf(-448.0f, q, amax), c, q);
+    o.fast = o.s >= 0x1p-60f && o.s <= 0x1p60f;           // (an infinity: NaN, and so the full division)
+    if (!o.fast) o.s = amax / 448.0f;
+    const float r0 = __builtin_amdgcn_rcpf(o.s);
+    o.rcp = fmaf(fmaf(-o.s, r0, 1.0f), r0, r0);
+    return o;
+}
+
+// Four quotients x / s -> four E4M3 codes (nearest even).  FAST (finite x, |x| <= absmax, s in [2^-60, 2^60]): q = x * r, the
+// residual e = fma(q, s, -x), fma(e, -r, q), whose code is that of the IEEE quotient, sign of zero included (a zero's residual
+// is +0, and +0 times -r adds nothing to either zero); no quotient passes 448 by more than its rounding.  Otherwise the
+// full division, saturating at +-448 (a NaN becomes -448).  FAST is a template argument so that the choice is made once per
+// row, not per element.
+template <bool FAST>
+__device__ __forceinline__ float fq_quotient(float x, float s, float rcp) {
+    if (!FAST) return fminf(fmaxf(x / s, -448.f), 448.f);
+    const float q = x * rcp;
+    return fmaf(fmaf(q, s, -x), -rcp, q);
+}
+
 template <bool FAST>
 __device__ __forceinline__ unsigned fq_quant4(float a, float b, float c, float d, float s, float rcp) {
-    a = fminf(fmaxf(fq_quotient<FAST>(a, s, rcp), -448.f), 448.f);
-    b = fminf(fmaxf(fq_quotient<FAST>(b, s, rcp), -448.f), 448.f);
-    c = fminf(fmaxf(fq_quotient<FAST>(c, s, rcp), -448.f), 448.f);
-    d = fminf(fmaxf(fq_quotient<FAST>(d, s, rcp), -448.f), 448.f);
+    a = fq_quotient<FAST>(a, s, rcp);
+    b = fq_quotient<FAST>(b, s, rcp);
+    c = fq_quotient<FAST>(c, s, rcp);
+    d = fq_quotient<FAST>(d, s, rcp);
     int r = 0;
     r = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, r, false);
     r = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, r, true);

@@ -30,6 +30,17 @@ __device__ __forceinline__ unsigned fqs_a_offset(int lane, int m0, int M, int K,
     return m < M ? (unsigned)m * (unsigned)K + (unsigned)(lane & 3) * 16u : oob;
 }
 
+// The larger of a's two halves in lanes 0-31 and of b's in lanes 32-63; of a's neighbouring quarters in quarters 0 and 2, of b's
+// in 1 and 3.
+__device__ __forceinline__ unsigned fqs_swap32_max(unsigned a, unsigned b) {
+    const auto h = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    return h[0] > h[1] ? h[0] : h[1];
+}
+__device__ __forceinline__ unsigned fqs_swap16_max(unsigned a, unsigned b) {
+    const auto h = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    return h[0] > h[1] ? h[0] : h[1];
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------------------------
@@ -51,7 +62,6 @@ __device__ __forceinline__ unsigned fqs_a_offset(int lane, int m0, int M, int K,
 #define FQS16_THREADS 512
 #define FQS16_WAVES 8
 #define FQS16_MAXCOLS 112                                 // channels of a workgroup (7 sub-tiles: 56 KiB of partial sums in LDS)
-#define FQS16_FUSED_MAX_M 6                               // rows up to which quantising inside the GEMM kernel pays (<= waves)
 #define FQS16_OOB 0xFFFFFF00u                             // beyond any 32-bit buffer size
 // byte `i` (0..3, compile-time) of a word of E4M3 codes -> float
 __device__ __forceinline__ float fq_e4m3_byte_to_float(unsigned w, int i) {
@@ -142,23 +152,25 @@ struct fqs16_ring {
     }
 };
 
-// FUSEDQ (M <= 6, K <= 4096): `A` holds the bf16 activations X [M,K] instead of E4M3 codes, and the
-// kernel quantises them itself (Sec. 2.1 eq. 2, the arithmetic of the quantiser kernel): wave w reads
-// row w of X whole (coalesced 16-byte loads into registers), takes its maximum, converts it and
-// leaves the codes in LDS ([M rows][K + 16 bytes]: the pad spreads the rows over the banks); after one
-// barrier every wave fetches the operands of its K slice from there.  All of that happens while the
-// weights are on their way.  Every workgroup repeats it for all of X, which for a few rows costs
-// less than a second kernel (measured at N = 14336, K = 4096: 8.4 against 10.0 us at M = 1, 8.8 against
-// 10.1 at M = 4, 10.5 against 10.3 at M = 8: the conversion is some ten instructions per element, on
-// every compute unit).  `a_scale` is not read;
-// `a_scale_out` (may be NULL) receives the row scales.  Dynamic LDS: 8 * (K + 16) bytes.
-template <int NSUB, bool ROUNDS, int BATCH_, bool TURN, bool FUSEDQ = false>
+// FUSEDQ (M <= QROWS <= 8, K <= 4096): `A` holds the bf16 activations X [M,K] instead of E4M3 codes, and the kernel quantises
+// them itself (Sec. 2.1 eq. 2, the arithmetic of the quantiser kernel) while the weights are on their way; every workgroup
+// repeats it for all of X, some six instructions per element, which for a few rows costs less than a second kernel.
+// Up to four sub-tiles a wave reads the part of every row that its own slice of K multiplies, one 16-byte load per lane and row;
+// the waves exchange the parts' largest patterns through LDS, and each converts its part and turns the codes into operands through
+// LDS of its own.  The weights are requested when all waves have asked for their activations: the later waves' would queue up
+// behind the weights of those before them (4096 x 4096, M = 1 / 4 / 8: 3.92 / 4.54 / 5.28 us without that barrier, 3.44 / 3.84 / 4.90
+// with it; 5.22 / 5.29 with the first form of the conversion, a row per wave, 6.26 with two kernels at M = 8).  BYROW: wave w reads,
+// converts and leaves row w for all, which is the faster way with five sub-tiles and more, where a wave's weights alone fill the
+// queues (28672 x 4096, M = 1 and 4: by slices 13.3 and 14.2 us, by rows 12.8 and 13.0), and for short slices (fq_launch_linear16).
+// `a_scale` is not read; `a_scale_out` (may be NULL) receives the row scales.
+template <int NSUB, bool ROUNDS, int BATCH_, bool TURN, int QROWS = 0, bool BYROW_ = false>
 __global__ __launch_bounds__(FQS16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void fq_gemm_small16_kernel(
     const uint8_t* __restrict__ A, const float* __restrict__ a_scale, const uint8_t* __restrict__ wp,
     const uint8_t* __restrict__ gs, float tscale, uint16_t* Y, int M, int N, int K, int cols,
     int swiglu, const uint16_t* R, float* __restrict__ a_scale_out) {
-    static_assert(!(FUSEDQ && ROUNDS), "the fused form serves K <= 4096: a slice is at most four groups");
+    constexpr bool FUSEDQ = QROWS > 0;                    // rows the fused form has room for
+    static_assert(!(FUSEDQ && (ROUNDS || BATCH_ != 4)) && QROWS <= 16, "the fused form serves K <= 4096: a slice is at most four groups");
     typedef fqs16_ring<NSUB, BATCH_> ring_t;
     constexpr int BATCH = ring_t::BATCH;
     __shared__ float red[FQS16_WAVES][NSUB][4][64];
@@ -215,63 +227,134 @@ void fq_gemm_small16_kernel(
     for (int j = 0; j < NSUB; ++j) acc[j] = (fq_v4f){0.f, 0.f, 0.f, 0.f};
 
     ring_t ring;
-    extern __shared__ __attribute__((aligned(16))) uint8_t codes[];   // FUSEDQ: [8][K + 16] E4M3 codes
-    __shared__ float srow[FQS16_WAVES];                   // FUSEDQ: row scales
-    constexpr int XCH = 8;                                // 16-byte chunks of a row per lane: K <= 4096
-    fq_v4i xr[FUSEDQ ? XCH : 1];
-    const bool my_row = FUSEDQ && wave < M;               // wave w quantises row w (M <= 6 < number of waves)
+    constexpr bool BYROW = FUSEDQ && BYROW_;              // wave w quantises row w, else its own slice of all rows
+    constexpr int XN = !FUSEDQ ? 1 : BYROW ? 8 : QROWS;   // 16-byte chunks a lane holds: of its row (K <= 4096), or one per row
+    // codes: rows 528 bytes apart in each wave's part, or 4112 (which spreads the rows of an operand over the banks)
+    constexpr int QSTRIDE = BYROW ? 4096 + 16 : 512 + 16;
+    __shared__ __attribute__((aligned(16))) uint8_t codes[!FUSEDQ || BYROW ? 1 : FQS16_WAVES][FUSEDQ ? QROWS * QSTRIDE : 1];
+    __shared__ __attribute__((aligned(16))) unsigned tops[FUSEDQ ? 16 : 1][FQS16_WAVES];   // largest pattern by row and wave
+    __shared__ float srow[FUSEDQ ? FQS16_WAVES : 1];      // row scales
+    fq_v4i xr[XN];
+    const bool my_row = BYROW && wave < M;
+    const bool mine = lane < 16 * (g_end - g_begin);      // lanes whose chunk lies in the wave's slice
     if (FUSEDQ) {                                         // first in the queue: they are needed first
 #pragma unroll
-        for (int c = 0; c < XCH; ++c) {
+        for (int c = 0; c < XN; ++c) {
             const int chunk = lane + 64 * c;
-            const unsigned off = (my_row && chunk < (K >> 3)) ? ((unsigned)wave * (unsigned)K * 2u + (unsigned)chunk * 16u) : FQS16_OOB;
-            xr[c] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsA, off, 0, 0));
+            const unsigned off = BYROW ? (unsigned)wave * (unsigned)K * 2u + (unsigned)chunk * 16u
+                                       : (unsigned)c * (unsigned)K * 2u + (unsigned)g_begin * (2u * FQ_GROUP) + (unsigned)lane * 16u;
+            const bool on = BYROW ? my_row && chunk < (K >> 3) : mine && c < M;
+            xr[c] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsA, on ? off : FQS16_OOB, 0, 0));
         }
+        __builtin_amdgcn_sched_barrier(0);
+        if (!BYROW) asm volatile("s_barrier");
+        __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int i = 0; i < BATCH; ++i) ring.template issue<!FUSEDQ, TURN>(i, rsA, rsW, rsG, aoff, woff, goff, g_begin + i, g_end);
     __builtin_amdgcn_sched_barrier(0);                    // all requests go out before any arithmetic
-    if (FUSEDQ) {
-        const int stride = K + 16;
-        if (my_row) {
-            float amax = 0.f;
-#pragma unroll
-            for (int c = 0; c < XCH; ++c)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const unsigned w = (unsigned)xr[c][e];
-                    amax = fmaxf(amax, fmaxf(fabsf(fq_bf16_lo(w)), fabsf(fq_bf16_hi(w))));
-                }
+    if constexpr (FUSEDQ) {
+        // the largest of a wave's numbers where there are NaN among them
+        auto numbers_top = [&](float amax) __attribute__((always_inline)) {
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
-            const float s = amax == 0.f ? 1.0f : amax / 448.0f;   // the quantiser's scale (an all-zero row: 1)
-            const float rcp = 1.0f / s;
-            if (lane == 0) {
-                srow[wave] = s;
-                if (a_scale_out != nullptr && blockIdx.x == 0) a_scale_out[wave] = s;
+            return __float_as_uint(amax) >> 16;
+        };
+        uint8_t* own = codes[BYROW ? 0 : wave];
+        float s_out = 0.f;                                // lane l < M: the scale of row l (BYROW: every lane the wave's row's)
+        if constexpr (BYROW) {
+            if (my_row) {
+                fq_v2us most = {0, 0};
+#pragma unroll
+                for (int c = 0; c < XN; ++c) most = fq_pattern_max(most, xr[c]);
+                unsigned top = fq_wave_max(most[0] > most[1] ? most[0] : most[1]);
+                const bool nan = top > FQ_BF16_INF;
+                if (nan) {
+                    float amax = 0.f;
+#pragma unroll
+                    for (int c = 0; c < XN; ++c) amax = fq_absmax_numbers(amax, xr[c]);
+                    top = numbers_top(amax);
+                }
+                const fq_row_scale sc = fq_scale_of(top);
+                if (lane == 0) {
+                    srow[wave] = sc.s;
+                    if (a_scale_out != nullptr && blockIdx.x == 0) a_scale_out[wave] = sc.s;
+                }
+                auto convert = [&](auto fast_tag) __attribute__((always_inline)) {
+                    constexpr bool FAST = decltype(fast_tag)::value;
+#pragma unroll
+                    for (int c = 0; c < XN; ++c)
+                        if (lane + 64 * c < (K >> 3))
+                            *reinterpret_cast<fq_v2i*>(own + wave * QSTRIDE + (lane + 64 * c) * 8) = fq_quant8<FAST>(xr[c], sc.s, sc.rcp);
+                };
+                if (__builtin_amdgcn_readfirstlane((int)(sc.fast && !nan))) convert(std::true_type());
+                else convert(std::false_type());
             }
-            // one choice of quotient per row (s is the same in every lane), then straight-line code
+            __syncthreads();
+            own += g_begin * FQ_GROUP;
+        } else {
+            // lane l holds row l % 16's largest pattern, as the maxima of all waves make it
+            auto row_top = [&]() __attribute__((always_inline)) {
+                __syncthreads();
+                unsigned v = 0u;
+#pragma unroll
+                for (int w = 0; w < FQS16_WAVES; ++w) { const unsigned o = tops[r16][w]; v = o > v ? o : v; }
+                return r16 < M ? v : 0u;
+            };
+            unsigned v[QROWS];
+#pragma unroll
+            for (int m = 0; m < QROWS; ++m) {
+                const fq_v2us p = fq_pattern_max((fq_v2us){0, 0}, xr[m]);
+                v[m] = p[0] > p[1] ? p[0] : p[1];
+            }
+            if constexpr (QROWS == 1) {
+                const unsigned o = fq_wave_max(v[0]);
+                if (lane == 0) tops[0][wave] = o;
+            } else {
+                // four rows to a register: halves and quarters change places until quarter j of the wave holds row j
+                static_assert(QROWS % 4 == 0, "whole registers of rows");
+#pragma unroll
+                for (int m = 0; m < QROWS; m += 4) {
+                    const unsigned o = fq_row16_max(fqs_swap16_max(fqs_swap32_max(v[m], v[m + 2]), fqs_swap32_max(v[m + 1], v[m + 3])));
+                    if (r16 == 0) tops[m + kq][wave] = o;
+                }
+            }
+            unsigned top = row_top();
+            const bool nan = __any(top > FQ_BF16_INF);    // the same in every wave
+            if (nan) {
+                __syncthreads();
+#pragma unroll
+                for (int m = 0; m < QROWS; ++m) {
+                    const unsigned o = numbers_top(fq_absmax_numbers(0.f, xr[m]));
+                    if (lane == 0) tops[m][wave] = o;
+                }
+                top = row_top();
+            }
+            const fq_row_scale sc = fq_scale_of(top);
+            s_out = sc.s;
+            if (a_scale_out != nullptr && blockIdx.x == 0 && threadIdx.x < (unsigned)M) a_scale_out[threadIdx.x] = sc.s;
+            // one choice of quotient for all rows (the full division gives the same codes), then straight-line code
             auto convert = [&](auto fast_tag) __attribute__((always_inline)) {
                 constexpr bool FAST = decltype(fast_tag)::value;
 #pragma unroll
-                for (int c = 0; c < XCH; ++c) {
-                    const int chunk = lane + 64 * c;
-                    if (chunk < (K >> 3))
-                        *reinterpret_cast<fq_v2i*>(codes + wave * stride + chunk * 8) = fq_quant8<FAST>(xr[c], s, rcp);
-                }
+                for (int m = 0; m < QROWS; ++m)
+                    if (m < M) {
+                        const float s = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(sc.s), m));
+                        const float rcp = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(sc.rcp), m));
+                        *reinterpret_cast<fq_v2i*>(own + m * QSTRIDE + lane * 8) = fq_quant8<FAST>(xr[m], s, rcp);
+                    }
             };
-            if (__builtin_amdgcn_readfirstlane((int)fq_scale_is_fast(s))) convert(std::true_type());
+            if (!nan && __all(sc.fast)) convert(std::true_type());
             else convert(std::false_type());
+            fqs_wave_order();                             // (the wave's own LDS: its accesses stay in order)
         }
-        __syncthreads();
         // operands of this wave's slice: row r16 (rows past M repeat the last one, as the unfused form does)
-        const uint8_t* arow = codes + (r16 < M ? r16 : M - 1) * stride + kq * 32;
+        const uint8_t* arow = own + (r16 < M ? r16 : M - 1) * QSTRIDE + kq * 32;
 #pragma unroll
         for (int i = 0; i < BATCH; ++i) {
-            const int g = g_begin + i;
-            if (g < g_end) {
-                ring.aq[i][0] = *reinterpret_cast<const fq_v4i*>(arow + g * FQ_GROUP);
-                ring.aq[i][1] = *reinterpret_cast<const fq_v4i*>(arow + g * FQ_GROUP + 16);
+            if (!BYROW || g_begin + i < g_end) {          // (a wave's own part holds zeros past its slice)
+                ring.aq[i][0] = *reinterpret_cast<const fq_v4i*>(arow + i * FQ_GROUP);
+                ring.aq[i][1] = *reinterpret_cast<const fq_v4i*>(arow + i * FQ_GROUP + 16);
             } else {
                 ring.aq[i][0] = ring.aq[i][1] = (fq_v4i){0, 0, 0, 0};
             }
@@ -279,8 +362,8 @@ void fq_gemm_small16_kernel(
 #pragma unroll
         for (int i = 0; i < NOUT; ++i) {
             const int idx = threadIdx.x + i * FQS16_THREADS;
-            const int m = 4 * ((idx & 63) >> 4) + ((idx >> 6) & 3);
-            osc[i] = srow[m < M ? m : M - 1];
+            const int m = 4 * ((idx & 63) >> 4) + ((idx >> 6) & 3), mc = m < M ? m : M - 1;
+            osc[i] = BYROW ? srow[mc] : __shfl(s_out, mc, 64);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -376,19 +459,21 @@ void fq_launch_small16b(unsigned grid, hipStream_t stream, const uint8_t* A, con
                        A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R, static_cast<float*>(nullptr));
 }
 
-// The fused form (bf16 activations in, quantised by the kernel): slices of at most four groups per wave
-// (K <= 4096), for which a slice of X fits into registers beside the ring.
+// The fused form (bf16 activations in, quantised by the kernel): slices of at most four groups per wave (K <= 4096), of which a
+// lane holds a chunk per row.
 template <int NSUB>
 bool fq_launch_linear16(int per, unsigned grid, hipStream_t stream, const uint16_t* X, float* a_scale_out,
                         const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols) {
     if (per > 4) return false;
-    const size_t lds = (size_t)8 * (size_t)(K + 16);      // the codes of X
-    static fq_device_once attr_once;                       // (one per template instance)
-    fq_once_per_device(attr_once, [] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fq_gemm_small16_kernel<NSUB, false, 4, false, true>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 8 * (4096 + 16));
-    });
-    hipLaunchKernelGGL((fq_gemm_small16_kernel<NSUB, false, 4, false, true>), dim3(grid), dim3(FQS16_THREADS), lds, stream,
+    // by rows or by slices (see the kernel): by rows with five sub-tiles and more, and where slices are so short that most of a wave's
+    // lanes would have nothing of them (by rows / by slices, us: 4 x 4096 x 1024 3.70 / 3.95, 6 rows 4.01 / 4.58, 2 rows 3.59 / 3.59;
+    // 6 x 4096 x 1152 4.07 / 4.60, 6 x 12288 x 1408 6.17 / 6.29; on the other side 6 x 4096 x 2048 4.74 / 4.61, 4 rows 4.24 / 3.99)
+    constexpr bool WIDE = NSUB > 4;
+    auto kernel = M == 1 ? fq_gemm_small16_kernel<NSUB, false, 4, false, 1, WIDE> : M <= 4 ? fq_gemm_small16_kernel<NSUB, false, 4, false, 4, WIDE>
+                                                                                           : fq_gemm_small16_kernel<NSUB, false, 4, false, 8, WIDE>;
+    if (M >= 3 && K <= 1536)
+        kernel = M <= 4 ? fq_gemm_small16_kernel<NSUB, false, 4, false, 4, true> : fq_gemm_small16_kernel<NSUB, false, 4, false, 8, true>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(FQS16_THREADS), 0, stream,
                        reinterpret_cast<const uint8_t*>(X), static_cast<const float*>(nullptr), wp, gs, tscale, Y, M, N, K, cols,
                        0, static_cast<const uint16_t*>(nullptr), a_scale_out);
     return true;
@@ -751,13 +836,18 @@ fqs_shape fqs_shape_of(int M, int N, int K, int max_cols) {
 
 }  // namespace
 
-bool fq_linear_small_serves(int M, int K) {
-    return M >= 1 && M <= FQS16_FUSED_MAX_M && (K / FQ_GROUP + FQS16_WAVES - 1) / FQS16_WAVES <= 4;
+// Rows up to which quantising inside the GEMM kernel pays, for slices of at most four groups: one kernel / two kernels, us, at 7 and 8
+// rows: 4096 x 4096 5.3 / 6.2 and 4.9 / 6.3, 14336 x 4096 9.0 / 9.2 and 9.3 / 9.4, 1024 x 4096 4.6 / 6.0, 4096 x 1024 4.9 / 5.5; 12 rows, an
+// earlier form: 4096 x 4096 7.2 / 6.5, 14336 x 4096 11.6 / 9.9.  With more than
+// 64 channels per compute unit up to six (6 x 28672 x 4096 15.3 us in one kernel, 8 rows 14.4 in two).
+bool fq_linear_small_serves(int M, int N, int K) {
+    if (M < 1 || M > 8 || (K / FQ_GROUP + FQS16_WAVES - 1) / FQS16_WAVES > 4) return false;
+    return M <= 6 || fqs_shape_of(M, N, K, FQS16_MAXCOLS).nsub <= 4;
 }
 
 bool fq_launch_linear_small(const uint16_t* X, float* a_scale_out, const uint8_t* wp, const uint8_t* gs, float tscale,
                             uint16_t* Y, int M, int N, int K, hipStream_t stream) {
-    if (!fq_linear_small_serves(M, K)) return false;
+    if (!fq_linear_small_serves(M, N, K)) return false;
     const fqs_shape sh = fqs_shape_of(M, N, K, FQS16_MAXCOLS);
     switch (sh.nsub) {
         case 1: return fq_launch_linear16<1>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);

@@ -2,13 +2,10 @@
 //   beta = absmax / 448 in FP32 (1 for an all-zero row); quotient as IEEE FP32 division would give
 //   it; conversion to OCP E4M3 round-to-nearest-even by the hardware converter, after clamping to
 //   +-448 so that the result saturates instead of becoming NaN.
-// The quotient.  A full IEEE division is about eleven instructions per element.  With r = 1 / beta
-// (one IEEE division per row), q = x * r, the residual e = fma(-q, beta, x) (exact) and
-// q' = fma(e, r, q), then the sign of x put on q' (beta > 0), the stored E4M3 code equals that of
-// the IEEE quotient for every finite bf16 x with |x| <= absmax and every beta = absmax / 448 in
-// [2^-60, 2^60]: checked exhaustively on the host (5.3e8 pairs; the few quotients that differ in
-// their last bit all come from subnormal x and round to zero).  Rows with beta outside that range
-// take the full division.
+// The quotient.  A full IEEE division is about eleven instructions per element.  With r = 1 / beta, q = x * r, the residual
+// e = fma(q, beta, -x) (exact) and q' = fma(e, -r, q), the stored E4M3 code equals that of the IEEE quotient, the sign of
+// zero included, for every finite bf16 x with |x| <= absmax and every beta = absmax / 448 in [2^-60, 2^60]: checked
+// exhaustively on the host (5.3e8 pairs).  Rows with beta outside that range, or with a NaN, take the full division.
 #include <type_traits>
 #include "fq_common.h"
 #include "fq_kernels.h"
@@ -19,6 +16,11 @@ __device__ __forceinline__ float fq_sum8(fq_v2i o) {
     const fq_v2f a = __builtin_amdgcn_cvt_pk_f32_fp8(o[0], false), b = __builtin_amdgcn_cvt_pk_f32_fp8(o[0], true);
     const fq_v2f c = __builtin_amdgcn_cvt_pk_f32_fp8(o[1], false), d = __builtin_amdgcn_cvt_pk_f32_fp8(o[1], true);
     return ((a[0] + a[1]) + (b[0] + b[1])) + ((c[0] + c[1]) + (d[0] + d[1]));
+}
+
+template <int CTRL>
+__device__ __forceinline__ float fq_dpp_add(float v) {
+    return v + __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, false));
 }
 
 // WPR waves per row, up to CH chunks (of 16 bytes, 8 bf16) of it per thread in registers between the search for the
@@ -41,7 +43,7 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(c
     static_assert(PARTS == 1 || (WPR >= 4 && !ZP && !REREAD), "one row per workgroup, codes only");
     constexpr int WAVES = WPR > 4 ? WPR : 4, ROWS = WAVES / WPR, T = 64 * WPR;
     constexpr int MAXG = T * CH / 16 + 16;           // groups of a row, padded
-    __shared__ float red[WAVES];
+    __shared__ unsigned red[WAVES];
     __shared__ __attribute__((aligned(16))) uint16_t zrow[ZP ? ROWS : 1][2][ZP ? MAXG : 8];   // [row][plane][group]
     const int row = (int)threadIdx.x / T, t = (int)threadIdx.x % T;
     const int m = PARTS > 1 ? (int)blockIdx.x / PARTS : (int)blockIdx.x * ROWS + row, mine = (int)blockIdx.x % PARTS;
@@ -56,14 +58,7 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(c
     const fq_v4i* x = reinterpret_cast<const fq_v4i*>(X + (size_t)(on ? m : M - 1) * K);
     fq_v2i* a = reinterpret_cast<fq_v2i*>(A + (size_t)(on ? m : M - 1) * K);
     fq_v4i keep[CH];
-    float amax = 0.f;
-    auto search = [&](fq_v4i v) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const unsigned w = (unsigned)v[j];
-            amax = fmaxf(amax, fmaxf(fabsf(fq_bf16_lo(w)), fabsf(fq_bf16_hi(w))));
-        }
-    };
+    fq_v2us most = {0, 0};
     if (!REREAD) {
 #pragma unroll
         for (int i = 0; i < CH; ++i) {               // all of the thread's chunks are requested before the first is used
@@ -74,22 +69,39 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(c
             if (CH <= 2 || i * T < nchunk) keep[i] = x[c];
         }
 #pragma unroll
-        for (int i = 0; i < CH; ++i) search(keep[i]);
+        for (int i = 0; i < CH; ++i) most = fq_pattern_max(most, keep[i]);
     } else {
-        for (int c = t; c < nchunk; c += T) search(x[c]);
+        for (int c = t; c < nchunk; c += T) most = fq_pattern_max(most, x[c]);
     }
+    // (WPR > 1: a workgroup is one row)
+    auto over_row = [&](unsigned v) __attribute__((always_inline)) {
+        if (WPR > 1) {
+            if ((t & 63) == 0) red[t >> 6] = v;
+            __syncthreads();
+            v = red[0];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
-    if (WPR > 1) {
-        if ((t & 63) == 0) red[row * WPR + (t >> 6)] = amax;
-        __syncthreads();
-        amax = red[row * WPR];
+            for (int i = 1; i < WPR; ++i) v = red[i] > v ? red[i] : v;
+        }
+        return v;
+    };
+    unsigned top = over_row(fq_wave_max(most[0] > most[1] ? most[0] : most[1]));
+    const bool nan = top > FQ_BF16_INF;                   // the same for the whole row
+    if (nan) {                                            // the largest of the numbers, then
+        float amax = 0.f;
+        if (!REREAD) {
 #pragma unroll
-        for (int i = 1; i < WPR; ++i) amax = fmaxf(amax, red[row * WPR + i]);
+            for (int i = 0; i < CH; ++i) amax = fq_absmax_numbers(amax, keep[i]);
+        } else {
+            for (int c = t; c < nchunk; c += T) amax = fq_absmax_numbers(amax, x[c]);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+        if (WPR > 1) __syncthreads();
+        top = over_row(__float_as_uint(amax) >> 16);
     }
-    const float s = (amax == 0.f) ? 1.0f : amax / 448.0f;
+    const fq_row_scale sc = fq_scale_of(top);
+    const float s = sc.s, rcp = sc.rcp;
     if (t == 0 && on && mine == 0) a_scale[m] = s;
-    const float rcp = 1.0f / s;
     // One choice of quotient per row (s is the same in every thread of a wave): the range the
     // short quotient was checked on, else the full division; straight-line code either way.
     auto convert = [&](auto fast_tag) __attribute__((always_inline)) {
@@ -110,10 +122,10 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(c
                     // a group is 16 consecutive chunks = 16 consecutive lanes (nchunk is a multiple of 16,
                     // so a group's lanes are all here or all absent)
                     float z = fq_sum8(o);
-                    z += __shfl_xor(z, 1, 64);
-                    z += __shfl_xor(z, 2, 64);
-                    z += __shfl_xor(z, 4, 64);
-                    z += __shfl_xor(z, 8, 64);
+                    z = fq_dpp_add<0xB1>(z);              // pairs, quads, eights, sixteens
+                    z = fq_dpp_add<0x4E>(z);
+                    z = fq_dpp_add<0x141>(z);
+                    z = fq_dpp_add<0x140>(z);
                     if ((t & 15) == 0) {
                         z *= -0.015625f;
                         const _Float16 hi = (_Float16)z;                  // round to nearest even
@@ -125,7 +137,7 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(c
             }
         }
     };
-    if (__builtin_amdgcn_readfirstlane((int)fq_scale_is_fast(s))) convert(std::true_type());
+    if (__builtin_amdgcn_readfirstlane((int)(sc.fast && !nan))) convert(std::true_type());
     else convert(std::false_type());
     if (ZP) {
         // padding groups are zero; then one 16-byte store per (plane, 8 groups) of a row, rows of a workgroup side by side

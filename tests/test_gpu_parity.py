@@ -591,7 +591,7 @@ def test_ws_entry_points_replay_in_a_hip_graph(fq, shape):
     check_gemm(got[0], Yr, B, "graph replay")
 
 
-# ---- the whole layer from bf16 activations (one kernel for M <= 6, K <= 4096) -------------------
+# ---- the whole layer from bf16 activations (one kernel for a few rows, K <= 4096) -------------------
 
 LINEAR_SHAPES = [(6, 256, 512), (1, 32, 128), (5, 100, 384), (6, 4120, 512), (6, 8192, 4096), (4, 4096, 4096),
                  (3, 9000, 256), (6, 14336, 4096), (1, 14336, 4096), (5, 300, 1408), (2, 6144, 3072), (7, 100, 384),
@@ -639,6 +639,52 @@ def test_linear_on_every_bf16_magnitude(fq):
     assert np.array_equal(bf16_bits_from_gpu(Yl), bf16_bits_from_gpu(Y2))
     An, sn = oracle.quantize_act(Xb)
     assert np.array_equal(A.cpu().numpy() & 0x7F, An & 0x7F) and np.array_equal(s.cpu().numpy(), sn)
+
+
+@pytest.mark.parametrize("K", [128, 640, 1024, 1536, 1664, 3968, 4096])
+@pytest.mark.parametrize("N", [40, 1000, 9000, 16640])        # one, one, three and five sub-tiles per compute unit
+def test_linear_at_the_edges_of_its_one_kernel_forms(fq, N, K):
+    """1 to 9 rows: both ways of sharing the conversion out, all sizes of their row loops, slices of K that are partly or wholly
+    empty, and beside ordinary rows ones of zeros of both signs, with scales outside the short quotient's range, with NaN and with
+    infinities: bit for bit the quantiser and the GEMM."""
+    d = workloads.draw(9, N, K, seed=N + K, outlier_frac=0.02)
+    packed, gs = fq.fq_pack_weights(_gpu(d["q"])), _gpu(d["gscale"])
+    plain = to_gpu_bf16(d["X_bf16"])
+    odd = plain.float()
+    odd[0] = torch.where(torch.arange(K, device="cuda") % 2 == 0, 0.0, -0.0)
+    odd[3] *= 2.0 ** -100
+    for M in range(1, 10):
+        for X in (plain[:M], odd[:M].to(torch.bfloat16)):
+            A, s = fq.fq_quantize_act(X)
+            assert torch.equal(fq.fq_w4a8_linear(X, packed, gs, 1.0, N).view(torch.int16), fq.fq_w4a8_gemm(A, s, packed, gs, 1.0, N).view(torch.int16)), M
+    odd[1, K - 1], odd[2, 5], odd[4, 0] = float("nan"), float("inf"), -float("inf")
+    for M in (2, 3, 6, 8):
+        X = odd[:M].to(torch.bfloat16)
+        A, s = fq.fq_quantize_act(X)
+        Y, Y2 = fq.fq_w4a8_linear(X, packed, gs, 1.0, N), fq.fq_w4a8_gemm(A, s, packed, gs, 1.0, N)
+        assert torch.equal(torch.nan_to_num(Y), torch.nan_to_num(Y2)) and torch.equal(Y.isnan(), Y2.isnan()), M
+
+
+@pytest.mark.parametrize("M,K", [(1, 8), (3, 1408), (16, 4096), (5, 14336), (32, 32016), (70, 4096), (1600, 2048), (70, 11008), (700, 4224),
+                                 (3, 40000), (2, 70000)])
+def test_quantiser_codes_with_signs_and_rows_that_are_not_finite(fq, M, K):
+    """Every byte of the codes, the sign of zero included, against FP32 division and the library's cast: ordinary rows, zeros of
+    both signs, every scale of the exponent's range; a NaN is passed over in the search and comes out as -448, a row
+    with an infinity has an infinite scale."""
+    g = torch.Generator().manual_seed(M + K)
+    x = torch.randn((M, K), generator=g)
+    x[:, ::5] = torch.where(torch.arange(len(range(0, K, 5))) % 2 == 0, 0.0, -0.0)
+    x *= torch.exp2(torch.randint(-120, 120, (M, 1), generator=g).float()) if M > 2 else 1.0
+    if M > 2:
+        x[M - 1, 1], x[M // 2, K - 1], x[M // 2, 2] = float("nan"), float("inf"), float("nan")
+    X = x.to(torch.bfloat16)
+    f = X.float()
+    amax = torch.nan_to_num(f, nan=0.0, posinf=float("inf"), neginf=-float("inf")).abs().amax(dim=1)
+    s = torch.where(amax == 0, torch.ones_like(amax), amax / 448.0)
+    quot = torch.nan_to_num(f / s[:, None], nan=-448.0).clamp(-448.0, 448.0)
+    A, sg = fq.fq_quantize_act(X.cuda())
+    assert torch.equal(sg.cpu(), s)
+    assert torch.equal(A.cpu().view(torch.uint8), quot.to(torch.float8_e4m3fn).view(torch.uint8))
 
 
 # ---- the paper's table mode (Sec. 3.1.1 step 1) ----------------------------------------------------

@@ -27,3 +27,13 @@ def test_short_quotient_gives_the_ieee_code(tmp_path):
     out = subprocess.run([exe, stride], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout
     assert "E4M3 code differences 0" in out.stdout
+
+
+@pytest.mark.skipif(shutil.which("gcc") is None or not _cpu_has_fma(), reason="needs gcc and a CPU with FMA")
+def test_scale_reciprocal_and_signed_quotient_are_the_ieee_ones(tmp_path):
+    """The kernel's arithmetic as it stands: scale and reciprocal without a division, and the codes with the sign of zero."""
+    exe = str(tmp_path / "activation_quotient_check")
+    src = os.path.join(os.path.dirname(SRC), "activation_quotient_check.c")
+    subprocess.run(["gcc", "-O2", "-mfma", "-fopenmp", "-ffp-contract=off", src, "-o", exe, "-lm"], check=True)
+    out = subprocess.run([exe, "1" if os.environ.get("FQ_EXHAUSTIVE") else "3"], capture_output=True, text=True)
+    assert out.returncode == 0 and "differences 0" in out.stdout, out.stdout
