@@ -212,7 +212,7 @@ int fq_w4a8_gemm_swiglu_quant_ws(const uint8_t *A_fp8, const float *a_scale, con
  * GEMM of Sec. 2.2 eq. 3, with the result fq_quantize_act + fq_w4a8_gemm_ws give, bit for bit.
  * For M <= 6 and K <= 4096 (decode) it is ONE kernel: every workgroup quantises the few rows of
  * X itself while its weights are on their way, no codes or scales go through memory, and no
- * workspace is needed (7 and 8 rows of a layer with at most 64 channels per compute unit take the same kernel, but
+ * workspace is needed (7 and 8 rows, and up to 4 rows of longer K, take the same kernel where it is the faster way, but
  * a workspace is asked for).  Otherwise the call runs the quantiser and the GEMM one after the other
  * and keeps the codes, the row scales and the GEMM's own scratch in `workspace`
  * (fq_w4a8_linear_workspace_bytes(M,N,K) bytes, 16-byte aligned; FQ_ERR_MEMORY if it is missing

@@ -383,7 +383,8 @@ bool linear_is_fused(int M, int N, int K) {
 
 size_t fq_w4a8_linear_workspace_bytes(int M, int N, int K) {
     if (M <= 0 || N <= 0 || K <= 0 || (K % FQ_GROUP) != 0) return 0;
-    if (M <= 6 && linear_is_fused(M, N, K)) return 0;       // (more rows keep the size they have had, whichever kernels run)
+    // (more rows and longer ones keep the size they have had, whichever kernels run)
+    if (M <= 6 && K <= 4096 && linear_is_fused(M, N, K)) return 0;
     return round16((size_t)M * (size_t)K) + round16((size_t)M * sizeof(float)) + fq_w4a8_gemm_workspace_bytes(M, N, K);
 }
 

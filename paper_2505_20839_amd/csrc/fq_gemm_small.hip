@@ -152,10 +152,10 @@ struct fqs16_ring {
     }
 };
 
-// FUSEDQ (M <= QROWS <= 8, K <= 4096): `A` holds the bf16 activations X [M,K] instead of E4M3 codes, and the kernel quantises
+// FUSEDQ (M <= QROWS <= 8, slices no longer than the ring): `A` holds the bf16 activations X [M,K] instead of E4M3 codes, and the kernel quantises
 // them itself (Sec. 2.1 eq. 2, the arithmetic of the quantiser kernel) while the weights are on their way; every workgroup
 // repeats it for all of X, some six instructions per element, which for a few rows costs less than a second kernel.
-// Up to four sub-tiles a wave reads the part of every row that its own slice of K multiplies, one 16-byte load per lane and row;
+// Up to four sub-tiles a wave reads the part of every row that its own slice of K multiplies, one 16-byte load per lane, row and four groups;
 // the waves exchange the parts' largest patterns through LDS, and each converts its part and turns the codes into operands through
 // LDS of its own.  The weights are requested when all waves have asked for their activations: the later waves' would queue up
 // behind the weights of those before them (4096 x 4096, M = 1 / 4 / 8: 3.92 / 4.54 / 5.28 us without that barrier, 3.44 / 3.84 / 4.90
@@ -170,7 +170,7 @@ void fq_gemm_small16_kernel(
     const uint8_t* __restrict__ gs, float tscale, uint16_t* Y, int M, int N, int K, int cols,
     int swiglu, const uint16_t* R, float* __restrict__ a_scale_out) {
     constexpr bool FUSEDQ = QROWS > 0;                    // rows the fused form has room for
-    static_assert(!(FUSEDQ && (ROUNDS || BATCH_ != 4)) && QROWS <= 16, "the fused form serves K <= 4096: a slice is at most four groups");
+    static_assert(!(FUSEDQ && ROUNDS) && (!BYROW_ || BATCH_ == 4) && QROWS <= 8, "the fused form: a slice is all under way; by rows K <= 4096");
     typedef fqs16_ring<NSUB, BATCH_> ring_t;
     constexpr int BATCH = ring_t::BATCH;
     __shared__ float red[FQS16_WAVES][NSUB][4][64];
@@ -228,22 +228,22 @@ void fq_gemm_small16_kernel(
 
     ring_t ring;
     constexpr bool BYROW = FUSEDQ && BYROW_;              // wave w quantises row w, else its own slice of all rows
-    constexpr int XN = !FUSEDQ ? 1 : BYROW ? 8 : QROWS;   // 16-byte chunks a lane holds: of its row (K <= 4096), or one per row
-    // codes: rows 528 bytes apart in each wave's part, or 4112 (which spreads the rows of an operand over the banks)
-    constexpr int QSTRIDE = BYROW ? 4096 + 16 : 512 + 16;
+    constexpr int CPR = BATCH_ / 4;                       // 16-byte chunks of a row's slice per lane
+    constexpr int XN = !FUSEDQ ? 1 : BYROW ? 8 : QROWS * CPR;   // chunks a lane holds: of its row (K <= 4096), or of all rows' slices
+    // codes: rows 16 bytes further apart than they are long, which spreads the rows of an operand over the banks
+    constexpr int QSTRIDE = BYROW ? 4096 + 16 : BATCH_ * FQ_GROUP + 16;
     __shared__ __attribute__((aligned(16))) uint8_t codes[!FUSEDQ || BYROW ? 1 : FQS16_WAVES][FUSEDQ ? QROWS * QSTRIDE : 1];
     __shared__ __attribute__((aligned(16))) unsigned tops[FUSEDQ ? 16 : 1][FQS16_WAVES];   // largest pattern by row and wave
     __shared__ float srow[FUSEDQ ? FQS16_WAVES : 1];      // row scales
     fq_v4i xr[XN];
     const bool my_row = BYROW && wave < M;
-    const bool mine = lane < 16 * (g_end - g_begin);      // lanes whose chunk lies in the wave's slice
+    const int held = 16 * (g_end - g_begin);              // chunks of a row in the wave's slice
     if (FUSEDQ) {                                         // first in the queue: they are needed first
 #pragma unroll
         for (int c = 0; c < XN; ++c) {
-            const int chunk = lane + 64 * c;
-            const unsigned off = BYROW ? (unsigned)wave * (unsigned)K * 2u + (unsigned)chunk * 16u
-                                       : (unsigned)c * (unsigned)K * 2u + (unsigned)g_begin * (2u * FQ_GROUP) + (unsigned)lane * 16u;
-            const bool on = BYROW ? my_row && chunk < (K >> 3) : mine && c < M;
+            const int row = BYROW ? wave : c / CPR, chunk = lane + 64 * (BYROW ? c : c % CPR);
+            const unsigned off = (unsigned)row * (unsigned)K * 2u + (BYROW ? 0u : (unsigned)g_begin * (2u * FQ_GROUP)) + (unsigned)chunk * 16u;
+            const bool on = BYROW ? my_row && chunk < (K >> 3) : chunk < held && row < M;
             xr[c] = __builtin_bit_cast(fq_v4i, __builtin_amdgcn_raw_buffer_load_b128(rsA, on ? off : FQS16_OOB, 0, 0));
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -304,7 +304,9 @@ void fq_gemm_small16_kernel(
             unsigned v[QROWS];
 #pragma unroll
             for (int m = 0; m < QROWS; ++m) {
-                const fq_v2us p = fq_pattern_max((fq_v2us){0, 0}, xr[m]);
+                fq_v2us p = {0, 0};
+#pragma unroll
+                for (int c = 0; c < CPR; ++c) p = fq_pattern_max(p, xr[m * CPR + c]);
                 v[m] = p[0] > p[1] ? p[0] : p[1];
             }
             if constexpr (QROWS == 1) {
@@ -325,7 +327,10 @@ void fq_gemm_small16_kernel(
                 __syncthreads();
 #pragma unroll
                 for (int m = 0; m < QROWS; ++m) {
-                    const unsigned o = numbers_top(fq_absmax_numbers(0.f, xr[m]));
+                    float amax = 0.f;
+#pragma unroll
+                    for (int c = 0; c < CPR; ++c) amax = fq_absmax_numbers(amax, xr[m * CPR + c]);
+                    const unsigned o = numbers_top(amax);
                     if (lane == 0) tops[m][wave] = o;
                 }
                 top = row_top();
@@ -341,7 +346,9 @@ void fq_gemm_small16_kernel(
                     if (m < M) {
                         const float s = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(sc.s), m));
                         const float rcp = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(sc.rcp), m));
-                        *reinterpret_cast<fq_v2i*>(own + m * QSTRIDE + lane * 8) = fq_quant8<FAST>(xr[m], s, rcp);
+#pragma unroll
+                        for (int c = 0; c < CPR; ++c)
+                            *reinterpret_cast<fq_v2i*>(own + m * QSTRIDE + (lane + 64 * c) * 8) = fq_quant8<FAST>(xr[m * CPR + c], s, rcp);
                     }
             };
             if (!nan && __all(sc.fast)) convert(std::true_type());
@@ -459,20 +466,37 @@ void fq_launch_small16b(unsigned grid, hipStream_t stream, const uint8_t* A, con
                        A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R, static_cast<float*>(nullptr));
 }
 
-// The fused form (bf16 activations in, quantised by the kernel): slices of at most four groups per wave (K <= 4096), of which a
-// lane holds a chunk per row.
+// The fused form (bf16 activations in, quantised by the kernel); no kernel for what fq_linear_small_serves refuses.
 template <int NSUB>
-bool fq_launch_linear16(int per, unsigned grid, hipStream_t stream, const uint16_t* X, float* a_scale_out,
-                        const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols) {
-    if (per > 4) return false;
+auto fq_linear16_kernel(int per, int M, int K) -> decltype(&fq_gemm_small16_kernel<NSUB, false, 4, false>) {
     // by rows or by slices (see the kernel): by rows with five sub-tiles and more, and where slices are so short that most of a wave's
     // lanes would have nothing of them (by rows / by slices, us: 4 x 4096 x 1024 3.70 / 3.95, 6 rows 4.01 / 4.58, 2 rows 3.59 / 3.59;
     // 6 x 4096 x 1152 4.07 / 4.60, 6 x 12288 x 1408 6.17 / 6.29; on the other side 6 x 4096 x 2048 4.74 / 4.61, 4 rows 4.24 / 3.99)
     constexpr bool WIDE = NSUB > 4;
-    auto kernel = M == 1 ? fq_gemm_small16_kernel<NSUB, false, 4, false, 1, WIDE> : M <= 4 ? fq_gemm_small16_kernel<NSUB, false, 4, false, 4, WIDE>
-                                                                                           : fq_gemm_small16_kernel<NSUB, false, 4, false, 8, WIDE>;
-    if (M >= 3 && K <= 1536)
-        kernel = M <= 4 ? fq_gemm_small16_kernel<NSUB, false, 4, false, 4, true> : fq_gemm_small16_kernel<NSUB, false, 4, false, 8, true>;
+    if (per <= 4) {
+        if (M >= 3 && K <= 1536)
+            return M <= 4 ? fq_gemm_small16_kernel<NSUB, false, 4, false, 4, true> : fq_gemm_small16_kernel<NSUB, false, 4, false, 8, true>;
+        return M == 1 ? fq_gemm_small16_kernel<NSUB, false, 4, false, 1, WIDE> : M <= 4 ? fq_gemm_small16_kernel<NSUB, false, 4, false, 4, WIDE>
+                                                                                        : fq_gemm_small16_kernel<NSUB, false, 4, false, 8, WIDE>;
+    }
+    // longer slices: the rings of the unfused form (fq_launch_small16)
+    if constexpr (NSUB <= 4) {
+        if (per <= 8) return M == 1 ? fq_gemm_small16_kernel<NSUB, false, 8, false, 1> : fq_gemm_small16_kernel<NSUB, false, 8, false, 4>;
+    }
+    if constexpr (NSUB <= 2) {
+        if (per <= 12) return M == 1 ? fq_gemm_small16_kernel<NSUB, false, 12, false, 1> : fq_gemm_small16_kernel<NSUB, false, 12, false, 4>;
+    }
+    if constexpr (NSUB == 1) {
+        if (per <= 16) return M == 1 ? fq_gemm_small16_kernel<NSUB, false, 16, false, 1> : fq_gemm_small16_kernel<NSUB, false, 16, false, 4>;
+    }
+    return nullptr;
+}
+
+template <int NSUB>
+bool fq_launch_linear16(int per, unsigned grid, hipStream_t stream, const uint16_t* X, float* a_scale_out,
+                        const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols) {
+    const auto kernel = fq_linear16_kernel<NSUB>(per, M, K);
+    if (!kernel) return false;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(FQS16_THREADS), 0, stream,
                        reinterpret_cast<const uint8_t*>(X), static_cast<const float*>(nullptr), wp, gs, tscale, Y, M, N, K, cols,
                        0, static_cast<const uint16_t*>(nullptr), a_scale_out);
@@ -836,13 +860,19 @@ fqs_shape fqs_shape_of(int M, int N, int K, int max_cols) {
 
 }  // namespace
 
-// Rows up to which quantising inside the GEMM kernel pays, for slices of at most four groups: one kernel / two kernels, us, at 7 and 8
+// Rows up to which quantising inside the GEMM kernel pays.  Slices of at most four groups (K <= 4096): one kernel / two kernels, us, at 7 and 8
 // rows: 4096 x 4096 5.3 / 6.2 and 4.9 / 6.3, 14336 x 4096 9.0 / 9.2 and 9.3 / 9.4, 1024 x 4096 4.6 / 6.0, 4096 x 1024 4.9 / 5.5; 12 rows, an
 // earlier form: 4096 x 4096 7.2 / 6.5, 14336 x 4096 11.6 / 9.9.  With more than
 // 64 channels per compute unit up to six (6 x 28672 x 4096 15.3 us in one kernel, 8 rows 14.4 in two).
 bool fq_linear_small_serves(int M, int N, int K) {
-    if (M < 1 || M > 8 || (K / FQ_GROUP + FQS16_WAVES - 1) / FQS16_WAVES > 4) return false;
-    return M <= 6 || fqs_shape_of(M, N, K, FQS16_MAXCOLS).nsub <= 4;
+    if (M < 1 || M > 8) return false;
+    const fqs_shape sh = fqs_shape_of(M, N, K, FQS16_MAXCOLS);
+    if (sh.per <= 4) return M <= 6 || sh.nsub <= 4;
+    // longer slices, as far as the whole slice is under way at once (one kernel / two): one sub-tile 1 x 4096 x 14336 8.7 / 10.9,
+    // 2 rows 10.3 / 10.9, 3 rows 11.3 / 11.1; 1 x 4096 x 11008 7.2 / 9.5, 4 rows 9.4 / 9.7; 1 x 4096 x 8192 5.2 / 7.4, 4 rows 6.6 / 7.7; two
+    // 1 x 8192 x 8192 8.6 / 9.9, 3 rows 9.4 / 10.0; four 1 x 14336 x 5120 11.2 / 12.6, 2 rows 11.9 / 12.6, 4 rows 12.75 / 12.56; 4 x 16384 x 8192 18.1 / 18.0
+    if (sh.nsub <= 2) return M <= (sh.per <= 12 ? 4 : 2) && M * sh.per <= 44 && sh.per <= (sh.nsub == 1 ? 16 : 12);
+    return sh.nsub <= 4 && M <= 2 && sh.per <= 8;
 }
 
 bool fq_launch_linear_small(const uint16_t* X, float* a_scale_out, const uint8_t* wp, const uint8_t* gs, float tscale,

@@ -70,7 +70,7 @@ bool fq_launch_gemm_small(const uint8_t* A, const float* a_scale, const uint8_t*
                           float tscale, uint16_t* Y, int M, int N, int K, bool swiglu, const uint16_t* R,
                            hipStream_t stream);
 // M <= 16: quantiser and GEMM in one kernel, from bf16 activations X [M,K]; a_scale_out (may be NULL) receives
-// the row scales.  Serves M <= 6, up to 8 with fewer channels, with K <= 4096 (fq_linear_small_serves); returns false (nothing enqueued) otherwise.
+// the row scales.  Serves a few rows (fq_linear_small_serves); returns false (nothing enqueued) otherwise.
 bool fq_linear_small_serves(int M, int N, int K);
 bool fq_launch_linear_small(const uint16_t* X, float* a_scale_out, const uint8_t* wp, const uint8_t* gs, float tscale,
                             uint16_t* Y, int M, int N, int K, hipStream_t stream);

@@ -641,8 +641,9 @@ def test_linear_on_every_bf16_magnitude(fq):
     assert np.array_equal(A.cpu().numpy() & 0x7F, An & 0x7F) and np.array_equal(s.cpu().numpy(), sn)
 
 
-@pytest.mark.parametrize("K", [128, 640, 1024, 1536, 1664, 3968, 4096])
-@pytest.mark.parametrize("N", [40, 1000, 9000, 16640])        # one, one, three and five sub-tiles per compute unit
+@pytest.mark.parametrize("N,K", [(n, k) for n in (40, 1000, 9000, 16640) for k in (128, 640, 1024, 1536, 1664, 3968, 4096)] +
+                         [(40, 4224), (1000, 8192), (40, 8320), (1000, 12288), (200, 14336), (40, 16384), (40, 16512), (4200, 4224), (4200, 8192),
+                          (4200, 10240), (9000, 4224), (13000, 8192)])   # one, one, three and five sub-tiles per compute unit; two, and four
 def test_linear_at_the_edges_of_its_one_kernel_forms(fq, N, K):
     """1 to 9 rows: both ways of sharing the conversion out, all sizes of their row loops, slices of K that are partly or wholly
     empty, and beside ordinary rows ones of zeros of both signs, with scales outside the short quotient's range, with NaN and with
