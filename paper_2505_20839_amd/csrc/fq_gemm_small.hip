@@ -866,8 +866,9 @@ fqs_shape fqs_shape_of(int M, int N, int K, int max_cols) {
 // 64 channels per compute unit up to six (6 x 28672 x 4096 15.3 us in one kernel, 8 rows 14.4 in two).
 bool fq_linear_small_serves(int M, int N, int K) {
     if (M < 1 || M > 8) return false;
+    if (M <= 6 && K <= 4 * FQS16_WAVES * FQ_GROUP) return true;
     const fqs_shape sh = fqs_shape_of(M, N, K, FQS16_MAXCOLS);
-    if (sh.per <= 4) return M <= 6 || sh.nsub <= 4;
+    if (sh.per <= 4) return sh.nsub <= 4;
     // longer slices, as far as the whole slice is under way at once (one kernel / two): one sub-tile 1 x 4096 x 14336 8.7 / 10.9,
     // 2 rows 10.3 / 10.9, 3 rows 11.3 / 11.1; 1 x 4096 x 11008 7.2 / 9.5, 4 rows 9.4 / 9.7; 1 x 4096 x 8192 5.2 / 7.4, 4 rows 6.6 / 7.7; two
     // 1 x 8192 x 8192 8.6 / 9.9, 3 rows 9.4 / 10.0; four 1 x 14336 x 5120 11.2 / 12.6, 2 rows 11.9 / 12.6, 4 rows 12.75 / 12.56; 4 x 16384 x 8192 18.1 / 18.0

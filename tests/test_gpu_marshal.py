@@ -238,3 +238,38 @@ def test_another_stream_and_a_torch_function_mode(fq):
         y = fq.fq_w4a8_linear(x, w, gs, 1.0, 64)
     torch.cuda.synchronize()
     assert torch.equal(y, want) and "empty" in mode.names
+
+
+def test_outputs_are_seen_by_what_stands_before_an_allocation(fq):
+    """Dispatch modes, a profiler, inference mode and the filling of fresh memory see a native call's outputs as torch.empty's."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Sees(TorchDispatchMode):
+        def __init__(self):
+            super().__init__()
+            self.names = []
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.names.append(str(func))
+            return func(*args, **(kwargs or {}))
+
+    w, gs = _layer(fq, 64, 256)
+    x = _x(4, 256)
+    want = fq.fq_w4a8_linear(x, w, gs, 1.0, 64)
+    assert not want.requires_grad and want.is_contiguous() and want.untyped_storage().nbytes() == want.numel() * 2
+    with Sees() as mode:
+        y = fq.fq_w4a8_linear(x, w, gs, 1.0, 64)
+    assert any("empty" in n for n in mode.names) and torch.equal(y, want)
+    with torch.inference_mode():
+        y = fq.fq_w4a8_linear(x, w, gs, 1.0, 64)
+    assert y.is_inference() and torch.equal(y, want) and not want.is_inference()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]) as prof:
+        y = fq.fq_w4a8_linear(x, w, gs, 1.0, 64)
+    assert any(e.name == "aten::empty" for e in prof.events()) and torch.equal(y, want)
+    torch.use_deterministic_algorithms(True)
+    try:
+        assert fq.marshal().kv4_pack(torch.zeros((1, 32, 128), dtype=torch.int8, device="cuda"), False) is not None
+        y = fq.fq_w4a8_linear(x, w, gs, 1.0, 64)
+    finally:
+        torch.use_deterministic_algorithms(False)
+    assert torch.equal(y, want)
