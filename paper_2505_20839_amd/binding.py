@@ -480,7 +480,7 @@ def fq_w4a8_linear_workspace_bytes(M: int, N: int, K: int) -> int:
 def fq_w4a8_linear(X: torch.Tensor, Wq_packed: torch.Tensor, w_gscale: torch.Tensor, w_tscale: float, N: int,
                    out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Y[M,N] (bf16) of a whole linear layer from bf16 activations X[M,K] (quantiser + GEMM; one kernel
-    for M <= 6 and K <= 4096).  Calls fq_w4a8_linear_ws; the workspace is allocated here when not given."""
+    for a few rows).  Calls fq_w4a8_linear_ws; the workspace is allocated here when not given."""
     r = (_marshal or marshal()).linear(X, Wq_packed, w_gscale, w_tscale, N, out, workspace)
     if r is not None:
         if type(r) is int:
