@@ -156,8 +156,8 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(c
 namespace {
 
 // The figures below were taken before the row maximum, the quotient and the zero-point sums were shortened (some 13 vector
-// instructions per element then, 8 now) and stand for the order of the forms; with the choice here they are 0.80 to 0.94 of what they
-// were (us, before -> now, with zero-point terms above 64 rows): 16 x 4096 2.37 -> 2.15, 16 x 14336 3.01 -> 2.59, 32 x 32016 4.31 -> 3.49, 200 x
+// instructions per element then, 8 now) and stand for the order of the forms, which a sweep over 21 of these sizes has found as it was;
+// with the choice here they are 0.80 to 0.94 of what they were (us, before -> now, with zero-point terms above 64 rows): 16 x 4096 2.37 -> 2.15, 16 x 14336 3.01 -> 2.59, 32 x 32016 4.31 -> 3.49, 200 x
 // 11008 4.17 -> 3.60, 400 x 8320 5.41 -> 4.39, 1000 x 4096 4.46 -> 3.99, 1000 x 11008 9.10 -> 7.99, 4096 x 1024 4.86 -> 4.06, 2048 x 4096 6.53 -> 5.71,
 // 8192 x 4096 18.8 -> 17.4 (5.8 TB/s), 8192 x 8192 33.2 -> 31.2.
 // Waves per row and chunks per thread: few rows take many waves with two chunks each (a row's latency is all there is); many
@@ -191,8 +191,9 @@ void fq_launch_quantize_as(const uint16_t* X, uint8_t* A, float* a_scale, int M,
             else FQ_QUANTIZE_IN(16, 2, false, 2);
             return;
         }
+        // and four where a thread holds four chunks (32 x 32000 3.83 / 3.51 / 3.24 with one / two / four)
         if (M <= 32 && K > 4 * 4096 && K <= 8 * 4096) {
-            FQ_QUANTIZE_IN(16, 4, false, 2);
+            FQ_QUANTIZE_IN(16, 4, false, 4);
             return;
         }
     }

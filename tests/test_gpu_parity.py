@@ -666,7 +666,7 @@ def test_linear_at_the_edges_of_its_one_kernel_forms(fq, N, K):
         assert torch.equal(torch.nan_to_num(Y), torch.nan_to_num(Y2)) and torch.equal(Y.isnan(), Y2.isnan()), M
 
 
-@pytest.mark.parametrize("M,K", [(1, 8), (3, 1408), (16, 4096), (5, 14336), (32, 32016), (70, 4096), (1600, 2048), (70, 11008), (700, 4224),
+@pytest.mark.parametrize("M,K", [(1, 8), (3, 1408), (16, 4096), (5, 14336), (32, 32016), (1, 16392), (32, 24576), (33, 32768), (7, 32768), (70, 4096), (1600, 2048), (70, 11008), (700, 4224),
                                  (3, 40000), (2, 70000)])
 def test_quantiser_codes_with_signs_and_rows_that_are_not_finite(fq, M, K):
     """Every byte of the codes, the sign of zero included, against FP32 division and the library's cast: ordinary rows, zeros of
