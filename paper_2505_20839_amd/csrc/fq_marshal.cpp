@@ -11,11 +11,7 @@
 #include <Python.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
-#include <ATen/Context.h>
-#include <ATen/hip/EmptyTensor.h>
 #include <ATen/ops/empty.h>
-#include <ATen/record_function.h>
-#include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -85,18 +81,9 @@ bool truth(PyObject* o) {
     return o == Py_True;
 }
 
-// Whether anything stands between a call of torch.empty and its device function: a dispatch mode, a transform, a tracer, inference
-// mode (all of them keys that a thread adds or takes away), a profiler, or the filling of fresh memory.
-bool empty_is_plain() {
-    const auto keys = c10::impl::tls_local_dispatch_key_set();
-    return keys.included_ == c10::default_included_set && keys.excluded_ == c10::default_excluded_set && !at::hasCallbacks() &&
-           !(at::globalContext().deterministicAlgorithms() && at::globalContext().deterministicFillUninitializedMemory());
-}
-
-// A tensor from torch's allocator, without the way through the dispatcher where nothing would see it there (0.25 us of host time less
-// per tensor: scores 3.85 -> 3.65 us a call, the activation quantiser 4.6 -> 4.15, the output product with its scratch 7.6 -> 7.1)
+// A tensor as torch.empty gives it, through the dispatcher: modes, transforms, profilers, the filling of fresh memory and kernels that a
+// program has registered for it see every output (straight from the allocator 0.25 us less per tensor, and the last of these would not)
 at::Tensor fresh(at::IntArrayRef size, at::ScalarType t, const at::Tensor& like) {
-    if (empty_is_plain()) return at::Tensor(at::detail::empty_cuda(size, t, like.device(), std::nullopt));
     return at::empty(size, at::TensorOptions().dtype(t).device(like.device()));
 }
 

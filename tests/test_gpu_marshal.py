@@ -1,5 +1,7 @@
 """The native argument marshalling against the Python form of every call: the same results, exceptions and messages for
 everything a caller may pass (the native form declines what it does not take, and the Python form then decides)."""
+import math
+
 import numpy as np
 import pytest
 
@@ -266,10 +268,37 @@ def test_outputs_are_seen_by_what_stands_before_an_allocation(fq):
     with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]) as prof:
         y = fq.fq_w4a8_linear(x, w, gs, 1.0, 64)
     assert any(e.name == "aten::empty" for e in prof.events()) and torch.equal(y, want)
+    weights = torch.randn((64, 256), device="cuda").bfloat16()
+    n = int(fq.fq_pts_exponent(weights, None)[0])
+    dirty = torch.full((16,), 77, dtype=torch.int32, device="cuda")        # the block that the call's answer will get
+    torch.cuda.synchronize()
+    del dirty
     torch.use_deterministic_algorithms(True)
     try:
-        assert fq.marshal().kv4_pack(torch.zeros((1, 32, 128), dtype=torch.int8, device="cuda"), False) is not None
-        y = fq.fq_w4a8_linear(x, w, gs, 1.0, 64)
+        filled = fq.marshal().pts_exponent(weights, None).cpu()
     finally:
         torch.use_deterministic_algorithms(False)
-    assert torch.equal(y, want)
+    # (of the answer's 64 bytes the call writes the first word and, without scratch, words 8 and 9)
+    assert int(filled[0]) == n and (filled[1:8] == 2 ** 31 - 1).all() and (filled[10:] == 2 ** 31 - 1).all()
+
+
+def test_a_kernel_registered_for_empty_sees_outputs_and_scratch(fq):
+    """A program may register its own kernel for aten::empty on the GPU (torch.library): it makes the tensors of native calls too."""
+    w, gs = _layer(fq, 64, 256)
+    x = _x(9, 256)                                             # two kernels: an output and a workspace
+    want = fq.fq_w4a8_linear(x, w, gs, 1.0, 64)
+    made = []
+
+    def empty(size, dtype=None, layout=None, device=None, pin_memory=None, memory_format=None):
+        made.append(tuple(size))
+        return torch.empty_strided(size, [math.prod(size[i + 1:]) for i in range(len(size))], dtype=dtype, device=device)
+
+    registered = torch.library.Library("aten", "IMPL")
+    try:
+        registered.impl("empty.memory_format", empty, "CUDA")
+        y = fq.marshal().linear(x, w, gs, 1.0, 64, None, None)
+        torch.cuda.synchronize()
+    finally:
+        registered._destroy()
+    assert made == [(9, 64), (fq.fq_w4a8_linear_workspace_bytes(9, 64, 256),)] and torch.equal(y, want)
+    assert torch.equal(fq.marshal().linear(x, w, gs, 1.0, 64, None, None), want) and len(made) == 2
