@@ -217,7 +217,7 @@ int fq_w4a8_gemm_swiglu_quant_ws(const uint8_t *A_fp8, const float *a_scale, con
  * and keeps the codes, the row scales and the GEMM's own scratch in `workspace`
  * (fq_w4a8_linear_workspace_bytes(M,N,K) bytes, 16-byte aligned; FQ_ERR_MEMORY if it is missing
  * or too small).  X_bf16 [M,K] row-major, finite, 16-byte aligned; the other operands as for
- * fq_w4a8_gemm_ws.  Allocates nothing, keeps no state, never synchronises.
+ * fq_w4a8_gemm_ws.  Y_bf16 may lie over X_bf16 where a workspace is needed (two kernels then), not where none is.  Allocates nothing, keeps no state, never synchronises.
  */
 size_t fq_w4a8_linear_workspace_bytes(int M, int N, int K);
 int fq_w4a8_linear_ws(const uint16_t *X_bf16, const uint8_t *Wq_packed, const uint8_t *w_gscale,

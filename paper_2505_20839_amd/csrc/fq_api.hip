@@ -400,7 +400,11 @@ int fq_w4a8_linear_ws(const uint16_t* X_bf16, const uint8_t* Wq_packed, const ui
         if (!workspace || workspace_bytes < need) return FQ_ERR_MEMORY;
         if (!aligned16(workspace)) return FQ_ERR_ALIGN;
     }
-    if (linear_is_fused(M, N, K)) {
+    // Y over X (the layer in place): in one kernel a workgroup would write what others have not read yet; of two kernels the first
+    // reads all of X.  Shapes without a workspace have one kernel only.
+    const uintptr_t x0 = reinterpret_cast<uintptr_t>(X_bf16), y0 = reinterpret_cast<uintptr_t>(Y_bf16);
+    const bool apart = y0 >= x0 + (size_t)M * (size_t)K * 2 || x0 >= y0 + (size_t)M * (size_t)N * 2;
+    if ((apart || need == 0) && linear_is_fused(M, N, K)) {
         if (fq_launch_linear_small(X_bf16, nullptr, Wq_packed, w_gscale, w_tscale, Y_bf16, M, N, K, s)) return after_launch();
         return FQ_ERR_LAUNCH;                             // (the predicate and the launcher agree; not reached)
     }

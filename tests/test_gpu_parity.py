@@ -666,6 +666,19 @@ def test_linear_at_the_edges_of_its_one_kernel_forms(fq, N, K):
         assert torch.equal(torch.nan_to_num(Y), torch.nan_to_num(Y2)) and torch.equal(Y.isnan(), Y2.isnan()), M
 
 
+@pytest.mark.parametrize("M,K", [(7, 512), (8, 4096), (1, 8192), (2, 4224), (4, 8192), (12, 512), (70, 1024)])
+def test_linear_in_place_where_it_has_a_workspace(fq, M, K):
+    """The output over the input, whole and one row further on: as out of place, also where a few rows have one kernel otherwise."""
+    d = workloads.draw(M, K, K, seed=M + K, outlier_frac=0.02)
+    packed, gs, X = fq.fq_pack_weights(_gpu(d["q"])), _gpu(d["gscale"]), to_gpu_bf16(d["X_bf16"])
+    want = fq.fq_w4a8_linear(X, packed, gs, 1.0, K)
+    buf = torch.empty((M + 1, K), dtype=torch.bfloat16, device="cuda")
+    for first in (0, 1):
+        buf[:M] = X
+        fq.fq_w4a8_linear(buf[:M], packed, gs, 1.0, K, out=buf[first:first + M])
+        assert torch.equal(buf[first:first + M].view(torch.int16), want.view(torch.int16)), first
+
+
 @pytest.mark.parametrize("M,K", [(1, 8), (3, 1408), (16, 4096), (5, 14336), (32, 32016), (1, 16392), (32, 24576), (33, 32768), (7, 32768), (70, 4096), (1600, 2048), (70, 11008), (700, 4224),
                                  (3, 40000), (2, 70000)])
 def test_quantiser_codes_with_signs_and_rows_that_are_not_finite(fq, M, K):
