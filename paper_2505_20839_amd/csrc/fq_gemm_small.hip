@@ -62,6 +62,7 @@ __device__ __forceinline__ unsigned fqs_swap16_max(unsigned a, unsigned b) {
 #define FQS16_THREADS 512
 #define FQS16_WAVES 8
 #define FQS16_MAXCOLS 112                                 // channels of a workgroup (7 sub-tiles: 56 KiB of partial sums in LDS)
+#define FQS16_BYROW_K 1536                                // fused: the longest K that three rows and more convert by rows
 #define FQS16_OOB 0xFFFFFF00u                             // beyond any 32-bit buffer size
 // byte `i` (0..3, compile-time) of a word of E4M3 codes -> float
 __device__ __forceinline__ float fq_e4m3_byte_to_float(unsigned w, int i) {
@@ -474,7 +475,7 @@ auto fq_linear16_kernel(int per, int M, int K) -> decltype(&fq_gemm_small16_kern
     // 6 x 4096 x 1152 4.07 / 4.60, 6 x 12288 x 1408 6.17 / 6.29; on the other side 6 x 4096 x 2048 4.74 / 4.61, 4 rows 4.24 / 3.99)
     constexpr bool WIDE = NSUB > 4;
     if (per <= 4) {
-        if (M >= 3 && K <= 1536)
+        if (M >= 3 && K <= FQS16_BYROW_K)
             return M <= 4 ? fq_gemm_small16_kernel<NSUB, false, 4, false, 4, true> : fq_gemm_small16_kernel<NSUB, false, 4, false, 8, true>;
         return M == 1 ? fq_gemm_small16_kernel<NSUB, false, 4, false, 1, WIDE> : M <= 4 ? fq_gemm_small16_kernel<NSUB, false, 4, false, 4, WIDE>
                                                                                         : fq_gemm_small16_kernel<NSUB, false, 4, false, 8, WIDE>;
@@ -839,7 +840,7 @@ namespace {
 struct fqs_shape {
     int cols;
     unsigned grid;
-    int per, nsub;
+    int per, nsub, rounds;
 };
 
 fqs_shape fqs_shape_of(int M, int N, int K, int max_cols) {
@@ -848,11 +849,11 @@ fqs_shape fqs_shape_of(int M, int N, int K, int max_cols) {
     const int G = K / FQ_GROUP;
     sh.per = (G + FQS16_WAVES - 1) / FQS16_WAVES;
     if (sh.per > 4 && max_cols > 64) max_cols = 64;
-    const int rounds = (int)(((long long)N + (long long)cus * max_cols - 1) / ((long long)cus * max_cols));
-    const long long wgs = (long long)rounds * cus;
+    sh.rounds = (int)(((long long)N + (long long)cus * max_cols - 1) / ((long long)cus * max_cols));
+    const long long wgs = (long long)sh.rounds * cus;
     sh.cols = (int)((N + wgs - 1) / wgs + 7) & ~7;
     sh.cols = sh.cols < 8 ? 8 : (sh.cols > max_cols ? max_cols : sh.cols);
-    if (M > 16 && rounds > 1 && sh.cols > max_cols - 16) sh.cols = max_cols;
+    if (M > 16 && sh.rounds > 1 && sh.cols > max_cols - 16) sh.cols = max_cols;
     sh.grid = (unsigned)((N + sh.cols - 1) / sh.cols);
     sh.nsub = (sh.cols + 15) / 16;
     return sh;
@@ -860,20 +861,29 @@ fqs_shape fqs_shape_of(int M, int N, int K, int max_cols) {
 
 }  // namespace
 
-// Rows up to which quantising inside the GEMM kernel pays.  Slices of at most four groups (K <= 4096): one kernel / two kernels, us, at 7 and 8
-// rows: 4096 x 4096 5.3 / 6.2 and 4.9 / 6.3, 14336 x 4096 9.0 / 9.2 and 9.3 / 9.4, 1024 x 4096 4.6 / 6.0, 4096 x 1024 4.9 / 5.5; 12 rows, an
-// earlier form: 4096 x 4096 7.2 / 6.5, 14336 x 4096 11.6 / 9.9.  With more than
-// 64 channels per compute unit up to six (6 x 28672 x 4096 15.3 us in one kernel, 8 rows 14.4 in two).
+// Where quantising inside the GEMM kernel pays (one kernel / quantiser and GEMM, us, replayed from graphs, weights in turn from 600 MB).
+// One round of the compute units only, beyond six rows or K = 4096: every further round reads and converts X again (7 x 28680 x 4096
+// 17.0 / 15.0, 8 x 32000 x 4096 18.3 / 15.6, 2 x 16640 x 8192 19.0 / 17.4, 1 x 128256 x 8192 98.4 / 91.9; 1 x 22016 x 5120 17.1 / 17.2).
+// Slices of at most four groups, 7 and 8 rows: up to three sub-tiles (8 rows: 4096 x 4096 5.0 / 6.0, 8192 x 4096 6.7 / 7.3, 12288 x 4096 8.4 /
+// 8.6, 12288 x 2048 7.3 / 7.3), with four only where it converts by rows (14336 x 1024 6.8 / 7.3, 16384 x 1536 7.4 / 7.6; by slices
+// 14336 x 2048 8.3 / 8.0, 16384 x 3072 9.3 / 8.9); 12 rows, an earlier form: 4096 x 4096 7.2 / 6.5.
+// Longer slices, all under way at once: the more channels a workgroup has, the less time for a wave's conversions, rows x groups:
+//     8 channels    48   4 x 1024 x 11264 7.8 / 8.4, 4 x 2048 x 12288 8.2 / 9.0 (four rows and 12 groups, the kernels' most)
+//     16            36   4 x 3072 x 9216 8.70 / 8.67, 3 x 4096 x 12288 9.06 / 8.95, 3 x 4096 x 8320 8.3 / 8.7; 4 x 4096 x 11008 9.6 / 9.1
+//     24            24   2 x 5120 x 12288 10.3 / 10.7, 2 x 6144 x 12288 11.0 / 11.0; 3 x 6144 x 9216 11.2 / 10.7, 4 x 5120 x 9216 11.1 / 10.4
+//     32            20   2 x 8192 x 10240 12.0 / 11.9, 3 x 8192 x 6144 8.7 / 8.9; 2 x 8192 x 12288 12.9 / 12.2, 4 x 8192 x 8192 10.1 / 9.8
+//     up to 64      16   two rows: 9216 x 6144 9.8 / 10.1, 12288 x 8192 12.9 / 12.8, 16384 x 8192 17.7 / 17.7, 13824 x 8192 14.6 / 14.3; 4 x 14336 x 5120
+//                        12.75 / 12.56
+// and beyond 12 groups two rows (4096 x 14336 10.3 / 10.5, 4096 x 16384 10.95 / 10.56; 3 rows 11.3 / 11.1).
 bool fq_linear_small_serves(int M, int N, int K) {
     if (M < 1 || M > 8) return false;
     if (M <= 6 && K <= 4 * FQS16_WAVES * FQ_GROUP) return true;
     const fqs_shape sh = fqs_shape_of(M, N, K, FQS16_MAXCOLS);
-    if (sh.per <= 4) return sh.nsub <= 4;
-    // longer slices, as far as the whole slice is under way at once (one kernel / two): one sub-tile 1 x 4096 x 14336 8.7 / 10.9,
-    // 2 rows 10.3 / 10.9, 3 rows 11.3 / 11.1; 1 x 4096 x 11008 7.2 / 9.5, 4 rows 9.4 / 9.7; 1 x 4096 x 8192 5.2 / 7.4, 4 rows 6.6 / 7.7; two
-    // 1 x 8192 x 8192 8.6 / 9.9, 3 rows 9.4 / 10.0; four 1 x 14336 x 5120 11.2 / 12.6, 2 rows 11.9 / 12.6, 4 rows 12.75 / 12.56; 4 x 16384 x 8192 18.1 / 18.0
-    if (sh.nsub <= 2) return M <= (sh.per <= 12 ? 4 : 2) && M * sh.per <= 44 && sh.per <= (sh.nsub == 1 ? 16 : 12);
-    return sh.nsub <= 4 && M <= 2 && sh.per <= 8;
+    if (sh.rounds > 1) return false;
+    if (sh.per <= 4) return sh.nsub <= 3 || (sh.nsub == 4 && K <= FQS16_BYROW_K);
+    if (sh.nsub > 4 || sh.per > (sh.nsub == 1 ? 16 : sh.nsub == 2 ? 12 : 8)) return false;
+    if (M > (sh.nsub > 2 || sh.per > 12 ? 2 : 4)) return false;
+    return M * sh.per <= (sh.cols <= 8 ? 48 : sh.cols <= 16 ? 36 : sh.cols <= 24 ? 24 : sh.cols <= 32 ? 20 : 16);
 }
 
 bool fq_launch_linear_small(const uint16_t* X, float* a_scale_out, const uint8_t* wp, const uint8_t* gs, float tscale,

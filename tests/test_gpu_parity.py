@@ -666,6 +666,38 @@ def test_linear_at_the_edges_of_its_one_kernel_forms(fq, N, K):
         assert torch.equal(torch.nan_to_num(Y), torch.nan_to_num(Y2)) and torch.equal(Y.isnan(), Y2.isnan()), M
 
 
+@pytest.mark.parametrize("M,N,K,kernels", [
+    (6, 28680, 256, 1), (8, 28672, 256, 2), (8, 28680, 256, 2), (7, 32768, 1664, 2),      # more rounds than one, or too many sub-tiles
+    (8, 16384, 1536, 1), (8, 16384, 1664, 2), (8, 16392, 1536, 2), (8, 12288, 1664, 1), (9, 64, 256, 2),
+    (1, 16384, 4224, 1), (1, 16392, 4224, 2), (2, 22016, 5120, 2), (2, 8200, 8192, 1), (3, 8200, 4224, 2),
+    (4, 2048, 12288, 1), (4, 2056, 12288, 2), (2, 2048, 16384, 1), (3, 2048, 12416, 2), (4, 4096, 9216, 1), (4, 4096, 9344, 2),
+    (4, 6144, 6144, 1), (4, 6144, 6272, 2), (4, 8192, 5120, 1), (4, 8192, 5248, 2), (2, 8192, 10240, 1), (2, 8192, 10368, 2)])
+def test_linear_is_one_kernel_on_one_side_of_each_line(fq, M, N, K, kernels):
+    """Kernels that a call captured into a graph holds, on both sides of the lines of the dispatch (256 compute units); the replayed
+    result is that of quantiser and GEMM."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    packed = torch.randint(0, 256, (fq.fq_packed_weight_bytes(N, K),), generator=g, device="cuda", dtype=torch.uint8)
+    gs = torch.randint(0x18, 0x30, (N, K // 128), generator=g, device="cuda", dtype=torch.uint8)
+    X = torch.randn((M, K), generator=g, device="cuda").to(torch.bfloat16)
+    Y = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty((fq.fq_w4a8_linear_workspace_bytes(M, N, K),), dtype=torch.uint8, device="cuda")
+    A, s = fq.fq_quantize_act(X)
+    want = fq.fq_w4a8_gemm(A, s, packed, gs, 1.0, N)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        fq.fq_w4a8_linear(X, packed, gs, 1.0, N, out=Y, workspace=ws)
+    count = ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    assert count.value == kernels
+    for _ in range(2):
+        Y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y.view(torch.int16), want.view(torch.int16))
+
+
 @pytest.mark.parametrize("M,K", [(7, 512), (8, 4096), (1, 8192), (2, 4224), (4, 8192), (12, 512), (70, 1024)])
 def test_linear_in_place_where_it_has_a_workspace(fq, M, K):
     """The output over the input, whole and one row further on: as out of place, also where a few rows have one kernel otherwise."""
