@@ -191,9 +191,14 @@ void fq_launch_quantize_as(const uint16_t* X, uint8_t* A, float* a_scale, int M,
             else FQ_QUANTIZE_IN(16, 2, false, 2);
             return;
         }
-        // and four where a thread holds four chunks (32 x 32000 3.83 / 3.51 / 3.24 with one / two / four)
+        // A thread holds three or four chunks: four workgroups where the fourth has some of them, or up to 16 rows where the third is
+        // nearly whole, else two.  Two / four, us, inputs in turn from 600 MB | a copy that writes the input, then the quantiser: 32 x 32016
+        // 4.52 / 4.33 | 6.68 / 7.15, 24 x 32016 4.37 / 4.14 | 6.31 / 6.53, 16 x 32016 3.67 / 3.49 | 5.94 / 5.90, 8 x 32016 3.62 / 3.36 | 5.54 /
+        // 5.41 (the same 32 x 32016 again and again 3.38 / 3.13); 1 x 24576 3.11 / 2.86 | 4.82 / 4.65, 8 x 22528 3.17 / 3.15 | 4.88 / 4.83;
+        // on the other side 24 x 24576 3.35 / 3.56 | 5.54 / 5.95, 32 x 24576 4.04 / 3.96 | 5.85 / 6.41, 16 x 20480 3.17 / 3.23 | 5.03 / 5.19
         if (M <= 32 && K > 4 * 4096 && K <= 8 * 4096) {
-            FQ_QUANTIZE_IN(16, 4, false, 4);
+            if (K > 6 * 4096 || (M <= 16 && K > 22528)) FQ_QUANTIZE_IN(16, 4, false, 4);
+            else FQ_QUANTIZE_IN(16, 4, false, 2);
             return;
         }
     }

@@ -711,7 +711,7 @@ def test_linear_in_place_where_it_has_a_workspace(fq, M, K):
         assert torch.equal(buf[first:first + M].view(torch.int16), want.view(torch.int16)), first
 
 
-@pytest.mark.parametrize("M,K", [(1, 8), (3, 1408), (16, 4096), (5, 14336), (32, 32016), (1, 16392), (32, 24576), (33, 32768), (7, 32768), (70, 4096), (1600, 2048), (70, 11008), (700, 4224),
+@pytest.mark.parametrize("M,K", [(1, 8), (3, 1408), (16, 4096), (5, 14336), (32, 32016), (1, 16392), (16, 22528), (16, 22536), (17, 22536), (32, 24576), (32, 24584), (16, 32768), (33, 32768), (7, 32768), (70, 4096), (1600, 2048), (70, 11008), (700, 4224),
                                  (3, 40000), (2, 70000)])
 def test_quantiser_codes_with_signs_and_rows_that_are_not_finite(fq, M, K):
     """Every byte of the codes, the sign of zero included, against FP32 division and the library's cast: ordinary rows, zeros of
