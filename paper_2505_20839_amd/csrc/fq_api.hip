@@ -373,7 +373,7 @@ namespace {
 
 inline size_t round16(size_t v) { return (v + 15u) & ~(size_t)15u; }
 
-// one kernel for the whole layer: small M, short K, and no kernel forced from outside
+// one kernel for the whole layer: a few rows, and no kernel forced from outside
 bool linear_is_fused(int M, int N, int K) {
     const GemmKernel k = forced_kernel();
     return (k == GemmKernel::Auto || k == GemmKernel::Small) && fq_linear_small_serves(M, N, K);
@@ -405,7 +405,7 @@ int fq_w4a8_linear_ws(const uint16_t* X_bf16, const uint8_t* Wq_packed, const ui
     const uintptr_t x0 = reinterpret_cast<uintptr_t>(X_bf16), y0 = reinterpret_cast<uintptr_t>(Y_bf16);
     const bool apart = y0 >= x0 + (size_t)M * (size_t)K * 2 || x0 >= y0 + (size_t)M * (size_t)N * 2;
     if ((apart || need == 0) && linear_is_fused(M, N, K)) {
-        if (fq_launch_linear_small(X_bf16, nullptr, Wq_packed, w_gscale, w_tscale, Y_bf16, M, N, K, s)) return after_launch();
+        if (fq_launch_linear_small(X_bf16, Wq_packed, w_gscale, w_tscale, Y_bf16, M, N, K, s)) return after_launch();
         return FQ_ERR_LAUNCH;                             // (the predicate and the launcher agree; not reached)
     }
     uint8_t* A = static_cast<uint8_t*>(workspace);

@@ -155,7 +155,7 @@ struct fqs16_ring {
 
 // FUSEDQ (M <= QROWS <= 8, slices no longer than the ring): `A` holds the bf16 activations X [M,K] instead of E4M3 codes, and the kernel quantises
 // them itself (Sec. 2.1 eq. 2, the arithmetic of the quantiser kernel) while the weights are on their way; every workgroup
-// repeats it for all of X, some six instructions per element, which for a few rows costs less than a second kernel.
+// repeats it for all of X, some eight instructions per element, which for a few rows costs less than a second kernel.
 // Up to four sub-tiles a wave reads the part of every row that its own slice of K multiplies, one 16-byte load per lane, row and four groups;
 // the waves exchange the parts' largest patterns through LDS, and each converts its part and turns the codes into operands through
 // LDS of its own.  The weights are requested when all waves have asked for their activations: the later waves' would queue up
@@ -163,13 +163,13 @@ struct fqs16_ring {
 // with it; 5.22 / 5.29 with the first form of the conversion, a row per wave, 6.26 with two kernels at M = 8).  BYROW: wave w reads,
 // converts and leaves row w for all, which is the faster way with five sub-tiles and more, where a wave's weights alone fill the
 // queues (28672 x 4096, M = 1 and 4: by slices 13.3 and 14.2 us, by rows 12.8 and 13.0), and for short slices (fq_launch_linear16).
-// `a_scale` is not read; `a_scale_out` (may be NULL) receives the row scales.
+// `a_scale` is not read.
 template <int NSUB, bool ROUNDS, int BATCH_, bool TURN, int QROWS = 0, bool BYROW_ = false>
 __global__ __launch_bounds__(FQS16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void fq_gemm_small16_kernel(
     const uint8_t* __restrict__ A, const float* __restrict__ a_scale, const uint8_t* __restrict__ wp,
     const uint8_t* __restrict__ gs, float tscale, uint16_t* Y, int M, int N, int K, int cols,
-    int swiglu, const uint16_t* R, float* __restrict__ a_scale_out) {
+    int swiglu, const uint16_t* R) {
     constexpr bool FUSEDQ = QROWS > 0;                    // rows the fused form has room for
     static_assert(!(FUSEDQ && ROUNDS) && (!BYROW_ || BATCH_ == 4) && QROWS <= 8, "the fused form: a slice is all under way; by rows K <= 4096");
     typedef fqs16_ring<NSUB, BATCH_> ring_t;
@@ -277,10 +277,7 @@ void fq_gemm_small16_kernel(
                     top = numbers_top(amax);
                 }
                 const fq_row_scale sc = fq_scale_of(top);
-                if (lane == 0) {
-                    srow[wave] = sc.s;
-                    if (a_scale_out != nullptr && blockIdx.x == 0) a_scale_out[wave] = sc.s;
-                }
+                if (lane == 0) srow[wave] = sc.s;
                 auto convert = [&](auto fast_tag) __attribute__((always_inline)) {
                     constexpr bool FAST = decltype(fast_tag)::value;
 #pragma unroll
@@ -338,7 +335,6 @@ void fq_gemm_small16_kernel(
             }
             const fq_row_scale sc = fq_scale_of(top);
             s_out = sc.s;
-            if (a_scale_out != nullptr && blockIdx.x == 0 && threadIdx.x < (unsigned)M) a_scale_out[threadIdx.x] = sc.s;
             // one choice of quotient for all rows (the full division gives the same codes), then straight-line code
             auto convert = [&](auto fast_tag) __attribute__((always_inline)) {
                 constexpr bool FAST = decltype(fast_tag)::value;
@@ -464,7 +460,7 @@ void fq_launch_small16b(unsigned grid, hipStream_t stream, const uint8_t* A, con
         if (fqs16_turns(M, per, NSUB)) kernel = fq_gemm_small16_kernel<NSUB, ROUNDS, BATCH, true>;
     }
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(FQS16_THREADS), 0, stream,
-                       A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R, static_cast<float*>(nullptr));
+                       A, a_scale, wp, gs, tscale, Y, M, N, K, cols, swiglu, R);
 }
 
 // The fused form (bf16 activations in, quantised by the kernel); no kernel for what fq_linear_small_serves refuses.
@@ -494,13 +490,13 @@ auto fq_linear16_kernel(int per, int M, int K) -> decltype(&fq_gemm_small16_kern
 }
 
 template <int NSUB>
-bool fq_launch_linear16(int per, unsigned grid, hipStream_t stream, const uint16_t* X, float* a_scale_out,
+bool fq_launch_linear16(int per, unsigned grid, hipStream_t stream, const uint16_t* X,
                         const uint8_t* wp, const uint8_t* gs, float tscale, uint16_t* Y, int M, int N, int K, int cols) {
     const auto kernel = fq_linear16_kernel<NSUB>(per, M, K);
     if (!kernel) return false;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(FQS16_THREADS), 0, stream,
                        reinterpret_cast<const uint8_t*>(X), static_cast<const float*>(nullptr), wp, gs, tscale, Y, M, N, K, cols,
-                       0, static_cast<const uint16_t*>(nullptr), a_scale_out);
+                       0, static_cast<const uint16_t*>(nullptr));
     return true;
 }
 
@@ -886,18 +882,18 @@ bool fq_linear_small_serves(int M, int N, int K) {
     return M * sh.per <= (sh.cols <= 8 ? 48 : sh.cols <= 16 ? 36 : sh.cols <= 24 ? 24 : sh.cols <= 32 ? 20 : 16);
 }
 
-bool fq_launch_linear_small(const uint16_t* X, float* a_scale_out, const uint8_t* wp, const uint8_t* gs, float tscale,
+bool fq_launch_linear_small(const uint16_t* X, const uint8_t* wp, const uint8_t* gs, float tscale,
                             uint16_t* Y, int M, int N, int K, hipStream_t stream) {
     if (!fq_linear_small_serves(M, N, K)) return false;
     const fqs_shape sh = fqs_shape_of(M, N, K, FQS16_MAXCOLS);
     switch (sh.nsub) {
-        case 1: return fq_launch_linear16<1>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 2: return fq_launch_linear16<2>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 3: return fq_launch_linear16<3>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 4: return fq_launch_linear16<4>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 5: return fq_launch_linear16<5>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        case 6: return fq_launch_linear16<6>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
-        default: return fq_launch_linear16<7>(sh.per, sh.grid, stream, X, a_scale_out, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 1: return fq_launch_linear16<1>(sh.per, sh.grid, stream, X, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 2: return fq_launch_linear16<2>(sh.per, sh.grid, stream, X, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 3: return fq_launch_linear16<3>(sh.per, sh.grid, stream, X, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 4: return fq_launch_linear16<4>(sh.per, sh.grid, stream, X, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 5: return fq_launch_linear16<5>(sh.per, sh.grid, stream, X, wp, gs, tscale, Y, M, N, K, sh.cols);
+        case 6: return fq_launch_linear16<6>(sh.per, sh.grid, stream, X, wp, gs, tscale, Y, M, N, K, sh.cols);
+        default: return fq_launch_linear16<7>(sh.per, sh.grid, stream, X, wp, gs, tscale, Y, M, N, K, sh.cols);
     }
 }
 
