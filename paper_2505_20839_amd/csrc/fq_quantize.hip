@@ -1,7 +1,8 @@
 // Per-token FP8 quantisation of activations (Sec. 2.1 eq. 2):  A = FP8(x / beta), beta per row.
 //   beta = absmax / 448 in FP32 (1 for an all-zero row); quotient as IEEE FP32 division would give
-//   it; conversion to OCP E4M3 round-to-nearest-even by the hardware converter, after clamping to
-//   +-448 so that the result saturates instead of becoming NaN.
+//   it; conversion to OCP E4M3 round-to-nearest-even by the hardware converter.  No quotient of the short form passes 448 by more
+//   than its rounding (|x| <= absmax, which is why a row with a NaN may not take it); the full division clamps to +-448: a
+//   NaN, and an infinity over its row's infinite scale, become -448.
 // The quotient.  A full IEEE division is about eleven instructions per element.  With r = 1 / beta, q = x * r, the residual
 // e = fma(q, beta, -x) (exact) and q' = fma(e, -r, q), the stored E4M3 code equals that of the IEEE quotient, the sign of
 // zero included, for every finite bf16 x with |x| <= absmax and every beta = absmax / 448 in [2^-60, 2^60]: checked
@@ -155,25 +156,20 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void fq_quantize_kernel(c
 
 namespace {
 
-// The figures below were taken before the row maximum, the quotient and the zero-point sums were shortened (some 13 vector
-// instructions per element then, 8 now) and stand for the order of the forms, which a sweep over 21 of these sizes has found as it was;
-// with the choice here they are 0.80 to 0.94 of what they were (us, before -> now, with zero-point terms above 64 rows): 16 x 4096 2.37 -> 2.15, 16 x 14336 3.01 -> 2.59, 32 x 32016 4.31 -> 3.49, 200 x
-// 11008 4.17 -> 3.60, 400 x 8320 5.41 -> 4.39, 1000 x 4096 4.46 -> 3.99, 1000 x 11008 9.10 -> 7.99, 4096 x 1024 4.86 -> 4.06, 2048 x 4096 6.53 -> 5.71,
-// 8192 x 4096 18.8 -> 17.4 (5.8 TB/s), 8192 x 8192 33.2 -> 31.2.
 // Waves per row and chunks per thread: few rows take many waves with two chunks each (a row's latency is all there is); many
 // rows fewer waves with more (other rows hide the latency, fewer waves meet at a barrier), as long as the last chunk of every
-// thread is not mostly empty.  One process, alternating; us without / with zero-point terms, one workgroup of 4 waves with up to
-// 8 chunks for every row (the former form) | the choice here | its neighbours:
-//     1536 x 2048   4.1 / 4.7 | <4, 2> 3.8 / 4.4; <1, 4> 3.7 / 4.7.    2048 x 2048   4.7 / 5.6 | <1, 4> 4.0 / 4.9; <4, 2> 4.4 / 5.1
-//     512 x 4224    3.6 / 4.6 | <8, 2> 3.3 / 4.0; <4, 3> 3.3 / 4.3.    640 x 4224    3.8 / 4.9 | <4, 3> 3.6 / 4.6; <8, 2> 3.9 / 4.7
-//     2048 x 4224   6.5 / 8.1 | <4, 3> 6.3 / 7.9; <8, 2> 7.1 / 8.7.    5120 x 6144   17.4 / 19.9 | <4, 3> 16.2 / 18.0; <8, 2> 16.4 / 18.9
-//     2048 x 8192   10.4 / 12.9 | <8, 2> 9.8 / 11.7.                   8192 x 8192   32.8 / 36.6 | <8, 2> 30.3 / 33.4
-//     256 x 8320    3.9 / 5.2 | <16, 2> 3.4 / 4.1; <4, 6> 3.5 / 4.7.   400 x 8320    4.3 / 5.8 | <4, 6> 4.1 / 5.4; <16, 2> 4.5 / 5.5
-//     1536 x 8320   8.1 / 10.5 | <4, 6> 8.2 / 10.5; <8, 4> 9.1 / 10.6. 1024 x 9600   6.7 / 8.5 | <4, 6> 6.3 / 8.1; <8, 4> 7.1 / 8.2
-//     400 x 11008   4.9 / 6.5 | <16, 2> 4.8 / 5.8; <8, 4> 4.5 / 5.6.   1024 x 11008  7.7 / 9.8 | <8, 4> 7.7 / 9.1; <16, 2> 8.2 / 9.8
-//     512 x 16384   6.2 / 8.1 | <16, 2> 5.7 / 6.9; <8, 4> 5.5 / 6.9.   4096 x 16384  34.7 / 40.5 | <8, 4> 32.0 / 34.7; <16, 2> 31.0 / 35.5
-//     1024 x 16512  12.6 | <16, 4> 11.7; <16, 8> 17.5.                 2048 x 32768 49.2 | <16, 4> 32.6; <16, 8> 40.6
-//     512 x 40960   19.9 | <16, 8> 15.9 (rows read twice by 16 waves: 14.6).  Longer rows do not fit and are read twice.
+// thread is not mostly empty.  Inputs in turn from 600 MB, replayed from graphs, us without / with zero-point terms, the choice here first:
+//     1536 x 1024   <4, 2> 3.4 / 3.9; <1, 4> 3.1 / 3.6      1600 x 1024   <1, 4> 3.1 / 3.6; <4, 2> 3.4 / 4.0
+//     1536 x 2048   <4, 2> 4.0 / 4.5; <1, 4> 4.1 / 4.7      2048 x 2048   <1, 4> 4.7 / 5.3; <4, 2> 4.6 / 5.3
+//     512 x 4224    <8, 2> 3.5 / 4.1; <4, 3> 3.6 / 4.2      640 x 4224    <4, 3> 3.9 / 4.5; <8, 2> 3.9 / 4.7
+//     2048 x 4224   <4, 3> 7.1 / 8.1; <8, 2> 7.6 / 8.8      5120 x 6144   <4, 3> 16.3 / 17.6; <8, 2> 17.0 / 18.8
+//     2048 x 8192   <8, 2> 10.6 / 11.6; <4, 8> 10.3 / 11.9  8192 x 8192   <8, 2> 31.8 / 33.6; <4, 8> 31.9 / 33.6
+//     256 x 8320    <16, 2> 3.4 / 4.0; <4, 6> 3.7 / 4.4     400 x 8320    <4, 6> 4.5 / 5.3; <16, 2> 4.5 / 5.2
+//     1536 x 8320   <4, 6> 9.2 / 10.4; <8, 4> 9.4 / 10.3    1024 x 9600   <4, 6> 7.8 / 8.8; <8, 4> 7.5 / 8.6
+//     400 x 11008   <16, 2> 5.3 / 6.0; <8, 4> 5.3 / 6.1     1024 x 11008  <8, 4> 8.3 / 9.5; <16, 2> 8.8 / 10.1
+//     512 x 16384   <16, 2> 7.0 / 8.1; <8, 4> 7.1 / 8.1     4096 x 16384  <8, 4> 31.9 / 33.9; <16, 2> 33.3 / 34.7
+//     1024 x 16512  <16, 4> 11.6; <16, 8> 11.9              2048 x 32768  <16, 4> 33.9; <16, 8> 34.1
+//     512 x 40960   <16, 8> 12.9; rows read twice by 16 waves 16.6.  Longer rows do not fit and are read twice.
 template <bool ZP>
 void fq_launch_quantize_as(const uint16_t* X, uint8_t* A, float* a_scale, int M, int K, uint16_t* planes, hipStream_t stream) {
 #define FQ_QUANTIZE_IN(WPR_, CH_, REREAD_, PARTS_) \
@@ -182,9 +178,11 @@ void fq_launch_quantize_as(const uint16_t* X, uint8_t* A, float* a_scale, int M,
                        dim3(WPR_ > 4 ? 64 * WPR_ : 256), 0, stream, X, A, a_scale, K, planes, M)
 #define FQ_QUANTIZE(WPR_, CH_, REREAD_) FQ_QUANTIZE_IN(WPR_, CH_, REREAD_, 1)
     if constexpr (!ZP) {
-        // few rows: two workgroups each (one / two per row, us: 16 x 4096 2.51 / 2.35, 64 x 4096 2.58 / 2.41, 64 x 8192 2.82 / 2.72, 16 x
-        // 14336 3.23 / 2.95, 64 x 14336 3.35 / 3.20, 128 x 16384 3.58 / 4.33; 32 x 32016 4.78 / 4.35, 64 x 32016 5.01 / 5.21; a
-        // row whose second half of chunks is empty gains nothing: 1 x 2048 the same)
+        // few rows: two workgroups each, unless the second half of the chunks is empty.  One / two per row, us, inputs in turn | the same input
+        // again | a copy that writes the input, then the quantiser: 1 x 4096 1.76 / 1.72 | 1.74 / 1.63 | 3.31 / 3.32, 16 x 4096 2.03 / 2.20 | 1.99 /
+        // 1.84 | 3.61 / 3.81, 16 x 8192 2.53 / 2.40 | 2.20 / 2.00 | 4.11 / 3.85, 64 x 8192 2.63 / 2.66 | 2.26 / 2.14 | 4.32 / 4.29, 16 x 14336 2.84 / 2.69 |
+        // 2.50 / 2.25 | 4.37 / 4.24, 64 x 14336 3.42 / 3.34 | 2.60 / 2.38 | 5.11 / 5.46; in turn 128 x 8192 2.93 / 3.14, 128 x 16384 3.59 / 3.94, 64 x 32016
+        // 4.34 / 4.44
         if (M <= 64 && K > 2048 && K <= 4 * 4096) {
             if (K <= 4096) FQ_QUANTIZE_IN(4, 2, false, 2);
             else if (K <= 2 * 4096) FQ_QUANTIZE_IN(8, 2, false, 2);

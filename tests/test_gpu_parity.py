@@ -591,7 +591,7 @@ def test_ws_entry_points_replay_in_a_hip_graph(fq, shape):
     check_gemm(got[0], Yr, B, "graph replay")
 
 
-# ---- the whole layer from bf16 activations (one kernel for a few rows, K <= 4096) -------------------
+# ---- the whole layer from bf16 activations (one kernel for a few rows) ------------------------------
 
 LINEAR_SHAPES = [(6, 256, 512), (1, 32, 128), (5, 100, 384), (6, 4120, 512), (6, 8192, 4096), (4, 4096, 4096),
                  (3, 9000, 256), (6, 14336, 4096), (1, 14336, 4096), (5, 300, 1408), (2, 6144, 3072), (7, 100, 384),
@@ -643,7 +643,8 @@ def test_linear_on_every_bf16_magnitude(fq):
 
 @pytest.mark.parametrize("N,K", [(n, k) for n in (40, 1000, 9000, 16640) for k in (128, 640, 1024, 1536, 1664, 3968, 4096)] +
                          [(40, 4224), (1000, 8192), (40, 8320), (1000, 12288), (200, 14336), (40, 16384), (40, 16512), (4200, 4224), (4200, 8192),
-                          (4200, 10240), (9000, 4224), (13000, 8192)])   # one, one, three and five sub-tiles per compute unit; two, and four
+                          (4200, 10240), (9000, 4224), (13000, 8192), (4200, 1536), (4200, 4096), (13000, 1536), (13000, 4096),
+                          (22016, 1024), (22016, 4096), (28672, 1536), (28672, 3968)])   # one, one, three and five sub-tiles; two, four; six and seven
 def test_linear_at_the_edges_of_its_one_kernel_forms(fq, N, K):
     """1 to 9 rows: both ways of sharing the conversion out, all sizes of their row loops, slices of K that are partly or wholly
     empty, and beside ordinary rows ones of zeros of both signs, with scales outside the short quotient's range, with NaN and with
